@@ -7,6 +7,7 @@
 #include "../../include/marlaas_lora.h"
 #include "common.h"
 
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -47,7 +48,8 @@ struct marlaas_segmap {
   int32_t* seg_off_dev = nullptr;   // [n_cap + 2]
   int32_t* block_hist = nullptr;    // counting-sort scratch
   int32_t* flags_dev = nullptr;     // [2]
-  int32_t* readback = nullptr;      // pinned host: seg_off[n_cap + 2], flags[2]
+  int32_t* readback = nullptr;      // pinned host: seg_off[n + 2], flags[2], number of the update that wrote them
+  int32_t seq = 0;                  // number of the last update in one launch
   std::vector<int32_t> seg_off;     // host copy
   bool identity = false;            // ids were already grouped: kernels skip the gather
   int max_seg = 0;                  // largest adapter segment
@@ -257,7 +259,8 @@ extern "C" int marlaas_segmap_create(marlaas_ctx* ctx, int64_t T_max, int32_t n_
     if ((e = hipMalloc((void**)&m->chunks_dev, sizeof(RowChunk) * (size_t)segmap_chunk_bound(T_max, n_adapters_max))) != hipSuccess) break;
     if ((e = hipMalloc((void**)&m->order_dev, sizeof(int32_t) * (size_t)(n_adapters_max > 0 ? n_adapters_max : 1))) != hipSuccess) break;
     if ((e = hipMalloc((void**)&m->chunk_base_dev, sizeof(int32_t) * ((size_t)n_adapters_max + 1))) != hipSuccess) break;
-    e = hipHostMalloc((void**)&m->readback, sizeof(int32_t) * (nn + 2), hipHostMallocDefault);
+    e = hipHostMalloc((void**)&m->readback, sizeof(int32_t) * (nn + 3), hipHostMallocDefault);
+    if (e == hipSuccess) memset(m->readback, 0, sizeof(int32_t) * (nn + 3));
   } while (0);
   if (e != hipSuccess) {
     marlaas_segmap_destroy(m);
@@ -283,11 +286,30 @@ extern "C" int marlaas_segmap_update(marlaas_ctx* ctx, marlaas_segmap* m, const 
     return fail(ctx, MARLAAS_EUNSUPPORTED, "segmap_update reads the segment sizes back and cannot run inside a stream capture");
   m->built = false;
   const size_t nn = (size_t)n_adapters + 2;
-  HIP_TRY(ctx, launch_segmap(token_adapter, T, n_adapters, m->perm_dev, m->grp_dev, m->seg_off_dev, m->block_hist, m->flags_dev,
-                             m->chunks_dev, m->order_dev, m->chunk_base_dev, st));
-  HIP_TRY(ctx, hipMemcpyAsync(m->readback, m->seg_off_dev, sizeof(int32_t) * nn, hipMemcpyDeviceToHost, st));
-  HIP_TRY(ctx, hipMemcpyAsync(m->readback + nn, m->flags_dev, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(ctx, hipStreamSynchronize(st));
+  if (segmap_is_small(T, n_adapters)) {
+    // one launch that leaves the sizes in pinned memory: the host watches for its number there (a
+    // wait on the stream costs more than the kernel), and looks at the stream now and then so that
+    // a failed launch ends the wait
+    volatile int32_t* done = m->readback + nn + 2;
+    m->seq = m->seq == 0x7fffffff ? 1 : m->seq + 1;
+    *done = 0;
+    HIP_TRY(ctx, launch_segmap_small(token_adapter, T, n_adapters, m->perm_dev, m->grp_dev, m->seg_off_dev, m->chunks_dev,
+                                     m->order_dev, m->chunk_base_dev, m->readback, m->seq, st));
+    for (int64_t polls = 1; *done != m->seq; ++polls) {
+      if (polls % 65536) continue;
+      const hipError_t q = hipStreamQuery(st);
+      if (q == hipErrorNotReady) continue;
+      HIP_TRY(ctx, q);
+      if (*done != m->seq) return fail(ctx, MARLAAS_EHIP, "segmap_update: the stream is idle and the grouping did not run");
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+  } else {
+    HIP_TRY(ctx, launch_segmap(token_adapter, T, n_adapters, m->perm_dev, m->grp_dev, m->seg_off_dev, m->block_hist, m->flags_dev,
+                               m->chunks_dev, m->order_dev, m->chunk_base_dev, st));
+    HIP_TRY(ctx, hipMemcpyAsync(m->readback, m->seg_off_dev, sizeof(int32_t) * nn, hipMemcpyDeviceToHost, st));
+    HIP_TRY(ctx, hipMemcpyAsync(m->readback + nn, m->flags_dev, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(ctx, hipStreamSynchronize(st));
+  }
   if (m->readback[nn]) return fail(ctx, MARLAAS_EINVAL, "segmap: token id outside [-1, %d)", n_adapters);
   m->T = T; m->n = n_adapters;
   m->seg_off.assign(m->readback, m->readback + nn);
@@ -343,7 +365,7 @@ extern "C" int marlaas_segmap_export(const marlaas_segmap* map, int32_t* perm, i
   if (!map || !map->built) return MARLAAS_EINVAL;
   if (seg_off) memcpy(seg_off, map->seg_off.data(), sizeof(int32_t) * map->seg_off.size());
   if (perm && map->T > 0) {
-    if (hipSetDevice(map->device) != hipSuccess) return MARLAAS_EHIP;
+    if (hipSetDevice(map->device) != hipSuccess || hipDeviceSynchronize() != hipSuccess) return MARLAAS_EHIP;
     if (hipMemcpy(perm, map->perm_dev, sizeof(int32_t) * (size_t)map->T, hipMemcpyDeviceToHost) != hipSuccess)
       return MARLAAS_EHIP;
   }

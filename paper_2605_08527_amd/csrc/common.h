@@ -128,6 +128,11 @@ __host__ __device__ inline int reduce_ragged_chunk(int64_t T_lora, int n) {
   if (c < 512) c = 512;
   return (int)((c + 63) / 64 * 64);
 }
+// The same in one launch (T <= 32768, n <= 800); host: pinned, receives seg_off[n + 2], the two
+// flags and then `seq`, in this order (n + 5 values).
+bool segmap_is_small(int64_t T, int n);
+hipError_t launch_segmap_small(const int32_t* ids, int64_t T, int n, int32_t* perm, int32_t* grp_ids, int32_t* seg_off,
+                               RowChunk* chunks, int32_t* order, int32_t* chunk_base, int32_t* host, int seq, hipStream_t stream);
 int segmap_blocks(int64_t T);
 // Row chunks of a grouped order with these segment offsets (n + 2 entries): how many there are.
 int64_t segmap_chunk_count(const int32_t* seg_off, int n);

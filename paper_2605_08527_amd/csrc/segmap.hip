@@ -1,4 +1,5 @@
-// Token grouping by adapter: a stable counting sort in three small kernels.
+// Token grouping by adapter: a stable counting sort, one launch of one block for the batches of a
+// serving step (segmap_small), three small kernels for very large ones.
 // The mixed-tenant batch carries one adapter id per token (paper Sec. 4.5,
 // cross-task batching of rollouts); every later kernel works on tokens grouped
 // by adapter, so this map is built once per batch and reused by all layers.
@@ -170,6 +171,155 @@ __global__ __launch_bounds__(1024) void segmap_order(const int32_t* __restrict__
     for (int s = 0; s < n; ++s) before += (len[s] > mine) || (len[s] == mine && s < t);
     order[before] = t;
   }
+}
+
+// ---- one launch for batches of up to SEG_SMALL_T tokens over up to SEG_SMALL_N adapters
+static constexpr int SM_THREADS = 1024, SM_WAVES = SM_THREADS / 64;
+static constexpr int64_t SEG_SMALL_T = 32768;
+static constexpr int SEG_SMALL_N = 800;       // one bucket per thread in the scans, [waves][buckets] counters in LDS
+
+// Exclusive prefix sum of one value per thread over the block (s_wave: SM_WAVES ints of LDS).
+__device__ __forceinline__ int block_scan(int v, int32_t* s_wave, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int inc = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) { const int o = __shfl_up(inc, d); if (lane >= d) inc += o; }
+  __syncthreads();                            // (the previous scan's sums have been read)
+  if (lane == 63) s_wave[wave] = inc;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < SM_WAVES; ++w) { if (w < wave) before += s_wave[w]; all += s_wave[w]; }
+  *total = all;
+  return before + inc - v;
+}
+
+// The whole grouping in one block: every wave owns a contiguous run of tokens, walks it 64 at a time
+// and counts its buckets (tokens of one bucket inside a wave find each other with one ballot per bit
+// of the bucket number); one scan over (bucket, wave) then gives every wave its first slot in every
+// bucket, and a second walk hands the slots out.  No atomics, order of equal ids = order of indices.
+// The segment sizes go straight to pinned host memory, behind them `seq`, which the host waits for.
+//
+// Bound: launch and latency.  As six launches and two copies the grouping of 512 tokens kept the host
+// waiting 45 us (each of them 4 us of launch for under 2 us of work) before it could enqueue the pass.
+__global__ __launch_bounds__(SM_THREADS) void segmap_small(const int32_t* __restrict__ ids, int T, int n, int nbits,
+                                                           int32_t* __restrict__ perm, int32_t* __restrict__ grp_ids,
+                                                           int32_t* __restrict__ seg_off, RowChunk* __restrict__ chunks,
+                                                           int32_t* __restrict__ order, int32_t* __restrict__ chunk_base,
+                                                           int32_t* __restrict__ host, int seq) {
+  extern __shared__ int32_t lds[];
+  const int nb = n + 1;                       // buckets; bucket n: tokens without an adapter
+  int32_t* cur = lds;                         // [SM_WAVES][nb] counts, then next slots
+  int32_t* off = cur + SM_WAVES * nb;         // [nb + 1] segment offsets
+  int32_t* first = off + nb + 1;              // [nb] first row chunk
+  int32_t* s_wave = first + nb;               // [SM_WAVES]
+  int32_t* flag = s_wave + SM_WAVES;          // [2]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  for (int i = tid; i < SM_WAVES * nb; i += SM_THREADS) cur[i] = 0;
+  if (tid < 2) flag[tid] = 0;
+  __syncthreads();
+  const int per = ((T + SM_THREADS - 1) / SM_THREADS) * 64;     // tokens per wave
+  const int beg = wave * per, end = beg + per < T ? beg + per : T;
+  int32_t* mine = cur + wave * nb;
+  bool bad = false, unsorted = false;
+#pragma unroll 1
+  for (int walk = 0; walk < 2; ++walk) {
+    for (int s0 = beg; s0 < end; s0 += 256) {
+      int idv[4], nxt[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = s0 + 64 * j + lane;
+        idv[j] = i < end ? ids[i] : -2;
+        nxt[j] = walk == 0 && i + 1 < T && i < end ? ids[i + 1] : idv[j];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = s0 + 64 * j + lane;
+        if (s0 + 64 * j >= end) break;
+        const bool ok = i < end && idv[j] >= -1 && idv[j] < n;
+        const int b = idv[j] < 0 ? n : idv[j];
+        if (walk == 0) {
+          bad |= i < end && !ok;
+          unsorted |= i < end && (nxt[j] < 0 ? n : nxt[j]) < b;
+        }
+        uint64_t same = __ballot(ok);
+        for (int bit = 0; bit < nbits; ++bit) {
+          const uint64_t m = __ballot((b >> bit) & 1);
+          same &= ((b >> bit) & 1) ? m : ~m;
+        }
+        if (!ok) continue;
+        const int rank = __popcll(same & below);
+        const int slot = mine[b] + rank;
+        asm volatile("" ::: "memory");        // (every lane has read its counter before the first of a bucket moves it)
+        if (rank == 0) mine[b] = slot + __popcll(same);
+        if (walk == 1) {
+          perm[slot] = i;
+          grp_ids[slot] = b < n ? b : -1;
+          const int pos = slot - off[b];      // inside the bucket: every ROW_CHUNK-th token writes a row chunk
+          if ((pos & (ROW_CHUNK - 1)) == 0) {
+            const int left = off[b + 1] - slot;
+            RowChunk ch;
+            ch.row0 = slot; ch.nrows = left < ROW_CHUNK ? left : ROW_CHUNK; ch.t = b < n ? b : -1; ch.pad = 0;
+            chunks[first[b] + pos / ROW_CHUNK] = ch;
+          }
+        }
+      }
+    }
+    if (walk == 1) break;
+    if (bad) flag[0] = 1;
+    if (unsorted) flag[1] = 1;
+    __syncthreads();
+    int total = 0;
+    if (tid < nb) for (int w = 0; w < SM_WAVES; ++w) total += cur[w * nb + tid];
+    int all;
+    const int start = block_scan(total, s_wave, &all);
+    if (tid < nb) {
+      off[tid] = start;
+      seg_off[tid] = start;
+      host[tid] = start;
+      int run = start;
+      for (int w = 0; w < SM_WAVES; ++w) { const int c = cur[w * nb + tid]; cur[w * nb + tid] = run; run += c; }
+    }
+    if (tid == 0) {
+      off[nb] = all; seg_off[nb] = all;
+      host[nb] = all; host[nb + 1] = flag[0]; host[nb + 2] = flag[1];
+    }
+    const int fc = block_scan((total + ROW_CHUNK - 1) / ROW_CHUNK, s_wave, &all);
+    if (tid < nb) first[tid] = fc;
+    __syncthreads();
+  }
+  // adapters by falling segment length, and the partial-sum slots of those that are cut (see segmap_order)
+  const int len = tid < n ? off[tid + 1] - off[tid] : 0;
+  const int tc = reduce_ragged_chunk(off[n], n);
+  const int nch = (len + tc - 1) / tc;
+  int slots;
+  const int cb = block_scan(tid < n && nch > 1 ? nch : 0, s_wave, &slots);
+  if (tid < n) {
+    chunk_base[tid] = cb;
+    int before = 0;
+    for (int s = 0; s < n; ++s) {
+      const int l = off[s + 1] - off[s];
+      before += (l > len) || (l == len && s < tid);
+    }
+    order[before] = tid;
+  }
+  if (tid == 0) chunk_base[n] = slots;
+  __threadfence_system();                     // this thread's part of the host's copy is out
+  __syncthreads();
+  if (tid == 0) __hip_atomic_store(host + nb + 3, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+bool segmap_is_small(int64_t T, int n) { return T > 0 && T <= SEG_SMALL_T && n <= SEG_SMALL_N; }
+
+hipError_t launch_segmap_small(const int32_t* ids, int64_t T, int n, int32_t* perm, int32_t* grp_ids, int32_t* seg_off,
+                               RowChunk* chunks, int32_t* order, int32_t* chunk_base, int32_t* host, int seq, hipStream_t stream) {
+  int nbits = 0;
+  while ((n >> nbits) > 0) ++nbits;
+  const size_t lds = sizeof(int32_t) * ((size_t)SM_WAVES * (n + 1) + (n + 2) + (n + 1) + SM_WAVES + 2);
+  hipLaunchKernelGGL(segmap_small, dim3(1), dim3(SM_THREADS), lds, stream, ids, (int)T, n, nbits, perm, grp_ids, seg_off, chunks,
+                     order, chunk_base, host, seq);
+  return hipGetLastError();
 }
 
 int64_t segmap_chunk_count(const int32_t* seg_off, int n) {
