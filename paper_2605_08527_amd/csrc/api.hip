@@ -676,6 +676,24 @@ static int resolve_bank(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* ws_t
   return MARLAAS_OK;
 }
 
+static bool inline_f32(const marlaas_lora_desc* d) { return d->in_dtype == MARLAAS_F32 && !d->table && d->n_adapters <= F32_INLINE; }
+
+// An fp32 call's adapters: the bank's device tables, or the pointer lists themselves.
+static TablesF32 tables_f32(const marlaas_lora_desc* d, const Bank& b, void* const* dA, void* const* dB) {
+  TablesF32 tb;
+  memset(&tb, 0, sizeof tb);
+  tb.table = b.entries; tb.grads = b.grads;
+  if (inline_f32(d)) {
+    tb.n_inl = d->n_adapters;
+    for (int t = 0; t < d->n_adapters; ++t) {
+      AdapterEntry& e = tb.entry[t];
+      e.A = d->A[t]; e.B = d->B[t]; e.rank = d->ranks[t]; e.scale = d->scales[t];
+      tb.grad[t].dA = dA ? (float*)dA[t] : nullptr; tb.grad[t].dB = dB ? (float*)dB[t] : nullptr;
+    }
+  }
+  return tb;
+}
+
 // The fused shrink reads rank offsets and extended columns; a workspace copy derives them now.
 static int bank_fuse(marlaas_ctx* ctx, const Bank& b, int n_adapters, hipStream_t st, GemmFuse* f) {
   if (b.in_ws) HIP_TRY(ctx, enqueue_derive(b.all, n_adapters, st));
@@ -767,7 +785,8 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
   }
   float* part = (have_ws && p.part_bytes) ? (float*)((char*)ws + p.part_off) : nullptr;
   Bank bank;
-  if (lora && (rc = resolve_bank(ctx, d, have_ws ? (char*)ws + p.tab_off : nullptr, p.tab_bytes, st, &bank)) != MARLAAS_OK) return rc;
+  // (small fp32 calls carry their pointer lists in the kernel arguments)
+  if (lora && !inline_f32(d) && (rc = resolve_bank(ctx, d, have_ws ? (char*)ws + p.tab_off : nullptr, p.tab_bytes, st, &bank)) != MARLAAS_OK) return rc;
   const AdapterEntry* table = bank.entries;
   const int32_t* perm = map->identity ? nullptr : map->perm_dev;
   // forward contracts over d_in: math W[d_in,d_out] is [contraction, output] (NN), torch is NT;
@@ -803,12 +822,9 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
                                   fused ? &fuse : nullptr, (have_ws && p.wt_bytes) ? (bf16_t*)((char*)ws + p.wt_off) : nullptr,
                                   p.wt_bytes, d->layout == MARLAAS_LAYOUT_MATH ? (const bf16_t*)d->W_t : nullptr, &dma, (const bf16_t*)d->W_packed_fwd, &dsync, st));
   } else {
-    if (lora)
-      PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_f32((const float*)d->x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters,
-                                     table, 0, form, u, rs, map->T_lora, st));
-    PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_f32((const float*)d->x, d->ldx, (const float*)d->W, d->ldw, form, d->T, d->d_in,
-                                 d->d_out, perm, map->seg_off_dev, d->n_adapters, table, 1, lora ? u : nullptr,
-                                 rs, y, ldy, out_f32, st));
+    PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_layer_f32((const float*)d->x, d->ldx, (const float*)d->W, d->ldw, form, d->T, d->d_in,
+                                 d->d_out, perm, lora ? map->grp_dev : nullptr, tables_f32(d, bank, nullptr, nullptr), 1, (float*)u_save, rs,
+                                 y, ldy, out_f32, st));
   }
   return MARLAAS_OK;
 }
@@ -1036,17 +1052,19 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
   const bool need_u = lora && want_grads && !u;
   if (need_u) u = (float*)((char*)ctx->ws + p.u_off);
   Bank bank;
-  if (d->n_adapters > 0 && (rc = resolve_bank(ctx, d, (char*)ctx->ws + p.tab_off, p.tab_bytes, st, &bank)) != MARLAAS_OK) return rc;
+  if (d->n_adapters > 0 && !inline_f32(d) && (rc = resolve_bank(ctx, d, (char*)ctx->ws + p.tab_off, p.tab_bytes, st, &bank)) != MARLAAS_OK) return rc;
   const AdapterEntry* table = bank.entries;
   const GradEntry* grads = bank.grads;
   if (want_grads && !opt && !grads_in_table && d->n_adapters > 0) {
     // explicit gradient pointer lists belong to descriptors that carry their own A / B lists; the
     // per-call copy of the tables in the workspace receives them
-    if (!bank.in_ws)
+    if (d->table)
       return fail(ctx, MARLAAS_EINVAL, "with an adapter table, register the gradient buffers in the table and pass MARLAAS_GRADS_IN_TABLE");
-    std::vector<GradEntry> host((size_t)d->n_adapters);
-    for (int t = 0; t < d->n_adapters; ++t) { host[t].dA = (float*)dA[t]; host[t].dB = (float*)dB[t]; }
-    HIP_TRY(ctx, enqueue_write_grads(bank.all, 0, d->n_adapters, host.data(), st));
+    if (bank.in_ws) {
+      std::vector<GradEntry> host((size_t)d->n_adapters);
+      for (int t = 0; t < d->n_adapters; ++t) { host[t].dA = (float*)dA[t]; host[t].dB = (float*)dB[t]; }
+      HIP_TRY(ctx, enqueue_write_grads(bank.all, 0, d->n_adapters, host.data(), st));
+    }
   }
   const int32_t* perm = map->identity ? nullptr : map->perm_dev;
   // forward-side forms (contraction over d_in) and backward-side forms (contraction over d_out)
@@ -1104,20 +1122,18 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
     if (opt) return fail(ctx, MARLAAS_EUNSUPPORTED, "the optimizer step is attached to the bf16 backward only");
     const float* x = (const float*)d->x;
     const float* dy = (const float*)dY;
+    const TablesF32 tb = tables_f32(d, bank, grads_in_table ? nullptr : dA, grads_in_table ? nullptr : dB);
+    const int32_t* grp = lora ? map->grp_dev : nullptr;
     if (need_u)
-      PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_f32(x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters, table, 0, fform,
-                                     u, rs, map->T_lora, st));
-    if (lora && (dX || want_grads))
-      PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_f32(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, table, 1, bform,
-                                     v, rs, map->T_lora, st));
-    if (dX && d->T > 0)
-      PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_f32(dy, lddy, (const float*)d->W, d->ldw, bform, d->T, d->d_out, d->d_in, perm,
-                                   map->seg_off_dev, d->n_adapters, table, 0, lora ? v : nullptr, rs, dX, lddx,
-                                   out_f32, st));
+      PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_layer_f32(x, d->ldx, nullptr, 0, fform, d->T, d->d_in, d->d_out, perm, grp, tb, 1,
+                                     u, rs, nullptr, 0, 0, st));
+    if (d->T > 0 && (dX || (lora && want_grads)))
+      PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_layer_f32(dy, lddy, (const float*)d->W, d->ldw, bform, d->T, d->d_out, d->d_in, perm, grp,
+                                   tb, 0, lora && want_grads ? v : nullptr, rs, dX, lddx, out_f32, st));
     if (want_grads && d->n_adapters > 0) {
-      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_f32(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, table, grads, 1,
+      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_f32(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, tb, 1,
                                      db_form, u, rs, accumulate, st));
-      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_f32(x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters, table, grads, 0,
+      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_f32(x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters, tb, 0,
                                      da_form, v, rs, accumulate, st));
     }
   }

@@ -261,19 +261,23 @@ hipError_t launch_reduce_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
 size_t reduce_partial_bytes(int64_t C, int n_adapters, int max_seg, int max_rank, bool always = false,
                             int ragged_chunk = 0, int ragged_slots = 0);
 
-// fp32 path (plain ALU arithmetic, any shape)
-hipError_t launch_shrink_f32(const float* X, int64_t ldx, int64_t C, const int32_t* perm,
-                             const int32_t* seg_off, int n_adapters, const AdapterEntry* table,
-                             int which, int lora_form, float* u, int r_stride, int64_t T_lora,
+// fp32 path (fp32 matrix instructions, any shape).  The adapters of a call: device tables, or, for
+// up to F32_INLINE adapters given as pointer lists, entries that travel in the kernel arguments
+// (n_inl > 0), which saves the launch that writes them to device memory.
+static constexpr int F32_INLINE = 16;
+struct TablesF32 {
+  const AdapterEntry* table; const GradEntry* grads;
+  int n_inl;
+  AdapterEntry entry[F32_INLINE];
+  GradEntry grad[F32_INLINE];
+};
+// out[perm[m], :] = X[perm[m], :] * W + u(m) * L_t with u = scale_t X L'_t computed by the same
+// launch (grp: adapter of every grouped row, null for none); u_out (nullable) receives u.  out = null: only u.
+hipError_t launch_layer_f32(const float* X, int64_t ldx, const float* W, int64_t ldw, int form, int64_t T, int64_t Kc, int64_t Nout,
+                            const int32_t* perm, const int32_t* grp, const TablesF32& tb, int which, float* u_out, int r_stride,
+                            void* out, int64_t ldo, int out_is_f32, hipStream_t stream);
+hipError_t launch_reduce_f32(const float* X, int64_t ldx, int64_t C, const int32_t* perm, const int32_t* seg_off, int n_adapters,
+                             const TablesF32& tb, int which, int out_form, const float* V, int r_stride, int accumulate,
                              hipStream_t stream);
-hipError_t launch_gemm_f32(const float* Aop, int64_t lda, const float* Bop, int64_t ldb, int form,
-                           int64_t T, int64_t Kc, int64_t Nout, const int32_t* perm,
-                           const int32_t* seg_off, int n_adapters, const AdapterEntry* table,
-                           int which, const float* U, int r_stride, void* out, int64_t ldo,
-                           int out_is_f32, hipStream_t stream);
-hipError_t launch_reduce_f32(const float* X, int64_t ldx, int64_t C, const int32_t* perm,
-                             const int32_t* seg_off, int n_adapters, const AdapterEntry* table,
-                             const GradEntry* grads, int which, int out_form, const float* V,
-                             int r_stride, int accumulate, hipStream_t stream);
 
 }  // namespace marlaas

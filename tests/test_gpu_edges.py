@@ -3,9 +3,29 @@ import numpy as np
 import pytest
 import torch
 
+from harness import workloads as wl
 from paper_2605_08527_amd import api
+from test_gpu_parity import _check_layer
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    from oracle import lora_oracle
+    return lora_oracle
+
+
+# rows and columns around the 16-wide tiles, a contraction shorter than the waves' share, ranks around
+# the 16-wide shrink tiles, more adapters in a row block than one pass takes, more than the inline table
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,K,N,ranks,table", [(1, 8, 8, [1], False), (5, 264, 40, [3, 17], True), (33, 512, 1032, [8, 16, 128], False),
+                                               (48, 136, 520, [1 + 5 * (t % 7) for t in range(23)], False), (300, 1024, 1024, [16] * 4, True)])
+def test_fp32_layer(oracle, T, K, N, ranks, table, layout):
+    rng = np.random.default_rng(T)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    w = wl.make_layer(T, T, K, N, ranks, [0.5 + (t % 3) for t in range(len(ranks))], ids, dtype="f32", layout=layout, want_dY=True)
+    _check_layer(oracle, w, bwd=True, tol=(1e-4, 1e-5), tag="fp32", table="table" if table else "lists")
 
 
 @pytest.mark.parametrize("T,n", [(1, 1), (63, 800), (64, 1), (65, 2), (1024, 31), (1025, 32), (4097, 800), (4097, 801), (32768, 64), (32769, 64)])
