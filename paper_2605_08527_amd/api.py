@@ -147,7 +147,9 @@ def _check(ctx, status):
 
 def _stream_ptr(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream of the current device; torch.cuda.current_stream() builds a Stream object
+        # around the same handle, 2.8 us against 0.1 (a small pass takes 10 us in all)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
