@@ -812,9 +812,10 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
                                       map->max_seg, table, 0, form, u, rs, map->T_lora, part, part ? p.part_bytes : 0, u2,
                                       &have_u2, (const bf16_t*)ctx->zero_dev, bank.mult8, st));
     LoraDma dma;
+    dma.zero_line = (const bf16_t*)ctx->zero_dev;
     if (have_u2 && have_ws && p.lt_bytes) {
       dma.u2 = u2; dma.tiles = (int32_t*)((char*)ws + p.lt_off); dma.tiles_bytes = p.lt_bytes;
-      dma.zero_line = (const bf16_t*)ctx->zero_dev; dma.ranks_mult8 = bank.mult8;
+      dma.ranks_mult8 = bank.mult8;
     }
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16((const bf16_t*)d->x, d->ldx, (const bf16_t*)d->W, d->ldw, form, d->T, d->d_in,
                                   d->d_out, perm, map->seg_off_dev, d->n_adapters, table, 1, lora ? u : nullptr,
@@ -1100,9 +1101,10 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
       PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_bf16(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
                                       table, 1, bform, v, rs, map->T_lora, part, part ? p.part_bytes : 0, v2, &have_v2, (const bf16_t*)ctx->zero_dev, bank.mult8, st));
     LoraDma dma;
+    dma.zero_line = (const bf16_t*)ctx->zero_dev;
     if (have_v2 && p.lt_bytes) {
       dma.u2 = v2; dma.tiles = (int32_t*)((char*)ctx->ws + p.lt_off); dma.tiles_bytes = p.lt_bytes;
-      dma.zero_line = (const bf16_t*)ctx->zero_dev; dma.ranks_mult8 = bank.mult8;
+      dma.ranks_mult8 = bank.mult8;
     }
     if (dX && d->T > 0)
       PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16(dy, lddy, (const bf16_t*)d->W, d->ldw, bform, d->T, d->d_out, d->d_in, perm,

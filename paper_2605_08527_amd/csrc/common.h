@@ -169,8 +169,8 @@ static constexpr int DECODE_SYNC_INTS = 4096;
 
 // What lets the large-batch GEMM fetch the expand's operands by DMA: u (or v) as a two-term bf16
 // split written by the shrink, scratch for the row tiles' lists of extra contraction tiles
-// (lora_tiles_bytes(T) bytes), 16 zero bytes in device memory, and whether every rank is a
-// multiple of 8.
+// (lora_tiles_bytes(T) bytes), and whether every rank is a multiple of 8; zero_line: 16 zero bytes in
+// device memory (always given).
 struct LoraDma {
   const bf16_t* u2 = nullptr;
   int32_t* tiles = nullptr; size_t tiles_bytes = 0;

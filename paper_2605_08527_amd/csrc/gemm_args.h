@@ -1,5 +1,5 @@
 // Kernel arguments and LDS layout helpers shared by the GEMM kernels (large-batch, small-batch and
-// decode) and the split-contraction finish kernel.
+// decode) and the split-contraction finish kernels.
 #pragma once
 #include "common.h"
 
@@ -48,18 +48,52 @@ struct GemmArgs {
   int fin_in_kernel, out_is_f32, lform, spin_limit;
   int32_t* sync;
   const int32_t* grp_ids;
-  // Large-batch kernel, LoRA expand by DMA (lora_dma = 1): U2 is u as a two-term bf16 split
-  // ([T][2 r_stride], row m = [u_hi (r_pad) | u_lo (r_pad)] of its adapter), lora_tiles the list
-  // of 64-wide extra contraction tiles of every 256-row tile (lora_tile_list_kernel), zero_line
-  // 16 readable zero bytes that masked DMA lanes fetch.
-  const bf16_t* U2; const int32_t* lora_tiles; const bf16_t* zero_line; int lora_dma;
   ProjEntry proj[MAX_PROJ];     // by value: read with wave-uniform loads from the kernel arguments
 };
 
-// List of one 256-row tile's extra contraction tiles: int32 [LT_STRIDE]: count (-1: more than
-// LT_MAX, the kernel then stages the expand through registers), then {adapter, first row, end row,
-// first contraction index} per tile.
-static constexpr int LT_MAX = 15, LT_STRIDE = 64;
+// Large-batch kernel (gemm_wide.hip).  LoraTile: one 64-wide piece of the extra contraction values
+// [u_hi | u_lo] x [L_t ; L_t] of the adapter whose rows [lo, hi) lie in a row tile: its factor, first
+// value, rank.  A row tile's list is LT_MAX + 1 records, record 0 holding the count in `lo` (-1: more
+// than LT_MAX, the kernel then stages the expand through registers).
+struct LoraTile { uint64_t L; int32_t lo, hi, kc, rank; int32_t pad[2]; };
+static constexpr int LT_MAX = 127;
+static_assert(sizeof(LoraTile) == 32, "two 16-byte DMA pieces");
+enum { WIDE_LORA_NONE = 0, WIDE_LORA_LISTS = 1, WIDE_LORA_STAGED = 2 };
+struct WideArgs {
+  const bf16_t* A; int64_t lda;      // rows gathered through perm
+  const bf16_t* B; int64_t ldb;
+  int64_t T, Kc, Nout;
+  const int32_t* perm; const int32_t* seg_off;
+  int n_adapters; const AdapterEntry* table; int which;    // which: 0: L_t = entry.A, 1: L_t = entry.B
+  int lora;                          // WIDE_LORA_*: none, by DMA from lists and U2, staged through registers from U
+  const float* U; int r_stride;
+  const bf16_t* U2;                  // [T][2 r_stride]: row m = [u_hi (r_pad) | u_lo (r_pad)] of its adapter
+  const LoraTile* lora_tiles;
+  const bf16_t* zero_line;           // 16 readable zero bytes that masked DMA lanes fetch
+  void* out; int64_t ldo;
+  float* partials;
+  int tiles_m, tiles_n, rounds, tail_tiles, tail_split; int64_t tail_kchunk;
+};
+// rounds * 256 whole tiles of 32 mt rows x 256 columns, then tail_tiles tiles in tail_split pieces of
+// tail_kchunk contraction values (the last one takes the rest).
+struct WidePlan {
+  int mt = 8, tiles_m = 0, tiles_n = 0, rounds = 0, tail_tiles = 0, tail_split = 1;
+  int64_t tail_kchunk = 0;
+  size_t part_bytes = 0;
+  double us = 0.0;                   // estimated run time
+};
+WidePlan wide_plan(int64_t T, int64_t Kc, int64_t Nout, bool can_split);
+hipError_t launch_gemm_wide(WideArgs a, const WidePlan& p, int form, int lform, int out_is_f32, LoraTile* lists, hipStream_t stream);
+// Tile t in walking order -> its column tile (and row tile *tm): groups of 2048 rows share their column tiles.
+__host__ __device__ inline int wide_tile(int t, int mt, int tiles_m, int tiles_n, int* tm) {
+  const int GM = 64 / mt;
+  const int per_group = GM * tiles_n;
+  const int gid = t / per_group, first_m = gid * GM;
+  const int gsz = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
+  const int in_g = t - gid * per_group;
+  *tm = first_m + in_g % gsz;
+  return in_g / gsz;
+}
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;

@@ -43,3 +43,21 @@ def test_segment_map_one_launch_and_several(T, n):
         key = np.where(ids < 0, n, ids)
         assert np.array_equal(perm, np.argsort(key, kind="stable"))
         assert np.array_equal(off, np.concatenate([[0], np.cumsum(np.bincount(key, minlength=n + 1))]))
+
+
+# The large-batch GEMM: tile heights of 128, 192 and 256 rows with ragged last tiles, contractions that
+# are no multiple of 64 (shorter than one k-tile, one and two k-tiles and a piece), the last round of
+# tiles cut along the contraction, factors whose ranks leave the DMA path, more adapters in a row tile
+# than a list of extra contraction tiles holds.
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,K,N,ranks,odd", [(4200, 40, 2056, [8, 16], False), (4200, 72, 2056, [8, 16], False), (4097, 136, 4104, [64, 8, 16, 128], False),
+                                             (3070, 200, 4096, [16] * 5, True), (8300, 2048, 1032, [32, 8], False), (8300, 2048, 1032, [5, 24], True),
+                                             (2500, 264, 8200, [128, 64] * 48, False)])
+def test_large_batch_gemm_edges(oracle, T, K, N, ranks, odd, layout):
+    rng = np.random.default_rng(T + K + N)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    if odd:
+        ids = np.sort(ids)[::-1].copy()
+    w = wl.make_layer(T + K, T, K, N, ranks, [0.5 + (t % 3) for t in range(len(ranks))], ids, dtype="bf16", layout=layout, want_dY=True)
+    _check_layer(oracle, w, bwd=True, tag="wide")
+    _check_layer(oracle, w, bwd=True, out_dtype=torch.bfloat16, tol=(1e-2, 2.5e-3), tag="wide bf16 out")
