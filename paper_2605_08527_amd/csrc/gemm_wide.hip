@@ -113,7 +113,9 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
     int _t;                                                                                               \
     kbeg = 0; kend = a.Kc; split = 0; ptile = -1;                                                         \
     if ((i_) < a.rounds) {                                                                                \
-      _t = (xcd * a.rounds + (i_)) * 32 + idx;                                                            \
+      /* (turned by one per round: else a workgroup keeps its row tile, and the one whose row tile has */  \
+      /* the most adapters is late in every round)                                                      */  \
+      _t = (xcd * a.rounds + (i_)) * 32 + ((idx + (i_)) & 31);                                            \
     } else {                                                                                              \
       const int _j = xcd * tq + (xcd < tr ? xcd : tr) + idx;                                              \
       split = _j / a.tail_tiles;                                                                          \
