@@ -7,6 +7,7 @@
 #include "../../include/marlaas_lora.h"
 #include "common.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
@@ -759,6 +760,60 @@ static DecodeSync decode_sync_of(const marlaas_ctx* ctx, const marlaas_segmap* m
   return s;
 }
 
+// Extended columns the row tiles of a small batch carry: all of the call's where they fit (`room`
+// columns), whatever the grouping; else, for batches of a few row tiles, each tile's own adapters.
+// Returns the columns of the fullest tile.
+static int ext_rows_of(const marlaas_lora_desc* descs, int32_t n_proj, int n_ext, int room, ExtRows* rows) {
+  *rows = ExtRows();
+  const marlaas_lora_desc* d = &descs[0];
+  const int64_t tiles = (d->T + 127) / 128;
+  if (n_ext <= room || tiles > EXT_ROW_TILES) return n_ext;
+  rows->on = 1;
+  const std::vector<int32_t>& off = d->map->seg_off;
+  const int n = d->n_adapters;
+  int most = 0;
+  for (int64_t tm = 0; tm < tiles; ++tm) {
+    const int64_t m0 = tm * 128, m1 = (tm + 1) * 128 < d->map->T_lora ? (tm + 1) * 128 : d->map->T_lora;
+    int t0 = 0, t1 = 0;                      // adapters [t0, t1) have rows in the tile
+    if (m0 < m1) {
+      t0 = (int)(std::upper_bound(off.begin(), off.begin() + n + 1, (int32_t)m0) - off.begin()) - 1;
+      t1 = (int)(std::lower_bound(off.begin(), off.begin() + n + 1, (int32_t)m1) - off.begin());
+    }
+    int64_t count = 0, base = 0;
+    for (int p = 0; p < n_proj; ++p) {
+      const int32_t* ranks = ranks_of(&descs[p]);
+      int64_t before = 0, span = 0, all = 0;
+      for (int t = 0; t < n; ++t) {
+        if (t < t0) before += ranks[t];
+        else if (t < t1) span += ranks[t];
+        all += ranks[t];
+      }
+      rows->start[tm][p] = (int32_t)count;
+      rows->base[tm][p] = (int32_t)(base + before);
+      count += span;
+      base += all;
+    }
+    rows->count[tm] = (int32_t)count;
+    if (count > most) most = (int)count;
+  }
+  return most;
+}
+
+// The most 16-rank tiles that the adapters of T rows can have, however the rows are grouped.
+static int max_rank_tiles(const marlaas_lora_desc* d) {
+  const int32_t* ranks = ranks_of(d);
+  int count[MARLAAS_MAX_RANK / 16 + 1] = {0};
+  for (int t = 0; t < d->n_adapters; ++t) ++count[(ranks[t] + 15) / 16];
+  int64_t left = d->T;
+  int tiles = 0;
+  for (int k = MARLAAS_MAX_RANK / 16; k > 0 && left > 0; --k) {
+    const int64_t n = count[k] < left ? count[k] : left;
+    tiles += (int)n * k;
+    left -= n;
+  }
+  return tiles;
+}
+
 // ------------------------------------------------------------------ forward
 static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64_t ldy, void* u_save, void* stream,
                     void* ws, size_t ws_bytes) {
@@ -794,13 +849,23 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
   const int form = d->layout == MARLAAS_LAYOUT_MATH ? FORM_NN : FORM_NT;
   const int out_f32 = d->out_dtype == MARLAAS_F32;
   const DecodeSync dsync = decode_sync_of(ctx, map);
-  if (d->in_dtype == MARLAAS_BF16) {
+  if (d->in_dtype == MARLAAS_BF16 && d->W_packed_fwd && gemm_thin_ok(form, d->T, lora, rs, &dsync)) {
+    // few rows on the packed weight: one launch
+    ProjEntry pe;
+    memset(&pe, 0, sizeof pe);
+    pe.W = d->W_packed_fwd; pe.ldw = packed_weight_ksteps(d->d_in); pe.Nout = d->d_out; pe.out = y; pe.ldo = ldy;
+    PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_thin((const bf16_t*)d->x, d->ldx, form, d->T, d->d_in, perm, lora ? d->n_adapters : 0,
+                                  table, 1, &pe, 1, out_f32, u, rs, lora ? max_rank_tiles(d) : 0, &dsync, st));
+  } else if (d->in_dtype == MARLAAS_BF16) {
     // small batches: the GEMM computes the shrink itself and no shrink kernel runs
     GemmFuse fuse;
     bool fused = false;
+    const bool use_packed = !lora || form == FORM_NT;
+    int need = lora ? ext_rows_of(d, 1, bank.n_ext, gemm_ext_room(d->d_out), &fuse.rows) : 0;
     if (lora && part && bank_can_fuse(bank)) {
-      fused = gemm_can_fuse_shrink(form, d->T, d->d_in, d->d_out, bank.n_ext, bank.mult8, p.part_bytes);
+      fused = gemm_can_fuse_shrink(form, d->T, d->d_in, d->d_out, need, bank.mult8, use_packed && d->W_packed_fwd, p.part_bytes);
       if (fused) {
+        fuse.need = need;
         if ((rc = bank_fuse(ctx, bank, d->n_adapters, st, &fuse)) != MARLAAS_OK) return rc;
         fuse.u_out = u;
       }
@@ -820,8 +885,8 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16((const bf16_t*)d->x, d->ldx, (const bf16_t*)d->W, d->ldw, form, d->T, d->d_in,
                                   d->d_out, perm, map->seg_off_dev, d->n_adapters, table, 1, lora ? u : nullptr,
                                   rs, y, ldy, out_f32, part, part ? p.part_bytes : 0, map->chunks_dev, map->n_chunks,
-                                  fused ? &fuse : nullptr, (have_ws && p.wt_bytes) ? (bf16_t*)((char*)ws + p.wt_off) : nullptr,
-                                  p.wt_bytes, d->layout == MARLAAS_LAYOUT_MATH ? (const bf16_t*)d->W_t : nullptr, &dma, (const bf16_t*)d->W_packed_fwd, &dsync, st));
+                                  fused ? &fuse : nullptr, need, (have_ws && p.wt_bytes) ? (bf16_t*)((char*)ws + p.wt_off) : nullptr,
+                                  p.wt_bytes, d->layout == MARLAAS_LAYOUT_MATH ? (const bf16_t*)d->W_t : nullptr, &dma, (const bf16_t*)d->W_packed_fwd, use_packed, &dsync, st));
   } else {
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_layer_f32((const float*)d->x, d->ldx, (const float*)d->W, d->ldw, form, d->T, d->d_in,
                                  d->d_out, perm, lora ? map->grp_dev : nullptr, tables_f32(d, bank, nullptr, nullptr), 1, (float*)u_save, rs,
@@ -949,12 +1014,36 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
   multi_proj_host(descs, n_proj, y, ldy, &proj, &n_ext, &mult8);
   if (!lora) n_ext = 0;
   const bool shared = multi_shares_table(descs, n_proj);
+  // packed copies of every projection's weight (and factors stored contraction-contiguous, or no
+  // adapters): the kernels that read those
+  bool packed = !lora || form == FORM_NT;
+  for (int p = 0; p < n_proj; ++p) if (!descs[p].W_packed_fwd) packed = false;
+  const DecodeSync dsync = decode_sync_of(ctx, map);
+  int rs_all = 0;
+  for (int p = 0; p < n_proj; ++p) { const int r = (int)marlaas_u_stride(&descs[p]); if (r > rs_all) rs_all = r; }
+  if (packed && n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && (!lora || shared) && gemm_thin_ok(form, d0->T, lora, rs_all, &dsync) &&
+      ctx->ws_bytes >= (size_t)n_proj * d0->T * rs_all * sizeof(float)) {
+    // few rows: everything in one launch
+    HIP_TRY(ctx, hipSetDevice(ctx->device));
+    int tiles = 0;
+    for (int p = 0; p < n_proj; ++p) {
+      proj[p].W = descs[p].W_packed_fwd; proj[p].ldw = packed_weight_ksteps(d0->d_in);
+      if (lora) { const int k = max_rank_tiles(&descs[p]); if (k > tiles) tiles = k; }
+    }
+    hipStream_t thin_st = (hipStream_t)stream;
+    PROFILED(ctx, MARLAAS_KERNEL_GEMM, thin_st, launch_gemm_bf16_thin((const bf16_t*)d0->x, d0->ldx, form, d0->T, d0->d_in, map->identity ? nullptr : map->perm_dev,
+                                       lora ? d0->n_adapters : 0, lora ? d0->table->dev.entries : nullptr, 1, proj.data(), n_proj,
+                                       d0->out_dtype == MARLAAS_F32, (float*)ctx->ws, rs_all, tiles, &dsync, thin_st));
+    return MARLAAS_OK;
+  }
   // descriptors that refer to tables, but not to one table in projection order, have no combined tables
   bool fused = n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && ctx->ws != nullptr && (!lora || shared || !d0->table);
   MultiPlan mp;
+  GemmFuse fuse;
+  if (lora) fuse.need = ext_rows_of(descs, n_proj, n_ext, gemm_multi_ext_room(proj.data(), n_proj), &fuse.rows);
   if (fused) {
     mp = plan_multi(descs, n_proj, proj.data(), n_ext, lora);
-    fused = ctx->ws_bytes >= mp.total && gemm_multi_ok(form, d0->T, d0->d_in, proj.data(), n_proj, n_ext, mult8, mp.part_bytes);
+    fused = ctx->ws_bytes >= mp.total && gemm_multi_ok(form, d0->T, d0->d_in, proj.data(), n_proj, fuse.need, mult8, packed, mp.part_bytes);
     if (fused && lora && n_ext > (shared ? d0->table->dev.ext_cap : EXT_CAP_MAX)) fused = false;
   }
   if (!fused) {
@@ -968,7 +1057,6 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
   const int n = d0->n_adapters;
   // combined tables: adapters as [projection][adapter], extended columns over all of them
   const AdapterEntry* table = nullptr;
-  GemmFuse fuse;
   if (lora) {
     DevTables all;
     if (shared) {
@@ -989,13 +1077,8 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
     fuse.n_ext = n_ext; fuse.ranks_mult8 = mult8; fuse.u_out = nullptr; fuse.t0 = 0; fuse.ext_base = 0;
   }
   const int32_t* perm = map->identity ? nullptr : map->perm_dev;
-  // packed copies of every projection's weight (and factors stored contraction-contiguous, or no
-  // adapters): the decode kernel reads those
-  bool packed = !lora || form == FORM_NT;
-  for (int p = 0; p < n_proj; ++p) if (!descs[p].W_packed_fwd) packed = false;
   if (packed)
     for (int p = 0; p < n_proj; ++p) { proj[p].W = descs[p].W_packed_fwd; proj[p].ldw = packed_weight_ksteps(d0->d_in); }
-  const DecodeSync dsync = decode_sync_of(ctx, map);
   PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_multi((const bf16_t*)d0->x, d0->ldx, form, d0->T, d0->d_in, perm,
                                       map->seg_off_dev, n, table, proj.data(), n_proj,
                                       d0->out_dtype == MARLAAS_F32, (float*)ctx->ws, mp.part_bytes, map->chunks_dev,
@@ -1088,16 +1171,26 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
     // small batches: the dX GEMM computes v itself (and leaves it in `v` for the dA reduction)
     GemmFuse fuse;
     bool fused = false;
-    if (lora && dX && part && bank_can_fuse(bank)) {
-      fused = gemm_can_fuse_shrink(bform, d->T, d->d_out, d->d_in, bank.n_ext, bank.mult8, p.part_bytes);
+    const bool use_packed = !lora || bform == FORM_NT;
+    const int need = lora ? ext_rows_of(d, 1, bank.n_ext, gemm_ext_room(d->d_in), &fuse.rows) : 0;
+    const bool thin = dX && d->W_packed_bwd && gemm_thin_ok(bform, d->T, lora, rs, &dsync);
+    if (thin) {
+      ProjEntry pe;
+      memset(&pe, 0, sizeof pe);
+      pe.W = d->W_packed_bwd; pe.ldw = packed_weight_ksteps(d->d_out); pe.Nout = d->d_in; pe.out = dX; pe.ldo = lddx;
+      PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_thin(dy, lddy, bform, d->T, d->d_out, perm, lora ? d->n_adapters : 0, table, 0, &pe, 1,
+                                    out_f32, v, rs, lora ? max_rank_tiles(d) : 0, &dsync, st));
+    } else if (lora && dX && part && bank_can_fuse(bank)) {
+      fused = gemm_can_fuse_shrink(bform, d->T, d->d_out, d->d_in, need, bank.mult8, use_packed && d->W_packed_bwd, p.part_bytes);
       if (fused) {
+        fuse.need = need;
         if ((rc = bank_fuse(ctx, bank, d->n_adapters, st, &fuse)) != MARLAAS_OK) return rc;
         fuse.u_out = v;
       }
     }
     bool have_v2 = false;
     bf16_t* v2 = (have_ws && p.uv2_bytes && dX) ? (bf16_t*)((char*)ctx->ws + p.v2_off) : nullptr;
-    if (lora && (dX || want_grads) && !fused)
+    if (lora && (dX || want_grads) && !fused && !thin)
       PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_bf16(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
                                       table, 1, bform, v, rs, map->T_lora, part, part ? p.part_bytes : 0, v2, &have_v2, (const bf16_t*)ctx->zero_dev, bank.mult8, st));
     LoraDma dma;
@@ -1106,12 +1199,12 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
       dma.u2 = v2; dma.tiles = (int32_t*)((char*)ctx->ws + p.lt_off); dma.tiles_bytes = p.lt_bytes;
       dma.ranks_mult8 = bank.mult8;
     }
-    if (dX && d->T > 0)
+    if (dX && d->T > 0 && !thin)
       PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16(dy, lddy, (const bf16_t*)d->W, d->ldw, bform, d->T, d->d_out, d->d_in, perm,
                                     map->seg_off_dev, d->n_adapters, table, 0, lora ? v : nullptr, rs, dX, lddx,
                                     out_f32, part, part ? p.part_bytes : 0, map->chunks_dev, map->n_chunks,
-                                    fused ? &fuse : nullptr, (have_ws && p.wt_bytes) ? (bf16_t*)((char*)ctx->ws + p.wt_off) : nullptr,
-                                    p.wt_bytes, d->layout == MARLAAS_LAYOUT_TORCH ? (const bf16_t*)d->W_t : nullptr, &dma, (const bf16_t*)d->W_packed_bwd, &dsync, st));
+                                    fused ? &fuse : nullptr, need, (have_ws && p.wt_bytes) ? (bf16_t*)((char*)ctx->ws + p.wt_off) : nullptr,
+                                    p.wt_bytes, d->layout == MARLAAS_LAYOUT_TORCH ? (const bf16_t*)d->W_t : nullptr, &dma, (const bf16_t*)d->W_packed_bwd, use_packed, &dsync, st));
     if (want_grads && d->n_adapters > 0) {
       PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_bf16(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
                                       table, grads, 1, db_form, u, rs, accumulate, part, part ? p.part_bytes : 0, opt ? &opt[1] : nullptr, map->order_dev, map->chunk_base_dev,

@@ -59,6 +59,17 @@ struct ProjEntry {
 };
 static constexpr int MAX_PROJ = 8;
 
+// Which extended columns the row tiles (128 rows) of a small batch carry.  Rows are grouped by adapter,
+// so a row tile needs the factors of consecutive adapters only: columns base[tm][p] .. of projection p,
+// laid out from column start[tm][p] of the tile on, count[tm] in all.  on = 0: every tile carries the
+// call's columns 0 .. n_ext - 1, whatever the grouping.
+static constexpr int EXT_ROW_TILES = 8;
+struct ExtRows {
+  int32_t on = 0;
+  int32_t count[EXT_ROW_TILES] = {0};
+  int32_t start[EXT_ROW_TILES][MAX_PROJ] = {{0}}, base[EXT_ROW_TILES][MAX_PROJ] = {{0}};
+};
+
 // The per-adapter tables of one call as the kernels read them, all in device memory.  They live
 // either in an adapter table object (written when an adapter is registered or swapped) or in a
 // slice of the caller's workspace (written at the start of the call); the passes only read them.
@@ -189,6 +200,8 @@ struct GemmFuse {
   // the bank's entries and t0 is the entry index of the call's table[0]; roff values are offsets
   // in the bank's extended-column space and ext_base is the call's first one (roff of table[0]).
   int t0 = 0, ext_base = 0;
+  int need = 0;            // extended columns the fullest row tile carries (n_ext where `rows` is off)
+  ExtRows rows;
 };
 
 // out[perm[m], :] = Aop[perm[m], :] * Bop + (m in segment t) U[m, :] * L_t
@@ -197,20 +210,29 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
                             const int32_t* seg_off, int n_adapters, const AdapterEntry* table,
                             int which, const float* U, int r_stride, void* out, int64_t ldo,
                             int out_is_f32, float* partials, size_t partial_bytes, const RowChunk* chunks,
-                            int n_chunks, const GemmFuse* fuse, bf16_t* wt_scratch, size_t wt_bytes, const bf16_t* Bt_kept, const LoraDma* dma,
-                            const bf16_t* Bpacked, const DecodeSync* sync, hipStream_t stream);
-// (Bpacked: optional packed copy of Bop for this contraction, used by small batches; with it the
+                            int n_chunks, const GemmFuse* fuse, int need_unfused, bf16_t* wt_scratch, size_t wt_bytes, const bf16_t* Bt_kept, const LoraDma* dma,
+                            const bf16_t* Bpacked, bool use_packed, const DecodeSync* sync, hipStream_t stream);
+// (need_unfused: extended columns the row tiles would have needed, for the choice of kernel; use_packed: Bpacked may be read; Bpacked: optional packed copy of Bop for this contraction, used by small batches; with it the
 // shrink is only fused when the adapters' factors are stored contraction-contiguous, which the
 // caller says by passing fuse only then.)
+// A call of few rows on packed weights (gemm_thin.hip): all of it, shrink included, in one launch.
+// proj: the call's projections (W packed copies, ldw their k-steps), table: [projection][adapter], u:
+// [n_proj][T][r_stride] fp32, receives u; max_tiles: the most 16-rank tiles the adapters of T rows can
+// have in any projection.
+bool gemm_thin_ok(int form, int64_t T, bool lora, int r_stride, const DecodeSync* sync);
+hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, int n_adapters,
+                                 const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
+                                 float* u, int r_stride, int max_tiles, const DecodeSync* sync, hipStream_t stream);
 // Several projections of the same input in one pass (small batches only: 128 x 128 tiles with
 // the shrink carried as extended columns, or no adapters at all).  `proj_host` holds the n_proj
 // entries (host memory); `table` is the combined adapter table ([projection][adapter]), `fuse` (null:
 // no adapters) the combined extended-column tables, ExtCol::t indexing the combined table.  The
 // projection entries travel in the kernel arguments.
 // gemm_multi_ok tells whether the sizes qualify; otherwise the caller runs the projections one by one.
-bool gemm_multi_ok(int form, int64_t T, int64_t Kc, const ProjEntry* proj_host, int n_proj, int n_ext,
-                   bool ranks_mult8, size_t partial_bytes);
+bool gemm_multi_ok(int form, int64_t T, int64_t Kc, const ProjEntry* proj_host, int n_proj, int need,
+                   bool ranks_mult8, bool packed, size_t partial_bytes);
 size_t gemm_multi_bytes(int64_t T, int64_t Kc, const ProjEntry* proj_host, int n_proj, int n_ext);
+int gemm_multi_ext_room(const ProjEntry* proj_host, int n_proj);
 hipError_t launch_gemm_bf16_multi(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc,
                                   const int32_t* perm, const int32_t* seg_off, int n_adapters,
                                   const AdapterEntry* table, const ProjEntry* proj_host,
@@ -236,8 +258,11 @@ size_t gemm_splitk_bytes(int64_t T, int64_t Kc, int64_t Nout, int n_ext);
 // Small batches: the GEMM can compute the shrink itself (as extra output columns over every
 // adapter's factor; the finish kernel keeps each row's own adapter).  When this holds the caller
 // skips the shrink launch and passes a GemmFuse; U is then ignored and u_out receives u.
-bool gemm_can_fuse_shrink(int form, int64_t T, int64_t Kc, int64_t Nout, int n_ext, bool ranks_mult8,
+// need: extended columns of the fullest row tile.
+bool gemm_can_fuse_shrink(int form, int64_t T, int64_t Kc, int64_t Nout, int need, bool ranks_mult8, bool packed,
                           size_t partial_bytes);
+// Extended columns that one row tile of these output columns can carry.
+int gemm_ext_room(int64_t Nout);
 
 // out_t(c, q) (+)= sum_{m in seg t} X[perm[m], c] * V[m, q]
 // out_form FORM_NN: out_t[c * r_t + q]; FORM_NT: out_t[q * C + c].

@@ -48,6 +48,8 @@ struct GemmArgs {
   int fin_in_kernel, out_is_f32, lform, spin_limit;
   int32_t* sync;
   const int32_t* grp_ids;
+  ExtRows ext;                  // the row tiles' shares of the extended columns
+  int n_prod;                   // few-row kernel: workgroups that compute u (a multiple of n_proj)
   ProjEntry proj[MAX_PROJ];     // by value: read with wave-uniform loads from the kernel arguments
 };
 
@@ -117,6 +119,23 @@ __device__ __forceinline__ bf16x8 lds_read_frag_tr(const char* p0, const char* p
 // s_waitcnt immediate that waits only for the vector-memory counter (6 bits, split 3:0 / 15:14)
 #define VMCNT(n) (0x0F70 | ((n) & 15) | ((((n) >> 4) & 3) << 14))
 
+// Extended column e of row tile tm (counted from the tile's first) -> column of the call, e past the
+// end repeating the last `unit` columns; columns the tile carries; column (counted from the tile's
+// first) of rank 0 of the adapter of projection p whose rank offset is roff.
+__device__ __forceinline__ int ext_carried(const GemmArgs& a, int tm) { return a.ext.on ? a.ext.count[tm] : a.n_ext; }
+__device__ __forceinline__ int ext_column(const GemmArgs& a, int tm, int e, int unit) {
+  const int n = ext_carried(a, tm);
+  if (e >= n) e = n - unit;
+  if (e < 0) e = 0;
+  if (!a.ext.on) return e;
+  int p = 0;
+  for (int q = 1; q < a.n_proj; ++q) if (e >= a.ext.start[tm][q]) p = q;
+  return n > 0 ? a.ext.base[tm][p] + e - a.ext.start[tm][p] : 0;
+}
+__device__ __forceinline__ int ext_local(const GemmArgs& a, int tm, int p, int roff) {
+  return roff - a.ext_base + (a.ext.on ? a.ext.start[tm][p] - a.ext.base[tm][p] : 0);
+}
+
 // Small-batch kernels: tile of the partial sums and of the finish kernel's grid.
 static constexpr int SK_BM = 128, SK_BN = 128, SK_BX = 32;
 
@@ -125,5 +144,12 @@ static constexpr int SK_BM = 128, SK_BN = 128, SK_BX = 32;
 // copy, ldb (ProjEntry::ldw) its k-steps per column block; the adapters' factors must be stored
 // contraction-contiguous when the shrink is fused (n_ext > 0).
 hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t stream);
+
+// Few rows (T <= THIN_ROWS) on packed weights, one launch (gemm_thin.hip): every ProjEntry filled in
+// (also for one projection; W packed, ldw its k-steps, tile0 set here), u_part = [n_proj][T][r_stride]
+// fp32 that receives the scaled u, sync = counters, n_prod = n_proj times the most 16-rank tiles that
+// any grouping of T rows can use.  Factors of the shrink stored contraction-contiguous.
+static constexpr int THIN_ROWS = 64;
+hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream);
 
 }  // namespace marlaas

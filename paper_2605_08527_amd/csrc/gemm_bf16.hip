@@ -77,16 +77,12 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs a) {
     if (FORM == FORM_NT) {           // tile [32 e][64 k]: row = extended column, factor stored [r][Kc]
       const int row = wave * 8 + (lane >> 3);
       const int unit = (lane & 7) ^ ((row >> 1) & 7);
-      int e = tn * SK_BX + row;
-      if (e >= a.n_ext) e = a.n_ext - 1;
-      const ExtCol c = a.ext_cols[e];
+      const ExtCol c = a.ext_cols[ext_column(a, tm, tn * SK_BX + row, 1)];
       x_src = (const bf16_t*)(a.which ? c.A : c.B) + (int64_t)c.q * a.Kc + kbeg + unit * 8;
       x_step = BK;
     } else {                         // tile [64 k][32 e], 64-byte rows: factor stored [Kc][r], r % 8 == 0
       const int k = wave * 16 + (lane >> 2);
-      int e = tn * SK_BX + (lane & 3) * 8;
-      if (e >= a.n_ext) e = a.n_ext - 8;
-      const ExtCol c = a.ext_cols[e];
+      const ExtCol c = a.ext_cols[ext_column(a, tm, tn * SK_BX + (lane & 3) * 8, 8)];
       const AdapterEntry en = a.table[c.t - a.ext_t0];     // (this storage form needs the rank)
       x_src = (const bf16_t*)(a.which ? en.A : en.B) + (kbeg + k) * en.rank + c.q;
       x_step = (int64_t)BK * en.rank;
@@ -463,17 +459,13 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs a) {
       char* xs = bs + SK_B_BYTES;
       if (FORM == FORM_NT) {
         const int lc = tid & 7, row = tid >> 3;             // 32 rows x 8 units
-        int e = tn * SK_BX + row;
-        if (e >= a.n_ext) e = a.n_ext - 1;
-        const ExtCol c = a.ext_cols[e];
+        const ExtCol c = a.ext_cols[ext_column(a, tm, tn * SK_BX + row, 1)];
         uint4 w = zero4;
         if ((k0 + lc * 8) < kend) w = *(const uint4*)((const bf16_t*)(a.which ? c.A : c.B) + (int64_t)c.q * a.Kc + k0 + lc * 8);
         *(uint4*)(xs + swz_rowk(row, lc)) = w;
       } else {
         const int lc = tid & 3, k = tid >> 2;               // 64 k-rows x 4 units
-        int e = tn * SK_BX + lc * 8;
-        if (e >= a.n_ext) e = a.n_ext - 8;
-        const ExtCol c = a.ext_cols[e];
+        const ExtCol c = a.ext_cols[ext_column(a, tm, tn * SK_BX + lc * 8, 8)];
         uint4 w = zero4;
         const AdapterEntry en = a.table[c.t - a.ext_t0];
         if ((k0 + k) < kend) w = *(const uint4*)((const bf16_t*)(a.which ? en.A : en.B) + (k0 + k) * en.rank + c.q);
@@ -522,9 +514,8 @@ __global__ __launch_bounds__(FIN_THREADS) void splitk_finish_kernel(GemmArgs a) 
   // the projection this column chunk belongs to (block-uniform)
   int64_t Nout = a.Nout, ldo = a.ldo, pcol0 = 0;
   void* outp = a.out;
-  int tab0 = 0;
+  int tab0 = 0, p = 0;
   if (a.n_proj > 1) {
-    int p = 0;
     for (int q = 1; q < a.n_proj; ++q) if (col >= a.proj[q].fin0) p = q;
     const ProjEntry pe = a.proj[p];
     Nout = pe.Nout; ldo = pe.ldo; outp = pe.out; tab0 = pe.tab0;
@@ -551,14 +542,14 @@ __global__ __launch_bounds__(FIN_THREADS) void splitk_finish_kernel(GemmArgs a) 
     const int r = e.rank;
     if (a.n_ext > 0) {
       // fused shrink: u = scale * (sum over the splits of this adapter's extended columns)
-      const int roff = a.ext_roff[tab0 + ch.t] - a.ext_base;
+      const int roff = a.ext_roff[tab0 + ch.t];
       const int64_t ustride = a.pm * a.ldu;
 #pragma unroll
       for (int i = 0; i < UPT; ++i) {
         const int j = (tid >> 7) + i * (FIN_THREADS >> 7), q = tid & 127;
         float sum = 0.f;
         if (j < ch.nrows && q < r) {
-          const float* up = a.u_part + (int64_t)(ch.row0 + j) * a.ldu + roff + q;
+          const float* up = a.u_part + (int64_t)(ch.row0 + j) * a.ldu + ext_local(a, (ch.row0 + j) / SK_BM, p, roff) + q;
           for (int ks0 = 0; ks0 < a.ksplit; ks0 += 4) {
             float pu[4];
 #pragma unroll
@@ -788,74 +779,92 @@ static GemmPlan small_plan(int64_t s, int64_t T, int64_t Kc, int64_t Nout, int n
 }
 
 // Estimated run time of a small-batch plan in microseconds, from rates measured with one workgroup
-// per compute unit: time per 64-deep k-tile (bound by the LDS fill rate, less so when fewer than 256
-// workgroups share it), a fixed cost per round of workgroups, a separate shrink launch where the
-// GEMM does not carry it, and the partial sums written once and read once at about 5 TB/s.  Only
-// the ordering of the candidates matters.
-static double small_cost(const GemmPlan& p, int n_ext) {
+// per compute unit: time per 64-deep k-tile (bound by the fill rate, less so when fewer than 256
+// workgroups share it; the packed weight skips LDS), a fixed cost per round of workgroups, a separate
+// shrink launch where the GEMM does not carry it, and the partial sums written once and read once.
+// Only the ordering of the candidates matters.
+static double small_cost(const GemmPlan& p, int n_ext, bool packed) {
   const int64_t wgs = (int64_t)p.tiles_m * p.tiles_n * p.ksplit;
   const int64_t rounds = (wgs + CUS - 1) / CUS;
   const int64_t ktiles = (p.kchunk + BK - 1) / BK;
-  const double share = 0.75 + 0.25 * (wgs < CUS ? (double)wgs / CUS : 1.0);
-  double us = (double)rounds * (ktiles * 0.9 * share + 4.5);
-  if (n_ext > 0 && p.u_bytes == 0) us += 7.0;
-  return us + 3.5 + 2.0 * (double)(p.bytes + p.u_bytes) / 5.0e6;
+  const double busy = wgs < CUS ? (double)wgs / CUS : 1.0;
+  const double shrink = n_ext > 0 && p.u_bytes == 0 ? 15.0 : 0.0;
+  if (!packed) return rounds * (ktiles * 0.9 * (0.75 + 0.25 * busy) + 4.5) + shrink + 3.5 + 2.0 * (double)(p.bytes + p.u_bytes) / 5.0e6;
+  // (an unsplit contraction is finished in the kernel)
+  const double finish = p.ksplit == 1 ? (n_ext > 0 ? 8.0 : 0.0) : 6.0 + 2.0 * (double)(p.bytes + p.u_bytes) / 8.0e6;
+  return rounds * (ktiles * (0.45 + 0.22 * busy) + 9.0) + shrink + finish;
+}
+
+// The same for the large-batch kernel with adapters: the shrink and the row tiles' lists as launches,
+// and per tile its extra contraction tiles (need: ranks of the adapters of a row tile, or of all).
+static double wide_cost(const WidePlan& w, int64_t T, int need) {
+  if (need <= 0) return w.us;
+  const double share = T > 32 * w.mt ? (double)(32 * w.mt) / T : 1.0;
+  const double extra = 1.0 + 2.0 * need / 64.0 * share;
+  return w.us + 16.0 + (w.rounds + (w.tail_tiles ? 1 : 0)) * 1.4 * extra;
 }
 
 // The best small-batch plan for these sizes (us: its estimated time; left alone when none qualifies).
-static bool best_small(int64_t T, int64_t Kc, int64_t Nout, int n_ext, double* us, GemmPlan* best) {
+static bool best_small(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, double* us, GemmPlan* best) {
   bool found = false;
   int64_t max_s = Kc / 256;                         // contraction values per split, at least
   if (max_s > 32) max_s = 32;
+  if (max_s < 1) max_s = 1;
   int last = 0;
   for (int64_t s = 1; s <= max_s; ++s) {
-    const GemmPlan p = small_plan(s, T, Kc, Nout, n_ext);
+    const GemmPlan p = small_plan(s, T, Kc, Nout, need);
     if (p.ksplit == last) continue;                 // rounding the chunk to whole k-tiles gave the same split
     last = p.ksplit;
     if ((int64_t)p.tiles_m * p.tiles_n * p.ksplit > 4 * CUS) break;
-    const double c = small_cost(p, n_ext);
+    const double c = small_cost(p, need, packed);
     if (c < *us) { *us = c; *best = p; found = true; }
   }
   return found;
 }
 
+// need: extended columns of the fullest row tile; packed: the weight has a packed copy.
 // small_only: only the 128 x 128 kernels are candidates (the several-projections pass exists for
 // them alone); the large-batch plan is returned when none of them qualifies.
-static GemmPlan gemm_plan(int64_t T, int64_t Kc, int64_t Nout, int n_ext, bool small_only = false) {
+static GemmPlan gemm_plan(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, bool small_only = false) {
   GemmPlan best;
   best.w = wide_plan(T, Kc, Nout, true);
   best.bytes = best.w.part_bytes;
   // at least half a round of 256 x 256 tiles: the large-batch kernel
   const int64_t G = ((T + 255) / 256) * ((Nout + 255) / 256);
   if (T <= 0 || Nout <= 0 || G > CUS / 2) return best;
-  double us = small_only ? 1e30 : best.w.us + (n_ext > 0 ? 7.0 : 0.0);
-  best_small(T, Kc, Nout, n_ext, &us, &best);
+  double us = small_only ? 1e30 : wide_cost(best.w, T, need);
+  best_small(T, Kc, Nout, need, packed, &us, &best);
   return best;
 }
 
-// (room for whichever kernel a call takes: a descriptor's packed weight is not known here)
+int gemm_ext_room(int64_t Nout) { return (int)((Nout + SK_BN - 1) / SK_BN) * SK_BX; }
+
+// (room for whichever kernel a call takes: a descriptor's packed weight and, where the map object is
+// reused, the grouping are not known here)
 size_t gemm_splitk_bytes(int64_t T, int64_t Kc, int64_t Nout, int n_ext) {
   if (T <= 0 || Nout <= 0) return 0;
-  const GemmPlan p = gemm_plan(T, Kc, Nout, n_ext);
-  size_t need = p.bytes + p.u_bytes;
+  const int need = n_ext < gemm_ext_room(Nout) ? n_ext : gemm_ext_room(Nout);
+  size_t bytes = wide_plan(T, Kc, Nout, true).part_bytes;
   const int64_t G = ((T + 255) / 256) * ((Nout + 255) / 256);
-  GemmPlan q;
-  double us = 1e30;
-  if (p.wide && G <= CUS / 2 && best_small(T, Kc, Nout, n_ext, &us, &q) && q.bytes + q.u_bytes > need) need = q.bytes + q.u_bytes;
-  return need;
+  for (int packed = 0; packed < 2 && G <= CUS / 2; ++packed) {
+    GemmPlan q;
+    double us = 1e30;
+    if (best_small(T, Kc, Nout, need, packed != 0, &us, &q) && q.bytes + q.u_bytes > bytes) bytes = q.bytes + q.u_bytes;
+  }
+  return bytes;
 }
 
 size_t gemm_wt_bytes(int form, int64_t T, int64_t Kc, int64_t Nout) {
   if (form != FORM_NN || T < WT_MIN_ROWS || Kc <= 0 || Nout <= 0 || Kc > 65535 * 64) return 0;
-  if (!gemm_plan(T, Kc, Nout, 0).wide) return 0;
+  if (!gemm_plan(T, Kc, Nout, 0, false).wide) return 0;
   return (size_t)Kc * Nout * sizeof(bf16_t);
 }
 
-bool gemm_can_fuse_shrink(int form, int64_t T, int64_t Kc, int64_t Nout, int n_ext, bool ranks_mult8,
+bool gemm_can_fuse_shrink(int form, int64_t T, int64_t Kc, int64_t Nout, int need, bool ranks_mult8, bool packed,
                           size_t partial_bytes) {
-  if (T <= 0 || Nout <= 0 || n_ext <= 0) return false;
+  if (T <= 0 || Nout <= 0 || need <= 0) return false;
   if (form == FORM_NN && !ranks_mult8) return false;     // 16-byte DMA units must not straddle adapters
-  const GemmPlan p = gemm_plan(T, Kc, Nout, n_ext);
+  const GemmPlan p = gemm_plan(T, Kc, Nout, need, packed);
   return !p.wide && p.u_bytes > 0 && partial_bytes >= p.bytes + p.u_bytes;
 }
 
@@ -887,13 +896,14 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
                             const int32_t* seg_off, int n_adapters, const AdapterEntry* table,
                             int which, const float* U, int r_stride, void* out, int64_t ldo,
                             int out_is_f32, float* partials, size_t partial_bytes, const RowChunk* chunks,
-                            int n_chunks, const GemmFuse* fuse, bf16_t* wt_scratch, size_t wt_bytes, const bf16_t* Bt_kept, const LoraDma* dma,
-                            const bf16_t* Bpacked, const DecodeSync* sync, hipStream_t stream) {
+                            int n_chunks, const GemmFuse* fuse, int need_unfused, bf16_t* wt_scratch, size_t wt_bytes, const bf16_t* Bt_kept, const LoraDma* dma,
+                            const bf16_t* Bpacked, bool use_packed, const DecodeSync* sync, hipStream_t stream) {
   if (T <= 0 || Nout <= 0) return hipSuccess;
   if (ldb > (1 << 22)) return hipErrorInvalidValue;      // 32-bit byte offsets inside a weight tile
-  GemmPlan p = gemm_plan(T, Kc, Nout, fuse ? fuse->n_ext : 0);
+  const bool packed = Bpacked != nullptr && use_packed;
+  GemmPlan p = gemm_plan(T, Kc, Nout, fuse ? fuse->need : n_adapters > 0 ? need_unfused : 0, packed);
   // the caller skipped the shrink: the conditions of gemm_can_fuse_shrink() must hold
-  if (fuse && (!gemm_can_fuse_shrink(form, T, Kc, Nout, fuse->n_ext, fuse->ranks_mult8, partials ? partial_bytes : 0) || chunks == nullptr))
+  if (fuse && (!gemm_can_fuse_shrink(form, T, Kc, Nout, fuse->need, fuse->ranks_mult8, packed, partials ? partial_bytes : 0) || chunks == nullptr))
     return hipErrorInvalidValue;
   if (!fuse && (partials == nullptr || partial_bytes < p.bytes || (!p.wide && chunks == nullptr))) {
     p.wide = true;                                       // no scratch for partial sums
@@ -936,15 +946,13 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
   a.sync = nullptr; a.grp_ids = nullptr;
   if (fuse) {
     a.ext_cols = fuse->cols; a.ext_roff = fuse->roff; a.n_ext = fuse->n_ext;
-    a.ext_t0 = fuse->t0; a.ext_base = fuse->ext_base;
+    a.ext_t0 = fuse->t0; a.ext_base = fuse->ext_base; a.ext = fuse->rows;
     a.u_part = partials + p.bytes / sizeof(float); a.ldu = p.ldu; a.u_out = fuse->u_out;
     a.U = nullptr;
   }
   a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.ksplit = p.ksplit; a.kchunk = p.kchunk;
   a.ldp = p.ldp; a.pm = p.pm; a.partials = partials; a.chunks = chunks; a.n_chunks = n_chunks;
-  // a packed copy of the weight (and, when the shrink is fused, factors stored
-  // contraction-contiguous): the decode kernel reads the packed copy instead of Bop
-  const bool packed = Bpacked != nullptr && (fuse == nullptr || form == FORM_NT);
+  // a packed copy of the weight: the decode kernel reads it instead of Bop
   if (packed) {
     a.Bop = Bpacked; a.ldb = packed_weight_ksteps(Kc);
     a.fin_in_kernel = decode_finish_mode(sync, n_adapters, r_stride, p.tiles_m, p.tiles_n, p.ksplit);
@@ -955,6 +963,26 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
   return out_is_f32 ? launch_small<FORM_NN, true>(a, packed, stream) : launch_small<FORM_NN, false>(a, packed, stream);
 }
 
+// ---- few rows
+bool gemm_thin_ok(int form, int64_t T, bool lora, int r_stride, const DecodeSync* sync) {
+  return T > 0 && T <= THIN_ROWS && sync && sync->counters && (!lora || (form == FORM_NT && sync->grp_ids && r_stride <= 128)) &&
+         (sync->mode == DECODE_FINISH_AUTO || sync->mode == DECODE_FINISH_IN_KERNEL);
+}
+
+hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, int n_adapters,
+                                 const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
+                                 float* u, int r_stride, int max_tiles, const DecodeSync* sync, hipStream_t stream) {
+  if (n_proj < 1 || n_proj > MAX_PROJ) return hipErrorInvalidValue;
+  GemmArgs a;
+  memset(&a, 0, sizeof a);
+  a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.n_adapters = n_adapters; a.table = table; a.which = which;
+  a.u_part = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
+  a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit;
+  a.n_proj = n_proj; a.n_prod = n_adapters > 0 ? n_proj * max_tiles : 0;
+  for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
+  return launch_gemm_thin(a, stream);
+}
+
 // ---- several projections in one pass
 static int64_t multi_tiles(const ProjEntry* proj, int n_proj) {
   int64_t tiles = 0;
@@ -962,20 +990,27 @@ static int64_t multi_tiles(const ProjEntry* proj, int n_proj) {
   return tiles;
 }
 
+int gemm_multi_ext_room(const ProjEntry* proj_host, int n_proj) { return (int)multi_tiles(proj_host, n_proj) * SK_BX; }
+
 size_t gemm_multi_bytes(int64_t T, int64_t Kc, const ProjEntry* proj_host, int n_proj, int n_ext) {
   if (T <= 0 || n_proj <= 0) return 0;
-  const GemmPlan p = gemm_plan(T, Kc, multi_tiles(proj_host, n_proj) * SK_BN, n_ext, true);
-  return !p.wide ? p.bytes + p.u_bytes : 0;
+  const int room = gemm_multi_ext_room(proj_host, n_proj), need = n_ext < room ? n_ext : room;
+  size_t bytes = 0;
+  for (int packed = 0; packed < 2; ++packed) {
+    const GemmPlan p = gemm_plan(T, Kc, multi_tiles(proj_host, n_proj) * SK_BN, need, packed != 0, true);
+    if (!p.wide && p.bytes + p.u_bytes > bytes) bytes = p.bytes + p.u_bytes;
+  }
+  return bytes;
 }
 
-bool gemm_multi_ok(int form, int64_t T, int64_t Kc, const ProjEntry* proj_host, int n_proj, int n_ext,
-                   bool ranks_mult8, size_t partial_bytes) {
-  if (T <= 0 || n_proj < 2 || n_ext < 0) return false;
-  if (n_ext > 0 && form == FORM_NN && !ranks_mult8) return false;
+bool gemm_multi_ok(int form, int64_t T, int64_t Kc, const ProjEntry* proj_host, int n_proj, int need,
+                   bool ranks_mult8, bool packed, size_t partial_bytes) {
+  if (T <= 0 || n_proj < 2 || need < 0) return false;
+  if (need > 0 && form == FORM_NN && !ranks_mult8) return false;
   const int64_t tiles = multi_tiles(proj_host, n_proj);
   if (tiles * SK_BN > (1 << 24)) return false;
-  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, n_ext, true);
-  if (p.wide || (n_ext > 0 && p.u_bytes == 0)) return false;
+  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, need, packed, true);
+  if (p.wide || (need > 0 && p.u_bytes == 0)) return false;
   return partial_bytes >= p.bytes + p.u_bytes;
 }
 
@@ -986,12 +1021,12 @@ hipError_t launch_gemm_bf16_multi(const bf16_t* Aop, int64_t lda, int form, int6
                                   size_t partial_bytes, const RowChunk* chunks, int n_chunks,
                                   const GemmFuse* fuse, int packed, const DecodeSync* sync, int r_stride,
                                   hipStream_t stream) {
-  const int n_ext = fuse ? fuse->n_ext : 0;
-  if (!gemm_multi_ok(form, T, Kc, proj_host, n_proj, n_ext, fuse ? fuse->ranks_mult8 : true,
+  const int need = fuse ? fuse->need : 0;
+  if (!gemm_multi_ok(form, T, Kc, proj_host, n_proj, need, fuse ? fuse->ranks_mult8 : true, packed != 0,
                      partials ? partial_bytes : 0) || chunks == nullptr || n_proj > MAX_PROJ)
     return hipErrorInvalidValue;
   const int64_t tiles = multi_tiles(proj_host, n_proj);
-  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, n_ext, true);
+  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, need, packed != 0, true);
   GemmArgs a;
   a.Aop = Aop; a.lda = lda; a.Bop = (const bf16_t*)proj_host[0].W; a.ldb = proj_host[0].ldw;
   a.T = T; a.Kc = Kc; a.Nout = proj_host[0].Nout;
@@ -1002,8 +1037,8 @@ hipError_t launch_gemm_bf16_multi(const bf16_t* Aop, int64_t lda, int form, int6
   a.ext_cols = nullptr; a.ext_roff = nullptr; a.n_ext = 0; a.u_part = nullptr; a.ldu = 0; a.u_out = nullptr;
   a.ext_t0 = 0; a.ext_base = 0;
   if (fuse) {
-    a.ext_cols = fuse->cols; a.ext_roff = fuse->roff; a.n_ext = n_ext;
-    a.ext_t0 = fuse->t0; a.ext_base = fuse->ext_base;
+    a.ext_cols = fuse->cols; a.ext_roff = fuse->roff; a.n_ext = fuse->n_ext;
+    a.ext_t0 = fuse->t0; a.ext_base = fuse->ext_base; a.ext = fuse->rows;
     a.u_part = partials + p.bytes / sizeof(float); a.ldu = p.ldu;
   }
   memset(a.proj, 0, sizeof a.proj);

@@ -37,6 +37,7 @@
 //     trip in that tail costs 1 - 1.5 us and the whole comes out slower than the second launch,
 //     which is why it is not the default.
 #include "gemm_args.h"
+#include "agent_memory.h"
 
 #include <atomic>
 
@@ -70,13 +71,11 @@ extern "C" int marlaas_debug_decode_stamps(unsigned long long* host) {
 #define D_STAMP_CLEAR() do { } while (0)
 #endif
 
-// Waits on the vector-memory counter.  The weight fragments and the token indices are loaded by
+// Waits on the vector-memory counter (wait_vm).  The weight fragments and the token indices are loaded by
 // inline assembly, invisible to the compiler's own wait insertion (which, across the loop's
 // branches, would wait for every outstanding request before the first MFMA), so every wait on them
 // is written here: requests complete in order, and "at most n outstanding" means everything but
 // the n youngest has arrived.
-template <int N>
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 // n known at run time (wave-uniform); above 15 it waits as for 15, which is more than asked
 __device__ __forceinline__ void wait_vm_dyn(int n) {
   switch (n) {
@@ -97,18 +96,6 @@ __device__ __forceinline__ void wait_vm_dyn(int n) {
     case 14: wait_vm<14>(); break;
     default: wait_vm<15>(); break;
   }
-}
-
-// Memory shared between workgroups inside one launch (partial sums, u, counters) is accessed with
-// the agent-scope cache policy on the individual instruction (sc1: the access is performed at the
-// level all XCDs share), the way relaxed agent-scope atomics are: no write-back or invalidation of
-// a whole L2 is needed, which with 256 workgroups costs tens of microseconds.  A store is performed
-// once the vector-memory counter has counted it down.
-__device__ __forceinline__ void store4_agent(float* p, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void load4_agent(f32x4& v, const float* p) {     // complete after wait_vm<..>()
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
 }
 
 // src of the lane N places down in the 16-lane DPP row; `old` where the row has no such lane
@@ -203,8 +190,7 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
   uint64_t e_ptr = 0;
   int32_t e_q = 0;
   if (EXT && PHASE == 0) {
-    int e = tn * SK_BX + erow;
-    if (e >= a.n_ext) e = a.n_ext - 1;
+    const int e = ext_column(a, tm, tn * SK_BX + erow, 1);
     const char* ce = (const char*)(a.ext_cols + e);
     asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(e_ptr) : "v"(ce + (a.which ? 0 : 8)) : "memory");
     asm volatile("global_load_dword %0, %1, off" : "=v"(e_q) : "v"(ce + 20) : "memory");
@@ -363,7 +349,7 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
       rL_s[r] = on ? ent_L[j] : 0;
       rrank_s[r] = on ? (int32_t)(ent_rs[j] & 0xffffffffu) : 0;
       rscale_s[r] = on ? __uint_as_float((uint32_t)(ent_rs[j] >> 32)) : 0.f;
-      rroff_s[r] = ent_off[j] - a.ext_base;
+      rroff_s[r] = EXT ? ext_local(a, tm, p_idx, ent_off[j]) : 0;
     }
   }
   if (ntile > 0) {
@@ -429,9 +415,7 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
       }
       if (EXT && tid < 256) {
         const int row = tid >> 3;                  // 32 rows x 8 units
-        int e = tn * SK_BX + row;
-        if (e >= a.n_ext) e = a.n_ext - 1;
-        const ExtCol c = a.ext_cols[e];
+        const ExtCol c = a.ext_cols[ext_column(a, tm, tn * SK_BX + row, 1)];
         uint4 w = zero4;
         if (ka) w = *(const uint4*)((const bf16_t*)(a.which ? c.A : c.B) + (int64_t)c.q * a.Kc + k0 + lc * 8);
         *(uint4*)(smem + D_E_BASE + swz_rowk(row, lc)) = w;
@@ -539,7 +523,7 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
   const int tile_id = tm * a.tiles_n + tn;
   const int64_t fstride = (int64_t)ntiles_all * (SK_BM * SK_BN);          // floats between splits
   float* pf0 = a.partials + (int64_t)tile_id * (SK_BM * SK_BN) + lane * 4; // split 0, unit 0, column block 0
-  const bool carries = EXT && tn * SK_BX < a.n_ext;
+  const bool carries = EXT && tn * SK_BX < ext_carried(a, tm);
   if (PHASE == 0 && (a.ksplit > 1 || a.fin_in_kernel == 2)) {
     float* pf = pf0 + ks_idx * fstride;
 #pragma unroll
@@ -606,7 +590,8 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
   int32_t* done = a.sync + ntiles_all + tile_id;
   int32_t* u_ready = a.sync + 2 * ntiles_all + tm;
   int32_t* u_done = u_ready + a.tiles_m;
-  const int n_sig = (a.n_ext + SK_BX - 1) / SK_BX < a.tiles_n ? (a.n_ext + SK_BX - 1) / SK_BX : a.tiles_n;
+  const int n_car = (ext_carried(a, tm) + SK_BX - 1) / SK_BX;
+  const int n_sig = n_car < a.tiles_n ? n_car : a.tiles_n;
   const int u_need = n_sig * a.ksplit;
   const bool wants_u = EXT && lora_on;
   bool gave_up = false, u_ok = true;

@@ -1,0 +1,414 @@
+// Decode of few sequences (up to 64 rows) on the packed weight: the whole call in one launch.
+//
+//   out_p[tok(m), :] = x[tok(m), :] W_p  +  u_p(m) L_{t,p}        for every projection p of the call
+//
+// With few rows the weight is the traffic and the rest is latency: a 128-row tile (gemm_decode.hip)
+// multiplies mostly padding, cuts the contraction over workgroups to occupy the chip and pays a second
+// launch to add the pieces up (6 rows x 4096 x 4096: 17.9 + 6.9 us).  Here a workgroup owns all rows
+// times 16 NC output columns and its eight waves split the contraction, so a weight fragment is read
+// once, by the one wave that multiplies it, a wave requests 8 to 20 KB at a time, and the sums meet in
+// LDS.  x fragments come straight from L2 (for the row counts of this kernel no more bytes than the
+// weight).  Workgroups before the consumers ("producers") compute u: one per 16 ranks of an adapter
+// that has rows, the same loop over the adapter's factor in place of the weight.  They are scheduled
+// first and take as long as a consumer's loop, which then finds u ready: consumers wait for a counter,
+// with a bound, and recompute u themselves where it does not come in time, so no workgroup depends on
+// another one being scheduled.
+#include "gemm_args.h"
+#include "agent_memory.h"
+
+#include <atomic>
+
+namespace marlaas {
+
+static constexpr int TH_WAVES = 8, TH_THREADS = 64 * TH_WAVES;
+
+// R: 16-row blocks (T <= 16 R), NC: 16-column blocks per workgroup
+template <int R, int NC>
+__global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
+  constexpr int U = R + NC <= 2 ? 8 : R + NC <= 5 ? 4 : 2;      // k-steps requested together (twice: two sets of registers)
+  constexpr int TILES = R * NC;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  f32x4* red = (f32x4*)smem;                                    // [TH_WAVES][TILES][64]
+  float* u_s = (float*)(smem + TH_WAVES * TILES * 1024);        // [16 R][r_stride + 4]: the rows' u
+  const int us = a.r_stride + 4;
+  const int oct_max = 2 * a.r_stride;                           // octets (8 ranks of one adapter) a 16-row block can have
+  uint64_t* oct_L = (uint64_t*)(u_s + 16 * R * us);             // [R][oct_max]: address of the octet's ranks in row 0 of the factor
+  uint32_t* oct_tq = (uint32_t*)(oct_L + R * oct_max);           // adapter << 8 | first rank
+  int32_t* oct_r = (int32_t*)(oct_tq + R * oct_max);             // rank
+  uint64_t* rL_s = (uint64_t*)(oct_r + R * oct_max);             // per row: expand factor,
+  int32_t* tok_s = (int32_t*)(rL_s + 16 * R);                   // token (-1: past the end),
+  int32_t* t_s = tok_s + 16 * R;                                // adapter (-1: none),
+  int32_t* rank_s = t_s + 16 * R;                               // rank
+  int32_t* cnt_s = rank_s + 16 * R;                             // [R] octets (-1: plain expand); [R]: u is ready
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  const bool lora = a.n_adapters > 0 && a.table != nullptr;
+  const int b = blockIdx.x;
+  const bool producer = b < a.n_prod;
+  // the projection of this workgroup, and its first column
+  int p = 0;
+  int64_t n0 = 0;
+  if (producer) {
+    p = b / (a.n_prod / a.n_proj);
+  } else {
+    const int c = b - a.n_prod;
+    for (int q = 1; q < a.n_proj; ++q) if (c >= a.proj[q].tile0) p = q;
+    n0 = (int64_t)(c - a.proj[p].tile0) * (16 * NC);
+  }
+  const int64_t Nout = a.proj[p].Nout, ldb = a.proj[p].ldw;
+  const AdapterEntry* table = a.table + a.proj[p].tab0;
+  // counters of this projection, all zero between launches: producers whose u is performed, workgroups
+  // that are through with the counters (the last one clears both)
+  int32_t* ready = a.sync + 2 * p;
+  int32_t* done = ready + 1;
+  const int prods = a.n_prod / a.n_proj;
+  const int everyone = prods + (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
+  auto leave = [&]() {
+    if (__hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == everyone - 1) {
+      __hip_atomic_store(ready, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  };
+  float* u_p = a.u_part + (int64_t)p * a.T * a.r_stride;        // scaled u, [T][r_stride]
+
+  // this wave's part of the contraction, in 32-deep steps
+  const int steps = (int)((a.Kc + 31) >> 5), per = (steps + TH_WAVES - 1) / TH_WAVES;
+  const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
+
+  // tokens of the rows this lane supplies; adapter, and its entry, of row `lane`
+  int32_t tokr[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int64_t m = 16 * i + li < a.T ? 16 * i + li : a.T - 1;
+    tokr[i] = a.perm ? a.perm[m] : (int32_t)m;
+  }
+  int g = -1, g_before = -1;
+  if (lora && (producer || wave == 0) && lane < a.T && lane < 16 * R) {
+    g = a.grp_ids[lane];
+    if (lane > 0) g_before = a.grp_ids[lane - 1];
+  }
+
+#define TH_X(dst_, i_, ks_)                                                                               \
+  do {                                                                                                    \
+    const int64_t _k = (int64_t)(ks_) * 32 + 8 * lg;                                                      \
+    dst_ = make_uint4(0, 0, 0, 0);                                                                        \
+    if ((ks_) < s1 && _k < a.Kc) dst_ = *(const uint4*)(a.Aop + (int64_t)tokr[i_] * a.lda + _k);          \
+  } while (0)
+  union Frag { uint4 u; bf16x8 v; };
+
+  if (producer) {
+    AdapterEntry e;
+    e.A = e.B = nullptr; e.rank = 0; e.scale = 0.f;
+    if (g >= 0) e = table[g];
+    // the 16-rank tiles of the adapters in row order: a lane per row, the first row of an adapter counts
+    const int tiles = g >= 0 && g != g_before ? (e.rank + 15) >> 4 : 0;
+    int inc = tiles;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
+    const int j = b - p * prods;
+    const uint64_t hit = __ballot(inc - tiles <= j && j < inc);
+    if (hit == 0) {                                             // (the grid is sized for any grouping of T rows)
+      if (tid == 0) leave();
+      return;
+    }
+    const int row0 = __ffsll((unsigned long long)hit) - 1;
+    const int t = __builtin_amdgcn_readlane(g, row0);
+    const int q0 = (j - __builtin_amdgcn_readlane(inc - tiles, row0)) * 16;
+    const int r = __builtin_amdgcn_readlane(e.rank, row0);
+    const float scale = __shfl(e.scale, row0);
+    const int row1 = row0 + __popcll(__ballot(g == t));         // rows [row0, row1) are this adapter's
+    const uint64_t fp = (uint64_t)(uintptr_t)(a.which ? e.A : e.B);
+    const bf16_t* L = (const bf16_t*)(((uint64_t)(uint32_t)__shfl((int)(fp >> 32), row0) << 32) | (uint32_t)__shfl((int)fp, row0));
+    const bool row_in = q0 + li < r;
+    const bf16_t* lrow = L + (int64_t)(row_in ? q0 + li : 0) * a.Kc;
+#pragma unroll 1
+    for (int rb = row0 >> 4; rb <= (row1 - 1) >> 4; ++rb) {
+      int32_t tk = tokr[0];
+#pragma unroll
+      for (int i = 1; i < R; ++i) if (rb == i) tk = tokr[i];
+      const bf16_t* xrow = a.Aop + (int64_t)tk * a.lda;
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int s = s0; s < s1; s += 8) {
+        Frag xf[8], lf[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int64_t k = (int64_t)(s + i) * 32 + 8 * lg;
+          xf[i].u = lf[i].u = make_uint4(0, 0, 0, 0);
+          if (s + i < s1 && k < a.Kc) {
+            xf[i].u = *(const uint4*)(xrow + k);
+            if (row_in) lf[i].u = *(const uint4*)(lrow + k);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lf[i].v, xf[i].v, acc, 0, 0, 0);
+      }
+      red[wave * 64 + lane] = acc;
+      __syncthreads();
+      if (wave == 0) {
+        f32x4 s = red[lane];
+#pragma unroll
+        for (int w = 1; w < TH_WAVES; ++w) {
+          const f32x4 o = red[w * 64 + lane];
+          s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
+        }
+        // lane: row li of the block, ranks q0 + 4 lg .. + 3
+        const int row = rb * 16 + li;
+        if (row >= row0 && row < row1) {
+          s[0] *= scale; s[1] *= scale; s[2] *= scale; s[3] *= scale;
+          store4_agent(u_p + (int64_t)row * a.r_stride + q0 + 4 * lg, s);
+        }
+        wait_vm<0>();
+      }
+      __syncthreads();
+    }
+    if (tid == 0) {
+      __hip_atomic_fetch_add(ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      leave();
+    }
+    return;
+  }
+
+  // ---- consumers.  Column block c of this workgroup is block n0 / 16 + c of the packed weight
+  // (blocks past the last one repeat it: those columns are never stored)
+  const bf16_t* wp[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int64_t blocks = (Nout + 15) >> 4;
+    int64_t nb = (n0 >> 4) + c;
+    if (nb >= blocks) nb = blocks - 1;
+    wp[c] = (const bf16_t*)a.proj[p].W + ((nb * ldb) << 9) + lane * 8;
+  }
+#define TH_LOAD(set_, s_)                                                                                 \
+  do {                                                                                                    \
+    _Pragma("unroll") for (int _u = 0; _u < U; ++_u) {                                                    \
+      _Pragma("unroll") for (int _c = 0; _c < NC; ++_c) {                                                 \
+        set_[_u][R + _c].u = make_uint4(0, 0, 0, 0);                                                      \
+        if ((s_) + _u < s1) set_[_u][R + _c].u = *(const uint4*)(wp[_c] + (int64_t)((s_) + _u) * 512);    \
+      }                                                                                                   \
+      _Pragma("unroll") for (int _i = 0; _i < R; ++_i) TH_X(set_[_u][_i].u, _i, (s_) + _u);               \
+    }                                                                                                     \
+  } while (0)
+#define TH_MMA(set_)                                                                                      \
+  do {                                                                                                    \
+    _Pragma("unroll") for (int _u = 0; _u < U; ++_u)                                                      \
+      _Pragma("unroll") for (int _i = 0; _i < R; ++_i)                                                    \
+        _Pragma("unroll") for (int _c = 0; _c < NC; ++_c)                                                 \
+          acc[_i][_c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(set_[_u][R + _c].v, set_[_u][_i].v, acc[_i][_c], 0, 0, 0); \
+  } while (0)
+  f32x4 acc[R][NC];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  {
+    Frag fa[U][R + NC], fb[U][R + NC];
+    TH_LOAD(fa, s0);
+    if (wave == 0) {
+      // while those travel: the rows' tables, and per 16-row block the octets of its adapters (a lane
+      // per row; the first row of an adapter in the block appends the adapter's octets)
+      AdapterEntry e;
+      e.A = e.B = nullptr; e.rank = 0; e.scale = 0.f;
+      if (g >= 0) e = table[g];
+      const bool first = g >= 0 && (g != g_before || li == 0);
+      const int n_oct = first ? e.rank >> 3 : 0;
+      int inc = n_oct, bad = g >= 0 && (e.rank & 7) ? 1 : 0;
+#pragma unroll
+      for (int d = 1; d < 16; d <<= 1) { const int v = __shfl_up(inc, d, 16), w = __shfl_up(bad, d, 16); if (li >= d) { inc += v; bad |= w; } }
+      const uint64_t Lp = (uint64_t)(uintptr_t)(a.which ? e.B : e.A);
+      if (lane < 16 * R) {
+        tok_s[lane] = lane < a.T ? (a.perm ? a.perm[lane] : lane) : -1;
+        t_s[lane] = g; rank_s[lane] = e.rank; rL_s[lane] = Lp;
+        for (int q = 0, o = lg * oct_max + inc - n_oct; q < 8 * n_oct; q += 8, ++o) {
+          oct_L[o] = Lp + (uint64_t)q * sizeof(bf16_t);
+          oct_tq[o] = (uint32_t)g << 8 | q;
+          oct_r[o] = e.rank;
+        }
+        if (li == 15) cnt_s[lg] = a.lform == FORM_NT && bad == 0 ? inc : -1;
+      }
+      // the number of producers that have something to produce
+      int tiles = g >= 0 && g != g_before ? (e.rank + 15) >> 4 : 0;
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) tiles += __shfl_xor(tiles, d);
+      if (lane == 0) cnt_s[R] = tiles;
+    }
+    for (int s = s0; s < s1; s += 2 * U) {
+      if (s + U < s1) TH_LOAD(fb, s + U);
+      TH_MMA(fa);
+      if (s + U < s1) {
+        if (s + 2 * U < s1) TH_LOAD(fa, s + 2 * U);
+        TH_MMA(fb);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) red[(wave * TILES + i * NC + c) * 64 + lane] = acc[i][c];
+  __syncthreads();
+  constexpr int MINE = (TILES + TH_WAVES - 1) / TH_WAVES;       // output tiles finished by a wave
+  f32x4 y[MINE];
+#pragma unroll
+  for (int k = 0; k < MINE; ++k) {
+    const int tile = wave + k * TH_WAVES;
+    if (tile >= TILES) break;
+    f32x4 s = red[tile * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < TH_WAVES; ++w) {
+      const f32x4 o = red[(w * TILES + tile) * 64 + lane];
+      s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
+    }
+    y[k] = s;
+  }
+
+  if (lora) {
+    // the first octets' factor fragments depend on nothing that has to be waited for
+    Frag pre[MINE];
+#pragma unroll
+    for (int k = 0; k < MINE; ++k) {
+      const int tile = wave + k * TH_WAVES, rb = tile / NC, c = tile - rb * NC;
+      pre[k].u = make_uint4(0, 0, 0, 0);
+      if (tile < TILES && lg < cnt_s[rb]) {
+        const int64_t n = n0 + c * 16 + li;
+        const int o = rb * oct_max + lg;
+        if (n < Nout) pre[k].u = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
+      }
+    }
+    if (tid == 0) {
+      const int need = cnt_s[R];
+      int ok = need == 0;
+      for (int it = 0; it < a.spin_limit && !ok; ++it) {
+        ok = __hip_atomic_load(ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need;
+        if (!ok) __builtin_amdgcn_s_sleep(1);
+      }
+      cnt_s[R] = ok;
+    }
+    __syncthreads();
+    const bool u_ok = cnt_s[R] != 0;
+    for (int i = tid; i < 16 * R * (a.r_stride >> 2); i += TH_THREADS) {
+      const int row = i / (a.r_stride >> 2), q = (i - row * (a.r_stride >> 2)) * 4;
+      const int rank = t_s[row] >= 0 ? rank_s[row] : 0;
+      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (q < rank) {
+        if (u_ok) {
+          asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(u_p + (int64_t)row * a.r_stride + q) : "memory");
+        } else {
+          // (not reached in practice) the shrink of this row again, in plain fp32 arithmetic
+          const AdapterEntry en = table[t_s[row]];
+          const bf16_t* xr = a.Aop + (int64_t)tok_s[row] * a.lda;
+          for (int j = 0; j < 4 && q + j < rank; ++j) {
+            const bf16_t* lr = (const bf16_t*)(a.which ? en.A : en.B) + (int64_t)(q + j) * a.Kc;
+            float sum = 0.f;
+            for (int64_t k = 0; k < a.Kc; ++k) sum = fmaf(bf16_bits_to_float(xr[k]), bf16_bits_to_float(lr[k]), sum);
+            v[j] = en.scale * sum;
+          }
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
+      *(f32x4*)(u_s + row * us + q) = v;
+    }
+    __syncthreads();
+    if (tid == 0) leave();
+#pragma unroll
+    for (int k = 0; k < MINE; ++k) {
+      const int tile = wave + k * TH_WAVES, rb = tile / NC, c = tile - rb * NC;
+      if (tile >= TILES) break;
+      const int row = rb * 16 + li, cnt = cnt_s[rb];
+      if (cnt >= 0) {
+        // expand on the MFMAs: first operand 16 columns x 4 octets of the factors, second the rows' u in
+        // two bf16 terms (zeros where the octet is another adapter's)
+        for (int k0 = 0; k0 < cnt; k0 += 4) {
+          const bool valid = k0 + lg < cnt;
+          const int o = rb * oct_max + (valid ? k0 + lg : 0);
+          Frag f = pre[k];
+          if (k0 > 0) {
+            const int64_t n = n0 + c * 16 + li;
+            f.u = make_uint4(0, 0, 0, 0);
+            if (valid && n < Nout) f.u = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
+          }
+          const bool mine = valid && t_s[row] == (int)(oct_tq[o] >> 8);
+          const float* ur = u_s + row * us + (oct_tq[o] & 255);
+          const f32x4 ua = *(const f32x4*)ur, ub = *(const f32x4*)(ur + 4);
+          const float uv[8] = {ua[0], ua[1], ua[2], ua[3], ub[0], ub[1], ub[2], ub[3]};
+          union { uint32_t w[4]; bf16x8 v; } hi, lo;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v0 = mine ? uv[2 * e] : 0.f, v1 = mine ? uv[2 * e + 1] : 0.f;
+            const uint32_t h0 = float_to_bf16_bits(v0), h1 = float_to_bf16_bits(v1);
+            hi.w[e] = h0 | (h1 << 16);
+            lo.w[e] = float_to_bf16_bits(v0 - __uint_as_float(h0 << 16)) | ((uint32_t)float_to_bf16_bits(v1 - __uint_as_float(h1 << 16)) << 16);
+          }
+          y[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, lo.v, y[k], 0, 0, 0);
+          y[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, hi.v, y[k], 0, 0, 0);
+        }
+      } else if (t_s[row] >= 0) {
+        // ranks that are no multiples of 8, or factors stored rank-major: plain fp32 expand of this lane's row
+        const int rank = rank_s[row];
+        const bf16_t* L = (const bf16_t*)(uintptr_t)rL_s[row];
+        const int64_t n = n0 + c * 16 + 4 * lg;
+        if (n < Nout)
+          for (int q = 0; q < rank; ++q) {
+            const float uq = u_s[row * us + q];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              y[k][v] = fmaf(uq, bf16_bits_to_float(a.lform == FORM_NT ? L[(n + v) * rank + q] : L[(int64_t)q * Nout + n + v]), y[k][v]);
+          }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < MINE; ++k) {
+    const int tile = wave + k * TH_WAVES, rb = tile / NC, c = tile - rb * NC;
+    if (tile >= TILES) break;
+    const int32_t tok = tok_s[rb * 16 + li];
+    const int64_t n = n0 + c * 16 + 4 * lg;
+    if (tok < 0 || n >= Nout) continue;            // (Nout is a multiple of 8: four columns are in or out together)
+    if (a.out_is_f32) {
+      *(f32x4*)((float*)a.proj[p].out + (int64_t)tok * a.proj[p].ldo + n) = y[k];
+    } else {
+      uint2 o;
+      o.x = float_to_bf16_bits(y[k][0]) | ((uint32_t)float_to_bf16_bits(y[k][1]) << 16);
+      o.y = float_to_bf16_bits(y[k][2]) | ((uint32_t)float_to_bf16_bits(y[k][3]) << 16);
+      *(uint2*)((bf16_t*)a.proj[p].out + (int64_t)tok * a.proj[p].ldo + n) = o;
+    }
+  }
+}
+
+template <int R, int NC>
+static hipError_t launch_thin(const GemmArgs& a, hipStream_t stream) {
+  const size_t lds = (size_t)TH_WAVES * R * NC * 1024 + (size_t)16 * R * (a.r_stride + 4) * sizeof(float) +
+                     (size_t)R * 2 * a.r_stride * 16 + (size_t)16 * R * 20 + (R + 1) * 4 + 64;
+  static std::atomic<uint64_t> done_dev{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (!(done_dev.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute((const void*)gemm_thin_kernel<R, NC>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    done_dev.fetch_or(bit, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((gemm_thin_kernel<R, NC>), dim3(a.n_prod + a.tiles_n), dim3(TH_THREADS), lds, stream, a);
+  return hipGetLastError();
+}
+
+// Column blocks per workgroup: one while that keeps the launch near one workgroup per compute unit,
+// then two, then (up to 32 rows: registers) four, which reads x half and a quarter as often.
+hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream) {
+  const int R = a.T <= 16 ? 1 : a.T <= 32 ? 2 : 4;
+  int64_t blocks = 0;
+  for (int p = 0; p < a.n_proj; ++p) blocks += (a.proj[p].Nout + 15) / 16;
+  int nc = blocks <= 320 ? 1 : blocks <= 640 || R == 4 ? 2 : 4;
+  a.tiles_n = 0;
+  for (int p = 0; p < a.n_proj; ++p) {
+    a.proj[p].tile0 = a.tiles_n;
+    a.tiles_n += (int)((a.proj[p].Nout + 16 * nc - 1) / (16 * nc));
+  }
+#define TH_PICK(R_) (nc == 1 ? launch_thin<R_, 1>(a, stream) : launch_thin<R_, 2>(a, stream))
+  if (nc == 4) return R == 1 ? launch_thin<1, 4>(a, stream) : launch_thin<2, 4>(a, stream);
+  return R == 1 ? TH_PICK(1) : R == 2 ? TH_PICK(2) : TH_PICK(4);
+#undef TH_PICK
+}
+
+}  // namespace marlaas

@@ -427,7 +427,7 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
     }
     for (int v = 0; v < 4; ++v) {
       const int mr = row0 + 4 * g + v;
-      if (mr < hi) a.u[(int64_t)mr * a.r_stride + qt * 16 + li] = e.scale * sum[v];
+      if (mr < hi) shrink_store(a, mr, qt * 16 + li, r_pad, e.scale * sum[v]);
     }
   }
 }
@@ -480,7 +480,8 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
   a.partials = nullptr; a.T_lora = T_lora; a.u2 = nullptr; a.zero_line = zero_line;
   const int64_t real_blocks = (T_lora + SH_ROWS - 1) / SH_ROWS + n_adapters;
   if (lora_form == FORM_NT && real_blocks <= 96) {
-    a.ksplit = 1; a.kchunk = 0;
+    a.ksplit = 1; a.kchunk = 0; a.u2 = u2;
+    if (wrote_u2) *wrote_u2 = u2 != nullptr;
     const size_t lds = (size_t)SS_WAVES * (r_stride / 16) * 64 * sizeof(f32x4);
     hipLaunchKernelGGL(shrink_small_nt_kernel<0>, dim3((max_seg + 15) / 16, n_adapters), dim3(64 * SS_WAVES), lds,
                        stream, a);

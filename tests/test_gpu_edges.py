@@ -61,3 +61,23 @@ def test_large_batch_gemm_edges(oracle, T, K, N, ranks, odd, layout):
     w = wl.make_layer(T + K, T, K, N, ranks, [0.5 + (t % 3) for t in range(len(ranks))], ids, dtype="bf16", layout=layout, want_dY=True)
     _check_layer(oracle, w, bwd=True, tag="wide")
     _check_layer(oracle, w, bwd=True, out_dtype=torch.bfloat16, tol=(1e-2, 2.5e-3), tag="wide bf16 out")
+
+
+# Few rows on packed weights (one launch): row blocks of 16, 32 and 64, one to four column blocks per
+# workgroup, contractions shorter than the waves' shares and no multiple of 32, ranks off the octets,
+# adapters whose rows cross a row block, every row its own adapter, the bounded wait given up at once.
+@pytest.mark.parametrize("spin", [None, "0"])
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,K,N,ranks", [(1, 8, 8, [8]), (16, 1032, 264, [16] * 20), (17, 264, 6152, [128, 64, 8]), (32, 520, 12296, [24, 16]),
+                                         (33, 2056, 1032, [8 + 8 * (t % 4) for t in range(40)]), (64, 4096, 4096, [16, 32]), (64, 296, 6160, [5, 13, 7])])
+def test_few_rows_packed(oracle, monkeypatch, T, K, N, ranks, layout, spin):
+    if spin is not None:
+        monkeypatch.setenv("MARLAAS_SPIN_LIMIT", spin)
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    if layout:
+        ids = np.sort(ids)
+    w = wl.make_layer(T + N, T, K, N, ranks, [0.5 + (t % 3) for t in range(len(ranks))], ids, dtype="bf16", layout=layout, want_dY=True)
+    for rep in range(2):
+        _check_layer(oracle, w, bwd=True, tag="few rows", table="table+packed")
+    _check_layer(oracle, w, bwd=True, tag="few rows", table="lists+packed")
