@@ -26,7 +26,7 @@ struct marlaas_ctx {
   void* ws = nullptr;
   size_t ws_bytes = 0;
   void* static_ws = nullptr;     // device address of this GPU's static scratch array
-  int32_t* sync_dev = nullptr;   // counters of the decode kernel (zero between launches)
+  int32_t* sync_dev = nullptr;   // counters of the decode kernels, then u of the few-row kernel (zero between launches)
   int cu_count = 0;
   int spin_limit = 1 << 20;
   void* zero_dev = nullptr;    // 256 zero bytes (what masked DMA lanes fetch)
@@ -173,8 +173,8 @@ extern "C" int marlaas_create(marlaas_ctx** out, int device) {
   ctx->static_ws = sp;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->cu_count = prop.multiProcessorCount;
-  if (hipMalloc((void**)&ctx->sync_dev, DECODE_SYNC_INTS * sizeof(int32_t)) != hipSuccess ||
-      hipMemset(ctx->sync_dev, 0, DECODE_SYNC_INTS * sizeof(int32_t)) != hipSuccess ||
+  if (hipMalloc((void**)&ctx->sync_dev, (DECODE_SYNC_INTS + THIN_U_FLOATS) * sizeof(int32_t)) != hipSuccess ||
+      hipMemset(ctx->sync_dev, 0, (DECODE_SYNC_INTS + THIN_U_FLOATS) * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&ctx->zero_dev, 256) != hipSuccess || hipMemset(ctx->zero_dev, 0, 256) != hipSuccess) {
     (void)hipFree(ctx->zero_dev);
     (void)hipFree(ctx->sync_dev);
@@ -855,7 +855,7 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
     memset(&pe, 0, sizeof pe);
     pe.W = d->W_packed_fwd; pe.ldw = packed_weight_ksteps(d->d_in); pe.Nout = d->d_out; pe.out = y; pe.ldo = ldy;
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_thin((const bf16_t*)d->x, d->ldx, form, d->T, d->d_in, perm, lora ? d->n_adapters : 0,
-                                  table, 1, &pe, 1, out_f32, u, rs, lora ? max_rank_tiles(d) : 0, &dsync, st));
+                                  table, 1, &pe, 1, out_f32, (float*)u_save, rs, lora ? max_rank_tiles(d) : 0, &dsync, st));
   } else if (d->in_dtype == MARLAAS_BF16) {
     // small batches: the GEMM computes the shrink itself and no shrink kernel runs
     GemmFuse fuse;
@@ -1021,8 +1021,7 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
   const DecodeSync dsync = decode_sync_of(ctx, map);
   int rs_all = 0;
   for (int p = 0; p < n_proj; ++p) { const int r = (int)marlaas_u_stride(&descs[p]); if (r > rs_all) rs_all = r; }
-  if (packed && n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && (!lora || shared) && gemm_thin_ok(form, d0->T, lora, rs_all, &dsync) &&
-      ctx->ws_bytes >= (size_t)n_proj * d0->T * rs_all * sizeof(float)) {
+  if (packed && n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && (!lora || shared) && gemm_thin_ok(form, d0->T, lora, rs_all, &dsync)) {
     // few rows: everything in one launch
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     int tiles = 0;
@@ -1033,7 +1032,7 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
     hipStream_t thin_st = (hipStream_t)stream;
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, thin_st, launch_gemm_bf16_thin((const bf16_t*)d0->x, d0->ldx, form, d0->T, d0->d_in, map->identity ? nullptr : map->perm_dev,
                                        lora ? d0->n_adapters : 0, lora ? d0->table->dev.entries : nullptr, 1, proj.data(), n_proj,
-                                       d0->out_dtype == MARLAAS_F32, (float*)ctx->ws, rs_all, tiles, &dsync, thin_st));
+                                       d0->out_dtype == MARLAAS_F32, nullptr, rs_all, tiles, &dsync, thin_st));
     return MARLAAS_OK;
   }
   // descriptors that refer to tables, but not to one table in projection order, have no combined tables

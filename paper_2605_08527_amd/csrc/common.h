@@ -177,6 +177,9 @@ struct DecodeSync {
   int cu_count = 0;
 };
 static constexpr int DECODE_SYNC_INTS = 4096;
+static constexpr int THIN_ROWS = 64;                              // rows of the few-row kernel (gemm_thin.hip)
+static constexpr int THIN_SPLITS = 4;
+static constexpr int THIN_U_FLOATS = MAX_PROJ * THIN_SPLITS * THIN_ROWS * 128;   // what it hands u over in, follows the counters
 
 // What lets the large-batch GEMM fetch the expand's operands by DMA: u (or v) as a two-term bf16
 // split written by the shrink, scratch for the row tiles' lists of extra contraction tiles
@@ -216,8 +219,8 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
 // shrink is only fused when the adapters' factors are stored contraction-contiguous, which the
 // caller says by passing fuse only then.)
 // A call of few rows on packed weights (gemm_thin.hip): all of it, shrink included, in one launch.
-// proj: the call's projections (W packed copies, ldw their k-steps), table: [projection][adapter], u:
-// [n_proj][T][r_stride] fp32, receives u; max_tiles: the most 16-rank tiles the adapters of T rows can
+// proj: the call's projections (W packed copies, ldw their k-steps), table: [projection][adapter], u
+// (one projection; may be null): [T][r_stride] fp32, receives u; max_tiles: the most 16-rank tiles the adapters of T rows can
 // have in any projection.
 bool gemm_thin_ok(int form, int64_t T, bool lora, int r_stride, const DecodeSync* sync);
 hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, int n_adapters,

@@ -49,7 +49,8 @@ struct GemmArgs {
   int32_t* sync;
   const int32_t* grp_ids;
   ExtRows ext;                  // the row tiles' shares of the extended columns
-  int n_prod;                   // few-row kernel: workgroups that compute u (a multiple of n_proj)
+  int n_prod, n_split;          // few-row kernel: workgroups that compute u (a multiple of n_proj n_split), the splits of their contraction,
+  float* thin_u;                // and where it travels: [MAX_PROJ][THIN_SPLITS][THIN_ROWS][128], zero between launches
   ProjEntry proj[MAX_PROJ];     // by value: read with wave-uniform loads from the kernel arguments
 };
 
@@ -146,10 +147,9 @@ static constexpr int SK_BM = 128, SK_BN = 128, SK_BX = 32;
 hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t stream);
 
 // Few rows (T <= THIN_ROWS) on packed weights, one launch (gemm_thin.hip): every ProjEntry filled in
-// (also for one projection; W packed, ldw its k-steps, tile0 set here), u_part = [n_proj][T][r_stride]
-// fp32 that receives the scaled u, sync = counters, n_prod = n_proj times the most 16-rank tiles that
+// (also for one projection; W packed, ldw its k-steps, tile0 set here), u_out = [T][r_stride] fp32 that
+// receives the scaled u (one projection; may be null), sync = counters, n_prod = n_proj times the most 16-rank tiles that
 // any grouping of T rows can use.  Factors of the shrink stored contraction-contiguous.
-static constexpr int THIN_ROWS = 64;
 hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream);
 
 }  // namespace marlaas

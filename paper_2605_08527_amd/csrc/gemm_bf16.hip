@@ -976,8 +976,9 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
   GemmArgs a;
   memset(&a, 0, sizeof a);
   a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.n_adapters = n_adapters; a.table = table; a.which = which;
-  a.u_part = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
+  a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
   a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit;
+  a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
   a.n_proj = n_proj; a.n_prod = n_adapters > 0 ? n_proj * max_tiles : 0;
   for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
   return launch_gemm_thin(a, stream);

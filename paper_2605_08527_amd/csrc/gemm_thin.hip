@@ -10,9 +10,12 @@
 // LDS.  x fragments come straight from L2 (for the row counts of this kernel no more bytes than the
 // weight).  Workgroups before the consumers ("producers") compute u: one per 16 ranks of an adapter
 // that has rows, the same loop over the adapter's factor in place of the weight.  They are scheduled
-// first and take as long as a consumer's loop, which then finds u ready: consumers wait for a counter,
-// with a bound, and recompute u themselves where it does not come in time, so no workgroup depends on
-// another one being scheduled.
+// first and take little longer than a consumer's loop.  Every round trip through the fabric costs 1 to
+// 1.5 us, so u carries its own flag: it travels through an area of the context that is all zero bits
+// between launches, no value of u is stored as zero bits (+0 becomes -0), and a consumer reads its rows'
+// u until nothing is zero bits any more.  The reading is bounded; a consumer that does not get a value in
+// time computes it itself, so no workgroup depends on another one being scheduled.  The workgroup that is
+// last through with the area clears what was used of it.
 #include "gemm_args.h"
 #include "agent_memory.h"
 
@@ -22,10 +25,12 @@ namespace marlaas {
 
 static constexpr int TH_WAVES = 8, TH_THREADS = 64 * TH_WAVES;
 
+// Registers are held to what lets two workgroups share a compute unit: with one each, a launch of one
+// consumer per unit and a single producer took a second round of workgroups (1 row, 8 us against 15).
 // R: 16-row blocks (T <= 16 R), NC: 16-column blocks per workgroup
 template <int R, int NC>
-__global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
-  constexpr int U = R + NC <= 2 ? 8 : R + NC <= 5 ? 4 : 2;      // k-steps requested together (twice: two sets of registers)
+__global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
+  constexpr int U = R + NC <= 2 ? 4 : R + NC <= 3 ? 3 : R + NC <= 5 ? 2 : 1;   // k-steps requested together (twice: two sets of registers)
   constexpr int TILES = R * NC;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   f32x4* red = (f32x4*)smem;                                    // [TH_WAVES][TILES][64]
@@ -39,7 +44,7 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
   int32_t* tok_s = (int32_t*)(rL_s + 16 * R);                   // token (-1: past the end),
   int32_t* t_s = tok_s + 16 * R;                                // adapter (-1: none),
   int32_t* rank_s = t_s + 16 * R;                               // rank
-  int32_t* cnt_s = rank_s + 16 * R;                             // [R] octets (-1: plain expand); [R]: u is ready
+  int32_t* cnt_s = rank_s + 16 * R;                             // [R] octets (-1: plain expand)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
@@ -58,23 +63,30 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
   }
   const int64_t Nout = a.proj[p].Nout, ldb = a.proj[p].ldw;
   const AdapterEntry* table = a.table + a.proj[p].tab0;
-  // counters of this projection, all zero between launches: producers whose u is performed, workgroups
-  // that are through with the counters (the last one clears both)
-  int32_t* ready = a.sync + 2 * p;
-  int32_t* done = ready + 1;
-  const int prods = a.n_prod / a.n_proj;
+  // workgroups that are through with this projection's u, and its u: [split][T][r_stride], scaled; both
+  // all zero bits between launches
+  int32_t* done = a.sync + p;
+  float* u_p = a.thin_u + p * (THIN_SPLITS * THIN_ROWS * 128);
+  const int S = a.n_split, u_n = (int)a.T * a.r_stride;         // (u_n: floats of one split)
+  const int prods = a.n_proj > 0 ? a.n_prod / a.n_proj : 0;
   const int everyone = prods + (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
+  // (called by one whole wave whose requests are complete)
   auto leave = [&]() {
-    if (__hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == everyone - 1) {
-      __hip_atomic_store(ready, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(old) == everyone - 1) {
+      for (int i = lane; i < S * (u_n >> 2); i += 64) store4_agent(u_p + i * 4, f32x4{0.f, 0.f, 0.f, 0.f});
+      if (lane == 0) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
-  float* u_p = a.u_part + (int64_t)p * a.T * a.r_stride;        // scaled u, [T][r_stride]
 
   // this wave's part of the contraction, in 32-deep steps
-  const int steps = (int)((a.Kc + 31) >> 5), per = (steps + TH_WAVES - 1) / TH_WAVES;
-  const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
+  // (a producer's is cut over S workgroups first: its loads are row pieces from all over the factor, and
+  // what it takes is their latency times the rounds of them)
+  const int steps = (int)((a.Kc + 31) >> 5), S_here = producer ? S : 1;
+  const int part = (steps + S_here - 1) / S_here, p0 = producer ? b % S * part : 0, p1 = p0 + part < steps ? p0 + part : steps;
+  const int per = (part + TH_WAVES - 1) / TH_WAVES;
+  const int s0 = p0 + wave * per, s1 = s0 + per < p1 ? s0 + per : p1;
 
   // tokens of the rows this lane supplies; adapter, and its entry, of row `lane`
   int32_t tokr[R];
@@ -106,10 +118,10 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
     int inc = tiles;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
-    const int j = b - p * prods;
+    const int j = (b - p * prods) / S;
     const uint64_t hit = __ballot(inc - tiles <= j && j < inc);
     if (hit == 0) {                                             // (the grid is sized for any grouping of T rows)
-      if (tid == 0) leave();
+      if (wave == 0) leave();
       return;
     }
     const int row0 = __ffsll((unsigned long long)hit) - 1;
@@ -122,50 +134,65 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
     const bf16_t* L = (const bf16_t*)(((uint64_t)(uint32_t)__shfl((int)(fp >> 32), row0) << 32) | (uint32_t)__shfl((int)fp, row0));
     const bool row_in = q0 + li < r;
     const bf16_t* lrow = L + (int64_t)(row_in ? q0 + li : 0) * a.Kc;
-#pragma unroll 1
-    for (int rb = row0 >> 4; rb <= (row1 - 1) >> 4; ++rb) {
-      int32_t tk = tokr[0];
+    const int rb0 = row0 >> 4, rb1 = (row1 - 1) >> 4;           // its row blocks
+    constexpr int UP = R == 1 ? 4 : R == 2 ? 3 : 2;             // steps requested together (twice)
+    f32x4 pacc[R];
 #pragma unroll
-      for (int i = 1; i < R; ++i) if (rb == i) tk = tokr[i];
-      const bf16_t* xrow = a.Aop + (int64_t)tk * a.lda;
-      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int s = s0; s < s1; s += 8) {
-        Frag xf[8], lf[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int64_t k = (int64_t)(s + i) * 32 + 8 * lg;
-          xf[i].u = lf[i].u = make_uint4(0, 0, 0, 0);
-          if (s + i < s1 && k < a.Kc) {
-            xf[i].u = *(const uint4*)(xrow + k);
-            if (row_in) lf[i].u = *(const uint4*)(lrow + k);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lf[i].v, xf[i].v, acc, 0, 0, 0);
+    for (int i = 0; i < R; ++i) pacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Frag pa[UP][R + 1], pb[UP][R + 1];
+#define TH_PLOAD(set_, s_)                                                                                \
+  do {                                                                                                    \
+    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u) {                                                   \
+      const int64_t _k = (int64_t)((s_) + _u) * 32 + 8 * lg;                                              \
+      const bool _in = (s_) + _u < s1 && _k < a.Kc;                                                       \
+      set_[_u][R].u = make_uint4(0, 0, 0, 0);                                                             \
+      if (_in && row_in) set_[_u][R].u = *(const uint4*)(lrow + _k);                                      \
+      _Pragma("unroll") for (int _i = 0; _i < R; ++_i) {                                                  \
+        set_[_u][_i].u = make_uint4(0, 0, 0, 0);                                                          \
+        if (_i >= rb0 && _i <= rb1 && _in) set_[_u][_i].u = *(const uint4*)(a.Aop + (int64_t)tokr[_i] * a.lda + _k); \
+      }                                                                                                   \
+    }                                                                                                     \
+  } while (0)
+#define TH_PMMA(set_)                                                                                     \
+  do {                                                                                                    \
+    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u)                                                     \
+      _Pragma("unroll") for (int _i = 0; _i < R; ++_i)                                                    \
+        if (_i >= rb0 && _i <= rb1)                                                                       \
+          pacc[_i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(set_[_u][R].v, set_[_u][_i].v, pacc[_i], 0, 0, 0); \
+  } while (0)
+    TH_PLOAD(pa, s0);
+    for (int s = s0; s < s1; s += 2 * UP) {
+      if (s + UP < s1) TH_PLOAD(pb, s + UP);
+      TH_PMMA(pa);
+      if (s + UP < s1) {
+        if (s + 2 * UP < s1) TH_PLOAD(pa, s + 2 * UP);
+        TH_PMMA(pb);
       }
-      red[wave * 64 + lane] = acc;
-      __syncthreads();
-      if (wave == 0) {
-        f32x4 s = red[lane];
+    }
 #pragma unroll
-        for (int w = 1; w < TH_WAVES; ++w) {
-          const f32x4 o = red[w * 64 + lane];
-          s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
-        }
-        // lane: row li of the block, ranks q0 + 4 lg .. + 3
-        const int row = rb * 16 + li;
-        if (row >= row0 && row < row1) {
-          s[0] *= scale; s[1] *= scale; s[2] *= scale; s[3] *= scale;
-          store4_agent(u_p + (int64_t)row * a.r_stride + q0 + 4 * lg, s);
-        }
-        wait_vm<0>();
+    for (int i = 0; i < R; ++i)
+      if (i >= rb0 && i <= rb1) red[(wave * R + i) * 64 + lane] = pacc[i];
+    __syncthreads();
+    if (wave >= rb0 && wave <= rb1) {                           // wave i finishes row block i
+      f32x4 s = red[wave * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < TH_WAVES; ++w) {
+        const f32x4 o = red[(w * R + wave) * 64 + lane];
+        s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
       }
-      __syncthreads();
+      // lane: row li of the block, ranks q0 + 4 lg .. + 3
+      const int row = wave * 16 + li;
+      if (row >= row0 && row < row1) {
+        s[0] *= scale; s[1] *= scale; s[2] *= scale; s[3] *= scale;
+        f32x4 f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = __float_as_uint(s[j]) == 0u ? -0.f : s[j];
+        store4_agent(u_p + b % S * u_n + row * a.r_stride + q0 + 4 * lg, f);
+      }
+      wait_vm<0>();
     }
-    if (tid == 0) {
-      __hip_atomic_fetch_add(ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      leave();
-    }
+    __syncthreads();
+    if (wave == 0) leave();
     return;
   }
 
@@ -226,11 +253,6 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
         }
         if (li == 15) cnt_s[lg] = a.lform == FORM_NT && bad == 0 ? inc : -1;
       }
-      // the number of producers that have something to produce
-      int tiles = g >= 0 && g != g_before ? (e.rank + 15) >> 4 : 0;
-#pragma unroll
-      for (int d = 32; d > 0; d >>= 1) tiles += __shfl_xor(tiles, d);
-      if (lane == 0) cnt_s[R] = tiles;
     }
     for (int s = s0; s < s1; s += 2 * U) {
       if (s + U < s1) TH_LOAD(fb, s + U);
@@ -274,25 +296,32 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
         if (n < Nout) pre[k].u = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
       }
     }
-    if (tid == 0) {
-      const int need = cnt_s[R];
-      int ok = need == 0;
-      for (int it = 0; it < a.spin_limit && !ok; ++it) {
-        ok = __hip_atomic_load(ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need;
-        if (!ok) __builtin_amdgcn_s_sleep(1);
-      }
-      cnt_s[R] = ok;
-    }
-    __syncthreads();
-    const bool u_ok = cnt_s[R] != 0;
     for (int i = tid; i < 16 * R * (a.r_stride >> 2); i += TH_THREADS) {
       const int row = i / (a.r_stride >> 2), q = (i - row * (a.r_stride >> 2)) * 4;
       const int rank = t_s[row] >= 0 ? rank_s[row] : 0;
       f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
       if (q < rank) {
-        if (u_ok) {
-          asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(u_p + (int64_t)row * a.r_stride + q) : "memory");
-        } else {
+        bool ok = false;
+        for (int it = 0; it < a.spin_limit && !ok; ++it) {
+          // the splits' parts (a call of fewer splits reads its last one again)
+          f32x4 w[THIN_SPLITS];
+          const float* up = u_p + row * a.r_stride + q;
+          const float* up1 = up + (S > 1 ? u_n : 0);
+          const float* up2 = S > 2 ? up1 + u_n : up1;
+          const float* up3 = S > 3 ? up2 + u_n : up2;
+          asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                       "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
+                       : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]) : "v"(up), "v"(up1), "v"(up2), "v"(up3) : "memory");
+          ok = true;
+#pragma unroll
+          for (int k = 0; k < THIN_SPLITS; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              ok &= __float_as_uint(w[k][j]) != 0u;
+              v[j] = k == 0 ? w[0][j] : k < S ? v[j] + w[k][j] : v[j];
+            }
+        }
+        if (!ok) {
           // (not reached in practice) the shrink of this row again, in plain fp32 arithmetic
           const AdapterEntry en = table[t_s[row]];
           const bf16_t* xr = a.Aop + (int64_t)tok_s[row] * a.lda;
@@ -307,9 +336,10 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
       *(f32x4*)(u_s + row * us + q) = v;
+      if (a.u_out && b == a.n_prod && row < a.T && q < ((rank + 15) & ~15)) *(f32x4*)(a.u_out + (int64_t)row * a.r_stride + q) = v;
     }
     __syncthreads();
-    if (tid == 0) leave();
+    if (wave == TH_WAVES - 1) leave();       // (it has few output tiles, or none)
 #pragma unroll
     for (int k = 0; k < MINE; ++k) {
       const int tile = wave + k * TH_WAVES, rb = tile / NC, c = tile - rb * NC;
@@ -378,7 +408,7 @@ __global__ __launch_bounds__(TH_THREADS) void gemm_thin_kernel(GemmArgs a) {
 template <int R, int NC>
 static hipError_t launch_thin(const GemmArgs& a, hipStream_t stream) {
   const size_t lds = (size_t)TH_WAVES * R * NC * 1024 + (size_t)16 * R * (a.r_stride + 4) * sizeof(float) +
-                     (size_t)R * 2 * a.r_stride * 16 + (size_t)16 * R * 20 + (R + 1) * 4 + 64;
+                     (size_t)R * 2 * a.r_stride * 16 + (size_t)16 * R * 20 + R * 4 + 64;
   static std::atomic<uint64_t> done_dev{0};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -393,13 +423,19 @@ static hipError_t launch_thin(const GemmArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Column blocks per workgroup: one while that keeps the launch near one workgroup per compute unit,
-// then two, then (up to 32 rows: registers) four, which reads x half and a quarter as often.
+// Column blocks per workgroup: as few as keep the consumers near 160 (4096 columns, rank-16 adapters, 1
+// / 6 / 32 rows: 12.6 / 13.4 / 22.7 us with one block each, 10.3 / 11.8 / 16.4 with two: half as many
+// workgroups read u and x); at most two above 32 rows (LDS).
 hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream) {
+  // splits of a producer's contraction: so that a wave of it has about eight steps, two rounds of loads
+  const int64_t steps = ((a.Kc + 31) / 32 + TH_WAVES - 1) / TH_WAVES;
+  a.n_split = (int)(steps <= 8 ? 1 : steps <= 16 ? 2 : THIN_SPLITS);
+  if (a.T > 32 && a.n_split > 2) a.n_split = 2;      // (every consumer reads all of u)
+  a.n_prod *= a.n_split;
   const int R = a.T <= 16 ? 1 : a.T <= 32 ? 2 : 4;
   int64_t blocks = 0;
   for (int p = 0; p < a.n_proj; ++p) blocks += (a.proj[p].Nout + 15) / 16;
-  int nc = blocks <= 320 ? 1 : blocks <= 640 || R == 4 ? 2 : 4;
+  const int nc = blocks <= 160 ? 1 : blocks <= 320 || R == 4 ? 2 : 4;
   a.tiles_n = 0;
   for (int p = 0; p < a.n_proj; ++p) {
     a.proj[p].tile0 = a.tiles_n;
