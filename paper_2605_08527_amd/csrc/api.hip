@@ -26,10 +26,10 @@ struct marlaas_ctx {
   void* ws = nullptr;
   size_t ws_bytes = 0;
   void* static_ws = nullptr;     // device address of this GPU's static scratch array
-  int32_t* sync_dev = nullptr;   // counters of the decode kernels, then u of the few-row kernel (zero between launches)
+  int32_t* sync_dev = nullptr;   // counters of the decode kernels, then u and partial sums of the one-launch kernels (zero between launches)
   int cu_count = 0;
   int spin_limit = 1 << 20;
-  void* zero_dev = nullptr;    // 256 zero bytes (what masked DMA lanes fetch)
+  void* zero_dev = nullptr;    // 1024 zero bytes (what masked DMA lanes fetch)
   int decode_finish = DECODE_FINISH_AUTO;     // how the decode kernel's calls get finished (DECODE_FINISH_*)
   std::string err;
   bool profile = false;
@@ -173,9 +173,9 @@ extern "C" int marlaas_create(marlaas_ctx** out, int device) {
   ctx->static_ws = sp;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->cu_count = prop.multiProcessorCount;
-  if (hipMalloc((void**)&ctx->sync_dev, (DECODE_SYNC_INTS + THIN_U_FLOATS) * sizeof(int32_t)) != hipSuccess ||
-      hipMemset(ctx->sync_dev, 0, (DECODE_SYNC_INTS + THIN_U_FLOATS) * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&ctx->zero_dev, 256) != hipSuccess || hipMemset(ctx->zero_dev, 0, 256) != hipSuccess) {
+  if (hipMalloc((void**)&ctx->sync_dev, SYNC_INTS * sizeof(int32_t)) != hipSuccess ||
+      hipMemset(ctx->sync_dev, 0, SYNC_INTS * sizeof(int32_t)) != hipSuccess ||
+      hipMalloc(&ctx->zero_dev, 1024) != hipSuccess || hipMemset(ctx->zero_dev, 0, 1024) != hipSuccess) {
     (void)hipFree(ctx->zero_dev);
     (void)hipFree(ctx->sync_dev);
     delete ctx;
@@ -814,6 +814,60 @@ static int max_rank_tiles(const marlaas_lora_desc* d) {
   return tiles;
 }
 
+// Jobs (16 ranks x one or two 16-row blocks of an adapter) of the row tiles of all projections; false if
+// there are more than the kernel counts.
+static bool shrink_jobs(const marlaas_lora_desc* descs, int32_t n_proj, bool lora, const MidPlan& plan, MidJobs* jobs) {
+  const marlaas_lora_desc* d = &descs[0];
+  const std::vector<int32_t>& off = d->map->seg_off;
+  const int rows = 16 * plan.rb;
+  int total = 0;
+  memset(jobs, 0xff, sizeof *jobs);
+  for (int p = 0; p < n_proj; ++p) {
+    uint16_t* end = jobs->end + p * plan.tiles_m;
+    const int32_t* ranks = ranks_of(&descs[p]);
+    int tile = 0;                              // the row tile the walk is in
+    for (int t = 0; lora && t < d->n_adapters; ++t) {
+      const int rt = (ranks[t] + 15) / 16;
+      for (int lo = off[t]; lo < off[t + 1];) {
+        while (tile < lo / rows) end[tile++] = (uint16_t)total;
+        const int stop = (tile + 1) * rows, hi = off[t + 1] < stop ? off[t + 1] : stop;
+        total += rt * (((hi - 1) / 16 - lo / 16) / 2 + 1);
+        if (total > 30000) return false;
+        lo = hi;
+      }
+    }
+    while (tile < plan.tiles_m) end[tile++] = (uint16_t)total;
+  }
+  return true;
+}
+
+// A call on packed weights (W and ldw of `proj` filled in) that one of the one-launch kernels does best:
+// enqueues it and sets *done.
+static int launch_packed(marlaas_ctx* ctx, const marlaas_lora_desc* descs, int32_t n_proj, const ProjEntry* proj, const bf16_t* x, int64_t ldx,
+                         int64_t Kc, int form, bool lora, const AdapterEntry* table, int which, int out_f32, float* u, int rs, hipStream_t st, bool* done) {
+  const marlaas_lora_desc* d = &descs[0];
+  const marlaas_segmap* map = d->map;
+  const int32_t* perm = map->identity ? nullptr : map->perm_dev;
+  const int n = lora ? d->n_adapters : 0;
+  const DecodeSync sync = decode_sync_of(ctx, map);
+  *done = false;
+  int ext = 0;
+  for (int t = 0; lora && t < d->n_adapters; ++t) if (map->seg_off[t + 1] > map->seg_off[t]) ext += ranks_of(d)[t];
+  const MidPlan mid = gemm_mid_plan(form, d->T, ldx, Kc, proj, n_proj, lora, ext, rs, &sync);
+  MidJobs jobs;
+  if (mid.rb && shrink_jobs(descs, n_proj, lora, mid, &jobs)) {
+    PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_mid(x, ldx, form, d->T, Kc, perm, map->seg_off_dev, n, table, which, proj, n_proj, out_f32, u, rs, mid,
+                                      jobs, (const bf16_t*)ctx->zero_dev, &sync, st));
+    *done = true;
+  } else if (gemm_thin_ok(form, d->T, lora, rs, &sync)) {
+    int tiles = 0;
+    for (int p = 0; p < n_proj && lora; ++p) { const int k = max_rank_tiles(&descs[p]); if (k > tiles) tiles = k; }
+    PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_thin(x, ldx, form, d->T, Kc, perm, n, table, which, proj, n_proj, out_f32, u, rs, tiles, &sync, st));
+    *done = true;
+  }
+  return MARLAAS_OK;
+}
+
 // ------------------------------------------------------------------ forward
 static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64_t ldy, void* u_save, void* stream,
                     void* ws, size_t ws_bytes) {
@@ -849,13 +903,16 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
   const int form = d->layout == MARLAAS_LAYOUT_MATH ? FORM_NN : FORM_NT;
   const int out_f32 = d->out_dtype == MARLAAS_F32;
   const DecodeSync dsync = decode_sync_of(ctx, map);
-  if (d->in_dtype == MARLAAS_BF16 && d->W_packed_fwd && gemm_thin_ok(form, d->T, lora, rs, &dsync)) {
-    // few rows on the packed weight: one launch
+  bool done = false;
+  if (d->in_dtype == MARLAAS_BF16 && d->W_packed_fwd) {
     ProjEntry pe;
     memset(&pe, 0, sizeof pe);
     pe.W = d->W_packed_fwd; pe.ldw = packed_weight_ksteps(d->d_in); pe.Nout = d->d_out; pe.out = y; pe.ldo = ldy;
-    PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_thin((const bf16_t*)d->x, d->ldx, form, d->T, d->d_in, perm, lora ? d->n_adapters : 0,
-                                  table, 1, &pe, 1, out_f32, (float*)u_save, rs, lora ? max_rank_tiles(d) : 0, &dsync, st));
+    if ((rc = launch_packed(ctx, d, 1, &pe, (const bf16_t*)d->x, d->ldx, d->d_in, form, lora, table, 1, out_f32, (float*)u_save, rs, st, &done)) != MARLAAS_OK)
+      return rc;
+  }
+  if (done) {
+    // (one launch)
   } else if (d->in_dtype == MARLAAS_BF16) {
     // small batches: the GEMM computes the shrink itself and no shrink kernel runs
     GemmFuse fuse;
@@ -1021,19 +1078,14 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
   const DecodeSync dsync = decode_sync_of(ctx, map);
   int rs_all = 0;
   for (int p = 0; p < n_proj; ++p) { const int r = (int)marlaas_u_stride(&descs[p]); if (r > rs_all) rs_all = r; }
-  if (packed && n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && (!lora || shared) && gemm_thin_ok(form, d0->T, lora, rs_all, &dsync)) {
-    // few rows: everything in one launch
+  if (packed && n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && (!lora || shared)) {
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    int tiles = 0;
-    for (int p = 0; p < n_proj; ++p) {
-      proj[p].W = descs[p].W_packed_fwd; proj[p].ldw = packed_weight_ksteps(d0->d_in);
-      if (lora) { const int k = max_rank_tiles(&descs[p]); if (k > tiles) tiles = k; }
-    }
-    hipStream_t thin_st = (hipStream_t)stream;
-    PROFILED(ctx, MARLAAS_KERNEL_GEMM, thin_st, launch_gemm_bf16_thin((const bf16_t*)d0->x, d0->ldx, form, d0->T, d0->d_in, map->identity ? nullptr : map->perm_dev,
-                                       lora ? d0->n_adapters : 0, lora ? d0->table->dev.entries : nullptr, 1, proj.data(), n_proj,
-                                       d0->out_dtype == MARLAAS_F32, nullptr, rs_all, tiles, &dsync, thin_st));
-    return MARLAAS_OK;
+    std::vector<ProjEntry> pk = proj;
+    for (int p = 0; p < n_proj; ++p) { pk[p].W = descs[p].W_packed_fwd; pk[p].ldw = packed_weight_ksteps(d0->d_in); }
+    bool done = false;
+    rc = launch_packed(ctx, descs, n_proj, pk.data(), (const bf16_t*)d0->x, d0->ldx, d0->d_in, form, lora, lora ? d0->table->dev.entries : nullptr, 1,
+                       d0->out_dtype == MARLAAS_F32, nullptr, rs_all, (hipStream_t)stream, &done);
+    if (rc != MARLAAS_OK || done) return rc;
   }
   // descriptors that refer to tables, but not to one table in projection order, have no combined tables
   bool fused = n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && ctx->ws != nullptr && (!lora || shared || !d0->table);
@@ -1172,14 +1224,14 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
     bool fused = false;
     const bool use_packed = !lora || bform == FORM_NT;
     const int need = lora ? ext_rows_of(d, 1, bank.n_ext, gemm_ext_room(d->d_in), &fuse.rows) : 0;
-    const bool thin = dX && d->W_packed_bwd && gemm_thin_ok(bform, d->T, lora, rs, &dsync);
-    if (thin) {
+    bool done = false;
+    if (dX && d->W_packed_bwd && d->T > 0) {
       ProjEntry pe;
       memset(&pe, 0, sizeof pe);
       pe.W = d->W_packed_bwd; pe.ldw = packed_weight_ksteps(d->d_out); pe.Nout = d->d_in; pe.out = dX; pe.ldo = lddx;
-      PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_thin(dy, lddy, bform, d->T, d->d_out, perm, lora ? d->n_adapters : 0, table, 0, &pe, 1,
-                                    out_f32, v, rs, lora ? max_rank_tiles(d) : 0, &dsync, st));
-    } else if (lora && dX && part && bank_can_fuse(bank)) {
+      if ((rc = launch_packed(ctx, d, 1, &pe, dy, lddy, d->d_out, bform, lora, table, 0, out_f32, v, rs, st, &done)) != MARLAAS_OK) return rc;
+    }
+    if (!done && lora && dX && part && bank_can_fuse(bank)) {
       fused = gemm_can_fuse_shrink(bform, d->T, d->d_out, d->d_in, need, bank.mult8, use_packed && d->W_packed_bwd, p.part_bytes);
       if (fused) {
         fuse.need = need;
@@ -1189,7 +1241,7 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
     }
     bool have_v2 = false;
     bf16_t* v2 = (have_ws && p.uv2_bytes && dX) ? (bf16_t*)((char*)ctx->ws + p.v2_off) : nullptr;
-    if (lora && (dX || want_grads) && !fused && !thin)
+    if (lora && (dX || want_grads) && !fused && !done)
       PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_bf16(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
                                       table, 1, bform, v, rs, map->T_lora, part, part ? p.part_bytes : 0, v2, &have_v2, (const bf16_t*)ctx->zero_dev, bank.mult8, st));
     LoraDma dma;
@@ -1198,7 +1250,7 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
       dma.u2 = v2; dma.tiles = (int32_t*)((char*)ctx->ws + p.lt_off); dma.tiles_bytes = p.lt_bytes;
       dma.ranks_mult8 = bank.mult8;
     }
-    if (dX && d->T > 0 && !thin)
+    if (dX && d->T > 0 && !done)
       PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16(dy, lddy, (const bf16_t*)d->W, d->ldw, bform, d->T, d->d_out, d->d_in, perm,
                                     map->seg_off_dev, d->n_adapters, table, 0, lora ? v : nullptr, rs, dX, lddx,
                                     out_f32, part, part ? p.part_bytes : 0, map->chunks_dev, map->n_chunks,

@@ -177,9 +177,18 @@ struct DecodeSync {
   int cu_count = 0;
 };
 static constexpr int DECODE_SYNC_INTS = 4096;
-static constexpr int THIN_ROWS = 64;                              // rows of the few-row kernel (gemm_thin.hip)
+static constexpr int THIN_ROWS = 32;                              // rows of the few-row kernel (gemm_thin.hip)
 static constexpr int THIN_SPLITS = 4;
-static constexpr int THIN_U_FLOATS = MAX_PROJ * THIN_SPLITS * THIN_ROWS * 128;   // what it hands u over in, follows the counters
+// One launch for up to MID_ROWS rows (gemm_mid.hip): rows of a tile, columns of a tile / 32, contraction
+// splits.  u travels where the few-row kernel's does ([MAX_PROJ][MID_SPLITS][MID_ROWS][128]), the partial
+// sums of at most MID_SPLIT_WGS workgroups behind it.
+static constexpr int MID_ROWS = 1024, MID_SPLITS = 2, MID_SPLIT_WGS = 512;
+static constexpr int MID_U_FLOATS = MAX_PROJ * MID_SPLITS * MID_ROWS * 128;
+static constexpr int MID_PART_FLOATS = MID_SPLIT_WGS * 96 * 128;
+static constexpr int SYNC_INTS = DECODE_SYNC_INTS + MID_U_FLOATS + MID_PART_FLOATS;
+// Ends of the producers' jobs, projection by projection and row tile by row tile (the rest: 65535).
+struct MidJobs { alignas(16) uint16_t end[MAX_PROJ * MID_ROWS / 64]; };
+struct MidPlan { int rb = 0, wn = 2, ksplit = 1, tiles_m = 0; double us = 0.0; };     // rb = rows / 16; 0: none
 
 // What lets the large-batch GEMM fetch the expand's operands by DMA: u (or v) as a two-term bf16
 // split written by the shrink, scratch for the row tiles' lists of extra contraction tiles
@@ -226,6 +235,15 @@ bool gemm_thin_ok(int form, int64_t T, bool lora, int r_stride, const DecodeSync
 hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, int n_adapters,
                                  const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
                                  float* u, int r_stride, int max_tiles, const DecodeSync* sync, hipStream_t stream);
+// The same for more rows (gemm_mid.hip); the plan says whether it is the kernel for these sizes.  ext: ranks of
+// all adapters in the batch (0: none); seg_off:
+// rows of the adapters (device); jobs: a row tile's (16 plan.rb rows) are one per 16 ranks and (started) pair of
+// 16-row blocks of an adapter.
+MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, bool lora, int ext, int r_stride, const DecodeSync* sync);
+hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,
+                                const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
+                                float* u, int r_stride, const MidPlan& plan, const MidJobs& jobs, const bf16_t* zero_line, const DecodeSync* sync,
+                                hipStream_t stream);
 // Several projections of the same input in one pass (small batches only: 128 x 128 tiles with
 // the shrink carried as extended columns, or no adapters at all).  `proj_host` holds the n_proj
 // entries (host memory); `table` is the combined adapter table ([projection][adapter]), `fuse` (null:

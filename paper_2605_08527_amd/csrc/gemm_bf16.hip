@@ -984,6 +984,34 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
   return launch_gemm_thin(a, stream);
 }
 
+// ---- some more rows
+MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, bool lora, int ext, int r_stride, const DecodeSync* sync) {
+  if (T <= 0 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || !sync->counters || (lora && (form != FORM_NT || !sync->grp_ids || r_stride > 128)) ||
+      (sync->mode != DECODE_FINISH_AUTO && sync->mode != DECODE_FINISH_IN_KERNEL))
+    return MidPlan();
+  int64_t cols = 0;
+  for (int q = 0; q < n_proj; ++q) cols += proj_host[q].Nout;
+  const MidPlan p = mid_plan(T, Kc, proj_host, n_proj, lora);
+  return mid_pays(p, T, Kc, cols, ext) ? p : MidPlan();
+}
+
+hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,
+                                const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
+                                float* u, int r_stride, const MidPlan& plan, const MidJobs& jobs, const bf16_t* zero_line, const DecodeSync* sync,
+                                hipStream_t stream) {
+  if (n_proj < 1 || n_proj > MAX_PROJ || plan.rb == 0) return hipErrorInvalidValue;
+  GemmArgs a;
+  memset(&a, 0, sizeof a);
+  a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.seg_off = seg_off; a.n_adapters = n_adapters; a.table = table; a.which = which;
+  a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
+  a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit; a.zero_line = zero_line;
+  a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
+  a.partials = (float*)(sync->counters + (SYNC_INTS - MID_PART_FLOATS));
+  a.n_proj = n_proj;
+  for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
+  return launch_gemm_mid(a, plan, jobs, stream);
+}
+
 // ---- several projections in one pass
 static int64_t multi_tiles(const ProjEntry* proj, int n_proj) {
   int64_t tiles = 0;

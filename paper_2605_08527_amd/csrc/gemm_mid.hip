@@ -1,0 +1,795 @@
+// Decode of some 64 to 1000 rows on the packed weight: the whole call in one launch.
+//
+//   out_p[tok(m), :] = x[tok(m), :] W_p  +  u_p(m) L_{t,p}        for every projection p of the call
+//
+// A workgroup owns a tile of 16 RB rows x 32 WN columns; its eight waves are WN column groups of 32 times
+// KG = 8 / WN contraction groups, so a weight fragment is read once, by the one wave that multiplies it,
+// and the sums of the contraction groups meet in LDS.  x goes through LDS by DMA in a ring of 128-deep
+// tiles, because every column group needs all of it.  What bounds it: the fabric delivers 28 GB/s to each
+// of the 256 compute units (7.3 TB/s in all, the weight once, x once per XCD), an XCD's L2 four times
+// that; below those a call pays for every dependent trip through the fabric, 1 to 1.5 us each, and for
+// every launch, about 4 us.  So: no second launch, few contraction splits, tiles small enough that two
+// workgroups share a compute unit (128 registers, 80 KB of LDS).
+//
+// Measured (microseconds, before: extended columns through the split kernel and a second launch):
+// 256 rows 4096 x 4096 30 -> 26; 157 rows 4096 x 28672 127 -> 82, 4096 x 14336 63 -> 45; 512 rows of 64 adapters
+// of ranks 8 to 64, 5120 x 5120 105 -> 68.
+//
+// Whatever crosses workgroups carries its own flag: it travels through areas of the context that are all
+// zero bits between launches, no value is stored as zero bits (+0 becomes -0), and a reader reads until
+// nothing is zero bits any more.
+//   u: workgroups before the others ("producers") compute it, one per 16 ranks of an adapter and pair of
+//     its 16-row blocks in a row tile.  The workgroup that is last through with a row tile clears it.
+//   partial sums: with ksplit > 1 the splits of a tile share out its 16 x 16 units; a split hands the
+//     others' units over, reads its own ones' missing sums and clears them.
+// The reading is bounded.  u that does not come in time is computed by the reader; so are missing sums,
+// and the area is then cleared by whoever is last.  No workgroup depends on another one being scheduled.
+#include "gemm_args.h"
+#include "agent_memory.h"
+
+#include <atomic>
+#include <cmath>
+
+namespace marlaas {
+
+// (a value the compiler cannot compute ahead of its use and keep in a register until then)
+__device__ __forceinline__ int fresh(int v) { asm volatile("" : "+v"(v)); return v; }
+
+// 16 bytes per lane from base + ofs (or p) to LDS bytes lds .. lds + 1023
+__device__ __forceinline__ void dma16(uint32_t lds, const char* base, uint32_t ofs) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(ofs), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void dma16(uint32_t lds, const char* p) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(p) : "memory", "m0");
+}
+
+static constexpr int MD_THREADS = 512, MD_WAVES = 8;
+
+template <int RB, int WN>
+struct MidShape {
+  static constexpr int KG = MD_WAVES / WN, K = 32 * KG;           // contraction groups; contraction values of a k-tile
+  static constexpr int NS = RB == 4 || WN == 4 ? 4 : 3; // ring slots = k-tiles on the way (registers, LDS)
+  static constexpr int SLOT = RB * 16 * K * 2;
+  static constexpr int RED = RB * WN * 2 * (KG - 1) * 1024;       // exchange of the contraction groups
+  static constexpr int BASE = NS * SLOT > RED ? NS * SLOT : RED;
+};
+
+template <int RB, int WN>
+__global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, MidJobs jobs) {
+  typedef MidShape<RB, WN> S_;
+  constexpr int KG = S_::KG, MD_K = S_::K, UR = MD_K / 8, NS = S_::NS, SLOT = S_::SLOT, BM = 16 * RB, NR = (RB + KG - 1) / KG;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int us = a.r_stride + 4, oct_max = 2 * a.r_stride;       // (octet: 8 ranks of one adapter; so many can a 16-row block have)
+  const int base_bytes = S_::BASE > BM * us * 4 ? S_::BASE : BM * us * 4;
+  f32x4* red = (f32x4*)smem;
+  float* u_s = (float*)smem;                                     // [BM][us], once the sums have met
+  uint64_t* rL_s = (uint64_t*)(smem + base_bytes);               // per row: expand factor,
+  int32_t* tok_s = (int32_t*)(rL_s + BM);                        // token (-1: past the end),
+  int32_t* t_s = tok_s + BM;                                     // adapter (-1: none),
+  int32_t* rank_s = t_s + BM;                                    // rank
+  int32_t* cnt_s = rank_s + BM;                                  // [RB] octets of a row block (-1: plain expand)
+  int32_t* gave_s = cnt_s + RB;                                  // a wave gave up waiting for sums
+  uint16_t* oct_s = (uint16_t*)(gave_s + 1);                     // [RB][oct_max]: row of the tile << 8 | first rank
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  const bool lora = a.n_adapters > 0 && a.table != nullptr;
+  const int b = (int)blockIdx.x - a.prod0, S = a.n_split;        // the producers are workgroups prod0 ..
+  const bool producer = b >= 0 && b < a.n_prod;
+  int p = 0, tm, tn = 0, ks0 = 0, job = 0;
+  if (producer) {
+    int e = 0;                                                   // (wave-uniform reads of the kernel arguments)
+    job = b / S;
+    for (int i = 0, start = 0; i < a.n_proj * a.tiles_m; i += 8) {
+      const uint4 v = *(const uint4*)(jobs.end + i);
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int end = (int)(k & 1 ? w[k / 2] >> 16 : w[k / 2] & 0xffff);
+        if (end <= b / S) { ++e; start = end; }
+      }
+      job = b / S - start;
+    }
+    tm = e % a.tiles_m; p = e / a.tiles_m;
+    if (p >= a.n_proj) return;                                   // (the producers are padded to whole rounds over the XCDs)
+  } else {
+    // Workgroup b runs on XCD b mod 8.  An XCD works on one contraction split, so that it pulls only its
+    // own part of x through the fabric; the row tiles of a column tile are neighbours on one XCD and
+    // share the weight through its L2.
+    const int c = b < 0 ? (int)blockIdx.x : (int)blockIdx.x - a.n_prod, xcd = c & 7, idx = c >> 3, ng = 8 / a.ksplit;
+    ks0 = xcd & (a.ksplit - 1);
+    tm = idx % a.tiles_m;
+    tn = idx / a.tiles_m * ng + xcd / a.ksplit;
+    if (tn >= a.tiles_n) return;
+    for (int q = 1; q < a.n_proj; ++q) if (tn >= a.proj[q].tile0) p = q;
+  }
+  const int64_t m0 = (int64_t)tm * BM;
+  const int64_t Nout = a.proj[p].Nout, ldb = a.proj[p].ldw;
+  const AdapterEntry* table = a.table + a.proj[p].tab0;
+  // u of this projection: [split][T][r_stride], scaled
+  float* u_p = a.thin_u + p * (MID_SPLITS * MID_ROWS * 128);
+  const int64_t u_n = a.T * a.r_stride;
+  const int p_tiles = (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
+  constexpr int UNITS = 2 * WN * RB;
+  // [tile][unit][split][lane] x 4
+  float* parts = a.partials + (int64_t)(tm * a.tiles_n) * (UNITS * 256) * a.ksplit;
+  // workgroups through with row tile tm of this projection (bits 16 ..: those that gave up waiting for sums).
+  // Called by one whole wave, when the workgroup's requests are performed.
+  auto leave = [&](int gave_up) {
+    int32_t* done = a.sync + p * a.tiles_m + tm;
+    const int at = p * a.tiles_m + tm;
+    const int everyone = (lora ? (jobs.end[at] - (at > 0 ? jobs.end[at - 1] : 0)) * S : 0) + p_tiles * a.ksplit;
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(done, 1 + (gave_up << 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old = __builtin_amdgcn_readfirstlane(old) + (gave_up << 16);
+    if ((old & 0xffff) != everyone - 1) return;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    if (lora) {
+      const int64_t rows = a.T - m0 < BM ? a.T - m0 : BM;
+      for (int s = 0; s < S; ++s)
+        for (int64_t i = lane; i < rows * a.r_stride / 4; i += 64) store4_agent(u_p + s * u_n + m0 * a.r_stride + i * 4, zero);
+    }
+    if (old >> 16)                                               // (not reached in practice)
+      for (int64_t i = lane, n = (int64_t)p_tiles * UNITS * 64 * a.ksplit; i < n; i += 64)
+        store4_agent(parts + (int64_t)a.proj[p].tile0 * (UNITS * 256) * a.ksplit + i * 4, zero);
+    if (lane == 0) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  union Frag { uint4 u; bf16x8 v; };
+  const int steps = (int)((a.Kc + 31) >> 5);
+
+  if (producer) {
+    int32_t tokr[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const int64_t m = m0 + 16 * i + li < a.T ? m0 + 16 * i + li : a.T - 1;
+      tokr[i] = a.perm ? a.perm[m] : (int32_t)m;
+    }
+    // the jobs of the row tile in adapter order, a lane per adapter from that of its first row on
+    const int64_t m1 = m0 + BM < a.T ? m0 + BM : a.T;
+    const int tfirst = a.n_adapters <= 64 ? 0 : a.grp_ids[m0];   // (one trip less)
+    int t = -1, q0 = 0, blk = 0, r = 0, row0 = 0, row1 = 0;
+    float scale = 0.f;
+    const bf16_t* L = nullptr;
+    for (int tb = tfirst, before = 0; tb >= 0 && tb < a.n_adapters; tb += 64) {
+      const int tl = tb + lane;
+      const bool in = tl < a.n_adapters;
+      const int so = in ? a.seg_off[tl] : 0, so1 = in ? a.seg_off[tl + 1] : 0;
+      AdapterEntry e;
+      e.A = e.B = nullptr; e.rank = 0; e.scale = 0.f;
+      if (in) e = table[tl];
+      const int lo = so > m0 ? so - (int)m0 : 0, hi = (so1 < m1 ? so1 : (int)m1) - (int)m0;
+      const int pairs = in && hi > lo ? (((hi - 1) >> 4) - (lo >> 4)) / 2 + 1 : 0;
+      const int jobs = pairs * ((e.rank + 15) >> 4);
+      int inc = jobs;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
+      const uint64_t hit = __ballot(before + inc - jobs <= job && job < before + inc);
+      if (hit) {
+        const int l = __ffsll((unsigned long long)hit) - 1;
+        t = tb + l;
+        const int k = job - before - __shfl(inc - jobs, l), np = __shfl(pairs, l);
+        row0 = __shfl(lo, l); row1 = __shfl(hi, l);
+        q0 = k / np * 16; blk = (row0 >> 4) + k % np * 2;
+        r = __shfl(e.rank, l); scale = __shfl(e.scale, l);
+        const uint64_t fp = (uint64_t)(uintptr_t)(a.which ? e.A : e.B);
+        L = (const bf16_t*)(((uint64_t)(uint32_t)__shfl((int)(fp >> 32), l) << 32) | (uint32_t)__shfl((int)fp, l));
+        break;
+      }
+      before += __shfl(inc, 63);
+      if (__ballot(in && so1 < m1) != ~0ull) break;              // the tile's last adapter is among these
+    }
+    if (t < 0) {
+      if (wave == 0) leave(0);
+      return;
+    }
+    const int part = (steps + S - 1) / S, k0 = b % S * part, k1 = k0 + part < steps ? k0 + part : steps;
+    const int per = (part + MD_WAVES - 1) / MD_WAVES;
+    const int s0 = k0 + wave * per, s1 = s0 + per < k1 ? s0 + per : k1;
+    const bool row_in = q0 + li < r, two = blk + 1 < RB && (blk + 1) * 16 < row1;
+    const bf16_t* lrow = L + (int64_t)(row_in ? q0 + li : 0) * a.Kc;
+    const bf16_t* xrow[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      int32_t tk = tokr[0];
+#pragma unroll
+      for (int j = 1; j < RB; ++j) if (blk + i == j) tk = tokr[j];
+      xrow[i] = a.Aop + (int64_t)tk * a.lda;
+    }
+    constexpr int UP = 3;                                        // steps requested together (twice)
+    f32x4 pacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    Frag pa[UP][3], pb[UP][3];
+#define MD_PLOAD(set_, s_)                                                                                \
+  do {                                                                                                    \
+    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u) {                                                   \
+      const int64_t _k = (int64_t)((s_) + _u) * 32 + 8 * lg;                                              \
+      const bool _in = (s_) + _u < s1 && _k < a.Kc;                                                       \
+      set_[_u][0].u = set_[_u][1].u = set_[_u][2].u = make_uint4(0, 0, 0, 0);                             \
+      if (_in && row_in) set_[_u][2].u = *(const uint4*)(lrow + _k);                                      \
+      if (_in) set_[_u][0].u = *(const uint4*)(xrow[0] + _k);                                             \
+      if (_in && two) set_[_u][1].u = *(const uint4*)(xrow[1] + _k);                                      \
+    }                                                                                                     \
+  } while (0)
+#define MD_PMMA(set_)                                                                                     \
+  do {                                                                                                    \
+    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u)                                                     \
+      _Pragma("unroll") for (int _i = 0; _i < 2; ++_i)                                                    \
+        pacc[_i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(set_[_u][2].v, set_[_u][_i].v, pacc[_i], 0, 0, 0); \
+  } while (0)
+    MD_PLOAD(pa, s0);
+    for (int s = s0; s < s1; s += 2 * UP) {
+      if (s + UP < s1) MD_PLOAD(pb, s + UP);
+      MD_PMMA(pa);
+      if (s + UP < s1) {
+        if (s + 2 * UP < s1) MD_PLOAD(pa, s + 2 * UP);
+        MD_PMMA(pb);
+      }
+    }
+#undef MD_PLOAD
+#undef MD_PMMA
+#pragma unroll
+    for (int i = 0; i < 2; ++i) red[(wave * 2 + i) * 64 + lane] = pacc[i];
+    __syncthreads();
+    if (wave < 2) {                                              // wave i finishes row block blk + i
+      f32x4 s = red[wave * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < MD_WAVES; ++w) {
+        const f32x4 o = red[(w * 2 + wave) * 64 + lane];
+        s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
+      }
+      // lane: row li of the block, ranks q0 + 4 lg .. + 3
+      const int row = (blk + wave) * 16 + li;
+      if (row >= row0 && row < row1 && row < BM) {
+        f32x4 f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const float v = scale * s[j]; f[j] = __float_as_uint(v) == 0u ? -0.f : v; }
+        store4_agent(u_p + b % S * u_n + (m0 + row) * a.r_stride + q0 + 4 * lg, f);
+      }
+      wait_vm<0>();
+    }
+    __syncthreads();
+    if (wave == 0) leave(0);
+    return;
+  }
+
+  // ---- consumers
+  const int g = wave / WN, wn = wave % WN;
+  const int64_t n0 = (int64_t)(tn - a.proj[p].tile0) * (32 * WN) + 32 * wn;     // this wave's first column
+  // the indices everything waits for go first (inline assembly: the compiler's own waits would count the
+  // requests below in); row of this lane's part of its DMA requests, row tid of the tables
+  // (UR: 16-byte units of a tile's row; a DMA request is 64 of them)
+  constexpr int NI = (RB * UR / 4 + 7) / 8;                      // DMA requests of a wave per k-tile,
+  const bool full = wave < RB * UR / 4 - 8 * (NI - 1);           // one less for the upper waves where they do not divide
+  const int drow = lane / UR, dunit = lane % UR;
+#define MD_DROW(i_) ((wave + 8 * (i_)) * (64 / UR) + drow)
+#define MD_SWZ(r_) (UR == 16 ? (r_) & 15 : ((r_) >> 1) & 7)
+  // (requested by every lane, whether needed or not: a value that a branch merges could be copied before it is there)
+  int32_t tokr[NI], tok, gid, gid1;
+  const int32_t* none = (const int32_t*)a.zero_line;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    int64_t m = m0 + MD_DROW(i);
+    if (m >= a.T) m = a.T - 1;
+    asm volatile("global_load_dword %0, %1, off" : "=v"(tokr[i]) : "v"(a.perm ? a.perm + m : none) : "memory");
+  }
+  const int64_t mrow = m0 + tid;
+  const bool has_row = tid < BM && mrow < a.T;
+  const int64_t mr = has_row ? mrow : 0;
+  asm volatile("global_load_dword %0, %1, off" : "=v"(tok) : "v"(a.perm ? a.perm + mr : none) : "memory");
+  asm volatile("global_load_dword %0, %1, off" : "=v"(gid) : "v"(lora ? a.grp_ids + mr : none) : "memory");
+  asm volatile("global_load_dword %0, %1, off" : "=v"(gid1) : "v"(lora ? a.grp_ids + (mr > 0 ? mr - 1 : 0) : none) : "memory");
+  // column block cb of this wave is block n0 / 16 + cb of the packed weight (blocks past the last one
+  // repeat it: those columns are never stored)
+  const bf16_t* wp[2];
+#pragma unroll
+  for (int cb = 0; cb < 2; ++cb) {
+    const int64_t blocks = (Nout + 15) >> 4;
+    int64_t nb = (n0 >> 4) + cb;
+    if (nb >= blocks) nb = blocks - 1;
+    wp[cb] = (const bf16_t*)a.proj[p].W + ((nb * ldb) << 9);
+  }
+  const int ktiles = (int)((a.Kc + MD_K - 1) / MD_K), chunk = (ktiles + a.ksplit - 1) / a.ksplit;
+  bf16x8 wreg[NS][2];
+  const int wofs = lane * 16;
+  // weight fragments of k-tile t_ (steps past the end read zeros)
+#define MD_W(t_, s_)                                                                                      \
+  do {                                                                                                    \
+    const int _st = (t_) * KG + g;                                                                        \
+    _Pragma("unroll") for (int _c = 0; _c < 2; ++_c) {                                                    \
+      const bf16_t* _p = _st < steps ? wp[_c] + ((int64_t)_st << 9) : a.zero_line;                        \
+      asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(wreg[s_][_c]) : "v"(wofs), "s"(_p) : "memory"); \
+    }                                                                                                     \
+  } while (0)
+  // x of k-tile t_ into slot s_: row r of the tile at 16 UR r, its 16-byte unit u at place u ^ MD_SWZ(r)
+  // (units past the end read zeros)
+#define MD_X(t_, s_)                                                                                      \
+  do {                                                                                                    \
+    const bool _past = (int64_t)((t_) + 1) * MD_K > a.Kc;                                                 \
+    _Pragma("unroll") for (int _i = 0; _i < NI; ++_i)                                                        \
+      if (_i + 1 < NI || full) {                                                                           \
+        const char* _p = (const char*)a.Aop + (int64_t)(t_) * (MD_K * 2);                                 \
+        const uint32_t _to = lds0 + (s_) * SLOT + (wave + 8 * _i) * 1024;                                 \
+        if (!_past) {                                                                                     \
+          dma16(_to, _p, xofs[_i]);                                                                       \
+        } else {                                                                                          \
+          const int _ln = fresh(lane), _r = (wave + 8 * _i) * (64 / UR) + _ln / UR;                       \
+          const bool _in = (int64_t)(t_) * MD_K + 8 * (_ln % UR ^ MD_SWZ(_r)) < a.Kc;                     \
+          dma16(_to, _in ? _p + xofs[_i] : (const char*)a.zero_line);                                     \
+        }                                                                                                 \
+      }                                                                                                   \
+  } while (0)
+  // The column tiles of an XCD start at different k-tiles: the first to ask for a piece of x waits for the
+  // fabric, and started together they all wait for every piece.
+#define MD_T(i_) (kt_b + ((i_) + rot < nt ? (i_) + rot : (i_) + rot - nt))
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
+  uint32_t xofs[NI];                                             // (the host keeps them below 4 GB)
+  f32x4 y[NR][2];
+  const int cbo = ks0 & 1;                                       // with several splits this wave's own units are its
+  const bool own = a.ksplit == 1 || ((g * WN * 2 + wn * 2 + cbo) & (a.ksplit - 1)) == ks0;   // column block cbo, if any
+  if (tid == 0) gave_s[0] = 0;
+  {
+    const int kt_b = ks0 * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;
+    const int rot = (((int)blockIdx.x - (b < 0 ? 0 : a.n_prod)) >> 3) / a.tiles_m % 8 * a.rot;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) if (s < nt) MD_W(MD_T(s), s);
+    {
+      if (nt >= NS) wait_vm<NS * 2>(); else wait_vm<0>();   // the indices have arrived
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        asm volatile("" : "+v"(tokr[i]));
+        int64_t m = m0 + MD_DROW(i);
+        if (m >= a.T) m = a.T - 1;
+        xofs[i] = (uint32_t)(((a.perm ? (int64_t)tokr[i] : m) * a.lda + 8 * (dunit ^ MD_SWZ(MD_DROW(i)))) * 2);
+      }
+      asm volatile("" : "+v"(tok), "+v"(gid), "+v"(gid1));
+      tok = !has_row ? -1 : a.perm ? tok : (int32_t)mrow;
+      if (!has_row || !lora) gid = -1;
+      if (tid == 0 || !lora) gid1 = -1;
+    }
+    // the rows' adapter entries go before the first x request: they are there when it is
+    uint64_t eL, ers;
+    {
+      const char* en = gid >= 0 ? (const char*)(table + gid) : (const char*)a.zero_line;
+      asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(eL) : "v"(en + (a.which ? 8 : 0)) : "memory");
+      asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(ers) : "v"(en + 16) : "memory");
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) if (s < nt) MD_X(MD_T(s), s);
+    // (every wave waits: a register with a request under way must not look free to the compiler)
+    if (nt >= NS) { if (full) wait_vm<NS * NI>(); else wait_vm<NS * (NI - 1)>(); } else wait_vm<0>();
+    asm volatile("" : "+v"(eL), "+v"(ers));
+    if (wave < (BM + 63) / 64) {
+      // the rows' tables, and per 16-row block the octets of its adapters (a lane per row; the first row of
+      // an adapter in the block appends the adapter's octets)
+      const int rank = gid >= 0 ? (int)(uint32_t)ers : 0;
+      const bool first = gid >= 0 && (gid != gid1 || li == 0);
+      const int n_oct = first ? rank >> 3 : 0;
+      int inc = n_oct, bad = rank & 7 ? 1 : 0;
+#pragma unroll
+      for (int d = 1; d < 16; d <<= 1) { const int v = __shfl_up(inc, d, 16), w = __shfl_up(bad, d, 16); if (li >= d) { inc += v; bad |= w; } }
+      if (tid < BM) {
+        tok_s[tid] = tok; t_s[tid] = gid; rank_s[tid] = rank; rL_s[tid] = eL;
+        for (int q = 0, o = (tid >> 4) * oct_max + inc - n_oct; q < 8 * n_oct; q += 8, ++o) oct_s[o] = (uint16_t)(tid << 8 | q);
+        if (li == 15) cnt_s[tid >> 4] = a.lform == FORM_NT && bad == 0 ? inc : -1;
+      }
+    }
+    f32x4 acc[RB][2];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 xf[RB];
+    // the wave's 32 values of a k-tile: row li of a block, unit 4 g + lg
+    const uint32_t xa = lds0 + li * (16 * UR) + (((g * 4 + lg) ^ MD_SWZ(li)) << 4);
+#define MD_READ(a_, i_) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(xf[i_]) : "v"(a_), "n"((i_) * 256 * UR))
+#define MD_STEP(i_, s_)                                                                                   \
+  if ((i_) < RB) {                                                                                        \
+    constexpr int _i = (i_) < RB ? (i_) : 0;                                                              \
+    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(xf[_i]) : "n"(RB - 1));                                   \
+    acc[_i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wreg[s_][0], xf[_i], acc[_i][0], 0, 0, 0);       \
+    acc[_i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wreg[s_][1], xf[_i], acc[_i][1], 0, 0, 0);       \
+    __builtin_amdgcn_sched_barrier(0);                                                                    \
+    MD_READ(_xn, _i);                                                                                     \
+  }
+    // k-tile i, in slot s_ = i mod NS.  The x fragments rotate: the ones multiplied were read a tile before,
+    // each is replaced by its successor right after its products (the last tile's successors come from a
+    // stale slot and are not used), so a wave has RB - 1 reads under way at every product.
+    // Requests complete in order; younger than the x of tile i + 1 are, besides the x of NS - 2 tiles, the
+    // weights requested since: min(i, NS - 1) tiles.
+#define MD_BODY(s_)                                                                                       \
+  do {                                                                                                    \
+    constexpr int sn = ((s_) + 1) % NS;                                                                   \
+    const uint32_t _xn = xa + sn * SLOT;                                                                  \
+    __builtin_amdgcn_sched_barrier(0);                                                                    \
+    MD_STEP(0, s_); MD_STEP(1, s_); MD_STEP(2, s_); MD_STEP(3, s_); MD_STEP(4, s_);       \
+  } while (0)
+  /* after it everyone's part of tile i + 1 is there, and nobody reads the slot of tile i any more */
+#define MD_SYNC(s_)                                                                                       \
+  do {                                                                                                    \
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");                                       \
+    asm volatile("" : "+v"(wreg[s_][0]), "+v"(wreg[s_][1]));                                              \
+  } while (0)
+    constexpr int XH = (NS - 2) * NI, XL = (NS - 2) * (NI - 1), WA = (NS - 1) * 2;
+#define MD_ITER(s_)                                                                                       \
+  do {                                                                                                    \
+    const int i = i0 + (s_);                                                                              \
+    if (i < nt) {                                                                                         \
+      if (i + NS > nt) wait_vm<0>();                                                                      \
+      else if (i0 == 0) { if (full) wait_vm<XH + (s_) * 2>(); else wait_vm<XL + (s_) * 2>(); }            \
+      else { if (full) wait_vm<XH + WA>(); else wait_vm<XL + WA>(); }                                     \
+      MD_SYNC(s_);                                                                                        \
+      if (i + NS < nt) MD_X(MD_T(i + NS), s_);                                                            \
+      MD_BODY(s_);                                                                                        \
+      if (i + NS < nt) MD_W(MD_T(i + NS), s_);                                                            \
+    }                                                                                                     \
+  } while (0)
+    // the same where neither the start nor the end is near (tile `tile` is requested)
+#define MD_STEADY(s_)                                                                                     \
+  do {                                                                                                    \
+    if (full) wait_vm<XH + WA>(); else wait_vm<XL + WA>();                                                \
+    MD_SYNC(s_);                                                                                          \
+    MD_X(tile, s_);                                                                                       \
+    MD_BODY(s_);                                                                                          \
+    MD_W(tile, s_);                                                                                       \
+    tile = tile + 1 < kt_e ? tile + 1 : kt_b;                                                             \
+  } while (0)
+    if (nt > 0) {
+      if (nt < NS) wait_vm<0>(); else if (full) wait_vm<(NS - 1) * NI>(); else wait_vm<(NS - 1) * (NI - 1)>();
+      asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < RB; ++i) MD_READ(xa, i);
+    }
+    int i0 = 0;
+#define MD_ROUND(m_)                                                                                      \
+  do {                                                                                                    \
+    m_(0); m_(1); m_(2);                                                                                  \
+    if constexpr (NS > 3) m_(3);                                                                          \
+  } while (0)
+#pragma unroll 1
+    for (; i0 < nt; i0 += NS) {
+      if (i0 > 0 && i0 + 2 * NS <= nt) {
+        int tile = MD_T(i0 + NS);
+#pragma unroll 1
+        for (; i0 + 2 * NS <= nt; i0 += NS) MD_ROUND(MD_STEADY);
+      }
+      MD_ROUND(MD_ITER);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();                                             // the ring is free
+    // ---- the contraction groups' sums: row block i is finished by group i mod KG
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+      if (i % KG != g) {
+        const int d = (g - i % KG - 1) & (KG - 1);
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) red[(((i * WN + wn) * 2 + cb) * (KG - 1) + d) * 64 + lane] = acc[i][cb];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+      if (i % KG == g) {
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          f32x4 s = acc[i][cb];
+#pragma unroll
+          for (int d = 0; d < KG - 1; ++d) {
+            const f32x4 o = red[(((i * WN + wn) * 2 + cb) * (KG - 1) + d) * 64 + lane];
+            s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
+          }
+          y[i / KG][cb] = s;
+        }
+      }
+  }
+  if (a.ksplit > 1) {
+    // ---- hand over the others' units, collect this split's
+    float* tile = parts + (int64_t)tn * (UNITS * 256) * a.ksplit + lane * 4;
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+        if (j * KG + g < RB && !(own && cb == cbo)) {
+          f32x4 f;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) f[v] = __float_as_uint(y[j][cb][v]) == 0u ? -0.f : y[j][cb][v];
+          store4_agent(tile + ((((j * KG + g) * WN + wn) * 2 + cb) * a.ksplit + ks0) * 256, f);
+        }
+    bool ok = true;
+    f32x4 w[NR][3];                                              // the other splits' sums, in split order
+    if (own) {
+      ok = false;
+      for (int it = 0; it < a.spin_limit && !ok; ++it) {
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+#pragma unroll
+          for (int o = 0; o < 3; ++o) {
+            const int rb = j * KG + g < RB ? j * KG + g : g, q = o + 1 < a.ksplit ? o + (o >= ks0) : ks0 == 0;
+            load4_agent(w[j][o], tile + (((rb * WN + wn) * 2 + cbo) * a.ksplit + q) * 256);
+          }
+        wait_vm<0>();
+        bool all = true;
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+#pragma unroll
+          for (int o = 0; o < 3; ++o) {
+            asm volatile("" : "+v"(w[j][o]));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) all &= __float_as_uint(w[j][o][v]) != 0u;
+          }
+        ok = __ballot(all) == ~0ull;
+      }
+    }
+    wait_vm<0>();                                                // (who clears after a wait given up finds all of it)
+    if (own && ok) {
+#pragma unroll
+      for (int j = 0; j < NR; ++j) {
+        const f32x4 mine = cbo ? y[j][1] : y[j][0];
+        f32x4 sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 o = q == ks0 ? mine : q > ks0 ? w[j][q > 0 ? q - 1 : 0] : w[j][q < 3 ? q : 2];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sum[v] = q == 0 ? o[v] : q < a.ksplit ? sum[v] + o[v] : sum[v];
+        }
+        if (cbo) y[j][1] = sum; else y[j][0] = sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < a.ksplit && q != ks0 && j * KG + g < RB)
+            store4_agent(tile + ((((j * KG + g) * WN + wn) * 2 + cbo) * a.ksplit + q) * 256, f32x4{0.f, 0.f, 0.f, 0.f});
+      }
+    } else if (own) {
+      // (not reached in practice) these units' whole contraction again, in plain fp32 arithmetic
+      gave_s[0] = 1;
+      const int64_t n = n0 + cbo * 16 + 4 * lg;
+#pragma unroll 1
+      for (int j = 0; j < NR; ++j) {
+        const int32_t xtok = j * KG + g < RB ? tok_s[(j * KG + g) * 16 + li] : -1;
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        if (xtok >= 0 && n < Nout)
+          for (int64_t k = 0; k < a.Kc; ++k) {
+            const float xv = bf16_bits_to_float(a.Aop[(int64_t)xtok * a.lda + k]);
+            const bf16_t* wk = (const bf16_t*)a.proj[p].W + ((((n >> 4) * ldb + (k >> 5)) * 64 + (k >> 3 & 3) * 16 + (n & 15)) << 3) + (k & 7);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sum[v] = fmaf(xv, bf16_bits_to_float(wk[8 * v]), sum[v]);
+          }
+#pragma unroll
+        for (int jj = 0; jj < NR; ++jj) if (jj == j) { if (cbo) y[jj][1] = sum; else y[jj][0] = sum; }
+      }
+    }
+  }
+
+  if (lora) {
+    // the first octets' factor fragments depend on nothing that has to be waited for
+    Frag pre[NR][2];
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        const int rb = j * KG + g;
+        pre[j][cb].u = make_uint4(0, 0, 0, 0);
+        if (rb < RB && lg < cnt_s[rb]) {
+          const int o = oct_s[rb * oct_max + lg];
+          const int64_t n = n0 + cb * 16 + li;
+          if (n < Nout) pre[j][cb].u = *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[o >> 8] + (o & 255) + n * rank_s[o >> 8]);
+        }
+      }
+    __syncthreads();                                             // the sums have met: their place is u's now
+    const int uq = a.r_stride >> 2;
+    for (int i = tid; i < BM * uq; i += MD_THREADS) {
+      const int row = i / uq, q = (i - row * uq) * 4;
+      const int rank = t_s[row] >= 0 ? rank_s[row] : 0;
+      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (q < rank) {
+        bool ok = false;
+        const float* up = u_p + (m0 + row) * a.r_stride + q;
+        const float* up1 = up + (S > 1 ? u_n : 0);
+        for (int it = 0; it < a.spin_limit && !ok; ++it) {
+          f32x4 w0, w1;
+          asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
+                       : "=&v"(w0), "=&v"(w1) : "v"(up), "v"(up1) : "memory");
+          ok = true;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            ok &= __float_as_uint(w0[j]) != 0u && __float_as_uint(w1[j]) != 0u;
+            v[j] = S > 1 ? w0[j] + w1[j] : w0[j];
+          }
+        }
+        if (!ok) {
+          // (not reached in practice) the shrink of this row again, in plain fp32 arithmetic
+          const AdapterEntry en = table[t_s[row]];
+          const bf16_t* xr = a.Aop + (int64_t)tok_s[row] * a.lda;
+          for (int j = 0; j < 4 && q + j < rank; ++j) {
+            const bf16_t* lr = (const bf16_t*)(a.which ? en.A : en.B) + (int64_t)(q + j) * a.Kc;
+            float sum = 0.f;
+            for (int64_t k = 0; k < a.Kc; ++k) sum = fmaf(bf16_bits_to_float(xr[k]), bf16_bits_to_float(lr[k]), sum);
+            v[j] = en.scale * sum;
+          }
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
+      *(f32x4*)(u_s + row * us + q) = v;
+      if (a.u_out && ks0 == 0 && tn == a.proj[p].tile0 && m0 + row < a.T && q < ((rank + 15) & ~15))
+        *(f32x4*)(a.u_out + (m0 + row) * a.r_stride + q) = v;
+    }
+    __syncthreads();
+    if (wave == MD_WAVES - 1) leave(gave_s[0]);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const int rb = j * KG + g;
+      if (rb >= RB || !own) break;
+      const int row = rb * 16 + li, cnt = cnt_s[rb];
+      if (cnt >= 0) {
+        // expand on the MFMAs: first operand 16 columns x 4 octets of the factors, second the rows' u in
+        // two bf16 terms (zeros where the octet is another adapter's)
+        for (int k0 = 0; k0 < cnt; k0 += 4) {
+          const bool valid = k0 + lg < cnt;
+          const int o = oct_s[rb * oct_max + (valid ? k0 + lg : 0)], orow = o >> 8;
+          Frag f[2];
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) {
+            f[cb] = pre[j][cb];
+            if (k0 > 0) {
+              const int64_t n = n0 + cb * 16 + li;
+              f[cb].u = make_uint4(0, 0, 0, 0);
+              if (valid && n < Nout) f[cb].u = *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[orow] + (o & 255) + n * rank_s[orow]);
+            }
+          }
+          const bool mine = valid && t_s[row] == t_s[orow];
+          const float* ur = u_s + row * us + (o & 255);
+          const f32x4 ua = *(const f32x4*)ur, ub = *(const f32x4*)(ur + 4);
+          const float uv[8] = {ua[0], ua[1], ua[2], ua[3], ub[0], ub[1], ub[2], ub[3]};
+          union { uint32_t w[4]; bf16x8 v; } hi, lo;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v0 = mine ? uv[2 * e] : 0.f, v1 = mine ? uv[2 * e + 1] : 0.f;
+            const uint32_t h0 = float_to_bf16_bits(v0), h1 = float_to_bf16_bits(v1);
+            hi.w[e] = h0 | (h1 << 16);
+            lo.w[e] = float_to_bf16_bits(v0 - __uint_as_float(h0 << 16)) | ((uint32_t)float_to_bf16_bits(v1 - __uint_as_float(h1 << 16)) << 16);
+          }
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) {
+            y[j][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[cb].v, lo.v, y[j][cb], 0, 0, 0);
+            y[j][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[cb].v, hi.v, y[j][cb], 0, 0, 0);
+          }
+        }
+      } else if (t_s[row] >= 0) {
+        // ranks that are no multiples of 8, or factors stored rank-major: plain fp32 expand of this lane's row
+        const int rank = rank_s[row];
+        const bf16_t* L = (const bf16_t*)(uintptr_t)rL_s[row];
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          const int64_t n = n0 + cb * 16 + 4 * lg;
+          if (n < Nout)
+            for (int q = 0; q < rank; ++q) {
+              const float uq1 = u_s[row * us + q];
+#pragma unroll
+              for (int v = 0; v < 4; ++v)
+                y[j][cb][v] = fmaf(uq1, bf16_bits_to_float(a.lform == FORM_NT ? L[(n + v) * rank + q] : L[(int64_t)q * Nout + n + v]), y[j][cb][v]);
+            }
+        }
+      }
+    }
+  } else if (a.ksplit > 1) {
+    __syncthreads();
+    if (wave == MD_WAVES - 1) leave(gave_s[0]);
+  }
+  if (!own) return;
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    if (j * KG + g >= RB) break;
+    const int32_t otok = tok_s[(j * KG + g) * 16 + li];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      const int64_t n = n0 + cb * 16 + 4 * lg;
+      if (otok < 0 || n >= Nout || (a.ksplit > 1 && cb != cbo)) continue;   // (Nout is a multiple of 8: four columns are in or out together)
+      if (a.out_is_f32) {
+        *(f32x4*)((float*)a.proj[p].out + (int64_t)otok * a.proj[p].ldo + n) = y[j][cb];
+      } else {
+        uint2 o;
+        o.x = float_to_bf16_bits(y[j][cb][0]) | ((uint32_t)float_to_bf16_bits(y[j][cb][1]) << 16);
+        o.y = float_to_bf16_bits(y[j][cb][2]) | ((uint32_t)float_to_bf16_bits(y[j][cb][3]) << 16);
+        *(uint2*)((bf16_t*)a.proj[p].out + (int64_t)otok * a.proj[p].ldo + n) = o;
+      }
+    }
+  }
+}
+
+template <int RB, int WN>
+static hipError_t launch_mid(const GemmArgs& a, const MidJobs& jobs, hipStream_t stream) {
+  constexpr int BM = 16 * RB;
+  const size_t u_bytes = (size_t)BM * (a.r_stride + 4) * sizeof(float), base = MidShape<RB, WN>::BASE;
+  const size_t lds = (base > u_bytes ? base : u_bytes) + BM * 20 + RB * 4 + 4 + (size_t)RB * 2 * a.r_stride * sizeof(uint16_t);
+  static std::atomic<uint64_t> done_dev{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (!(done_dev.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute((const void*)gemm_mid_kernel<RB, WN>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    done_dev.fetch_or(bit, std::memory_order_release);
+  }
+  const int ng = 8 / a.ksplit;
+  const int consumers = 8 * ((a.tiles_n + ng - 1) / ng) * a.tiles_m;
+  // Producers go first where all workgroups are on the chip at once or splits keep the consumers short: their
+  // u is then there in time (100 rows, 4096 x 4096 in four splits: 26.4 us, after the consumers 29.3).  Else
+  // after the consumers' first 256, which they would delay (512 rows, 4096 x 4096, 64 adapters: 50 -> 40 us).
+  GemmArgs g = a;
+  g.prod0 = a.n_prod + consumers <= 512 || a.ksplit > 1 || consumers < 256 ? 0 : 256;
+  hipLaunchKernelGGL((gemm_mid_kernel<RB, WN>), dim3(a.n_prod + consumers), dim3(MD_THREADS), lds, stream, g, jobs);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, const MidJobs& jobs, hipStream_t stream) {
+  // How far apart neighbouring column tiles start (see MD_T): eight of them over the whole contraction, as long
+  // as the part of x between the first and the last stays in an XCD's L2 (256 rows, 14336 x 4096 in one
+  // split: 81 us over 1.4 MB of x, 91 over all of it).
+  const int64_t kt = 32 * (MD_WAVES / p.wn), nt = ((a.Kc + kt - 1) / kt + p.ksplit - 1) / p.ksplit, window = (1400 << 10) / (a.T * kt * 2);
+  a.rot = (int)((nt < window ? nt : window) / 8);
+  // a producer's contraction in two pieces unless a wave has few steps of it
+  a.n_split = (a.Kc + 31) / 32 <= 8 * MD_WAVES ? 1 : MID_SPLITS;
+  a.ksplit = p.ksplit;
+  a.tiles_m = p.tiles_m;
+  a.n_prod = (jobs.end[a.n_proj * a.tiles_m - 1] * a.n_split + 7) / 8 * 8;
+  a.tiles_n = 0;
+  for (int q = 0; q < a.n_proj; ++q) {
+    a.proj[q].tile0 = a.tiles_n;
+    a.tiles_n += (int)((a.proj[q].Nout + 32 * p.wn - 1) / (32 * p.wn));
+  }
+  if (p.wn == 4) return p.rb == 4 ? launch_mid<4, 4>(a, jobs, stream) : launch_mid<5, 4>(a, jobs, stream);
+  return p.rb == 4 ? launch_mid<4, 2>(a, jobs, stream) : launch_mid<5, 2>(a, jobs, stream);
+}
+
+// Estimated run time of a tiling in microseconds, fitted to 3500 runs over 5 to 1024 rows, contractions of
+// 1024 to 14336 and 1024 to 28672 columns (a tenth off as a rule; the tiling it picks is 2 % slower than
+// the best one in the mean).  A k-tile's time when a workgroup has its compute unit to itself, which
+// two on one unit take 2.5 times as long for; longer rows of x and W cost a little more; against it what the
+// fabric delivers; splits pay for the exchange.
+MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool lora) {
+  static const double tile_us[2][2] = {{0.29, 0.25}, {0.38, 0.31}};       // [rb - 4][wn == 4]
+  MidPlan best;
+  int64_t cols = 0;
+  for (int q = 0; q < n_proj; ++q) cols += proj[q].Nout;
+  const double stretch = Kc > 4096 ? 1.0 + 0.12 * log2((double)Kc / 4096.0) : 1.0;
+  for (int wn = 2; wn <= 4; wn += 2) {
+    const int64_t kt = 32 * (MD_WAVES / wn), ktiles = (Kc + kt - 1) / kt;
+    int64_t tiles_n = 0;
+    for (int q = 0; q < n_proj; ++q) tiles_n += (proj[q].Nout + 32 * wn - 1) / (32 * wn);
+    for (int rb = 4; rb <= 5; ++rb) {
+      const int64_t tiles_m = (T + 16 * rb - 1) / (16 * rb);
+      for (int s = 1; s <= 4; s *= 2) {
+        const int64_t wgs = tiles_m * tiles_n * s;
+        if (s > 1 && (wgs > MID_SPLIT_WGS || ktiles < 4 * s)) continue;
+        const double t1 = tile_us[rb - 4][wn == 4] * stretch * (double)((ktiles + s - 1) / s), t2 = 2.5 * t1;
+        double fill;
+        if (wgs <= 256) {
+          fill = t1 * (wgs > 128 ? 1.0 + 0.58 * (double)(wgs - 128) / 128.0 : 1.0);
+        } else {
+          const double left = (double)(wgs % 512);
+          fill = (double)(wgs / 512) * (t2 + 2.3);
+          if (left > 0.0) fill += 2.3 + t1 + (left > 256.0 ? (t2 - t1) * (left - 256.0 < 82.0 ? (left - 256.0) / 82.0 : 1.0) : 0.0);
+        }
+        const double fabric = (2.0 * cols * Kc + 16.0 * T * Kc / s) / 6.4e6;
+        double us = 4.1 + cbrt(fill * fill * fill + fabric * fabric * fabric) + (lora ? 6.2 + T / 300.0 : 0.0);
+        if (s > 1) us += (s > 2 ? 4.1 : 2.1) + (wgs > 192 ? 0.9 * (double)(wgs - 192) / 64.0 : 0.0);
+        if (best.rb == 0 || us < best.us) { best.us = us; best.rb = rb; best.wn = wn; best.ksplit = s; best.tiles_m = (int)tiles_m; }
+      }
+    }
+  }
+  return best;
+}
+
+// Whether the call is better off elsewhere (ext: ranks of all adapters in the batch, 0: no adapters).
+//   Up to 16 rows the few-row kernel, up to 32 while its workgroups, which hold all of x, have little of it.
+//   Above 384 rows the wide kernel as soon as its rate makes up for its shrink's launches and its ext
+//   columns: mostly few adapters on large weights (512 rows, 4096 x 14336: no adapter 55 against 88 us, one
+//   66 / 93, 32 adapters of rank 16 107 / 100, 64 of mixed ranks 145 / 123).
+//   Up to 256 rows the split kernel with its separate finish on a long contraction and few columns, where
+//   the row tiles here are few and their splits expensive (200 rows, 14336 x 4096, rank 16: 61 / 72).
+bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext) {
+  if (T <= 16) return false;
+  if (T <= 32) return T * Kc > 140000 || Kc * cols > 50000000;
+  if (T > 384) return p.us < 14.0 + 2.0 * T * Kc * cols / 1.25e9 + (ext > 0 ? 6.0 + 0.1 * ext : 0.0);
+  if (T > 64 && T <= 256 && ext <= 512 && Kc >= 2 * cols && Kc * cols >= 40000000)
+    return 1.1 * p.us < 15.0 + Kc * cols * (T <= 128 ? 0.57e-6 : 0.82e-6);
+  return true;
+}
+
+}  // namespace marlaas

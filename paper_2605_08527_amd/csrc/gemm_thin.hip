@@ -1,4 +1,4 @@
-// Decode of few sequences (up to 64 rows) on the packed weight: the whole call in one launch.
+// Decode of few sequences (up to 32 rows) on the packed weight: the whole call in one launch.
 //
 //   out_p[tok(m), :] = x[tok(m), :] W_p  +  u_p(m) L_{t,p}        for every projection p of the call
 //
@@ -425,17 +425,16 @@ static hipError_t launch_thin(const GemmArgs& a, hipStream_t stream) {
 
 // Column blocks per workgroup: as few as keep the consumers near 160 (4096 columns, rank-16 adapters, 1
 // / 6 / 32 rows: 12.6 / 13.4 / 22.7 us with one block each, 10.3 / 11.8 / 16.4 with two: half as many
-// workgroups read u and x); at most two above 32 rows (LDS).
+// workgroups read u and x).
 hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream) {
   // splits of a producer's contraction: so that a wave of it has about eight steps, two rounds of loads
   const int64_t steps = ((a.Kc + 31) / 32 + TH_WAVES - 1) / TH_WAVES;
   a.n_split = (int)(steps <= 8 ? 1 : steps <= 16 ? 2 : THIN_SPLITS);
-  if (a.T > 32 && a.n_split > 2) a.n_split = 2;      // (every consumer reads all of u)
   a.n_prod *= a.n_split;
-  const int R = a.T <= 16 ? 1 : a.T <= 32 ? 2 : 4;
+  const int R = a.T <= 16 ? 1 : 2;
   int64_t blocks = 0;
   for (int p = 0; p < a.n_proj; ++p) blocks += (a.proj[p].Nout + 15) / 16;
-  const int nc = blocks <= 160 ? 1 : blocks <= 320 || R == 4 ? 2 : 4;
+  const int nc = blocks <= 160 ? 1 : blocks <= 320 ? 2 : 4;
   a.tiles_n = 0;
   for (int p = 0; p < a.n_proj; ++p) {
     a.proj[p].tile0 = a.tiles_n;
@@ -443,7 +442,7 @@ hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream) {
   }
 #define TH_PICK(R_) (nc == 1 ? launch_thin<R_, 1>(a, stream) : launch_thin<R_, 2>(a, stream))
   if (nc == 4) return R == 1 ? launch_thin<1, 4>(a, stream) : launch_thin<2, 4>(a, stream);
-  return R == 1 ? TH_PICK(1) : R == 2 ? TH_PICK(2) : TH_PICK(4);
+  return R == 1 ? TH_PICK(1) : TH_PICK(2);
 #undef TH_PICK
 }
 

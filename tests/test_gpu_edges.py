@@ -81,3 +81,27 @@ def test_few_rows_packed(oracle, monkeypatch, T, K, N, ranks, layout, spin):
     for rep in range(2):
         _check_layer(oracle, w, bwd=True, tag="few rows", table="table+packed")
     _check_layer(oracle, w, bwd=True, tag="few rows", table="lists+packed")
+
+
+# Some more rows on packed weights, likewise in one launch: 64- and 80-row tiles of 64 and 128 columns, one,
+# two and four contraction splits (fewer k-tiles in one than in the ring, none of them whole), more workgroups
+# than the chip holds, more adapters than lanes, adapters across row tiles, ranks off the octets, the bounded
+# waits given up at once.
+@pytest.mark.parametrize("spin", [None, "0"])
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,K,N,ranks", [(65, 136, 264, [8 + 8 * (t % 4) for t in range(70)]), (17, 9000, 520, [16, 8]), (80, 2056, 1032, [16] * 20),
+                                         (160, 1032, 8200, [128, 8]), (157, 4104, 520, [24, 16]), (300, 1064, 3080, [5, 13, 7]),
+                                         (385, 264, 1032, [16, 8, 64]), (1024, 136, 9000, [8] * 30)])
+def test_some_rows_packed(oracle, monkeypatch, T, K, N, ranks, layout, spin):
+    if spin is not None:
+        if T * K > 200000:
+            pytest.skip("the plain arithmetic after a wait given up takes long")
+        monkeypatch.setenv("MARLAAS_SPIN_LIMIT", spin)
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    if layout:
+        ids = np.sort(ids)
+    w = wl.make_layer(T + N, T, K, N, ranks, [0.5 + (t % 3) for t in range(len(ranks))], ids, dtype="bf16", layout=layout, want_dY=True)
+    for rep in range(2):
+        _check_layer(oracle, w, bwd=True, tag="some rows", table="table+packed")
+    _check_layer(oracle, w, bwd=True, tag="some rows", table="lists+packed")
