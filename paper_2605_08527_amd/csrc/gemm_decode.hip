@@ -38,6 +38,7 @@
 //     which is why it is not the default.
 #include "gemm_args.h"
 #include "agent_memory.h"
+#include "lora_expand.h"
 
 #include <atomic>
 
@@ -632,43 +633,13 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
     const int cnt = oct_cnt_s[rb];
     const int64_t nb = n0 + wnu * 32;
     if (cnt > 0) {
-      // expand on the MFMAs: first operand 16 columns x 4 octets of the factors, second the rows'
-      // u in two bf16 terms (zeros where the octet is another adapter's)
-      for (int k0 = 0; k0 < cnt; k0 += 4) {
-        const int o = k0 + lg;
-        const bool valid = o < cnt;
-        const int oi = rb * D_MAXOCT + (valid ? o : 0);
-        const int r = oct_r_s[oi];
-        union { uint4 u; bf16x8 v; } fa[2];
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-          fa[cb].u = make_uint4(0, 0, 0, 0);
-          const int64_t n = nb + cb * 16 + li;
-          if (k0 == 0) fa[cb].u = pre[cb];
-          else if (valid && n < Nout) fa[cb].u = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L_s[oi] + n * r);
-        }
-        float uv[8];
-        const bool mine = valid && radp_s[row] == oct_t_s[oi];
-        {
-          const float* ur = u_s + row * rs + oct_q_s[oi];
-          const float4 ua = *(const float4*)ur, ub = *(const float4*)(ur + 4);
-          uv[0] = ua.x; uv[1] = ua.y; uv[2] = ua.z; uv[3] = ua.w; uv[4] = ub.x; uv[5] = ub.y; uv[6] = ub.z; uv[7] = ub.w;
-        }
-        union { uint32_t w[4]; bf16x8 v; } hi, lo;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float u0 = mine ? uv[2 * e] : 0.f, u1 = mine ? uv[2 * e + 1] : 0.f;
-          const uint32_t h0 = float_to_bf16_bits(u0), h1 = float_to_bf16_bits(u1);
-          const uint32_t l0 = float_to_bf16_bits(u0 - __uint_as_float(h0 << 16)), l1 = float_to_bf16_bits(u1 - __uint_as_float(h1 << 16));
-          hi.w[e] = h0 | (h1 << 16);
-          lo.w[e] = l0 | (l1 << 16);
-        }
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-          s[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[cb].v, lo.v, s[cb], 0, 0, 0);
-          s[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[cb].v, hi.v, s[cb], 0, 0, 0);
-        }
-      }
+      expand_octets(s, pre, cnt, lg, radp_s[row], u_s + row * rs,
+                    [&](int i) { const int oi = rb * D_MAXOCT + i; return oct_t_s[oi] << 8 | oct_q_s[oi]; },
+                    [&](int i, int cb) {
+                      const int oi = rb * D_MAXOCT + i;
+                      const int64_t n = nb + cb * 16 + li;
+                      return n < Nout ? *(const uint4*)((const bf16_t*)(uintptr_t)oct_L_s[oi] + n * oct_r_s[oi]) : make_uint4(0, 0, 0, 0);
+                    });
     } else if (cnt < 0 && tok >= 0 && rrank_s[row] > 0) {
       // plain fp32 expand of this lane's row
       const int rank = rrank_s[row];

@@ -26,6 +26,7 @@
 // and the area is then cleared by whoever is last.  No workgroup depends on another one being scheduled.
 #include "gemm_args.h"
 #include "agent_memory.h"
+#include "lora_expand.h"
 
 #include <atomic>
 #include <cmath>
@@ -556,17 +557,17 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
 
   if (lora) {
     // the first octets' factor fragments depend on nothing that has to be waited for
-    Frag pre[NR][2];
+    uint4 pre[NR][2];
 #pragma unroll
     for (int j = 0; j < NR; ++j)
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) {
         const int rb = j * KG + g;
-        pre[j][cb].u = make_uint4(0, 0, 0, 0);
+        pre[j][cb] = make_uint4(0, 0, 0, 0);
         if (rb < RB && lg < cnt_s[rb]) {
           const int o = oct_s[rb * oct_max + lg];
           const int64_t n = n0 + cb * 16 + li;
-          if (n < Nout) pre[j][cb].u = *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[o >> 8] + (o & 255) + n * rank_s[o >> 8]);
+          if (n < Nout) pre[j][cb] = *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[o >> 8] + (o & 255) + n * rank_s[o >> 8]);
         }
       }
     __syncthreads();                                             // the sums have met: their place is u's now
@@ -616,39 +617,13 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
       if (rb >= RB || !own) break;
       const int row = rb * 16 + li, cnt = cnt_s[rb];
       if (cnt >= 0) {
-        // expand on the MFMAs: first operand 16 columns x 4 octets of the factors, second the rows' u in
-        // two bf16 terms (zeros where the octet is another adapter's)
-        for (int k0 = 0; k0 < cnt; k0 += 4) {
-          const bool valid = k0 + lg < cnt;
-          const int o = oct_s[rb * oct_max + (valid ? k0 + lg : 0)], orow = o >> 8;
-          Frag f[2];
-#pragma unroll
-          for (int cb = 0; cb < 2; ++cb) {
-            f[cb] = pre[j][cb];
-            if (k0 > 0) {
-              const int64_t n = n0 + cb * 16 + li;
-              f[cb].u = make_uint4(0, 0, 0, 0);
-              if (valid && n < Nout) f[cb].u = *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[orow] + (o & 255) + n * rank_s[orow]);
-            }
-          }
-          const bool mine = valid && t_s[row] == t_s[orow];
-          const float* ur = u_s + row * us + (o & 255);
-          const f32x4 ua = *(const f32x4*)ur, ub = *(const f32x4*)(ur + 4);
-          const float uv[8] = {ua[0], ua[1], ua[2], ua[3], ub[0], ub[1], ub[2], ub[3]};
-          union { uint32_t w[4]; bf16x8 v; } hi, lo;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float v0 = mine ? uv[2 * e] : 0.f, v1 = mine ? uv[2 * e + 1] : 0.f;
-            const uint32_t h0 = float_to_bf16_bits(v0), h1 = float_to_bf16_bits(v1);
-            hi.w[e] = h0 | (h1 << 16);
-            lo.w[e] = float_to_bf16_bits(v0 - __uint_as_float(h0 << 16)) | ((uint32_t)float_to_bf16_bits(v1 - __uint_as_float(h1 << 16)) << 16);
-          }
-#pragma unroll
-          for (int cb = 0; cb < 2; ++cb) {
-            y[j][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[cb].v, lo.v, y[j][cb], 0, 0, 0);
-            y[j][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[cb].v, hi.v, y[j][cb], 0, 0, 0);
-          }
-        }
+        expand_octets(y[j], pre[j], cnt, lg, t_s[row], u_s + row * us,
+                      [&](int i) { const int o = oct_s[rb * oct_max + i]; return t_s[o >> 8] << 8 | (o & 255); },
+                      [&](int i, int cb) {
+                        const int o = oct_s[rb * oct_max + i], orow = o >> 8;
+                        const int64_t n = n0 + cb * 16 + li;
+                        return n < Nout ? *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[orow] + (o & 255) + n * rank_s[orow]) : make_uint4(0, 0, 0, 0);
+                      });
       } else if (t_s[row] >= 0) {
         // ranks that are no multiples of 8, or factors stored rank-major: plain fp32 expand of this lane's row
         const int rank = rank_s[row];

@@ -18,6 +18,7 @@
 // last through with the area clears what was used of it.
 #include "gemm_args.h"
 #include "agent_memory.h"
+#include "lora_expand.h"
 
 #include <atomic>
 
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
     for (int c = 0; c < NC; ++c) red[(wave * TILES + i * NC + c) * 64 + lane] = acc[i][c];
   __syncthreads();
   constexpr int MINE = (TILES + TH_WAVES - 1) / TH_WAVES;       // output tiles finished by a wave
-  f32x4 y[MINE];
+  f32x4 y[MINE][1];
 #pragma unroll
   for (int k = 0; k < MINE; ++k) {
     const int tile = wave + k * TH_WAVES;
@@ -280,20 +281,20 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
       const f32x4 o = red[(w * TILES + tile) * 64 + lane];
       s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
     }
-    y[k] = s;
+    y[k][0] = s;
   }
 
   if (lora) {
     // the first octets' factor fragments depend on nothing that has to be waited for
-    Frag pre[MINE];
+    uint4 pre[MINE][1];
 #pragma unroll
     for (int k = 0; k < MINE; ++k) {
       const int tile = wave + k * TH_WAVES, rb = tile / NC, c = tile - rb * NC;
-      pre[k].u = make_uint4(0, 0, 0, 0);
+      pre[k][0] = make_uint4(0, 0, 0, 0);
       if (tile < TILES && lg < cnt_s[rb]) {
         const int64_t n = n0 + c * 16 + li;
         const int o = rb * oct_max + lg;
-        if (n < Nout) pre[k].u = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
+        if (n < Nout) pre[k][0] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
       }
     }
     for (int i = tid; i < 16 * R * (a.r_stride >> 2); i += TH_THREADS) {
@@ -346,32 +347,12 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
       if (tile >= TILES) break;
       const int row = rb * 16 + li, cnt = cnt_s[rb];
       if (cnt >= 0) {
-        // expand on the MFMAs: first operand 16 columns x 4 octets of the factors, second the rows' u in
-        // two bf16 terms (zeros where the octet is another adapter's)
-        for (int k0 = 0; k0 < cnt; k0 += 4) {
-          const bool valid = k0 + lg < cnt;
-          const int o = rb * oct_max + (valid ? k0 + lg : 0);
-          Frag f = pre[k];
-          if (k0 > 0) {
-            const int64_t n = n0 + c * 16 + li;
-            f.u = make_uint4(0, 0, 0, 0);
-            if (valid && n < Nout) f.u = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
-          }
-          const bool mine = valid && t_s[row] == (int)(oct_tq[o] >> 8);
-          const float* ur = u_s + row * us + (oct_tq[o] & 255);
-          const f32x4 ua = *(const f32x4*)ur, ub = *(const f32x4*)(ur + 4);
-          const float uv[8] = {ua[0], ua[1], ua[2], ua[3], ub[0], ub[1], ub[2], ub[3]};
-          union { uint32_t w[4]; bf16x8 v; } hi, lo;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float v0 = mine ? uv[2 * e] : 0.f, v1 = mine ? uv[2 * e + 1] : 0.f;
-            const uint32_t h0 = float_to_bf16_bits(v0), h1 = float_to_bf16_bits(v1);
-            hi.w[e] = h0 | (h1 << 16);
-            lo.w[e] = float_to_bf16_bits(v0 - __uint_as_float(h0 << 16)) | ((uint32_t)float_to_bf16_bits(v1 - __uint_as_float(h1 << 16)) << 16);
-          }
-          y[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, lo.v, y[k], 0, 0, 0);
-          y[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, hi.v, y[k], 0, 0, 0);
-        }
+        expand_octets(y[k], pre[k], cnt, lg, t_s[row], u_s + row * us, [&](int i) { return (int)oct_tq[rb * oct_max + i]; },
+                      [&](int i, int) {
+                        const int o = rb * oct_max + i;
+                        const int64_t n = n0 + c * 16 + li;
+                        return n < Nout ? *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]) : make_uint4(0, 0, 0, 0);
+                      });
       } else if (t_s[row] >= 0) {
         // ranks that are no multiples of 8, or factors stored rank-major: plain fp32 expand of this lane's row
         const int rank = rank_s[row];
@@ -382,7 +363,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
             const float uq = u_s[row * us + q];
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-              y[k][v] = fmaf(uq, bf16_bits_to_float(a.lform == FORM_NT ? L[(n + v) * rank + q] : L[(int64_t)q * Nout + n + v]), y[k][v]);
+              y[k][0][v] = fmaf(uq, bf16_bits_to_float(a.lform == FORM_NT ? L[(n + v) * rank + q] : L[(int64_t)q * Nout + n + v]), y[k][0][v]);
           }
       }
     }
@@ -395,11 +376,11 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
     const int64_t n = n0 + c * 16 + 4 * lg;
     if (tok < 0 || n >= Nout) continue;            // (Nout is a multiple of 8: four columns are in or out together)
     if (a.out_is_f32) {
-      *(f32x4*)((float*)a.proj[p].out + (int64_t)tok * a.proj[p].ldo + n) = y[k];
+      *(f32x4*)((float*)a.proj[p].out + (int64_t)tok * a.proj[p].ldo + n) = y[k][0];
     } else {
       uint2 o;
-      o.x = float_to_bf16_bits(y[k][0]) | ((uint32_t)float_to_bf16_bits(y[k][1]) << 16);
-      o.y = float_to_bf16_bits(y[k][2]) | ((uint32_t)float_to_bf16_bits(y[k][3]) << 16);
+      o.x = float_to_bf16_bits(y[k][0][0]) | ((uint32_t)float_to_bf16_bits(y[k][0][1]) << 16);
+      o.y = float_to_bf16_bits(y[k][0][2]) | ((uint32_t)float_to_bf16_bits(y[k][0][3]) << 16);
       *(uint2*)((bf16_t*)a.proj[p].out + (int64_t)tok * a.proj[p].ldo + n) = o;
     }
   }

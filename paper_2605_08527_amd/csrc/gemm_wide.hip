@@ -77,6 +77,16 @@ __device__ __forceinline__ void wide_meet() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)\n\ts_barrier" :: "n"(VM > 63 ? 63 : VM), "n"(LG) : "memory");
 }
 
+// a pointer that is the same in all lanes, in scalar registers
+__device__ __forceinline__ const char* uniform(const char* p) {
+  const uint64_t v = (uint64_t)(uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return (const char*)(uintptr_t)((uint64_t)hi << 32 | lo);
+}
+
+// every vector-memory request of this wave is complete
+__device__ __forceinline__ void wide_drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // The MFMAs take the weight fragment as their first operand, so a block of the accumulators is the
 // transpose of the output block: in a 16 x 16 block lane l holds output row (token) l % 16 and the
 // four consecutive output columns 4 (l / 16) .. + 3.
@@ -190,7 +200,7 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
         b_off[j] = (uint32_t)((_k * a.ldb + (_n - n0)) * 2);                                              \
       }                                                                                                   \
     }                                                                                                     \
-    b_base = (const char*)(FORM == FORM_NT ? a.B + n0 * a.ldb + kbeg : a.B + kbeg * a.ldb + n0);          \
+    b_base = uniform((const char*)(FORM == FORM_NT ? a.B + n0 * a.ldb + kbeg : a.B + kbeg * a.ldb + n0)); \
   } while (0)
   // the last k-tile of a contraction that is no multiple of 64 fetches zeros beyond the end
 #define W_DMA_A(slot_, j_, tail_)                                                                              \
@@ -372,6 +382,7 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
       if (_r0 + 16 > (lo_) && _r0 < (hi_)) {                                                              \
         _Pragma("unroll") for (int _n = 0; _n < W_NT; ++_n)                                               \
           acc[_mt][_n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(_wf[_n], _xf[_mt], acc[_mt][_n], 0, 0, 0); \
+        shared_rows |= __builtin_amdgcn_readfirstlane(_r0 < (lo_) || _r0 + 16 > (hi_)) << _mt;            \
       }                                                                                                   \
     }                                                                                                     \
   } while (0)
@@ -394,6 +405,7 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
     } else {
       wide_meet<0, 0>();
     }
+    int shared_rows = 0;             // row blocks of this wave that hold rows of several adapters
     int lt_cnt = 0;
     if (a.lora == WIDE_LORA_LISTS && split == 0) lt_cnt = __builtin_amdgcn_readfirstlane(((const LoraTile*)lt_s)->lo);
     int lslot = 0;                   // slot of the first extra contraction tile
@@ -495,6 +507,21 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
         }
       }
     }
+    // In a block of rows of several adapters the others' u is 0, and 0 times a factor that is infinite or
+    // not a number is not 0: such sums are computed again behind the stores.
+    bool again = false;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (shared_rows >> mt & 1) {
+        float z = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < W_NT; ++nt) {
+          const f32x4 c = acc_read(acc[mt][nt]);
+          z = fmaf(c[0], 0.f, fmaf(c[1], 0.f, fmaf(c[2], 0.f, fmaf(c[3], 0.f, z))));
+        }
+        again |= z != 0.f;
+      }
+    again = __ballot(again) != 0;
     // ---- the next item's first requests, then this item's results
     const int64_t em0 = m0, en0 = n0;
     const int eptile = ptile, esplit = split;
@@ -539,6 +566,43 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
       }
     }
     asm volatile("" ::: "memory");
+    if (again) {
+      // (a broken adapter) the wave's row blocks of several adapters in plain fp32, a row's own adapter only
+      const int64_t k0 = eptile >= 0 ? esplit * a.tail_kchunk : 0, k1 = eptile >= 0 && esplit + 1 < a.tail_split ? k0 + a.tail_kchunk : a.Kc;
+      wide_drain();                  // (the stores above)
+#pragma unroll 1
+      for (int mt = 0; mt < MT; ++mt) {
+        const int row = wm * (16 * MT) + mt * 16 + erow;
+        const int64_t m = em0 + row;
+        if (!(shared_rows >> mt & 1) || m >= a.T) continue;
+        const int64_t tok = tok3[(item % 3) * ROWS + row];
+        const int t = m < a.seg_off[a.n_adapters] ? segment_of(a.seg_off, a.n_adapters, (int)m) : -1;
+#pragma unroll 1
+        for (int c = 0; c < W_NT * 4; ++c) {
+          const int64_t n = en0 + wn * 128 + (c >> 2) * 16 + 4 * eg + (c & 3);
+          if (n >= a.Nout) continue;
+          float sum = 0.f;
+          for (int64_t k = k0; k < k1; k += 8) {       // (contraction lengths are multiples of 8)
+            union { uint4 u; bf16_t h[8]; } x, w;
+            x.u = *(const uint4*)(a.A + tok * a.lda + k);
+            if (FORM == FORM_NT) w.u = *(const uint4*)(a.B + n * a.ldb + k);
+            else for (int i = 0; i < 8; ++i) w.h[i] = a.B[(k + i) * a.ldb + n];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum = fmaf(bf16_bits_to_float(x.h[i]), bf16_bits_to_float(w.h[i]), sum);
+          }
+          if (t >= 0 && esplit == 0) {
+            const AdapterEntry e = a.table[t];
+            const bf16_t* L = (const bf16_t*)(a.which ? e.B : e.A);
+            for (int q = 0; q < e.rank; ++q)
+              sum = fmaf(a.U[m * a.r_stride + q], bf16_bits_to_float(LFORM == FORM_NT ? L[n * e.rank + q] : L[(int64_t)q * a.Nout + n]), sum);
+          }
+          if (eptile >= 0) a.partials[((((int64_t)(esplit * a.tail_tiles + eptile) * 4 + wave) * MT + mt) * W_NT + (c >> 2)) * 256 + el * 4 + (c & 3)] = sum;
+          else if (OUT_F32) ((float*)a.out)[tok * a.ldo + n] = sum;
+          else ((bf16_t*)a.out)[tok * a.ldo + n] = float_to_bf16_bits(sum);
+        }
+      }
+      wide_drain();
+    }
   }
 }
 

@@ -172,9 +172,15 @@ __global__ __launch_bounds__(F_THREADS) void layer_f32_kernel(LayerF32Args a) {
     if (NC > 0 && wave < NC && n_e > 0) {
       int64_t col = n0 + 16 * wave + li;
       if (col >= a.Nout) col = a.Nout - 1;
+      int gr[4];                                // adapters of this lane's four output rows
+#pragma unroll
+      for (int v = 0; v < 4; ++v) gr[v] = __shfl(g, 4 * lg + v);
 #pragma unroll
       for (int e = 0; e < F_E; ++e)
         if (e < n_e) {
+          // (only the adapter's own rows take the sum: the others' u is 0, and 0 times a factor that is
+          // infinite or not a number is not 0)
+          f32x4 z = y;
           const AdapterEntry& en = entry_of(a.tb, et[e]);
           const float* L = (const float*)(a.which ? en.B : en.A);
           const int r = er[e], q = eq[e] + 4 * lg;
@@ -184,7 +190,9 @@ __global__ __launch_bounds__(F_THREADS) void layer_f32_kernel(LayerF32Args a) {
           for (int j = 0; j < 4; ++j)
             if (q + j < r) lv[j] = FORM == FORM_NT ? L[col * r + q + j] : L[(int64_t)(q + j) * a.Nout + col];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) y = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[j], lv[j], y, 0, 0, 0);
+          for (int j = 0; j < 4; ++j) z = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[j], lv[j], z, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) y[v] = gr[v] == et[e] ? z[v] : y[v];
         }
     }
   }
