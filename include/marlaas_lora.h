@@ -222,10 +222,14 @@ int marlaas_transpose_weight(marlaas_ctx* ctx, const void* W, int64_t ldw, int64
  * are in flight.  It holds the intermediates u, v, partial sums, a transposed
  * weight copy for some large batches and, for descriptors without an adapter
  * table, a per-call copy of their pointer tables (written by a small kernel at
- * the start of the pass).  marlaas_workspace_bytes returns the size needed by
- * marlaas_lora_fwd (want_bwd = 0) or by fwd and bwd (want_bwd = 1) for this
- * descriptor (only sizes, ranks, dtypes, table and map are read), or 0 if the
- * descriptor is invalid.
+ * the start of the pass).  marlaas_workspace_bytes returns the size at which
+ * marlaas_lora_fwd (want_bwd = 0) or fwd and bwd (want_bwd = 1) run their
+ * fastest plans for this descriptor (only sizes, ranks, dtypes, table and map
+ * are read), or 0 if the descriptor is invalid.  With a smaller workspace a pass
+ * takes the best plan whose partial sums fit it, so that a workspace made for
+ * the largest batch serves smaller ones whose fastest plan would take more; it
+ * gives MARLAAS_ENOMEM where u, v, the tables and the sums it cannot do without
+ * do not fit.  Results then differ by the order of sums.
  */
 size_t marlaas_workspace_bytes(const marlaas_lora_desc* desc, int want_bwd);
 int marlaas_set_workspace(marlaas_ctx* ctx, void* dev_ptr, size_t bytes);
@@ -248,14 +252,14 @@ int marlaas_lora_fwd(marlaas_ctx* ctx, const marlaas_lora_desc* desc, void* y, i
 /*
  * marlaas_lora_fwd for callers that cannot allocate device memory or hand over
  * a workspace: code running under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc.  Same arguments, same kernels and same
- * results as marlaas_lora_fwd, but every intermediate (u, split-contraction
+ * harnesses that forbid hipMalloc.  Same arguments and same results as
+ * marlaas_lora_fwd with a workspace of that many bytes, but every intermediate (u, split-contraction
  * partial sums, the per-call copy of pointer tables) lives in one static array
  * of MARLAAS_STATIC_SCRATCH_BYTES in the library's device code: each GPU the
  * library runs on holds its own copy until the process ends, and the call
  * allocates nothing and ignores marlaas_set_workspace.  A descriptor whose
- * forward needs more scratch than that (marlaas_workspace_bytes(desc, 0)) gives
- * MARLAAS_ENOMEM with a message and enqueues nothing.  All calls on one GPU
+ * forward cannot run with that much scratch gives MARLAAS_ENOMEM with a message
+ * and enqueues nothing.  All calls on one GPU
  * share the array: calls that may overlap in time (different streams, different
  * contexts or threads) race on it; calls on one stream are ordered and safe.
  * Nothing in the array has to be cleared between calls.

@@ -532,14 +532,17 @@ extern "C" int64_t marlaas_u_stride(const marlaas_lora_desc* d) {
 static int64_t ws_ext_cap(int64_t n_ext) { return n_ext < EXT_CAP_MAX ? n_ext : EXT_CAP_MAX; }
 
 struct WsPlan {
-  size_t u_off = 0, v_off = 0, part_off = 0, part_bytes = 0, total = 0;   // part: reused by every kernel with partial sums
+  size_t u_off = 0, v_off = 0;
+  // partial sums, reused by every kernel that has some; last in the workspace, as many bytes as there are
+  // of what the fastest plans take.  total: bytes that hold all of it, least: that a pass runs with.
+  size_t part_off = 0, part_bytes = 0, total = 0, least = 0;
   size_t u2_off = 0, v2_off = 0, uv2_bytes = 0;   // two-term bf16 splits of u and v, [T][2 r_stride] (bf16 inputs)
   size_t lt_off = 0, lt_bytes = 0;                // the row tiles' lists of extra contraction tiles (large-batch GEMM)
   size_t wt_off = 0, wt_bytes = 0;   // transposed copy of the weight (large batches, output-contiguous storage)
   size_t tab_off = 0, tab_bytes = 0; // per-call copy of the adapter tables (descriptors without a table object)
 };
 
-static WsPlan plan_workspace(const marlaas_lora_desc* d, int want_bwd) {
+static WsPlan plan_workspace(const marlaas_lora_desc* d, int want_bwd, size_t ws_bytes) {
   WsPlan p;
   const size_t rs = (size_t)marlaas_u_stride(d);
   const size_t uv = align_up((size_t)(d->T > 0 ? d->T : 1) * rs * sizeof(float), WS_ALIGN);
@@ -548,52 +551,61 @@ static WsPlan plan_workspace(const marlaas_lora_desc* d, int want_bwd) {
   const bool bf = d->in_dtype == MARLAAS_BF16 && d->n_adapters > 0;
   if (bf) {
     p.uv2_bytes = uv; p.u2_off = off; off += uv;
-    p.lt_bytes = align_up(lora_tiles_bytes(d->T), WS_ALIGN); p.lt_off = off; off += p.lt_bytes;
   }
-  size_t part = 0;
+  size_t part = 0, part_least = 0;
   const int n_ext = sum_ranks_of(d);
-  if (d->in_dtype == MARLAAS_BF16) part = gemm_splitk_bytes(d->T, d->d_in, d->d_out, n_ext);
+  auto needs = [&](size_t bytes, size_t least) { part = std::max(part, bytes); part_least = std::max(part_least, least); };
+  if (d->in_dtype == MARLAAS_BF16)
+    needs(gemm_splitk_bytes(d->T, d->d_in, d->d_out, n_ext), gemm_splitk_min_bytes(d->T, d->d_in, d->d_out, n_ext));
   if (bf) {
     const size_t ps = shrink_partial_bytes(d->d_in, d->map->T_lora, d->n_adapters, (int)rs);
-    if (ps > part) part = ps;
+    needs(ps, ps);
   }
+  size_t wt = 0;
   if (want_bwd) {
     p.v_off = off; off += uv;
     if (bf) { p.v2_off = off; off += uv; }
     if (d->in_dtype == MARLAAS_BF16) {
       const size_t pv = d->n_adapters > 0 ? shrink_partial_bytes(d->d_out, d->map->T_lora, d->n_adapters, (int)rs) : 0;
-      if (pv > part) part = pv;
+      needs(pv, pv);
       // (few adapters: room for the reductions' sums even where one chunk covers a segment, so
       // that a backward with the optimizer step attached can always run)
       const bool always = d->n_adapters <= OPT_MAX_ADAPTERS;
       const size_t pa = reduce_partial_bytes(d->d_in, d->n_adapters, d->map->max_seg, (int)rs, always, d->map->ragged_chunk, d->map->ragged_slots);
       const size_t pb = reduce_partial_bytes(d->d_out, d->n_adapters, d->map->max_seg, (int)rs, always, d->map->ragged_chunk, d->map->ragged_slots);
-      const size_t pg = gemm_splitk_bytes(d->T, d->d_out, d->d_in, n_ext);
-      if (pa > part) part = pa;
-      if (pb > part) part = pb;
-      if (pg > part) part = pg;
+      needs(pa, pa);
+      needs(pb, pb);
+      needs(gemm_splitk_bytes(d->T, d->d_out, d->d_in, n_ext), gemm_splitk_min_bytes(d->T, d->d_out, d->d_in, n_ext));
     }
   }
-  p.part_bytes = align_up(part, WS_ALIGN);
-  p.part_off = off; off += p.part_bytes;
   if (d->in_dtype == MARLAAS_BF16) {
-    size_t wt = d->layout == MARLAAS_LAYOUT_MATH ? gemm_wt_bytes(FORM_NN, d->T, d->d_in, d->d_out) : 0;
+    wt = d->layout == MARLAAS_LAYOUT_MATH ? gemm_wt_bytes(FORM_NN, d->T, d->d_in, d->d_out) : 0;
     if (want_bwd && d->layout == MARLAAS_LAYOUT_TORCH) wt = gemm_wt_bytes(FORM_NN, d->T, d->d_out, d->d_in);
     if (d->W_t) wt = 0;                  // the caller keeps the transposed copy
-    p.wt_bytes = align_up(wt, WS_ALIGN);
-    p.wt_off = off; off += p.wt_bytes;
+    wt = align_up(wt, WS_ALIGN);
   }
   if (!d->table && d->n_adapters > 0) {
     p.tab_bytes = dev_tables_bytes(d->n_adapters, ws_ext_cap(n_ext));
     p.tab_off = off; off += p.tab_bytes;
   }
-  p.total = off;
+  part = align_up(part, WS_ALIGN); part_least = align_up(part_least, WS_ALIGN);
+  // Without the lists the large-batch GEMM stages the expand through registers, without the transposed copy
+  // it reads the weight as it is stored: a third slower, so only the calls whose tiles occupy less than half
+  // of the chip go without where room is short.
+  const size_t lists = bf ? align_up(lora_tiles_bytes(d->T), WS_ALIGN) : 0;
+  const size_t wt_least = ((d->T + 255) / 256) * (((want_bwd && d->layout == MARLAAS_LAYOUT_TORCH ? d->d_in : d->d_out) + 255) / 256) > 128 ? wt : 0;
+  p.least = off + part_least + wt_least;
+  p.total = off + lists + wt + part;
+  if (wt && ws_bytes >= p.least - wt_least + wt) { p.wt_bytes = wt; p.wt_off = off; off += wt; }
+  if (lists && ws_bytes >= off + part_least + lists) { p.lt_bytes = lists; p.lt_off = off; off += lists; }
+  p.part_off = off;
+  p.part_bytes = std::min(p.total, std::max(ws_bytes, off)) - off;
   return p;
 }
 
 extern "C" size_t marlaas_workspace_bytes(const marlaas_lora_desc* d, int want_bwd) {
   if (check_sizes(nullptr, d) != MARLAAS_OK) return 0;
-  return plan_workspace(d, want_bwd).total;
+  return plan_workspace(d, want_bwd, 0).total;
 }
 
 extern "C" int marlaas_set_workspace(marlaas_ctx* ctx, void* dev_ptr, size_t bytes) {
@@ -885,11 +897,11 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
   const int rs = (int)marlaas_u_stride(d);
   float* u = (float*)u_save;
   const bool lora = d->n_adapters > 0 && map->T_lora > 0;
-  WsPlan p = plan_workspace(d, 0);
-  const bool have_ws = ws && ws_bytes >= p.total;
+  const WsPlan p = plan_workspace(d, 0, ws_bytes);
+  const bool have_ws = ws && ws_bytes >= p.least;
   if (lora && !u) {
     if (!have_ws)
-      return fail(ctx, MARLAAS_ENOMEM, "forward needs %zu workspace bytes, have %zu", p.total, ws_bytes);
+      return fail(ctx, MARLAAS_ENOMEM, "forward needs %zu workspace bytes, have %zu", p.least, ws_bytes);
     u = (float*)((char*)ws + p.u_off);
   }
   float* part = (have_ws && p.part_bytes) ? (float*)((char*)ws + p.part_off) : nullptr;
@@ -963,7 +975,7 @@ extern "C" int marlaas_lora_fwd_static(marlaas_ctx* ctx, const marlaas_lora_desc
   if (!ctx) return MARLAAS_EINVAL;
   int rc = check_sizes(ctx, d);
   if (rc != MARLAAS_OK) return rc;
-  const size_t need = plan_workspace(d, 0).total;
+  const size_t need = plan_workspace(d, 0, 0).least;
   if (need > (size_t)MARLAAS_STATIC_SCRATCH_BYTES)
     return fail(ctx, MARLAAS_ENOMEM, "this forward needs %zu scratch bytes, the static scratch holds %zu: use marlaas_lora_fwd with a workspace",
                 need, (size_t)MARLAAS_STATIC_SCRATCH_BYTES);
@@ -1035,7 +1047,7 @@ extern "C" size_t marlaas_workspace_bytes_multi(const marlaas_lora_desc* descs, 
   if (check_multi(nullptr, descs, n_proj) != MARLAAS_OK) return 0;
   size_t need = 0;
   for (int p = 0; p < n_proj; ++p) {
-    const size_t one = plan_workspace(&descs[p], 0).total;
+    const size_t one = plan_workspace(&descs[p], 0, 0).total;
     if (one > need) need = one;
   }
   if (n_proj > 1 && descs[0].in_dtype == MARLAAS_BF16) {
@@ -1179,9 +1191,9 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
   const marlaas_segmap* map = d->map;
   const int rs = (int)marlaas_u_stride(d);
   const bool lora = d->n_adapters > 0 && map->T_lora > 0;
-  WsPlan p = plan_workspace(d, 1);
-  if (d->n_adapters > 0 && (!ctx->ws || ctx->ws_bytes < p.total))
-    return fail(ctx, MARLAAS_ENOMEM, "backward needs %zu workspace bytes, have %zu", p.total, ctx->ws_bytes);
+  const WsPlan p = plan_workspace(d, 1, ctx->ws_bytes);
+  if (d->n_adapters > 0 && (!ctx->ws || ctx->ws_bytes < p.least))
+    return fail(ctx, MARLAAS_ENOMEM, "backward needs %zu workspace bytes, have %zu", p.least, ctx->ws_bytes);
   float* u = (float*)u_saved;
   float* v = d->n_adapters > 0 ? (float*)((char*)ctx->ws + p.v_off) : nullptr;
   const bool need_u = lora && want_grads && !u;
@@ -1210,7 +1222,7 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
   const int da_form = d->layout == MARLAAS_LAYOUT_MATH ? FORM_NN : FORM_NT;
   const int db_form = d->layout == MARLAAS_LAYOUT_MATH ? FORM_NT : FORM_NN;
   const int out_f32 = d->out_dtype == MARLAAS_F32;
-  const bool have_ws = ctx->ws && ctx->ws_bytes >= p.total;
+  const bool have_ws = ctx->ws && ctx->ws_bytes >= p.least;
   float* part = (have_ws && p.part_bytes) ? (float*)((char*)ctx->ws + p.part_off) : nullptr;
   const DecodeSync dsync = decode_sync_of(ctx, map);
   if (d->in_dtype == MARLAAS_BF16) {

@@ -274,8 +274,10 @@ hipError_t launch_pack_weight(const bf16_t* src, int64_t sc, int64_t so, int64_t
 size_t gemm_wt_bytes(int form, int64_t T, int64_t Kc, int64_t Nout);
 // dst[c][r] = src[r][c], bf16, R x C (both multiples of 8)
 hipError_t launch_transpose_bf16(const bf16_t* src, int64_t lds, bf16_t* dst, int64_t ldd, int64_t R, int64_t C, hipStream_t stream);
-// scratch for partial sums; n_ext = sum of the adapter ranks (0: no adapters)
+// scratch for partial sums: what the fastest plan takes, and what a pass cannot run without; n_ext = sum of the
+// adapter ranks (0: no adapters)
 size_t gemm_splitk_bytes(int64_t T, int64_t Kc, int64_t Nout, int n_ext);
+size_t gemm_splitk_min_bytes(int64_t T, int64_t Kc, int64_t Nout, int n_ext);
 // Small batches: the GEMM can compute the shrink itself (as extra output columns over every
 // adapter's factor; the finish kernel keeps each row's own adapter).  When this holds the caller
 // skips the shrink launch and passes a GemmFuse; U is then ignored and u_out receives u.

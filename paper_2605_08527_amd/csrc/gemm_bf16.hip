@@ -805,7 +805,7 @@ static double wide_cost(const WidePlan& w, int64_t T, int need) {
 }
 
 // The best small-batch plan for these sizes (us: its estimated time; left alone when none qualifies).
-static bool best_small(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, double* us, GemmPlan* best) {
+static bool best_small(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, size_t max_bytes, double* us, GemmPlan* best) {
   bool found = false;
   int64_t max_s = Kc / 256;                         // contraction values per split, at least
   if (max_s > 32) max_s = 32;
@@ -815,48 +815,62 @@ static bool best_small(int64_t T, int64_t Kc, int64_t Nout, int need, bool packe
     const GemmPlan p = small_plan(s, T, Kc, Nout, need);
     if (p.ksplit == last) continue;                 // rounding the chunk to whole k-tiles gave the same split
     last = p.ksplit;
-    if ((int64_t)p.tiles_m * p.tiles_n * p.ksplit > 4 * CUS) break;
+    if ((int64_t)p.tiles_m * p.tiles_n * p.ksplit > 4 * CUS || p.bytes + p.u_bytes > max_bytes) break;
     const double c = small_cost(p, need, packed);
     if (c < *us) { *us = c; *best = p; found = true; }
   }
   return found;
 }
 
-// need: extended columns of the fullest row tile; packed: the weight has a packed copy.
+// need: extended columns of the fullest row tile; packed: the weight has a packed copy; max_bytes: room
+// for partial sums (the best plan that fits; the large-batch kernel unsplit needs none).
 // small_only: only the 128 x 128 kernels are candidates (the several-projections pass exists for
 // them alone); the large-batch plan is returned when none of them qualifies.
-static GemmPlan gemm_plan(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, bool small_only = false) {
+static GemmPlan gemm_plan(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, size_t max_bytes, bool small_only = false) {
   GemmPlan best;
-  best.w = wide_plan(T, Kc, Nout, true);
+  best.w = wide_plan(T, Kc, Nout, max_bytes);
   best.bytes = best.w.part_bytes;
   // at least half a round of 256 x 256 tiles: the large-batch kernel
   const int64_t G = ((T + 255) / 256) * ((Nout + 255) / 256);
   if (T <= 0 || Nout <= 0 || G > CUS / 2) return best;
   double us = small_only ? 1e30 : wide_cost(best.w, T, need);
-  best_small(T, Kc, Nout, need, packed, &us, &best);
+  best_small(T, Kc, Nout, need, packed, max_bytes, &us, &best);
   return best;
 }
 
 int gemm_ext_room(int64_t Nout) { return (int)((Nout + SK_BN - 1) / SK_BN) * SK_BX; }
 
+static int ext_carried_at_most(int64_t Nout, int n_ext) { return n_ext < gemm_ext_room(Nout) ? n_ext : gemm_ext_room(Nout); }
+
 // (room for whichever kernel a call takes: a descriptor's packed weight and, where the map object is
 // reused, the grouping are not known here)
 size_t gemm_splitk_bytes(int64_t T, int64_t Kc, int64_t Nout, int n_ext) {
   if (T <= 0 || Nout <= 0) return 0;
-  const int need = n_ext < gemm_ext_room(Nout) ? n_ext : gemm_ext_room(Nout);
-  size_t bytes = wide_plan(T, Kc, Nout, true).part_bytes;
+  size_t bytes = wide_plan(T, Kc, Nout, SIZE_MAX).part_bytes;
   const int64_t G = ((T + 255) / 256) * ((Nout + 255) / 256);
   for (int packed = 0; packed < 2 && G <= CUS / 2; ++packed) {
     GemmPlan q;
     double us = 1e30;
-    if (best_small(T, Kc, Nout, need, packed != 0, &us, &q) && q.bytes + q.u_bytes > bytes) bytes = q.bytes + q.u_bytes;
+    if (best_small(T, Kc, Nout, ext_carried_at_most(Nout, n_ext), packed != 0, SIZE_MAX, &us, &q) && q.bytes + q.u_bytes > bytes) bytes = q.bytes + q.u_bytes;
   }
   return bytes;
 }
 
+// A deep contraction whose 256 x 256 tiles leave more than half of the chip idle has to be split: the sums
+// of the plan that needs the least room for them.  Elsewhere a pass does without where room is short: the
+// large-batch kernel runs its last round unsplit.
+size_t gemm_splitk_min_bytes(int64_t T, int64_t Kc, int64_t Nout, int n_ext) {
+  if (T <= 0 || Nout <= 0 || Kc < 2048) return 0;
+  const int64_t G = ((T + 255) / 256) * ((Nout + 255) / 256);
+  if (G > CUS / 2) return 0;
+  const GemmPlan p = small_plan(1, T, Kc, Nout, ext_carried_at_most(Nout, n_ext));
+  const size_t small = p.bytes + p.u_bytes, wide = 2 * (size_t)G * 256 * 256 * sizeof(float);
+  return small < wide ? small : wide;
+}
+
 size_t gemm_wt_bytes(int form, int64_t T, int64_t Kc, int64_t Nout) {
   if (form != FORM_NN || T < WT_MIN_ROWS || Kc <= 0 || Nout <= 0 || Kc > 65535 * 64) return 0;
-  if (!gemm_plan(T, Kc, Nout, 0, false).wide) return 0;
+  if (!gemm_plan(T, Kc, Nout, 0, false, SIZE_MAX).wide) return 0;
   return (size_t)Kc * Nout * sizeof(bf16_t);
 }
 
@@ -864,8 +878,8 @@ bool gemm_can_fuse_shrink(int form, int64_t T, int64_t Kc, int64_t Nout, int nee
                           size_t partial_bytes) {
   if (T <= 0 || Nout <= 0 || need <= 0) return false;
   if (form == FORM_NN && !ranks_mult8) return false;     // 16-byte DMA units must not straddle adapters
-  const GemmPlan p = gemm_plan(T, Kc, Nout, need, packed);
-  return !p.wide && p.u_bytes > 0 && partial_bytes >= p.bytes + p.u_bytes;
+  const GemmPlan p = gemm_plan(T, Kc, Nout, need, packed, partial_bytes);
+  return !p.wide && p.u_bytes > 0;
 }
 
 // Way the decode kernel's call is finished: the one asked for where its conditions hold, else the
@@ -901,13 +915,14 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
   if (T <= 0 || Nout <= 0) return hipSuccess;
   if (ldb > (1 << 22)) return hipErrorInvalidValue;      // 32-bit byte offsets inside a weight tile
   const bool packed = Bpacked != nullptr && use_packed;
-  GemmPlan p = gemm_plan(T, Kc, Nout, fuse ? fuse->need : n_adapters > 0 ? need_unfused : 0, packed);
+  if (partials == nullptr) partial_bytes = 0;
+  GemmPlan p = gemm_plan(T, Kc, Nout, fuse ? fuse->need : n_adapters > 0 ? need_unfused : 0, packed, partial_bytes);
   // the caller skipped the shrink: the conditions of gemm_can_fuse_shrink() must hold
-  if (fuse && (!gemm_can_fuse_shrink(form, T, Kc, Nout, fuse->need, fuse->ranks_mult8, packed, partials ? partial_bytes : 0) || chunks == nullptr))
+  if (fuse && (!gemm_can_fuse_shrink(form, T, Kc, Nout, fuse->need, fuse->ranks_mult8, packed, partial_bytes) || chunks == nullptr))
     return hipErrorInvalidValue;
-  if (!fuse && (partials == nullptr || partial_bytes < p.bytes || (!p.wide && chunks == nullptr))) {
-    p.wide = true;                                       // no scratch for partial sums
-    p.w = wide_plan(T, Kc, Nout, false);
+  if (!p.wide && chunks == nullptr) {
+    p.wide = true;
+    p.w = wide_plan(T, Kc, Nout, partial_bytes);
   }
   if (p.wide) {
     WideArgs w;
@@ -1026,7 +1041,7 @@ size_t gemm_multi_bytes(int64_t T, int64_t Kc, const ProjEntry* proj_host, int n
   const int room = gemm_multi_ext_room(proj_host, n_proj), need = n_ext < room ? n_ext : room;
   size_t bytes = 0;
   for (int packed = 0; packed < 2; ++packed) {
-    const GemmPlan p = gemm_plan(T, Kc, multi_tiles(proj_host, n_proj) * SK_BN, need, packed != 0, true);
+    const GemmPlan p = gemm_plan(T, Kc, multi_tiles(proj_host, n_proj) * SK_BN, need, packed != 0, SIZE_MAX, true);
     if (!p.wide && p.bytes + p.u_bytes > bytes) bytes = p.bytes + p.u_bytes;
   }
   return bytes;
@@ -1038,9 +1053,8 @@ bool gemm_multi_ok(int form, int64_t T, int64_t Kc, const ProjEntry* proj_host, 
   if (need > 0 && form == FORM_NN && !ranks_mult8) return false;
   const int64_t tiles = multi_tiles(proj_host, n_proj);
   if (tiles * SK_BN > (1 << 24)) return false;
-  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, need, packed, true);
-  if (p.wide || (need > 0 && p.u_bytes == 0)) return false;
-  return partial_bytes >= p.bytes + p.u_bytes;
+  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, need, packed, partial_bytes, true);
+  return !p.wide && (need == 0 || p.u_bytes > 0);
 }
 
 hipError_t launch_gemm_bf16_multi(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc,
@@ -1055,7 +1069,7 @@ hipError_t launch_gemm_bf16_multi(const bf16_t* Aop, int64_t lda, int form, int6
                      partials ? partial_bytes : 0) || chunks == nullptr || n_proj > MAX_PROJ)
     return hipErrorInvalidValue;
   const int64_t tiles = multi_tiles(proj_host, n_proj);
-  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, need, packed != 0, true);
+  const GemmPlan p = gemm_plan(T, Kc, tiles * SK_BN, need, packed != 0, partials ? partial_bytes : 0, true);
   GemmArgs a;
   a.Aop = Aop; a.lda = lda; a.Bop = (const bf16_t*)proj_host[0].W; a.ldb = proj_host[0].ldw;
   a.T = T; a.Kc = Kc; a.Nout = proj_host[0].Nout;

@@ -699,7 +699,7 @@ static double wide_ktile_us(int mt, int64_t busy) {
 }
 static constexpr double WIDE_ITEM_US = 6.0;                // store, first requests, expand: per tile
 
-WidePlan wide_plan(int64_t T, int64_t Kc, int64_t Nout, bool can_split) {
+WidePlan wide_plan(int64_t T, int64_t Kc, int64_t Nout, size_t max_bytes) {
   WidePlan best;
   best.us = 1e30;
   const int64_t nk = (Kc + WK - 1) / WK;
@@ -713,13 +713,14 @@ WidePlan wide_plan(int64_t T, int64_t Kc, int64_t Nout, bool can_split) {
     const double whole = p.rounds * (nk * wide_ktile_us(mt, 256) + WIDE_ITEM_US);
     p.us = whole + (p.tail_tiles ? nk * wide_ktile_us(mt, p.tail_tiles) + WIDE_ITEM_US : 0.0);
     if (p.us < best.us) best = p;
-    if (!can_split || p.tail_tiles == 0) continue;
+    if (p.tail_tiles == 0) continue;
     for (int s = 2; s <= 256 / p.tail_tiles && s <= 32 && s * 4 <= nk; ++s) {
       WidePlan q = p;
       const int64_t chunk = (nk + s - 1) / s;
       q.tail_split = (int)((nk + chunk - 1) / chunk);
       q.tail_kchunk = chunk * WK;
       q.part_bytes = (size_t)q.tail_split * q.tail_tiles * (32 * mt) * WN * sizeof(float);
+      if (q.part_bytes > max_bytes) continue;
       q.us = whole + chunk * wide_ktile_us(mt, q.tail_tiles * q.tail_split) + WIDE_ITEM_US + 5.0 + 2.0 * q.part_bytes / 15e6;
       if (q.us < best.us) best = q;
     }

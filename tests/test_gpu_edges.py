@@ -5,6 +5,7 @@ import torch
 
 from harness import workloads as wl
 from paper_2605_08527_amd import api
+from helpers import HipLayer, assert_close, to_host
 from test_gpu_parity import _check_layer
 
 pytestmark = pytest.mark.gpu
@@ -105,3 +106,65 @@ def test_some_rows_packed(oracle, monkeypatch, T, K, N, ranks, layout, spin):
     for rep in range(2):
         _check_layer(oracle, w, bwd=True, tag="some rows", table="table+packed")
     _check_layer(oracle, w, bwd=True, tag="some rows", table="lists+packed")
+
+
+# Scratch: a workspace below marlaas_workspace_bytes runs the plans that fit it (no lists of extra contraction
+# tiles, no transposed copy, no split of the last round, fewer splits) or is refused, down to none at all.
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,K,N,ranks", [(1082, 424, 6368, [16, 8]), (5120, 512, 4096, [16] * 4), (4200, 264, 1032, [5, 16]), (300, 4096, 1032, [16, 8])])
+def test_short_workspace(T, K, N, ranks, layout):
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    w = wl.make_layer(T + K, T, K, N, ranks, [0.5 + t % 3 for t in range(len(ranks))], ids, dtype="bf16", layout=layout, want_dY=True)
+    L = HipLayer(w, want_bwd=True)
+    y, u = L.fwd(save_u=True)
+    dX, dA, dB = L.bwd(u_saved=u)
+    full = api.marlaas_workspace_bytes(L.desc, True)
+    ran = refused = 0
+    for size in sorted({full >> k for k in range(12)} | {full - 256, full - (1 << 20), full * 3 // 4 // 256 * 256}, reverse=True):
+        if size <= 0:
+            continue
+        api.marlaas_set_workspace(L.ctx, L.ws[:size])
+        try:
+            y1, u1 = L.fwd(save_u=True)
+            dX1, dA1, dB1 = L.bwd()
+        except api.MarlaasError as e:
+            assert e.status == -4
+            refused += 1
+            continue
+        assert refused == 0, "a larger workspace was refused"
+        ran += 1
+        for a, b, what in [(y, y1, "y"), (u, u1, "u"), (dX, dX1, "dX")] + list(zip(dA + dB, dA1 + dB1, ["dA"] * len(dA) + ["dB"] * len(dB))):
+            # (the same products, added in another order: fp32 rounding of sums of up to 6368 terms)
+            assert_close(to_host(b), to_host(a), "%s at %d of %d bytes" % (what, size, full), tol_max=1e-3, tol_mean=2e-5)
+    assert ran >= 2 and refused >= 1
+
+
+# The static scratch holds what a pass needs, not what its fastest plan would take; a workspace for 6144 rows serves fewer.
+@pytest.mark.parametrize("T,K,N", [(1082, 424, 6368), (6273, 2976, 2672), (4109, 616, 1608)])
+def test_static_scratch_takes_what_fits(oracle, T, K, N):
+    rng = np.random.default_rng(T)
+    ids = np.sort(rng.integers(0, 4, size=T)).astype(np.int32)
+    w = wl.make_layer(T, T, K, N, [16, 8, 16, 32], [2.0, 1.0, 0.5, 1.0], ids, dtype="bf16", layout=wl.TORCH)
+    L = HipLayer(w, table=True)
+    y, _ = L.fwd()
+    ys = torch.full_like(y, float("nan"))
+    api.marlaas_lora_fwd_static(L.ctx, L.desc, ys)
+    torch.cuda.synchronize()
+    assert_close(to_host(ys), to_host(y), "static", tol_max=1e-3, tol_mean=2e-5)
+
+
+def test_workspace_of_a_large_batch_serves_smaller_ones():
+    rng = np.random.default_rng(3)
+    sizes = {}
+    for T in (6144, 5120):
+        ids = rng.integers(0, 16, size=T).astype(np.int32)
+        w = wl.make_layer(T, T, 4096, 4096, [16] * 16, [1.0] * 16, ids, dtype="bf16", layout=wl.TORCH)
+        L = HipLayer(w, table=True)
+        sizes[T] = api.marlaas_workspace_bytes(L.desc, False)
+        if T == 5120:
+            y, _ = L.fwd()
+            api.marlaas_set_workspace(L.ctx, L.ws[:min(sizes.values())])
+            y1, _ = L.fwd()
+            assert_close(to_host(y1), to_host(y), "short workspace", tol_max=1e-3, tol_mean=2e-5)
+    assert sizes[6144] < sizes[5120]
