@@ -329,7 +329,8 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
   if (tid == 0) gave_s[0] = 0;
   {
     const int kt_b = ks0 * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;
-    const int rot = (((int)blockIdx.x - (b < 0 ? 0 : a.n_prod)) >> 3) / a.tiles_m % 8 * a.rot;
+    int rot = (((int)blockIdx.x - (b < 0 ? 0 : a.n_prod)) >> 3) / a.tiles_m % 8 * a.rot;
+    if (rot >= nt) rot = 0;                                      // (the last split can be shorter than the others)
 #pragma unroll
     for (int s = 0; s < NS; ++s) if (s < nt) MD_W(MD_T(s), s);
     {

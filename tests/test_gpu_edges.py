@@ -168,3 +168,13 @@ def test_workspace_of_a_large_batch_serves_smaller_ones():
             y1, _ = L.fwd()
             assert_close(to_host(y1), to_host(y), "short workspace", tol_max=1e-3, tol_mean=2e-5)
     assert sizes[6144] < sizes[5120]
+
+
+# Column tiles that start in the middle of their contraction, whose last split is shorter than the others (5 or 6
+# k-tiles of 9, 13 of 16): every k-tile counts once.
+@pytest.mark.parametrize("T,K,N", [(20, 4104, 1024), (40, 4200, 1024), (65, 7720, 1024), (128, 7688, 1024)])
+def test_some_rows_short_last_split(oracle, T, K, N):
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(-1, 3, size=T).astype(np.int32)
+    w = wl.make_layer(T, T, K, N, [16, 8, 16], [2.0, 1.0, 0.5], ids, dtype="bf16", layout=wl.TORCH)
+    _check_layer(oracle, w, bwd=False, tag="short last split", table="table+packed")
