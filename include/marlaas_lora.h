@@ -144,6 +144,13 @@ void marlaas_segmap_destroy(marlaas_segmap* map);
  * give MARLAAS_ESHAPE, ids outside [-1, n_adapters) MARLAAS_EINVAL (the object
  * then holds no map until the next successful update), a capturing stream
  * MARLAAS_EUNSUPPORTED.  marlaas_segmap_build = create(T, n_adapters) + update.
+ *
+ * The host plans a pass from the sizes of the grouping at the time of the call,
+ * and a captured pass replays that plan: capture again after an update.  A
+ * forward of up to 64 rows on packed weights (marlaas_pack_weight) whose factors
+ * are stored contraction-contiguous is planned for any grouping: captured once
+ * (with at least one token that has an adapter, and a workspace set), it serves
+ * every later update of the map to the same T and n_adapters.
  */
 int marlaas_segmap_create(marlaas_ctx* ctx, int64_t T_max, int32_t n_adapters_max, marlaas_segmap** out);
 int marlaas_segmap_update(marlaas_ctx* ctx, marlaas_segmap* map, const int32_t* token_adapter, int64_t T,

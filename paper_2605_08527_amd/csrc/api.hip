@@ -826,31 +826,12 @@ static int max_rank_tiles(const marlaas_lora_desc* d) {
   return tiles;
 }
 
-// Jobs (16 ranks x one or two 16-row blocks of an adapter) of the row tiles of all projections; false if
-// there are more than the kernel counts.
-static bool shrink_jobs(const marlaas_lora_desc* descs, int32_t n_proj, bool lora, const MidPlan& plan, MidJobs* jobs) {
-  const marlaas_lora_desc* d = &descs[0];
-  const std::vector<int32_t>& off = d->map->seg_off;
-  const int rows = 16 * plan.rb;
-  int total = 0;
-  memset(jobs, 0xff, sizeof *jobs);
-  for (int p = 0; p < n_proj; ++p) {
-    uint16_t* end = jobs->end + p * plan.tiles_m;
-    const int32_t* ranks = ranks_of(&descs[p]);
-    int tile = 0;                              // the row tile the walk is in
-    for (int t = 0; lora && t < d->n_adapters; ++t) {
-      const int rt = (ranks[t] + 15) / 16;
-      for (int lo = off[t]; lo < off[t + 1];) {
-        while (tile < lo / rows) end[tile++] = (uint16_t)total;
-        const int stop = (tile + 1) * rows, hi = off[t + 1] < stop ? off[t + 1] : stop;
-        total += rt * (((hi - 1) / 16 - lo / 16) / 2 + 1);
-        if (total > 30000) return false;
-        lo = hi;
-      }
-    }
-    while (tile < plan.tiles_m) end[tile++] = (uint16_t)total;
-  }
-  return true;
+// The most shrink jobs of gemm_mid.hip that the adapters of T rows can have, however the rows are grouped: each
+// adapter's 16-rank tiles once, and again for every pair of row blocks that begins inside an adapter's rows.
+static int max_shrink_jobs(const marlaas_lora_desc* d, const MidPlan& plan) {
+  const int64_t rows = 16 * plan.rb;
+  const int64_t pairs = d->T / rows * ((plan.rb + 1) / 2) + (d->T % rows + 31) / 32;
+  return max_rank_tiles(d) + (int)(pairs - 1) * ((max_rank_of(d) + 15) / 16);
 }
 
 // A call on packed weights (W and ldw of `proj` filled in) that one of the one-launch kernels does best:
@@ -859,15 +840,16 @@ static int launch_packed(marlaas_ctx* ctx, const marlaas_lora_desc* descs, int32
                          int64_t Kc, int form, bool lora, const AdapterEntry* table, int which, int out_f32, float* u, int rs, hipStream_t st, bool* done) {
   const marlaas_lora_desc* d = &descs[0];
   const marlaas_segmap* map = d->map;
-  const int32_t* perm = map->identity ? nullptr : map->perm_dev;
+  const int32_t* perm = map->perm_dev;       // (also of a grouped batch: a captured call serves the map's later batches)
   const int n = lora ? d->n_adapters : 0;
   const DecodeSync sync = decode_sync_of(ctx, map);
   *done = false;
   int ext = 0;
   for (int t = 0; lora && t < d->n_adapters; ++t) if (map->seg_off[t + 1] > map->seg_off[t]) ext += ranks_of(d)[t];
   const MidPlan mid = gemm_mid_plan(form, d->T, ldx, Kc, proj, n_proj, lora, ext, rs, &sync);
-  MidJobs jobs;
-  if (mid.rb && shrink_jobs(descs, n_proj, lora, mid, &jobs)) {
+  if (mid.rb) {
+    int jobs = 0;
+    for (int p = 0; p < n_proj && lora; ++p) jobs = std::max(jobs, max_shrink_jobs(&descs[p], mid));
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_mid(x, ldx, form, d->T, Kc, perm, map->seg_off_dev, n, table, which, proj, n_proj, out_f32, u, rs, mid,
                                       jobs, (const bf16_t*)ctx->zero_dev, &sync, st));
     *done = true;

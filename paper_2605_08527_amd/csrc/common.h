@@ -186,8 +186,9 @@ static constexpr int MID_ROWS = 1024, MID_SPLITS = 2, MID_SPLIT_WGS = 512;
 static constexpr int MID_U_FLOATS = MAX_PROJ * MID_SPLITS * MID_ROWS * 128;
 static constexpr int MID_PART_FLOATS = MID_SPLIT_WGS * 96 * 128;
 static constexpr int SYNC_INTS = DECODE_SYNC_INTS + MID_U_FLOATS + MID_PART_FLOATS;
-// Ends of the producers' jobs, projection by projection and row tile by row tile (the rest: 65535).
-struct MidJobs { alignas(16) uint16_t end[MAX_PROJ * MID_ROWS / 64]; };
+// (the counter of a row tile holds its consumers and MID_JOBS, more than the shrink jobs it can have, in 16 bits)
+static constexpr int MID_JOBS = 2048, MID_CONSUMERS = 65535 - MID_JOBS;
+static_assert(80 * 8 * MID_SPLITS < MID_JOBS, "every row its own adapter of rank 128");
 struct MidPlan { int rb = 0, wn = 2, ksplit = 1, tiles_m = 0; double us = 0.0; };     // rb = rows / 16; 0: none
 
 // What lets the large-batch GEMM fetch the expand's operands by DMA: u (or v) as a two-term bf16
@@ -236,13 +237,13 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
                                  const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
                                  float* u, int r_stride, int max_tiles, const DecodeSync* sync, hipStream_t stream);
 // The same for more rows (gemm_mid.hip); the plan says whether it is the kernel for these sizes.  ext: ranks of
-// all adapters in the batch (0: none); seg_off:
-// rows of the adapters (device); jobs: a row tile's (16 plan.rb rows) are one per 16 ranks and (started) pair of
-// 16-row blocks of an adapter.
+// all adapters in the batch (0: none); seg_off: rows of the adapters (device); proj_jobs: the most shrink jobs
+// (16 ranks of an adapter x a pair of 16-row blocks of a row tile, 16 plan.rb rows) that any grouping of T rows
+// has in any projection.
 MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, bool lora, int ext, int r_stride, const DecodeSync* sync);
 hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,
                                 const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
-                                float* u, int r_stride, const MidPlan& plan, const MidJobs& jobs, const bf16_t* zero_line, const DecodeSync* sync,
+                                float* u, int r_stride, const MidPlan& plan, int proj_jobs, const bf16_t* zero_line, const DecodeSync* sync,
                                 hipStream_t stream);
 // Several projections of the same input in one pass (small batches only: 128 x 128 tiles with
 // the shrink carried as extended columns, or no adapters at all).  `proj_host` holds the n_proj

@@ -50,7 +50,7 @@ struct GemmArgs {
   const int32_t* grp_ids;
   ExtRows ext;                  // the row tiles' shares of the extended columns
   int n_prod, n_split;          // few-row kernel: workgroups that compute u (a multiple of n_proj n_split), the splits of their contraction,
-  int prod0, rot;               // (the kernel for more rows: the first of those; k-tiles between neighbouring column tiles' starts)
+  int prod0, proj_jobs, rot;    // (the kernel for more rows: the first of those, shrink jobs of a projection; k-tiles between neighbouring column tiles' starts)
   const bf16_t* zero_line;      // 1024 readable zero bytes
   float* thin_u;                // and where it travels: [MAX_PROJ][THIN_SPLITS][THIN_ROWS][128], zero between launches
   ProjEntry proj[MAX_PROJ];     // by value: read with wave-uniform loads from the kernel arguments
@@ -154,7 +154,7 @@ hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t stream);
 // any grouping of T rows can use.  Factors of the shrink stored contraction-contiguous.
 hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream);
 // Up to MID_ROWS rows likewise (gemm_mid.hip); partials, thin_u: the context's areas.
-hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, const MidJobs& jobs, hipStream_t stream);
+hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, hipStream_t stream);
 MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool lora);
 bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext);
 

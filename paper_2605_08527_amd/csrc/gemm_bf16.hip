@@ -1007,12 +1007,14 @@ MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEn
   int64_t cols = 0;
   for (int q = 0; q < n_proj; ++q) cols += proj_host[q].Nout;
   const MidPlan p = mid_plan(T, Kc, proj_host, n_proj, lora);
+  for (int q = 0; q < n_proj; ++q)
+    if ((proj_host[q].Nout + 32 * p.wn - 1) / (32 * p.wn) * p.ksplit > MID_CONSUMERS) return MidPlan();
   return mid_pays(p, T, Kc, cols, ext) ? p : MidPlan();
 }
 
 hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,
                                 const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
-                                float* u, int r_stride, const MidPlan& plan, const MidJobs& jobs, const bf16_t* zero_line, const DecodeSync* sync,
+                                float* u, int r_stride, const MidPlan& plan, int proj_jobs, const bf16_t* zero_line, const DecodeSync* sync,
                                 hipStream_t stream) {
   if (n_proj < 1 || n_proj > MAX_PROJ || plan.rb == 0) return hipErrorInvalidValue;
   GemmArgs a;
@@ -1024,7 +1026,8 @@ hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_
   a.partials = (float*)(sync->counters + (SYNC_INTS - MID_PART_FLOATS));
   a.n_proj = n_proj;
   for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
-  return launch_gemm_mid(a, plan, jobs, stream);
+  a.proj_jobs = n_adapters > 0 ? proj_jobs : 0;
+  return launch_gemm_mid(a, plan, stream);
 }
 
 // ---- several projections in one pass

@@ -27,6 +27,7 @@
 #include "gemm_args.h"
 #include "agent_memory.h"
 #include "lora_expand.h"
+#include "lora_shrink.h"
 
 #include <atomic>
 #include <cmath>
@@ -55,8 +56,73 @@ struct MidShape {
   static constexpr int BASE = NS * SLOT > RED ? NS * SLOT : RED;
 };
 
+// Job `job` of a projection's shrink, counted over all row tiles (16 RB rows each): 16 ranks of an adapter for its
+// rows in a pair of row blocks (32 rows of a tile from a multiple of 32 on).  Fills in *j (but for the split)
+// and returns the row tile, -1: there are fewer jobs.  Rows are grouped by adapter, so a lane per adapter
+// counts its pairs from its rows' ends alone; where the adapters are more than the lanes a thread counts
+// those of two rows (tmp: 16 ints of LDS).  All waves call it.
+template <int RB>
+__device__ __forceinline__ int find_job(const GemmArgs& a, const AdapterEntry* table, int job, int32_t* tmp, int wave, int lane, ShrinkJob* j) {
+  constexpr int BM = 16 * RB, PAIRS = (RB + 1) / 2;
+  int lo = 0, hi = 0;                                            // rows of the job's adapter
+  int pair = -1;                                                 // pair of row blocks, counted over all row tiles
+  auto pair_of = [&](int m) { return (int)((uint32_t)m / BM * PAIRS + (uint32_t)m % BM / 32); };
+  AdapterEntry e;
+  e.A = e.B = nullptr; e.rank = 0; e.scale = 0.f;
+  if (a.n_adapters <= 64) {
+    const bool in = lane < a.n_adapters;
+    const int so = in ? a.seg_off[lane] : 0, so1 = in ? a.seg_off[lane + 1] : 0;
+    if (in) e = table[lane];
+    const int p0 = pair_of(so), pairs = so1 > so ? pair_of(so1 - 1) - p0 + 1 : 0;
+    const int jobs = pairs * ((e.rank + 15) >> 4);
+    int inc = jobs;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
+    const uint64_t hit = __ballot(inc - jobs <= job && job < inc);
+    if (hit == 0) return -1;
+    const int l = __ffsll((unsigned long long)hit) - 1;
+    const int k = job - __shfl(inc - jobs, l), np = __shfl(pairs, l);
+    lo = __shfl(so, l); hi = __shfl(so1, l);
+    pair = __shfl(p0, l) + k % np;
+    j->q0 = k / np * 16;
+    j->rank = __shfl(e.rank, l); j->scale = __shfl(e.scale, l);
+    const uint64_t fp = (uint64_t)(uintptr_t)(a.which ? e.A : e.B);
+    j->L = (const bf16_t*)(((uint64_t)(uint32_t)__shfl((int)(fp >> 32), l) << 32) | (uint32_t)__shfl((int)fp, l));
+  } else {
+    const int m = 2 * (wave * 64 + lane);
+    static_assert(MID_ROWS <= 2 * MD_THREADS && BM % 2 == 0, "two rows a thread");
+    const int g0 = m < a.T ? a.grp_ids[m] : -1, g1 = m + 1 < a.T ? a.grp_ids[m + 1] : -1, gb = m > 0 && m < a.T ? a.grp_ids[m - 1] : -1;
+    const int n0 = g0 >= 0 && (g0 != gb || m % BM % 32 == 0) ? (table[g0].rank + 15) >> 4 : 0;
+    const int n1 = g1 >= 0 && g1 != g0 ? (table[g1].rank + 15) >> 4 : 0;
+    int inc = n0 + n1;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
+    if (lane == 63) tmp[wave] = inc;
+    if (wave == 0 && lane < 2) tmp[MD_WAVES + lane] = -1;
+    __syncthreads();
+    int k = job - (inc - n0 - n1);
+    for (int w = 0; w < wave; ++w) k -= tmp[w];
+    if (k >= 0 && k < n0 + n1) { tmp[MD_WAVES] = k < n0 ? m : m + 1; tmp[MD_WAVES + 1] = k < n0 ? k : k - n0; }
+    __syncthreads();
+    const int row = tmp[MD_WAVES];
+    if (row < 0) return -1;
+    const int t = a.grp_ids[row];
+    e = table[t];
+    lo = row; hi = a.seg_off[t + 1];
+    pair = pair_of(row);
+    j->q0 = tmp[MD_WAVES + 1] * 16;
+    j->rank = e.rank; j->scale = e.scale;
+    j->L = (const bf16_t*)(a.which ? e.A : e.B);
+    __syncthreads();                                             // (tmp is free)
+  }
+  const int tm = pair / PAIRS, m0 = tm * BM, r0 = pair % PAIRS * 32, end = r0 + 32 < BM ? r0 + 32 : BM;
+  j->row0 = lo > m0 + r0 ? lo - m0 : r0;
+  j->row1 = hi < m0 + end ? hi - m0 : end;
+  return tm;
+}
+
 template <int RB, int WN>
-__global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, MidJobs jobs) {
+__global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   typedef MidShape<RB, WN> S_;
   constexpr int KG = S_::KG, MD_K = S_::K, UR = MD_K / 8, NS = S_::NS, SLOT = S_::SLOT, BM = 16 * RB, NR = (RB + KG - 1) / KG;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -69,190 +135,75 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
   int32_t* t_s = tok_s + BM;                                     // adapter (-1: none),
   int32_t* rank_s = t_s + BM;                                    // rank
   int32_t* cnt_s = rank_s + BM;                                  // [RB] octets of a row block (-1: plain expand)
-  int32_t* gave_s = cnt_s + RB;                                  // a wave gave up waiting for sums
-  uint16_t* oct_s = (uint16_t*)(gave_s + 1);                     // [RB][oct_max]: row of the tile << 8 | first rank
+  int32_t* gave_s = cnt_s + RB;                                  // [0] a wave gave up waiting for sums,
+                                                                 // [2, 3] shrink jobs of the tile's first 64 rows, of the others
+  uint16_t* oct_s = (uint16_t*)(gave_s + 4);                     // [RB][oct_max]: row of the tile << 8 | first rank
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
   const bool lora = a.n_adapters > 0 && a.table != nullptr;
   const int b = (int)blockIdx.x - a.prod0, S = a.n_split;        // the producers are workgroups prod0 ..
-  const bool producer = b >= 0 && b < a.n_prod;
-  int p = 0, tm, tn = 0, ks0 = 0, job = 0;
-  if (producer) {
-    int e = 0;                                                   // (wave-uniform reads of the kernel arguments)
-    job = b / S;
-    for (int i = 0, start = 0; i < a.n_proj * a.tiles_m; i += 8) {
-      const uint4 v = *(const uint4*)(jobs.end + i);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int end = (int)(k & 1 ? w[k / 2] >> 16 : w[k / 2] & 0xffff);
-        if (end <= b / S) { ++e; start = end; }
-      }
-      job = b / S - start;
-    }
-    tm = e % a.tiles_m; p = e / a.tiles_m;
-    if (p >= a.n_proj) return;                                   // (the producers are padded to whole rounds over the XCDs)
-  } else {
-    // Workgroup b runs on XCD b mod 8.  An XCD works on one contraction split, so that it pulls only its
-    // own part of x through the fabric; the row tiles of a column tile are neighbours on one XCD and
-    // share the weight through its L2.
-    const int c = b < 0 ? (int)blockIdx.x : (int)blockIdx.x - a.n_prod, xcd = c & 7, idx = c >> 3, ng = 8 / a.ksplit;
-    ks0 = xcd & (a.ksplit - 1);
-    tm = idx % a.tiles_m;
-    tn = idx / a.tiles_m * ng + xcd / a.ksplit;
-    if (tn >= a.tiles_n) return;
-    for (int q = 1; q < a.n_proj; ++q) if (tn >= a.proj[q].tile0) p = q;
-  }
-  const int64_t m0 = (int64_t)tm * BM;
-  const int64_t Nout = a.proj[p].Nout, ldb = a.proj[p].ldw;
-  const AdapterEntry* table = a.table + a.proj[p].tab0;
-  // u of this projection: [split][T][r_stride], scaled
-  float* u_p = a.thin_u + p * (MID_SPLITS * MID_ROWS * 128);
-  const int64_t u_n = a.T * a.r_stride;
-  const int p_tiles = (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
+  const int64_t u_n = a.T * a.r_stride;                          // u of a projection: [split][T][r_stride], scaled
   constexpr int UNITS = 2 * WN * RB;
-  // [tile][unit][split][lane] x 4
-  float* parts = a.partials + (int64_t)(tm * a.tiles_n) * (UNITS * 256) * a.ksplit;
-  // workgroups through with row tile tm of this projection (bits 16 ..: those that gave up waiting for sums).
+  // Workgroups through with row tile tm of projection p (bits 16 ..: those that gave up waiting for sums).  Only
+  // a consumer knows how many producers the tile has: the one of the first column tile and split counts for
+  // MID_JOBS less those, so that the count is the same, consumers + MID_JOBS, for every grouping.
   // Called by one whole wave, when the workgroup's requests are performed.
-  auto leave = [&](int gave_up) {
+  auto leave = [&](int p, int tm, int mine) {
+    const int p_tiles = (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
+    const int64_t m0 = (int64_t)tm * BM;
     int32_t* done = a.sync + p * a.tiles_m + tm;
-    const int at = p * a.tiles_m + tm;
-    const int everyone = (lora ? (jobs.end[at] - (at > 0 ? jobs.end[at - 1] : 0)) * S : 0) + p_tiles * a.ksplit;
     int old = 0;
-    if (lane == 0) old = __hip_atomic_fetch_add(done, 1 + (gave_up << 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    old = __builtin_amdgcn_readfirstlane(old) + (gave_up << 16);
-    if ((old & 0xffff) != everyone - 1) return;
+    if (lane == 0) old = __hip_atomic_fetch_add(done, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old = __builtin_amdgcn_readfirstlane(old) + mine;
+    if ((old & 0xffff) != p_tiles * a.ksplit + MID_JOBS) return;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     if (lora) {
       const int64_t rows = a.T - m0 < BM ? a.T - m0 : BM;
+      float* u = a.thin_u + p * (MID_SPLITS * MID_ROWS * 128) + m0 * a.r_stride;
       for (int s = 0; s < S; ++s)
-        for (int64_t i = lane; i < rows * a.r_stride / 4; i += 64) store4_agent(u_p + s * u_n + m0 * a.r_stride + i * 4, zero);
+        for (int64_t i = lane; i < rows * a.r_stride / 4; i += 64) store4_agent(u + s * u_n + i * 4, zero);
     }
-    if (old >> 16)                                               // (not reached in practice)
-      for (int64_t i = lane, n = (int64_t)p_tiles * UNITS * 64 * a.ksplit; i < n; i += 64)
-        store4_agent(parts + (int64_t)a.proj[p].tile0 * (UNITS * 256) * a.ksplit + i * 4, zero);
+    if (old >> 16) {                                             // (not reached in practice)
+      float* part = a.partials + ((int64_t)tm * a.tiles_n + a.proj[p].tile0) * (UNITS * 256) * a.ksplit;
+      for (int64_t i = lane, n = (int64_t)p_tiles * UNITS * 64 * a.ksplit; i < n; i += 64) store4_agent(part + i * 4, zero);
+    }
     if (lane == 0) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  union Frag { uint4 u; bf16x8 v; };
-  const int steps = (int)((a.Kc + 31) >> 5);
 
-  if (producer) {
-    int32_t tokr[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      const int64_t m = m0 + 16 * i + li < a.T ? m0 + 16 * i + li : a.T - 1;
-      tokr[i] = a.perm ? a.perm[m] : (int32_t)m;
-    }
-    // the jobs of the row tile in adapter order, a lane per adapter from that of its first row on
-    const int64_t m1 = m0 + BM < a.T ? m0 + BM : a.T;
-    const int tfirst = a.n_adapters <= 64 ? 0 : a.grp_ids[m0];   // (one trip less)
-    int t = -1, q0 = 0, blk = 0, r = 0, row0 = 0, row1 = 0;
-    float scale = 0.f;
-    const bf16_t* L = nullptr;
-    for (int tb = tfirst, before = 0; tb >= 0 && tb < a.n_adapters; tb += 64) {
-      const int tl = tb + lane;
-      const bool in = tl < a.n_adapters;
-      const int so = in ? a.seg_off[tl] : 0, so1 = in ? a.seg_off[tl + 1] : 0;
-      AdapterEntry e;
-      e.A = e.B = nullptr; e.rank = 0; e.scale = 0.f;
-      if (in) e = table[tl];
-      const int lo = so > m0 ? so - (int)m0 : 0, hi = (so1 < m1 ? so1 : (int)m1) - (int)m0;
-      const int pairs = in && hi > lo ? (((hi - 1) >> 4) - (lo >> 4)) / 2 + 1 : 0;
-      const int jobs = pairs * ((e.rank + 15) >> 4);
-      int inc = jobs;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
-      const uint64_t hit = __ballot(before + inc - jobs <= job && job < before + inc);
-      if (hit) {
-        const int l = __ffsll((unsigned long long)hit) - 1;
-        t = tb + l;
-        const int k = job - before - __shfl(inc - jobs, l), np = __shfl(pairs, l);
-        row0 = __shfl(lo, l); row1 = __shfl(hi, l);
-        q0 = k / np * 16; blk = (row0 >> 4) + k % np * 2;
-        r = __shfl(e.rank, l); scale = __shfl(e.scale, l);
-        const uint64_t fp = (uint64_t)(uintptr_t)(a.which ? e.A : e.B);
-        L = (const bf16_t*)(((uint64_t)(uint32_t)__shfl((int)(fp >> 32), l) << 32) | (uint32_t)__shfl((int)fp, l));
-        break;
-      }
-      before += __shfl(inc, 63);
-      if (__ballot(in && so1 < m1) != ~0ull) break;              // the tile's last adapter is among these
-    }
-    if (t < 0) {
-      if (wave == 0) leave(0);
-      return;
-    }
-    const int part = (steps + S - 1) / S, k0 = b % S * part, k1 = k0 + part < steps ? k0 + part : steps;
-    const int per = (part + MD_WAVES - 1) / MD_WAVES;
-    const int s0 = k0 + wave * per, s1 = s0 + per < k1 ? s0 + per : k1;
-    const bool row_in = q0 + li < r, two = blk + 1 < RB && (blk + 1) * 16 < row1;
-    const bf16_t* lrow = L + (int64_t)(row_in ? q0 + li : 0) * a.Kc;
-    const bf16_t* xrow[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      int32_t tk = tokr[0];
-#pragma unroll
-      for (int j = 1; j < RB; ++j) if (blk + i == j) tk = tokr[j];
-      xrow[i] = a.Aop + (int64_t)tk * a.lda;
-    }
-    constexpr int UP = 3;                                        // steps requested together (twice)
-    f32x4 pacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    Frag pa[UP][3], pb[UP][3];
-#define MD_PLOAD(set_, s_)                                                                                \
-  do {                                                                                                    \
-    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u) {                                                   \
-      const int64_t _k = (int64_t)((s_) + _u) * 32 + 8 * lg;                                              \
-      const bool _in = (s_) + _u < s1 && _k < a.Kc;                                                       \
-      set_[_u][0].u = set_[_u][1].u = set_[_u][2].u = make_uint4(0, 0, 0, 0);                             \
-      if (_in && row_in) set_[_u][2].u = *(const uint4*)(lrow + _k);                                      \
-      if (_in) set_[_u][0].u = *(const uint4*)(xrow[0] + _k);                                             \
-      if (_in && two) set_[_u][1].u = *(const uint4*)(xrow[1] + _k);                                      \
-    }                                                                                                     \
-  } while (0)
-#define MD_PMMA(set_)                                                                                     \
-  do {                                                                                                    \
-    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u)                                                     \
-      _Pragma("unroll") for (int _i = 0; _i < 2; ++_i)                                                    \
-        pacc[_i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(set_[_u][2].v, set_[_u][_i].v, pacc[_i], 0, 0, 0); \
-  } while (0)
-    MD_PLOAD(pa, s0);
-    for (int s = s0; s < s1; s += 2 * UP) {
-      if (s + UP < s1) MD_PLOAD(pb, s + UP);
-      MD_PMMA(pa);
-      if (s + UP < s1) {
-        if (s + 2 * UP < s1) MD_PLOAD(pa, s + 2 * UP);
-        MD_PMMA(pb);
-      }
-    }
-#undef MD_PLOAD
-#undef MD_PMMA
-#pragma unroll
-    for (int i = 0; i < 2; ++i) red[(wave * 2 + i) * 64 + lane] = pacc[i];
+  if (b >= 0 && b < a.n_prod) {
+    // ---- producers
+    const int pp = b / (a.proj_jobs * S);
+    if (pp >= a.n_proj) return;                                  // (they are padded to whole rounds over the XCDs)
+    ShrinkJob job;
+    job.split = b % S;
+    const int tile = find_job<RB>(a, a.table + a.proj[pp].tab0, b / S - pp * a.proj_jobs, (int32_t*)smem, wave, lane, &job);
+    if (tile < 0) return;                                        // (there are as many as any grouping of T rows needs)
+    const int64_t r0 = (int64_t)tile * BM + (job.row0 & ~15) + li, last = a.T - 1;
+    const int64_t i0 = r0 < last ? r0 : last, i1 = r0 + 16 < last ? r0 + 16 : last;
+    const int32_t tok0 = a.perm ? a.perm[i0] : (int32_t)i0, tok1 = a.perm ? a.perm[i1] : (int32_t)i1;
+    shrink_job<3, 2>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, a.thin_u + pp * (MID_SPLITS * MID_ROWS * 128) + job.split * u_n + (int64_t)tile * BM * a.r_stride,
+                     a.r_stride, wave, lane);
     __syncthreads();
-    if (wave < 2) {                                              // wave i finishes row block blk + i
-      f32x4 s = red[wave * 64 + lane];
-#pragma unroll
-      for (int w = 1; w < MD_WAVES; ++w) {
-        const f32x4 o = red[(w * 2 + wave) * 64 + lane];
-        s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
-      }
-      // lane: row li of the block, ranks q0 + 4 lg .. + 3
-      const int row = (blk + wave) * 16 + li;
-      if (row >= row0 && row < row1 && row < BM) {
-        f32x4 f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { const float v = scale * s[j]; f[j] = __float_as_uint(v) == 0u ? -0.f : v; }
-        store4_agent(u_p + b % S * u_n + (m0 + row) * a.r_stride + q0 + 4 * lg, f);
-      }
-      wait_vm<0>();
-    }
-    __syncthreads();
-    if (wave == 0) leave(0);
+    if (wave == 0) leave(pp, tile, 1);
     return;
   }
 
-  // ---- consumers
+  // ---- consumers.  Workgroup b runs on XCD b mod 8.  An XCD works on one contraction split, so that it pulls
+  // only its own part of x through the fabric; the row tiles of a column tile are neighbours on one XCD and
+  // share the weight through its L2.
+  const int c = b < 0 ? (int)blockIdx.x : (int)blockIdx.x - a.n_prod, ng = 8 / a.ksplit;
+  const int ks0 = c & (a.ksplit - 1), tm = (c >> 3) % a.tiles_m, tn = (c >> 3) / a.tiles_m * ng + (c & 7) / a.ksplit;
+  if (tn >= a.tiles_n) return;
+  int p = 0;
+  for (int q = 1; q < a.n_proj; ++q) if (tn >= a.proj[q].tile0) p = q;
+  const int64_t m0 = (int64_t)tm * BM;
+  const int64_t Nout = a.proj[p].Nout, ldb = a.proj[p].ldw;
+  const AdapterEntry* table = a.table + a.proj[p].tab0;
+  float* u_p = a.thin_u + p * (MID_SPLITS * MID_ROWS * 128);
+  float* parts = a.partials + (int64_t)(tm * a.tiles_n) * (UNITS * 256) * a.ksplit;    // [tile][unit][split][lane] x 4
+  const int steps = (int)((a.Kc + 31) >> 5);
+  const bool lead = ks0 == 0 && tn == a.proj[p].tile0;
   const int g = wave / WN, wn = wave % WN;
   const int64_t n0 = (int64_t)(tn - a.proj[p].tile0) * (32 * WN) + 32 * wn;     // this wave's first column
   // the indices everything waits for go first (inline assembly: the compiler's own waits would count the
@@ -326,7 +277,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
   f32x4 y[NR][2];
   const int cbo = ks0 & 1;                                       // with several splits this wave's own units are its
   const bool own = a.ksplit == 1 || ((g * WN * 2 + wn * 2 + cbo) & (a.ksplit - 1)) == ks0;   // column block cbo, if any
-  if (tid == 0) gave_s[0] = 0;
+  if (tid == 0) gave_s[0] = gave_s[1] = 0;
   {
     const int kt_b = ks0 * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;
     int rot = (((int)blockIdx.x - (b < 0 ? 0 : a.n_prod)) >> 3) / a.tiles_m % 8 * a.rot;
@@ -373,6 +324,12 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
         for (int q = 0, o = (tid >> 4) * oct_max + inc - n_oct; q < 8 * n_oct; q += 8, ++o) oct_s[o] = (uint16_t)(tid << 8 | q);
         if (li == 15) cnt_s[tid >> 4] = a.lform == FORM_NT && bad == 0 ? inc : -1;
       }
+      // jobs of these rows: the 16-wide tiles of ranks of every adapter in a pair of row blocks (1 .. 8: four bits)
+      const int rt = gid >= 0 && (gid != gid1 || (lane & 31) == 0) ? (rank + 15) >> 4 : 0;
+      int jobs = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) jobs += __popcll(__ballot(rt >> k & 1)) << k;
+      if (lane == 0) gave_s[2 + wave] = jobs;
     }
     f32x4 acc[RB][2];
 #pragma unroll
@@ -607,11 +564,12 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
 #pragma unroll
       for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
       *(f32x4*)(u_s + row * us + q) = v;
-      if (a.u_out && ks0 == 0 && tn == a.proj[p].tile0 && m0 + row < a.T && q < ((rank + 15) & ~15))
+      if (a.u_out && lead && m0 + row < a.T && q < ((rank + 15) & ~15))
         *(f32x4*)(a.u_out + (m0 + row) * a.r_stride + q) = v;
     }
     __syncthreads();
-    if (wave == MD_WAVES - 1) leave(gave_s[0]);
+    if (wave == MD_WAVES - 1)
+      leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS - (gave_s[2] + (RB > 4 ? gave_s[3] : 0)) * S : 0));
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const int rb = j * KG + g;
@@ -644,7 +602,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
     }
   } else if (a.ksplit > 1) {
     __syncthreads();
-    if (wave == MD_WAVES - 1) leave(gave_s[0]);
+    if (wave == MD_WAVES - 1) leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS : 0));
   }
   if (!own) return;
 #pragma unroll
@@ -668,10 +626,10 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a, Mid
 }
 
 template <int RB, int WN>
-static hipError_t launch_mid(const GemmArgs& a, const MidJobs& jobs, hipStream_t stream) {
+static hipError_t launch_mid(const GemmArgs& a, hipStream_t stream) {
   constexpr int BM = 16 * RB;
   const size_t u_bytes = (size_t)BM * (a.r_stride + 4) * sizeof(float), base = MidShape<RB, WN>::BASE;
-  const size_t lds = (base > u_bytes ? base : u_bytes) + BM * 20 + RB * 4 + 4 + (size_t)RB * 2 * a.r_stride * sizeof(uint16_t);
+  const size_t lds = (base > u_bytes ? base : u_bytes) + BM * 20 + RB * 4 + 16 + (size_t)RB * 2 * a.r_stride * sizeof(uint16_t);
   static std::atomic<uint64_t> done_dev{0};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -689,11 +647,11 @@ static hipError_t launch_mid(const GemmArgs& a, const MidJobs& jobs, hipStream_t
   // after the consumers' first 256, which they would delay (512 rows, 4096 x 4096, 64 adapters: 50 -> 40 us).
   GemmArgs g = a;
   g.prod0 = a.n_prod + consumers <= 512 || a.ksplit > 1 || consumers < 256 ? 0 : 256;
-  hipLaunchKernelGGL((gemm_mid_kernel<RB, WN>), dim3(a.n_prod + consumers), dim3(MD_THREADS), lds, stream, g, jobs);
+  hipLaunchKernelGGL((gemm_mid_kernel<RB, WN>), dim3(a.n_prod + consumers), dim3(MD_THREADS), lds, stream, g);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, const MidJobs& jobs, hipStream_t stream) {
+hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, hipStream_t stream) {
   // How far apart neighbouring column tiles start (see MD_T): eight of them over the whole contraction, as long
   // as the part of x between the first and the last stays in an XCD's L2 (256 rows, 14336 x 4096 in one
   // split: 81 us over 1.4 MB of x, 91 over all of it).
@@ -703,14 +661,14 @@ hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, const MidJobs& jobs, hi
   a.n_split = (a.Kc + 31) / 32 <= 8 * MD_WAVES ? 1 : MID_SPLITS;
   a.ksplit = p.ksplit;
   a.tiles_m = p.tiles_m;
-  a.n_prod = (jobs.end[a.n_proj * a.tiles_m - 1] * a.n_split + 7) / 8 * 8;
+  a.n_prod = (a.n_proj * a.proj_jobs * a.n_split + 7) / 8 * 8;
   a.tiles_n = 0;
   for (int q = 0; q < a.n_proj; ++q) {
     a.proj[q].tile0 = a.tiles_n;
     a.tiles_n += (int)((a.proj[q].Nout + 32 * p.wn - 1) / (32 * p.wn));
   }
-  if (p.wn == 4) return p.rb == 4 ? launch_mid<4, 4>(a, jobs, stream) : launch_mid<5, 4>(a, jobs, stream);
-  return p.rb == 4 ? launch_mid<4, 2>(a, jobs, stream) : launch_mid<5, 2>(a, jobs, stream);
+  if (p.wn == 4) return p.rb == 4 ? launch_mid<4, 4>(a, stream) : launch_mid<5, 4>(a, stream);
+  return p.rb == 4 ? launch_mid<4, 2>(a, stream) : launch_mid<5, 2>(a, stream);
 }
 
 // Estimated run time of a tiling in microseconds, fitted to 3500 runs over 5 to 1024 rows, contractions of

@@ -1,0 +1,88 @@
+// u = scale x L of a few rows inside the kernels that finish a call in one launch (few rows, some more rows).
+#pragma once
+#include "common.h"
+#include "agent_memory.h"
+
+namespace marlaas {
+
+// One workgroup's share of u: 16 ranks (q0 ..) of one adapter for its rows [row0, row1) of a row tile, which
+// lie in one or two neighbouring 16-row blocks, over part `split` of S of the contraction.
+struct ShrinkJob {
+  const bf16_t* L;                 // the adapter's factor [rank][Kc]
+  float scale;
+  int rank, q0, row0, row1, split;
+};
+
+// Eight waves share the part's 32-deep steps, their sums meet in `red` (8 x NB x 64) and are added in wave
+// order: the bits do not depend on who computes the job.  u: [row of the tile][r_stride] of this split; no
+// value is stored as zero bits.  tok0, tok1: tokens of row lane % 16 of the first and of the second block.
+// UP: steps requested together (twice); NB: blocks a job can have.  All eight waves call it; the stores are complete behind the next barrier.
+template <int UP, int NB>
+__device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, int64_t lda, int64_t Kc, int32_t tok0, int32_t tok1, int S,
+                                           f32x4* red, float* u, int r_stride, int wave, int lane) {
+  constexpr int WAVES = 8;
+  union Frag { uint4 u; bf16x8 v; };
+  const int li = lane & 15, lg = lane >> 4;
+  const int steps = (int)((Kc + 31) >> 5), part = (steps + S - 1) / S;
+  const int k0 = j.split * part, k1 = k0 + part < steps ? k0 + part : steps;
+  const int per = (part + WAVES - 1) / WAVES;
+  const int s0 = k0 + wave * per, s1 = s0 + per < k1 ? s0 + per : k1;
+  const int blk = j.row0 >> 4;
+  const bool two = (j.row1 - 1) >> 4 > blk, row_in = j.q0 + li < j.rank;
+  const bf16_t* lrow = j.L + (int64_t)(row_in ? j.q0 + li : 0) * Kc;
+  const bf16_t* xrow[2] = {X + (int64_t)tok0 * lda, X + (int64_t)tok1 * lda};
+  f32x4 acc[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Frag fa[UP][NB + 1], fb[UP][NB + 1];
+  auto request = [&](Frag (&f)[UP][NB + 1], int s) {
+#pragma unroll
+    for (int i = 0; i < UP; ++i) {
+      const int64_t k = (int64_t)(s + i) * 32 + 8 * lg;
+      const bool in = s + i < s1 && k < Kc;
+#pragma unroll
+      for (int b = 0; b <= NB; ++b) f[i][b].u = make_uint4(0, 0, 0, 0);
+      if (in && row_in) f[i][NB].u = *(const uint4*)(lrow + k);
+      if (in) f[i][0].u = *(const uint4*)(xrow[0] + k);
+      if (NB > 1 && in && two) f[i][NB - 1].u = *(const uint4*)(xrow[1] + k);
+    }
+  };
+  auto multiply = [&](Frag (&f)[UP][NB + 1]) {
+#pragma unroll
+    for (int i = 0; i < UP; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i][NB].v, f[i][b].v, acc[b], 0, 0, 0);
+  };
+  request(fa, s0);
+#pragma unroll 1
+  for (int s = s0; s < s1; s += 2 * UP) {
+    if (s + UP < s1) request(fb, s + UP);
+    multiply(fa);
+    if (s + UP < s1) {
+      if (s + 2 * UP < s1) request(fa, s + 2 * UP);
+      multiply(fb);
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) red[(wave * NB + b) * 64 + lane] = acc[b];
+  __syncthreads();
+  if (wave < NB) {                                               // wave b finishes block blk + b
+    f32x4 s = red[wave * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+      const f32x4 o = red[(w * NB + wave) * 64 + lane];
+      s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
+    }
+    // lane: row li of the block, ranks q0 + 4 lg .. + 3
+    const int row = (blk + wave) * 16 + li;
+    if (row >= j.row0 && row < j.row1) {
+      f32x4 f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) { const float z = j.scale * s[v]; f[v] = __float_as_uint(z) == 0u ? -0.f : z; }
+      store4_agent(u + (int64_t)row * r_stride + j.q0 + 4 * lg, f);
+    }
+    wait_vm<0>();
+  }
+}
+
+}  // namespace marlaas
