@@ -181,8 +181,8 @@ extern "C" int marlaas_create(marlaas_ctx** out, int device) {
     delete ctx;
     return MARLAAS_ENOMEM;
   }
-  // MARLAAS_SPIN_LIMIT: polls of the decode kernel's one bounded wait (0: never wait, always take
-  // the slow recomputation; for tests of that path)
+  // MARLAAS_SPIN_LIMIT: readings of a bounded wait (0: never wait, always compute again; for tests of
+  // that path); the one-launch kernels take at most MID_POLLS
   if (const char* sl = getenv("MARLAAS_SPIN_LIMIT")) ctx->spin_limit = atoi(sl) < 0 ? 0 : atoi(sl);
   // MARLAAS_DECODE_FINISH: who finishes the decode kernel's calls.  Unset or 3: the kernel itself
   // when the contraction is not split, a second launch of its own finish when it is; 2: always

@@ -189,6 +189,9 @@ static constexpr int SYNC_INTS = DECODE_SYNC_INTS + MID_U_FLOATS + MID_PART_FLOA
 // (the counter of a row tile holds its consumers and MID_JOBS, more than the shrink jobs it can have, in 16 bits)
 static constexpr int MID_JOBS = 2048, MID_CONSUMERS = 65535 - MID_JOBS;
 static_assert(80 * 8 * MID_SPLITS < MID_JOBS, "every row its own adapter of rank 128");
+// Readings of a bounded wait, a round trip through the fabric each (1 to 1.5 us under load): what is waited for
+// takes a tenth of it where its workgroups are on the chip, and doing without costs a few hundred microseconds.
+static constexpr int MID_POLLS = 256;
 struct MidPlan { int rb = 0, wn = 2, ksplit = 1, tiles_m = 0; double us = 0.0; };     // rb = rows / 16; 0: none
 
 // What lets the large-batch GEMM fetch the expand's operands by DMA: u (or v) as a two-term bf16

@@ -992,7 +992,7 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
   memset(&a, 0, sizeof a);
   a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.n_adapters = n_adapters; a.table = table; a.which = which;
   a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
-  a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit;
+  a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit < MID_POLLS ? sync->spin_limit : MID_POLLS;
   a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
   a.n_proj = n_proj; a.n_prod = n_adapters > 0 ? n_proj * max_tiles : 0;
   for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
@@ -1021,13 +1021,13 @@ hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_
   memset(&a, 0, sizeof a);
   a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.seg_off = seg_off; a.n_adapters = n_adapters; a.table = table; a.which = which;
   a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
-  a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit; a.zero_line = zero_line;
+  a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit < MID_POLLS ? sync->spin_limit : MID_POLLS; a.zero_line = zero_line;
   a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
   a.partials = (float*)(sync->counters + (SYNC_INTS - MID_PART_FLOATS));
   a.n_proj = n_proj;
   for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
   a.proj_jobs = n_adapters > 0 ? proj_jobs : 0;
-  return launch_gemm_mid(a, plan, stream);
+  return launch_gemm_mid(a, plan, sync->cu_count, stream);
 }
 
 // ---- several projections in one pass

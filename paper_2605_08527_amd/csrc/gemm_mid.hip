@@ -22,8 +22,9 @@
 //     its 16-row blocks in a row tile.  The workgroup that is last through with a row tile clears it.
 //   partial sums: with ksplit > 1 the splits of a tile share out its 16 x 16 units; a split hands the
 //     others' units over, reads its own ones' missing sums and clears them.
-// The reading is bounded.  u that does not come in time is computed by the reader; so are missing sums,
-// and the area is then cleared by whoever is last.  No workgroup depends on another one being scheduled.
+// The reading is bounded (MID_POLLS).  u that does not come in time is computed by the reader; so are missing
+// sums, and the area is then cleared by whoever is last.  No workgroup depends on another one being scheduled,
+// and either way the sums are added in the same order: the bits are the same.
 #include "gemm_args.h"
 #include "agent_memory.h"
 #include "lora_expand.h"
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       for (int s = 0; s < S; ++s)
         for (int64_t i = lane; i < rows * a.r_stride / 4; i += 64) store4_agent(u + s * u_n + i * 4, zero);
     }
-    if (old >> 16) {                                             // (not reached in practice)
+    if (__builtin_expect(old >> 16, 0)) {                        // (not reached in practice)
       float* part = a.partials + ((int64_t)tm * a.tiles_n + a.proj[p].tile0) * (UNITS * 256) * a.ksplit;
       for (int64_t i = lane, n = (int64_t)p_tiles * UNITS * 64 * a.ksplit; i < n; i += 64) store4_agent(part + i * 4, zero);
     }
@@ -242,13 +243,15 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   const int ktiles = (int)((a.Kc + MD_K - 1) / MD_K), chunk = (ktiles + a.ksplit - 1) / a.ksplit;
   bf16x8 wreg[NS][2];
   const int wofs = lane * 16;
-  // weight fragments of k-tile t_ (steps past the end read zeros)
-#define MD_W(t_, s_)                                                                                      \
+  // Weight fragments of k-tile t_ (steps past the end read zeros).  dst_: "+v" inside the loops, which ties a
+  // slot to its registers: the compiler must not move a value that is still on its way (the code generated
+  // for nested loops with "=v" did, for one of many versions of the code behind them).
+#define MD_W(t_, s_, dst_)                                                                                \
   do {                                                                                                    \
     const int _st = (t_) * KG + g;                                                                        \
     _Pragma("unroll") for (int _c = 0; _c < 2; ++_c) {                                                    \
       const bf16_t* _p = _st < steps ? wp[_c] + ((int64_t)_st << 9) : a.zero_line;                        \
-      asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(wreg[s_][_c]) : "v"(wofs), "s"(_p) : "memory"); \
+      asm volatile("global_load_dwordx4 %0, %1, %2" : dst_(wreg[s_][_c]) : "v"(wofs), "s"(_p) : "memory"); \
     }                                                                                                     \
   } while (0)
   // x of k-tile t_ into slot s_: row r of the tile at 16 UR r, its 16-byte unit u at place u ^ MD_SWZ(r)
@@ -277,13 +280,13 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   f32x4 y[NR][2];
   const int cbo = ks0 & 1;                                       // with several splits this wave's own units are its
   const bool own = a.ksplit == 1 || ((g * WN * 2 + wn * 2 + cbo) & (a.ksplit - 1)) == ks0;   // column block cbo, if any
-  if (tid == 0) gave_s[0] = gave_s[1] = 0;
+  if (tid == 0) gave_s[0] = 0;
   {
     const int kt_b = ks0 * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;
-    int rot = (((int)blockIdx.x - (b < 0 ? 0 : a.n_prod)) >> 3) / a.tiles_m % 8 * a.rot;
+    int rot = (c >> 3) / a.tiles_m % 8 * a.rot;
     if (rot >= nt) rot = 0;                                      // (the last split can be shorter than the others)
 #pragma unroll
-    for (int s = 0; s < NS; ++s) if (s < nt) MD_W(MD_T(s), s);
+    for (int s = 0; s < NS; ++s) if (s < nt) MD_W(MD_T(s), s, "=v");
     {
       if (nt >= NS) wait_vm<NS * 2>(); else wait_vm<0>();   // the indices have arrived
 #pragma unroll
@@ -366,19 +369,21 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     asm volatile("" : "+v"(wreg[s_][0]), "+v"(wreg[s_][1]));                                              \
   } while (0)
     constexpr int XH = (NS - 2) * NI, XL = (NS - 2) * (NI - 1), WA = (NS - 1) * 2;
-#define MD_ITER(s_)                                                                                       \
+#define MD_ANY(s_, first_)                                                                                \
   do {                                                                                                    \
     const int i = i0 + (s_);                                                                              \
     if (i < nt) {                                                                                         \
       if (i + NS > nt) wait_vm<0>();                                                                      \
-      else if (i0 == 0) { if (full) wait_vm<XH + (s_) * 2>(); else wait_vm<XL + (s_) * 2>(); }            \
+      else if (first_) { if (full) wait_vm<XH + (s_) * 2>(); else wait_vm<XL + (s_) * 2>(); }            \
       else { if (full) wait_vm<XH + WA>(); else wait_vm<XL + WA>(); }                                     \
       MD_SYNC(s_);                                                                                        \
       if (i + NS < nt) MD_X(MD_T(i + NS), s_);                                                            \
       MD_BODY(s_);                                                                                        \
-      if (i + NS < nt) MD_W(MD_T(i + NS), s_);                                                            \
+      if (i + NS < nt) MD_W(MD_T(i + NS), s_, "+v");                                                      \
     }                                                                                                     \
   } while (0)
+#define MD_FIRST(s_) MD_ANY(s_, true)
+#define MD_ITER(s_) MD_ANY(s_, false)
     // the same where neither the start nor the end is near (tile `tile` is requested)
 #define MD_STEADY(s_)                                                                                     \
   do {                                                                                                    \
@@ -386,7 +391,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     MD_SYNC(s_);                                                                                          \
     MD_X(tile, s_);                                                                                       \
     MD_BODY(s_);                                                                                          \
-    MD_W(tile, s_);                                                                                       \
+    MD_W(tile, s_, "+v");                                                                                 \
     tile = tile + 1 < kt_e ? tile + 1 : kt_b;                                                             \
   } while (0)
     if (nt > 0) {
@@ -401,15 +406,13 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     m_(0); m_(1); m_(2);                                                                                  \
     if constexpr (NS > 3) m_(3);                                                                          \
   } while (0)
+    if (nt > 0) MD_ROUND(MD_FIRST);
+    i0 = NS;
+    int tile = MD_T(2 * NS);
 #pragma unroll 1
-    for (; i0 < nt; i0 += NS) {
-      if (i0 > 0 && i0 + 2 * NS <= nt) {
-        int tile = MD_T(i0 + NS);
+    for (; i0 + 2 * NS <= nt; i0 += NS) MD_ROUND(MD_STEADY);
 #pragma unroll 1
-        for (; i0 + 2 * NS <= nt; i0 += NS) MD_ROUND(MD_STEADY);
-      }
-      MD_ROUND(MD_ITER);
-    }
+    for (; i0 < nt; i0 += NS) MD_ROUND(MD_ITER);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();                                             // the ring is free
     // ---- the contraction groups' sums: row block i is finished by group i mod KG
@@ -437,6 +440,37 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       }
   }
   if (a.ksplit > 1) {
+    // row block rb of this wave's own units as split q adds it up: its contraction groups' products, k-tile
+    // after k-tile from where the column tile starts, then the groups from the one that finishes the block on
+    auto split_sum = [&](int rb, int q) {
+      union Frag { uint4 u; bf16x8 v; } wf, xf;
+      const int kt_b = q * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;
+      int rot = (c >> 3) / a.tiles_m % 8 * a.rot;
+      if (rot >= nt) rot = 0;
+      const int32_t tk = tok_s[rb * 16 + li];
+      const bf16_t* xr = a.Aop + (int64_t)(tk < 0 ? 0 : tk) * a.lda;
+      const int64_t last = ((Nout + 15) >> 4) - 1, nb = (n0 >> 4) + cbo;
+      const bf16_t* wr = (const bf16_t*)a.proj[p].W + (((nb < last ? nb : last) * ldb) << 9) + lane * 8;
+      f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int d = 0; d < KG; ++d) {
+        f32x4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int i = 0; i < nt; ++i) {
+          const int st = MD_T(i) * KG + ((rb + d) & (KG - 1));
+          const int64_t k = (int64_t)st * 32 + 8 * lg;
+          wf.u = xf.u = make_uint4(0, 0, 0, 0);
+          if (st < steps) wf.u = *(const uint4*)(wr + ((int64_t)st << 9));
+          if (k < a.Kc) xf.u = *(const uint4*)(xr + k);
+          part = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, xf.v, part, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[v] = d == 0 ? part[v] : s[v] + part[v];
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[v] = __float_as_uint(s[v]) == 0u ? -0.f : s[v];
+      return s;
+    };
     // ---- hand over the others' units, collect this split's
     float* tile = parts + (int64_t)tn * (UNITS * 256) * a.ksplit + lane * 4;
 #pragma unroll
@@ -492,21 +526,25 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
           if (q < a.ksplit && q != ks0 && j * KG + g < RB)
             store4_agent(tile + ((((j * KG + g) * WN + wn) * 2 + cbo) * a.ksplit + q) * 256, f32x4{0.f, 0.f, 0.f, 0.f});
       }
-    } else if (own) {
-      // (not reached in practice) these units' whole contraction again, in plain fp32 arithmetic
+    } else if (__builtin_expect(own, 0)) {
+      // (not reached in practice) the other splits' share of these units again
       gave_s[0] = 1;
-      const int64_t n = n0 + cbo * 16 + 4 * lg;
 #pragma unroll 1
-      for (int j = 0; j < NR; ++j) {
-        const int32_t xtok = j * KG + g < RB ? tok_s[(j * KG + g) * 16 + li] : -1;
-        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-        if (xtok >= 0 && n < Nout)
-          for (int64_t k = 0; k < a.Kc; ++k) {
-            const float xv = bf16_bits_to_float(a.Aop[(int64_t)xtok * a.lda + k]);
-            const bf16_t* wk = (const bf16_t*)a.proj[p].W + ((((n >> 4) * ldb + (k >> 5)) * 64 + (k >> 3 & 3) * 16 + (n & 15)) << 3) + (k & 7);
+      for (int j = 0; j < NR && j * KG + g < RB; ++j) {
+        f32x4 mine = {0.f, 0.f, 0.f, 0.f}, sum = mine;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sum[v] = fmaf(xv, bf16_bits_to_float(wk[8 * v]), sum[v]);
+        for (int jj = 0; jj < NR; ++jj)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float y0 = y[jj][0][v], y1 = y[jj][1][v];
+            if (jj == j) mine[v] = cbo ? y1 : y0;
           }
+#pragma unroll 1
+        for (int q = 0; q < a.ksplit; ++q) {
+          const f32x4 o = split_sum(j * KG + g, q);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) { const float x = q == ks0 ? mine[v] : o[v]; sum[v] = q == 0 ? x : sum[v] + x; }
+        }
 #pragma unroll
         for (int jj = 0; jj < NR; ++jj) if (jj == j) { if (cbo) y[jj][1] = sum; else y[jj][0] = sum; }
       }
@@ -530,37 +568,14 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       }
     __syncthreads();                                             // the sums have met: their place is u's now
     const int uq = a.r_stride >> 2;
-    for (int i = tid; i < BM * uq; i += MD_THREADS) {
+    for (int i = tid; i < BM * uq; i += MD_THREADS) {            // (whole waves)
       const int row = i / uq, q = (i - row * uq) * 4;
       const int rank = t_s[row] >= 0 ? rank_s[row] : 0;
       f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (q < rank) {
-        bool ok = false;
-        const float* up = u_p + (m0 + row) * a.r_stride + q;
-        const float* up1 = up + (S > 1 ? u_n : 0);
-        for (int it = 0; it < a.spin_limit && !ok; ++it) {
-          f32x4 w0, w1;
-          asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
-                       : "=&v"(w0), "=&v"(w1) : "v"(up), "v"(up1) : "memory");
-          ok = true;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            ok &= __float_as_uint(w0[j]) != 0u && __float_as_uint(w1[j]) != 0u;
-            v[j] = S > 1 ? w0[j] + w1[j] : w0[j];
-          }
-        }
-        if (!ok) {
-          // (not reached in practice) the shrink of this row again, in plain fp32 arithmetic
-          const AdapterEntry en = table[t_s[row]];
-          const bf16_t* xr = a.Aop + (int64_t)tok_s[row] * a.lda;
-          for (int j = 0; j < 4 && q + j < rank; ++j) {
-            const bf16_t* lr = (const bf16_t*)(a.which ? en.A : en.B) + (int64_t)(q + j) * a.Kc;
-            float sum = 0.f;
-            for (int64_t k = 0; k < a.Kc; ++k) sum = fmaf(bf16_bits_to_float(xr[k]), bf16_bits_to_float(lr[k]), sum);
-            v[j] = en.scale * sum;
-          }
-        }
-      }
+      bool ok = true;
+      if (q < rank) ok = read_u<MID_SPLITS>(u_p + (m0 + row) * a.r_stride + q, u_n, S, a.spin_limit, v);
+      if (__builtin_expect(__ballot(!ok) != 0, 0))               // (not reached in practice)
+        u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
 #pragma unroll
       for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
       *(f32x4*)(u_s + row * us + q) = v;
@@ -626,7 +641,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
 }
 
 template <int RB, int WN>
-static hipError_t launch_mid(const GemmArgs& a, hipStream_t stream) {
+static hipError_t launch_mid(const GemmArgs& a, int cu_count, hipStream_t stream) {
   constexpr int BM = 16 * RB;
   const size_t u_bytes = (size_t)BM * (a.r_stride + 4) * sizeof(float), base = MidShape<RB, WN>::BASE;
   const size_t lds = (base > u_bytes ? base : u_bytes) + BM * 20 + RB * 4 + 16 + (size_t)RB * 2 * a.r_stride * sizeof(uint16_t);
@@ -644,14 +659,16 @@ static hipError_t launch_mid(const GemmArgs& a, hipStream_t stream) {
   const int consumers = 8 * ((a.tiles_n + ng - 1) / ng) * a.tiles_m;
   // Producers go first where all workgroups are on the chip at once or splits keep the consumers short: their
   // u is then there in time (100 rows, 4096 x 4096 in four splits: 26.4 us, after the consumers 29.3).  Else
-  // after the consumers' first 256, which they would delay (512 rows, 4096 x 4096, 64 adapters: 50 -> 40 us).
+  // after one consumer for each compute unit, which they would delay (512 rows, 4096 x 4096, 64 adapters:
+  // 50 -> 40 us).  Where those consumers find only half of the chip free (another launch, a stream with fewer
+  // compute units) they hold every place, give up waiting and compute their u themselves.
   GemmArgs g = a;
-  g.prod0 = a.n_prod + consumers <= 512 || a.ksplit > 1 || consumers < 256 ? 0 : 256;
+  g.prod0 = a.n_prod + consumers <= 2 * cu_count || a.ksplit > 1 || consumers < cu_count ? 0 : cu_count;
   hipLaunchKernelGGL((gemm_mid_kernel<RB, WN>), dim3(a.n_prod + consumers), dim3(MD_THREADS), lds, stream, g);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, hipStream_t stream) {
+hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream_t stream) {
   // How far apart neighbouring column tiles start (see MD_T): eight of them over the whole contraction, as long
   // as the part of x between the first and the last stays in an XCD's L2 (256 rows, 14336 x 4096 in one
   // split: 81 us over 1.4 MB of x, 91 over all of it).
@@ -667,8 +684,8 @@ hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, hipStream_t stream) {
     a.proj[q].tile0 = a.tiles_n;
     a.tiles_n += (int)((a.proj[q].Nout + 32 * p.wn - 1) / (32 * p.wn));
   }
-  if (p.wn == 4) return p.rb == 4 ? launch_mid<4, 4>(a, stream) : launch_mid<5, 4>(a, stream);
-  return p.rb == 4 ? launch_mid<4, 2>(a, stream) : launch_mid<5, 2>(a, stream);
+  if (p.wn == 4) return p.rb == 4 ? launch_mid<4, 4>(a, cu_count, stream) : launch_mid<5, 4>(a, cu_count, stream);
+  return p.rb == 4 ? launch_mid<4, 2>(a, cu_count, stream) : launch_mid<5, 2>(a, cu_count, stream);
 }
 
 // Estimated run time of a tiling in microseconds, fitted to 3500 runs over 5 to 1024 rows, contractions of

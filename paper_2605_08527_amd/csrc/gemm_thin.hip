@@ -14,11 +14,12 @@
 // 1.5 us, so u carries its own flag: it travels through an area of the context that is all zero bits
 // between launches, no value of u is stored as zero bits (+0 becomes -0), and a consumer reads its rows'
 // u until nothing is zero bits any more.  The reading is bounded; a consumer that does not get a value in
-// time computes it itself, so no workgroup depends on another one being scheduled.  The workgroup that is
-// last through with the area clears what was used of it.
+// time computes u itself, in the same order of sums, so no workgroup depends on another one being scheduled
+// and no bit on who was.  The workgroup that is last through with the area clears what was used of it.
 #include "gemm_args.h"
 #include "agent_memory.h"
 #include "lora_expand.h"
+#include "lora_shrink.h"
 
 #include <atomic>
 
@@ -84,10 +85,8 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
   // this wave's part of the contraction, in 32-deep steps
   // (a producer's is cut over S workgroups first: its loads are row pieces from all over the factor, and
   // what it takes is their latency times the rounds of them)
-  const int steps = (int)((a.Kc + 31) >> 5), S_here = producer ? S : 1;
-  const int part = (steps + S_here - 1) / S_here, p0 = producer ? b % S * part : 0, p1 = p0 + part < steps ? p0 + part : steps;
-  const int per = (part + TH_WAVES - 1) / TH_WAVES;
-  const int s0 = p0 + wave * per, s1 = s0 + per < p1 ? s0 + per : p1;
+  const int steps = (int)((a.Kc + 31) >> 5), per = (steps + TH_WAVES - 1) / TH_WAVES;
+  const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
 
   // tokens of the rows this lane supplies; adapter, and its entry, of row `lane`
   int32_t tokr[R];
@@ -133,65 +132,12 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
     const int row1 = row0 + __popcll(__ballot(g == t));         // rows [row0, row1) are this adapter's
     const uint64_t fp = (uint64_t)(uintptr_t)(a.which ? e.A : e.B);
     const bf16_t* L = (const bf16_t*)(((uint64_t)(uint32_t)__shfl((int)(fp >> 32), row0) << 32) | (uint32_t)__shfl((int)fp, row0));
-    const bool row_in = q0 + li < r;
-    const bf16_t* lrow = L + (int64_t)(row_in ? q0 + li : 0) * a.Kc;
-    const int rb0 = row0 >> 4, rb1 = (row1 - 1) >> 4;           // its row blocks
-    constexpr int UP = R == 1 ? 4 : R == 2 ? 3 : 2;             // steps requested together (twice)
-    f32x4 pacc[R];
+    const int rb0 = row0 >> 4;
+    int32_t tok0 = tokr[0];
 #pragma unroll
-    for (int i = 0; i < R; ++i) pacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Frag pa[UP][R + 1], pb[UP][R + 1];
-#define TH_PLOAD(set_, s_)                                                                                \
-  do {                                                                                                    \
-    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u) {                                                   \
-      const int64_t _k = (int64_t)((s_) + _u) * 32 + 8 * lg;                                              \
-      const bool _in = (s_) + _u < s1 && _k < a.Kc;                                                       \
-      set_[_u][R].u = make_uint4(0, 0, 0, 0);                                                             \
-      if (_in && row_in) set_[_u][R].u = *(const uint4*)(lrow + _k);                                      \
-      _Pragma("unroll") for (int _i = 0; _i < R; ++_i) {                                                  \
-        set_[_u][_i].u = make_uint4(0, 0, 0, 0);                                                          \
-        if (_i >= rb0 && _i <= rb1 && _in) set_[_u][_i].u = *(const uint4*)(a.Aop + (int64_t)tokr[_i] * a.lda + _k); \
-      }                                                                                                   \
-    }                                                                                                     \
-  } while (0)
-#define TH_PMMA(set_)                                                                                     \
-  do {                                                                                                    \
-    _Pragma("unroll") for (int _u = 0; _u < UP; ++_u)                                                     \
-      _Pragma("unroll") for (int _i = 0; _i < R; ++_i)                                                    \
-        if (_i >= rb0 && _i <= rb1)                                                                       \
-          pacc[_i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(set_[_u][R].v, set_[_u][_i].v, pacc[_i], 0, 0, 0); \
-  } while (0)
-    TH_PLOAD(pa, s0);
-    for (int s = s0; s < s1; s += 2 * UP) {
-      if (s + UP < s1) TH_PLOAD(pb, s + UP);
-      TH_PMMA(pa);
-      if (s + UP < s1) {
-        if (s + 2 * UP < s1) TH_PLOAD(pa, s + 2 * UP);
-        TH_PMMA(pb);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-      if (i >= rb0 && i <= rb1) red[(wave * R + i) * 64 + lane] = pacc[i];
-    __syncthreads();
-    if (wave >= rb0 && wave <= rb1) {                           // wave i finishes row block i
-      f32x4 s = red[wave * 64 + lane];
-#pragma unroll
-      for (int w = 1; w < TH_WAVES; ++w) {
-        const f32x4 o = red[(w * R + wave) * 64 + lane];
-        s[0] += o[0]; s[1] += o[1]; s[2] += o[2]; s[3] += o[3];
-      }
-      // lane: row li of the block, ranks q0 + 4 lg .. + 3
-      const int row = wave * 16 + li;
-      if (row >= row0 && row < row1) {
-        s[0] *= scale; s[1] *= scale; s[2] *= scale; s[3] *= scale;
-        f32x4 f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f[j] = __float_as_uint(s[j]) == 0u ? -0.f : s[j];
-        store4_agent(u_p + b % S * u_n + row * a.r_stride + q0 + 4 * lg, f);
-      }
-      wait_vm<0>();
-    }
+    for (int i = 1; i < R; ++i) if (i == rb0) tok0 = tokr[i];
+    const ShrinkJob job = {L, scale, r, q0, row0, row1, b % S};
+    shrink_job<R == 1 ? 4 : 3, R>(job, a.Aop, a.lda, a.Kc, tok0, tokr[R - 1], S, red, u_p + b % S * u_n, a.r_stride, wave, lane);
     __syncthreads();
     if (wave == 0) leave();
     return;
@@ -297,43 +243,14 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
         if (n < Nout) pre[k][0] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
       }
     }
-    for (int i = tid; i < 16 * R * (a.r_stride >> 2); i += TH_THREADS) {
+    for (int i = tid; i < 16 * R * (a.r_stride >> 2); i += TH_THREADS) {      // (whole waves)
       const int row = i / (a.r_stride >> 2), q = (i - row * (a.r_stride >> 2)) * 4;
       const int rank = t_s[row] >= 0 ? rank_s[row] : 0;
       f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (q < rank) {
-        bool ok = false;
-        for (int it = 0; it < a.spin_limit && !ok; ++it) {
-          // the splits' parts (a call of fewer splits reads its last one again)
-          f32x4 w[THIN_SPLITS];
-          const float* up = u_p + row * a.r_stride + q;
-          const float* up1 = up + (S > 1 ? u_n : 0);
-          const float* up2 = S > 2 ? up1 + u_n : up1;
-          const float* up3 = S > 3 ? up2 + u_n : up2;
-          asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
-                       "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
-                       : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]) : "v"(up), "v"(up1), "v"(up2), "v"(up3) : "memory");
-          ok = true;
-#pragma unroll
-          for (int k = 0; k < THIN_SPLITS; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              ok &= __float_as_uint(w[k][j]) != 0u;
-              v[j] = k == 0 ? w[0][j] : k < S ? v[j] + w[k][j] : v[j];
-            }
-        }
-        if (!ok) {
-          // (not reached in practice) the shrink of this row again, in plain fp32 arithmetic
-          const AdapterEntry en = table[t_s[row]];
-          const bf16_t* xr = a.Aop + (int64_t)tok_s[row] * a.lda;
-          for (int j = 0; j < 4 && q + j < rank; ++j) {
-            const bf16_t* lr = (const bf16_t*)(a.which ? en.A : en.B) + (int64_t)(q + j) * a.Kc;
-            float sum = 0.f;
-            for (int64_t k = 0; k < a.Kc; ++k) sum = fmaf(bf16_bits_to_float(xr[k]), bf16_bits_to_float(lr[k]), sum);
-            v[j] = en.scale * sum;
-          }
-        }
-      }
+      bool ok = true;
+      if (q < rank) ok = read_u<THIN_SPLITS>(u_p + row * a.r_stride + q, u_n, S, a.spin_limit, v);
+      if (__builtin_expect(__ballot(!ok) != 0, 0))               // (not reached in practice)
+        u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
 #pragma unroll
       for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
       *(f32x4*)(u_s + row * us + q) = v;

@@ -59,7 +59,7 @@ __device__ __forceinline__ void expand_octets(f32x4 (&y)[NCB], const uint4 (&pre
   for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
     for (int v = 0; v < 4; ++v) z = fmaf(y[cb][v], 0.f, z);
-  if (__ballot(z != 0.f) == 0) return;
+  if (__builtin_expect(__ballot(z != 0.f) == 0, 1)) return;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) y[cb] = was[cb];
 #pragma unroll 1

@@ -85,4 +85,91 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
   }
 }
 
+// Four values of u, S <= MAXS splits added in split order; false if they are not there after `polls` readings
+// (a round trip through the fabric each).
+template <int MAXS>
+__device__ __forceinline__ bool read_u(const float* u, int64_t u_split, int S, int polls, f32x4& v) {
+  static_assert(MAXS == 2 || MAXS == 4, "");
+  const float* u1 = u + (S > 1 ? u_split : 0);                   // (a call of fewer splits reads its last one again)
+  const float* u2 = S > 2 ? u1 + u_split : u1;
+  const float* u3 = S > 3 ? u2 + u_split : u2;
+  for (int it = 0; it < polls; ++it) {
+    f32x4 w[MAXS];
+    if (MAXS == 2)
+      asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
+                   : "=&v"(w[0]), "=&v"(w[1]) : "v"(u), "v"(u1) : "memory");
+    else
+      asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                   "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
+                   : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[MAXS - 2]), "=&v"(w[MAXS - 1]) : "v"(u), "v"(u1), "v"(u2), "v"(u3) : "memory");
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < MAXS; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        ok &= __float_as_uint(w[k][j]) != 0u;
+        v[j] = k == 0 ? w[0][j] : k < S ? v[j] + w[k][j] : v[j];
+      }
+    if (ok) return true;
+  }
+  return false;
+}
+
+// The same values computed by the wave that wants them (they did not come in time: no workgroup depends on another
+// one being scheduled), with the sums in the order of shrink_job.  Lane: ranks q .. q + 3 of row `row` of the tile,
+// `miss` if it lacks them.  t_s, tok_s: adapter (-1: none) and token (-1: past the end) of the tile's rows.  All
+// lanes of the wave call it.
+__device__ __forceinline__ void u_again(const AdapterEntry* table, int which, const bf16_t* X, int64_t lda, int64_t Kc, int S, const int32_t* t_s,
+                                        const int32_t* tok_s, int row, int q, bool miss, int lane, f32x4& v) {
+  constexpr int WAVES = 8;
+  const int li = lane & 15, lg = lane >> 4;
+  const int steps = (int)((Kc + 31) >> 5), part = (steps + S - 1) / S, per = (part + WAVES - 1) / WAVES;
+#pragma unroll 1
+  for (uint64_t left = __ballot(miss); left; left = __ballot(miss)) {
+    const int l = __ffsll((unsigned long long)left) - 1;
+    const int r = __builtin_amdgcn_readlane(row, l), q0 = __builtin_amdgcn_readlane(q, l) & ~15;
+    const int t = __builtin_amdgcn_readfirstlane(t_s[r]);
+    const AdapterEntry e = table[t];
+    const int32_t tk = tok_s[(r & ~15) + li], own = tok_s[r];
+    const bf16_t* xr = X + (int64_t)(tk < 0 ? own : tk) * lda;
+    const bool row_in = q0 + li < e.rank;
+    const bf16_t* lr = (const bf16_t*)(which ? e.A : e.B) + (int64_t)(row_in ? q0 + li : 0) * Kc;
+    f32x4 u = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int split = 0; split < S; ++split) {
+      const int k0 = split * part, k1 = k0 + part < steps ? k0 + part : steps;
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int w = 0; w < WAVES; ++w) {
+        const int s0 = k0 + w * per, s1 = s0 + per < k1 ? s0 + per : k1;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int st = s0; st < s1; ++st) {
+          union { uint4 u; bf16x8 v; } lf, xf;
+          const int64_t k = (int64_t)st * 32 + 8 * lg;
+          lf.u = xf.u = make_uint4(0, 0, 0, 0);
+          if (k < Kc && row_in) lf.u = *(const uint4*)(lr + k);
+          if (k < Kc) xf.u = *(const uint4*)(xr + k);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lf.v, xf.v, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] = w == 0 ? acc[i] : sum[i] + acc[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float z = e.scale * sum[i], f = __float_as_uint(z) == 0u ? -0.f : z;
+        u[i] = split == 0 ? f : u[i] + f;
+      }
+    }
+    // lane li + 16 lg holds ranks q0 + 4 lg .. of row li of the block
+    const bool mine = miss && (row & ~15) == (r & ~15) && (q & ~15) == q0 && t_s[row] == t;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float got = __shfl(u[i], (row & 15) + 4 * (q & 12));
+      if (mine) v[i] = got;
+    }
+    if (mine) miss = false;
+  }
+}
+
 }  // namespace marlaas

@@ -1,0 +1,130 @@
+"""Loads issued by inline assembly are waited for by hand, so the compiler takes their destination for valid
+at the statement itself: a copy or a spill that it puts behind the load reads the register before the data is
+there, and the load then lands in a register that holds something else by that time, an address for
+instance.  Reads the code generated for every kernel that has such loads: nothing moves a loaded register
+before a wait.  (Moves only: whether a wait is the right one for a use that the source has is for the source
+to say, and the walk below also takes paths that no execution takes.)"""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_08527_amd import build
+
+FILES = ["gemm_mid", "gemm_decode", "gemm_bf16"]
+
+
+def _registers(operand):
+    m = re.match(r"^-?\|?([va])\[(\d+):(\d+)\]", operand)
+    if m:
+        return [m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1)]
+    m = re.match(r"^-?\|?([va]\d+)\b", operand)
+    return [m.group(1)] if m else []
+
+
+def _functions(text):
+    """(name, basic blocks in order) of the kernels: {label: [(text, op, operands, inline assembly)]}"""
+    name = None
+    for line in text.splitlines():
+        m = re.match(r"^(_Z\w+):", line)
+        if m and name is None:
+            name, blocks, label, asm = m.group(1), {"": []}, "", False
+            continue
+        if name is None:
+            continue
+        if line.startswith(".Lfunc_end"):
+            yield name, blocks
+            name = None
+            continue
+        asm = "#ASMSTART" in line or (asm and "#ASMEND" not in line)
+        s = line.split(";")[0].strip()
+        m = re.match(r"^(\.\w+):", s)
+        if m:
+            label = m.group(1)
+            blocks[label] = []
+        elif s and not s.startswith("."):
+            op, _, rest = s.partition(" ")
+            blocks[label].append((s, op, [t.strip() for t in rest.split(",")], asm))
+
+
+MOVES = re.compile(r"v_mov|v_swap|v_pk_mov|v_accvgpr|scratch_store|v_writelane")
+
+
+def early_moves(blocks):
+    """Moves of a register that an inline-assembly load writes, on some path with no wait in between."""
+    order = list(blocks)
+    after = dict(zip(order, order[1:]))
+    state, work, found = {"": frozenset()}, [""], []
+
+    def reach(label, pending):
+        if label is not None and not (label in state and pending <= state[label]):
+            state[label] = state.get(label, frozenset()) | pending
+            work.append(label)
+
+    while work:
+        label = work.pop()
+        pending = state[label]                       # {(counter, register)}
+        for s, op, operands, asm in blocks[label]:
+            if op == "s_waitcnt":
+                pending = frozenset(p for p in pending if p[0] not in s)
+                continue
+            if op == "s_barrier":                    # (the kernels meet with their own requests waited for)
+                pending = frozenset()
+            if op == "s_branch":
+                reach(operands[0], pending)
+                break
+            if op.startswith("s_cbranch"):
+                reach(operands[0], pending)
+            if op == "s_endpgm":
+                break
+            stores = "store" in op or op.startswith(("ds_write", "s_"))
+            sources = {r for t in (operands if stores else operands[1:]) for r in _registers(t)}
+            if MOVES.match(op) and any(r in sources for _, r in pending):
+                found.append(s)
+            if not stores:
+                pending = frozenset(p for p in pending if p[1] not in _registers(operands[0]))
+            if asm:
+                counter = "vmcnt" if re.match(r"global_load_dword", op) else "lgkmcnt" if op.startswith("ds_read") else None
+                if counter:
+                    pending = pending | {(counter, r) for r in _registers(operands[0])}
+        else:
+            reach(after.get(label), pending)
+    return found
+
+
+@pytest.fixture(scope="module")
+def listings(tmp_path_factory):
+    out = tmp_path_factory.mktemp("listings")
+    procs = {}
+    for f in FILES:
+        cmd = [build.HIPCC] + build.FLAGS + ["-S", "--cuda-device-only", os.path.join(build.CSRC, f + ".hip"), "-o", str(out / f)]
+        procs[f] = subprocess.Popen(cmd, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+    assert all(p.wait() == 0 for p in procs.values())
+    return {f: (out / f).read_text() for f in FILES}
+
+
+@pytest.mark.parametrize("f", FILES)
+def test_no_move_of_a_load_before_a_wait(listings, f):
+    seen = 0
+    for name, blocks in _functions(listings[f]):
+        seen += 1
+        assert not early_moves(blocks), name
+    assert seen > 0
+
+
+def test_early_move_is_seen():
+    text = """_Zk:
+\t;;#ASMSTART
+\tglobal_load_dwordx4 v[4:7], v0, s[2:3]
+\t;;#ASMEND
+%s
+\tv_mov_b64_e32 v[8:9], v[6:7]
+.LBB0_1:
+\ts_endpgm
+.Lfunc_end0:
+"""
+    waits = {"": 1, "\ts_waitcnt vmcnt(2)": 0, "\ts_waitcnt lgkmcnt(0)": 1, "\ts_cbranch_vccz .LBB0_1": 1}
+    for wait, moves in waits.items():
+        (_, blocks), = _functions(text % wait)
+        assert len(early_moves(blocks)) == moves, wait

@@ -178,3 +178,26 @@ def test_some_rows_short_last_split(oracle, T, K, N):
     ids = rng.integers(-1, 3, size=T).astype(np.int32)
     w = wl.make_layer(T, T, K, N, [16, 8, 16], [2.0, 1.0, 0.5], ids, dtype="bf16", layout=wl.TORCH)
     _check_layer(oracle, w, bwd=False, tag="short last split", table="table+packed")
+
+
+# A workgroup that gives up waiting computes what it waited for in the same order of sums: no bit depends on
+# which workgroups were on the chip.  (Limit 0: every wait is given up at once.)
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,K,N,ranks", [(1, 264, 520, [16]), (16, 4104, 4096, [16] * 12), (32, 2056, 1032, [24, 128, 8]), (65, 4200, 1024, [16, 8]),
+                                         (80, 8200, 1032, [16] * 70), (157, 4104, 4096, [24, 64]), (300, 1064, 3080, [5, 13, 7]), (512, 2048, 5120, [8, 16, 32, 64] * 8)])
+def test_waits_given_up_keep_the_bits(monkeypatch, T, K, N, ranks, layout):
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    w = wl.make_layer(T + N, T, K, N, ranks, [0.5 + t % 3 for t in range(len(ranks))], ids, dtype="bf16", layout=layout, want_dY=True)
+    out = []
+    for limit in (None, "0"):
+        if limit:
+            monkeypatch.setenv("MARLAAS_SPIN_LIMIT", limit)
+        L = HipLayer(w, want_bwd=True, table=True, packed=True)
+        for rep in range(2):
+            y, u = L.fwd(save_u=True)
+            dX, dA, dB = L.bwd(u_saved=u)
+            out.append([y, u, dX] + list(dA) + list(dB))
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert torch.equal(a, b)
