@@ -25,12 +25,17 @@
  *    marlaas_adapter_table_update) only enqueue kernels on it and return: they
  *    allocate nothing, copy nothing from host memory, wait for nothing, and may
  *    be recorded into a HIP graph by stream capture, first call included.
- *    Device memory is only ever allocated by the *_create / *_build calls.
+ *    Device memory is only ever allocated by the *_create / *_build calls and, 34 MB for a buffer
+ *    that a ctx has not been given before (at most 15 times), by marlaas_set_workspace.
  *    marlaas_segmap_update enqueues, then waits for its own kernels.
  *  - Argument errors are reported synchronously as negative status codes with a
  *    message retrievable by marlaas_last_error(); HIP failures map to
  *    MARLAAS_EHIP.  No C++ exception crosses this boundary.
- *  - A ctx may be used by one host thread at a time.
+ *  - A ctx may be used by one host thread at a time.  Calls that may overlap on the device (on
+ *    several streams, in branches of one captured graph, replays of several graphs) must each have
+ *    been enqueued with a workspace of their own set (marlaas_set_workspace before the call); calls
+ *    that share a workspace have to be ordered by the caller.  Calls with no workspace set (no
+ *    adapters, or u_save given) may overlap.
  *  - Two environment variables are read when a ctx is created; both only select between ways of
  *    computing the same result for small batches with a packed weight (see marlaas_pack_weight):
  *    MARLAAS_DECODE_FINISH = 0 | 1 | 2 | 3: who adds up the contraction splits and applies the
@@ -229,7 +234,11 @@ int marlaas_transpose_weight(marlaas_ctx* ctx, const void* W, int64_t ldw, int64
 /*
  * Scratch memory.  The caller hands over one device buffer (e.g. a torch
  * tensor) that must stay alive and unused by others while calls on this ctx
- * are in flight.  It holds the intermediates u, v, partial sums, a transposed
+ * are in flight.  Beside it the ctx holds, for each of the first 16 buffers it is
+ * given, an area through which the workgroups of one launch exchange values;
+ * with further buffers, or where there is no memory for an area, passes take the
+ * kernels that exchange nothing (for few rows on packed weights up to twice the
+ * time), so a program keeps its workspaces and does not allocate one per call.  It holds the intermediates u, v, partial sums, a transposed
  * weight copy for some large batches and, for descriptors without an adapter
  * table, a per-call copy of their pointer tables (written by a small kernel at
  * the start of the pass).  marlaas_workspace_bytes returns the size at which
@@ -272,7 +281,8 @@ int marlaas_lora_fwd(marlaas_ctx* ctx, const marlaas_lora_desc* desc, void* y, i
  * and enqueues nothing.  All calls on one GPU
  * share the array: calls that may overlap in time (different streams, different
  * contexts or threads) race on it; calls on one stream are ordered and safe.
- * Nothing in the array has to be cleared between calls.
+ * Nothing in the array has to be cleared between calls.  (What the workgroups of
+ * a launch exchange goes through a second static array of 34 MB, shared alike.)
  */
 #define MARLAAS_STATIC_SCRATCH_BYTES (32u << 20)
 int marlaas_lora_fwd_static(marlaas_ctx* ctx, const marlaas_lora_desc* desc, void* y, int64_t ldy,

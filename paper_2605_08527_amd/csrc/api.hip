@@ -21,12 +21,24 @@
 
 using namespace marlaas;
 
+static const int MAX_EXCHANGES = 16;
+
 struct marlaas_ctx {
   int device = 0;
   void* ws = nullptr;
   size_t ws_bytes = 0;
   void* static_ws = nullptr;     // device address of this GPU's static scratch array
-  int32_t* sync_dev = nullptr;   // counters of the decode kernels, then u and partial sums of the one-launch kernels (zero between launches)
+  // What the workgroups of one launch exchange through (SYNC_INTS: counters of the decode kernels, then u and
+  // partial sums of the one-launch kernels; all zero between launches).  A launch has it to itself as it has
+  // its scratch, so there is one area for every workspace that the context has been given: calls that may
+  // overlap (on other streams, in branches of one graph, graphs that are replayed later) use workspaces of
+  // their own, and an area stays with its workspace while the context lives.  Calls with a workspace beyond
+  // MAX_EXCHANGES, or with none, take the kernels that exchange nothing.
+  struct Exchange { const void* ws; int32_t* dev; };
+  Exchange exchanges[MAX_EXCHANGES] = {};        // [0]: allocated with the context, ws = null until the first workspace
+  int n_exchanges = 0;
+  int32_t* exchange = nullptr;           // of the current workspace
+  int32_t* static_exchange = nullptr;    // of the static scratch (this GPU's)
   int cu_count = 0;
   int spin_limit = 1 << 20;
   void* zero_dev = nullptr;    // 1024 zero bytes (what masked DMA lanes fetch)
@@ -86,20 +98,44 @@ static const int64_t EXT_CAP_MAX = 1 << 16;   // extended columns a table can de
 // call ever allocates it.  Host code must not use the array's name as an address: the device
 // address is looked up once per device (in marlaas_create, with that device current) and kept.
 static __device__ __align__(256) unsigned char scratch[MARLAAS_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) int32_t scratch_exchange[SYNC_INTS];      // (zero when the code object is loaded)
 static const int MAX_DEVICES = 64;
 static void* g_scratch_ptr[MAX_DEVICES];
+static void* g_scratch_exchange_ptr[MAX_DEVICES];
 static std::mutex g_scratch_mutex;
 
-static hipError_t static_scratch_of(int device, void** out) {
+static hipError_t static_scratch_of(int device, void** out, int32_t** exchange) {
   std::lock_guard<std::mutex> lock(g_scratch_mutex);
   if (!g_scratch_ptr[device]) {
-    void* p = nullptr;
+    void *p = nullptr, *x = nullptr;
     hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));   // for the current device
+    if (e == hipSuccess) e = hipGetSymbolAddress(&x, HIP_SYMBOL(scratch_exchange));
     if (e != hipSuccess) return e;
     g_scratch_ptr[device] = p;
+    g_scratch_exchange_ptr[device] = x;
   }
   *out = g_scratch_ptr[device];
+  *exchange = (int32_t*)g_scratch_exchange_ptr[device];
   return hipSuccess;
+}
+
+// A zeroed exchange area, null if there is no memory for it.  Also inside a stream capture of the caller's:
+// the fill runs on a stream of its own and is waited for here.
+static int32_t* new_exchange() {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
+  int32_t* dev = nullptr;
+  hipStream_t st = nullptr;
+  bool ok = hipMalloc((void**)&dev, SYNC_INTS * sizeof(int32_t)) == hipSuccess && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess &&
+            hipMemsetAsync(dev, 0, SYNC_INTS * sizeof(int32_t), st) == hipSuccess && hipStreamSynchronize(st) == hipSuccess;
+  if (st) (void)hipStreamDestroy(st);
+  if (!ok) {
+    (void)hipFree(dev);
+    (void)hipGetLastError();
+    dev = nullptr;
+  }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return dev;
 }
 
 static int fail(marlaas_ctx* ctx, int status, const char* fmt, ...) {
@@ -166,21 +202,24 @@ extern "C" int marlaas_create(marlaas_ctx** out, int device) {
   if (hipGetDeviceCount(&count) != hipSuccess || device < 0 || device >= count || device >= MAX_DEVICES) return MARLAAS_EHIP;
   if (hipSetDevice(device) != hipSuccess) return MARLAAS_EHIP;
   void* sp = nullptr;
-  if (static_scratch_of(device, &sp) != hipSuccess || !sp) return MARLAAS_EHIP;
+  int32_t* sx = nullptr;
+  if (static_scratch_of(device, &sp, &sx) != hipSuccess || !sp || !sx) return MARLAAS_EHIP;
   marlaas_ctx* ctx = new (std::nothrow) marlaas_ctx();
   if (!ctx) return MARLAAS_ENOMEM;
   ctx->device = device;
   ctx->static_ws = sp;
+  ctx->static_exchange = sx;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->cu_count = prop.multiProcessorCount;
-  if (hipMalloc((void**)&ctx->sync_dev, SYNC_INTS * sizeof(int32_t)) != hipSuccess ||
-      hipMemset(ctx->sync_dev, 0, SYNC_INTS * sizeof(int32_t)) != hipSuccess ||
+  if (hipMalloc((void**)&ctx->exchange, SYNC_INTS * sizeof(int32_t)) != hipSuccess || hipMemset(ctx->exchange, 0, SYNC_INTS * sizeof(int32_t)) != hipSuccess ||
       hipMalloc(&ctx->zero_dev, 1024) != hipSuccess || hipMemset(ctx->zero_dev, 0, 1024) != hipSuccess) {
     (void)hipFree(ctx->zero_dev);
-    (void)hipFree(ctx->sync_dev);
+    (void)hipFree(ctx->exchange);
     delete ctx;
     return MARLAAS_ENOMEM;
   }
+  ctx->exchanges[0].dev = ctx->exchange;
+  ctx->n_exchanges = 1;
   // MARLAAS_SPIN_LIMIT: readings of a bounded wait (0: never wait, always compute again; for tests of
   // that path); the one-launch kernels take at most MID_POLLS
   if (const char* sl = getenv("MARLAAS_SPIN_LIMIT")) ctx->spin_limit = atoi(sl) < 0 ? 0 : atoi(sl);
@@ -231,7 +270,7 @@ extern "C" void marlaas_destroy(marlaas_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   drop_spans(ctx);
-  (void)hipFree(ctx->sync_dev);
+  for (int i = 0; i < ctx->n_exchanges; ++i) (void)hipFree(ctx->exchanges[i].dev);
   (void)hipFree(ctx->zero_dev);
   delete ctx;
 }
@@ -614,6 +653,23 @@ extern "C" int marlaas_set_workspace(marlaas_ctx* ctx, void* dev_ptr, size_t byt
     return fail(ctx, MARLAAS_EALIGN, "workspace must be %zu-byte aligned", WS_ALIGN);
   ctx->ws = dev_ptr;
   ctx->ws_bytes = dev_ptr ? bytes : 0;
+  ctx->exchange = nullptr;
+  if (!dev_ptr) {
+    if (!ctx->exchanges[0].ws) ctx->exchange = ctx->exchanges[0].dev;      // (there has been no workspace yet)
+    return MARLAAS_OK;
+  }
+  int i = 0;
+  while (i < ctx->n_exchanges && ctx->exchanges[i].ws && ctx->exchanges[i].ws != dev_ptr) ++i;
+  if (i == ctx->n_exchanges && i < MAX_EXCHANGES) {
+    HIP_TRY(ctx, hipSetDevice(ctx->device));
+    ctx->exchanges[i].dev = new_exchange();
+    if (!ctx->exchanges[i].dev) return MARLAAS_OK;                         // (the kernels that need none)
+    ++ctx->n_exchanges;
+  }
+  if (i < ctx->n_exchanges) {
+    ctx->exchanges[i].ws = dev_ptr;
+    ctx->exchange = ctx->exchanges[i].dev;
+  }
   return MARLAAS_OK;
 }
 
@@ -766,9 +822,9 @@ extern "C" int marlaas_transpose_weight(marlaas_ctx* ctx, const void* W, int64_t
   return MARLAAS_OK;
 }
 
-static DecodeSync decode_sync_of(const marlaas_ctx* ctx, const marlaas_segmap* map) {
+static DecodeSync decode_sync_of(const marlaas_ctx* ctx, const marlaas_segmap* map, int32_t* exchange) {
   DecodeSync s;
-  s.mode = ctx->decode_finish; s.counters = ctx->sync_dev; s.grp_ids = map->grp_dev; s.spin_limit = ctx->spin_limit; s.cu_count = ctx->cu_count;
+  s.mode = ctx->decode_finish; s.counters = exchange; s.grp_ids = map->grp_dev; s.spin_limit = ctx->spin_limit; s.cu_count = ctx->cu_count;
   return s;
 }
 
@@ -836,13 +892,13 @@ static int max_shrink_jobs(const marlaas_lora_desc* d, const MidPlan& plan) {
 
 // A call on packed weights (W and ldw of `proj` filled in) that one of the one-launch kernels does best:
 // enqueues it and sets *done.
-static int launch_packed(marlaas_ctx* ctx, const marlaas_lora_desc* descs, int32_t n_proj, const ProjEntry* proj, const bf16_t* x, int64_t ldx,
+static int launch_packed(marlaas_ctx* ctx, int32_t* exchange, const marlaas_lora_desc* descs, int32_t n_proj, const ProjEntry* proj, const bf16_t* x, int64_t ldx,
                          int64_t Kc, int form, bool lora, const AdapterEntry* table, int which, int out_f32, float* u, int rs, hipStream_t st, bool* done) {
   const marlaas_lora_desc* d = &descs[0];
   const marlaas_segmap* map = d->map;
   const int32_t* perm = map->perm_dev;       // (also of a grouped batch: a captured call serves the map's later batches)
   const int n = lora ? d->n_adapters : 0;
-  const DecodeSync sync = decode_sync_of(ctx, map);
+  const DecodeSync sync = decode_sync_of(ctx, map, exchange);
   *done = false;
   int ext = 0;
   for (int t = 0; lora && t < d->n_adapters; ++t) if (map->seg_off[t + 1] > map->seg_off[t]) ext += ranks_of(d)[t];
@@ -864,7 +920,7 @@ static int launch_packed(marlaas_ctx* ctx, const marlaas_lora_desc* descs, int32
 
 // ------------------------------------------------------------------ forward
 static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64_t ldy, void* u_save, void* stream,
-                    void* ws, size_t ws_bytes) {
+                    void* ws, size_t ws_bytes, int32_t* exchange) {
   int rc = check_sizes(ctx, d);
   if (rc != MARLAAS_OK) return rc;
   if (d->T == 0) return MARLAAS_OK;
@@ -896,13 +952,13 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
   // A_t follows W for the shrink, B_t follows W for the expand.
   const int form = d->layout == MARLAAS_LAYOUT_MATH ? FORM_NN : FORM_NT;
   const int out_f32 = d->out_dtype == MARLAAS_F32;
-  const DecodeSync dsync = decode_sync_of(ctx, map);
+  const DecodeSync dsync = decode_sync_of(ctx, map, exchange);
   bool done = false;
   if (d->in_dtype == MARLAAS_BF16 && d->W_packed_fwd) {
     ProjEntry pe;
     memset(&pe, 0, sizeof pe);
     pe.W = d->W_packed_fwd; pe.ldw = packed_weight_ksteps(d->d_in); pe.Nout = d->d_out; pe.out = y; pe.ldo = ldy;
-    if ((rc = launch_packed(ctx, d, 1, &pe, (const bf16_t*)d->x, d->ldx, d->d_in, form, lora, table, 1, out_f32, (float*)u_save, rs, st, &done)) != MARLAAS_OK)
+    if ((rc = launch_packed(ctx, exchange, d, 1, &pe, (const bf16_t*)d->x, d->ldx, d->d_in, form, lora, table, 1, out_f32, (float*)u_save, rs, st, &done)) != MARLAAS_OK)
       return rc;
   }
   if (done) {
@@ -949,7 +1005,7 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
 extern "C" int marlaas_lora_fwd(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64_t ldy,
                                 void* u_save, void* stream) {
   if (!ctx) return MARLAAS_EINVAL;
-  return fwd_impl(ctx, d, y, ldy, u_save, stream, ctx->ws, ctx->ws_bytes);
+  return fwd_impl(ctx, d, y, ldy, u_save, stream, ctx->ws, ctx->ws_bytes, ctx->ws ? ctx->exchange : nullptr);
 }
 
 extern "C" int marlaas_lora_fwd_static(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64_t ldy,
@@ -961,7 +1017,7 @@ extern "C" int marlaas_lora_fwd_static(marlaas_ctx* ctx, const marlaas_lora_desc
   if (need > (size_t)MARLAAS_STATIC_SCRATCH_BYTES)
     return fail(ctx, MARLAAS_ENOMEM, "this forward needs %zu scratch bytes, the static scratch holds %zu: use marlaas_lora_fwd with a workspace",
                 need, (size_t)MARLAAS_STATIC_SCRATCH_BYTES);
-  return fwd_impl(ctx, d, y, ldy, u_save, stream, ctx->static_ws, (size_t)MARLAAS_STATIC_SCRATCH_BYTES);
+  return fwd_impl(ctx, d, y, ldy, u_save, stream, ctx->static_ws, (size_t)MARLAAS_STATIC_SCRATCH_BYTES, ctx->static_exchange);
 }
 
 // ------------------------------------------------------------------ forward, several projections
@@ -1069,7 +1125,7 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
   // adapters): the kernels that read those
   bool packed = !lora || form == FORM_NT;
   for (int p = 0; p < n_proj; ++p) if (!descs[p].W_packed_fwd) packed = false;
-  const DecodeSync dsync = decode_sync_of(ctx, map);
+  const DecodeSync dsync = decode_sync_of(ctx, map, ctx->exchange);
   int rs_all = 0;
   for (int p = 0; p < n_proj; ++p) { const int r = (int)marlaas_u_stride(&descs[p]); if (r > rs_all) rs_all = r; }
   if (packed && n_proj > 1 && d0->in_dtype == MARLAAS_BF16 && (!lora || shared)) {
@@ -1077,7 +1133,7 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
     std::vector<ProjEntry> pk = proj;
     for (int p = 0; p < n_proj; ++p) { pk[p].W = descs[p].W_packed_fwd; pk[p].ldw = packed_weight_ksteps(d0->d_in); }
     bool done = false;
-    rc = launch_packed(ctx, descs, n_proj, pk.data(), (const bf16_t*)d0->x, d0->ldx, d0->d_in, form, lora, lora ? d0->table->dev.entries : nullptr, 1,
+    rc = launch_packed(ctx, ctx->exchange, descs, n_proj, pk.data(), (const bf16_t*)d0->x, d0->ldx, d0->d_in, form, lora, lora ? d0->table->dev.entries : nullptr, 1,
                        d0->out_dtype == MARLAAS_F32, nullptr, rs_all, (hipStream_t)stream, &done);
     if (rc != MARLAAS_OK || done) return rc;
   }
@@ -1206,7 +1262,8 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
   const int out_f32 = d->out_dtype == MARLAAS_F32;
   const bool have_ws = ctx->ws && ctx->ws_bytes >= p.least;
   float* part = (have_ws && p.part_bytes) ? (float*)((char*)ctx->ws + p.part_off) : nullptr;
-  const DecodeSync dsync = decode_sync_of(ctx, map);
+  int32_t* exchange = ctx->ws ? ctx->exchange : nullptr;
+  const DecodeSync dsync = decode_sync_of(ctx, map, exchange);
   if (d->in_dtype == MARLAAS_BF16) {
     const bf16_t* x = (const bf16_t*)d->x;
     const bf16_t* dy = (const bf16_t*)dY;
@@ -1223,7 +1280,7 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
       ProjEntry pe;
       memset(&pe, 0, sizeof pe);
       pe.W = d->W_packed_bwd; pe.ldw = packed_weight_ksteps(d->d_out); pe.Nout = d->d_in; pe.out = dX; pe.ldo = lddx;
-      if ((rc = launch_packed(ctx, d, 1, &pe, dy, lddy, d->d_out, bform, lora, table, 0, out_f32, v, rs, st, &done)) != MARLAAS_OK) return rc;
+      if ((rc = launch_packed(ctx, exchange, d, 1, &pe, dy, lddy, d->d_out, bform, lora, table, 0, out_f32, v, rs, st, &done)) != MARLAAS_OK) return rc;
     }
     if (!done && lora && dX && part && bank_can_fuse(bank)) {
       fused = gemm_can_fuse_shrink(bform, d->T, d->d_out, d->d_in, need, bank.mult8, use_packed && d->W_packed_bwd, p.part_bytes);

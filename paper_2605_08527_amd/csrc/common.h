@@ -171,7 +171,7 @@ enum { DECODE_FINISH_GENERIC = 0,    // splitk_finish_kernel on fp32 rows (any s
        DECODE_FINISH_AUTO = 3 };     // whichever of the two is faster for the split count
 struct DecodeSync {
   int mode = DECODE_FINISH_GENERIC;  // the way asked for; the launcher falls back to the generic one
-  int32_t* counters = nullptr;       // at least DECODE_SYNC_INTS
+  int32_t* counters = nullptr;       // SYNC_INTS, all zero between launches; null: only kernels that exchange nothing
   const int32_t* grp_ids = nullptr;
   int spin_limit = 0;
   int cu_count = 0;

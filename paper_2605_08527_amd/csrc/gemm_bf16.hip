@@ -980,7 +980,7 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
 
 // ---- few rows
 bool gemm_thin_ok(int form, int64_t T, bool lora, int r_stride, const DecodeSync* sync) {
-  return T > 0 && T <= THIN_ROWS && sync && sync->counters && (!lora || (form == FORM_NT && sync->grp_ids && r_stride <= 128)) &&
+  return T > 0 && T <= THIN_ROWS && sync && (!lora || (sync->counters && form == FORM_NT && sync->grp_ids && r_stride <= 128)) &&
          (sync->mode == DECODE_FINISH_AUTO || sync->mode == DECODE_FINISH_IN_KERNEL);
 }
 
@@ -993,7 +993,7 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
   a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.n_adapters = n_adapters; a.table = table; a.which = which;
   a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
   a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit < MID_POLLS ? sync->spin_limit : MID_POLLS;
-  a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
+  if (sync->counters) a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
   a.n_proj = n_proj; a.n_prod = n_adapters > 0 ? n_proj * max_tiles : 0;
   for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
   return launch_gemm_thin(a, stream);
@@ -1001,12 +1001,12 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
 
 // ---- some more rows
 MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, bool lora, int ext, int r_stride, const DecodeSync* sync) {
-  if (T <= 0 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || !sync->counters || (lora && (form != FORM_NT || !sync->grp_ids || r_stride > 128)) ||
+  if (T <= 0 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || (lora && (!sync->counters || form != FORM_NT || !sync->grp_ids || r_stride > 128)) ||
       (sync->mode != DECODE_FINISH_AUTO && sync->mode != DECODE_FINISH_IN_KERNEL))
     return MidPlan();
   int64_t cols = 0;
   for (int q = 0; q < n_proj; ++q) cols += proj_host[q].Nout;
-  const MidPlan p = mid_plan(T, Kc, proj_host, n_proj, lora);
+  const MidPlan p = mid_plan(T, Kc, proj_host, n_proj, lora, sync->counters ? 4 : 1);     // (splits exchange sums)
   for (int q = 0; q < n_proj; ++q)
     if ((proj_host[q].Nout + 32 * p.wn - 1) / (32 * p.wn) * p.ksplit > MID_CONSUMERS) return MidPlan();
   return mid_pays(p, T, Kc, cols, ext) ? p : MidPlan();
@@ -1022,8 +1022,10 @@ hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_
   a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.seg_off = seg_off; a.n_adapters = n_adapters; a.table = table; a.which = which;
   a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
   a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit < MID_POLLS ? sync->spin_limit : MID_POLLS; a.zero_line = zero_line;
-  a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
-  a.partials = (float*)(sync->counters + (SYNC_INTS - MID_PART_FLOATS));
+  if (sync->counters) {
+    a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
+    a.partials = (float*)(sync->counters + (SYNC_INTS - MID_PART_FLOATS));
+  }
   a.n_proj = n_proj;
   for (int q = 0; q < n_proj; ++q) a.proj[q] = proj_host[q];
   a.proj_jobs = n_adapters > 0 ? proj_jobs : 0;

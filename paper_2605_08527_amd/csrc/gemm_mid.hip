@@ -693,7 +693,7 @@ hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream
 // the best one in the mean).  A k-tile's time when a workgroup has its compute unit to itself, which
 // two on one unit take 2.5 times as long for; longer rows of x and W cost a little more; against it what the
 // fabric delivers; splits pay for the exchange.
-MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool lora) {
+MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool lora, int max_split) {
   static const double tile_us[2][2] = {{0.29, 0.25}, {0.38, 0.31}};       // [rb - 4][wn == 4]
   MidPlan best;
   int64_t cols = 0;
@@ -705,7 +705,7 @@ MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool 
     for (int q = 0; q < n_proj; ++q) tiles_n += (proj[q].Nout + 32 * wn - 1) / (32 * wn);
     for (int rb = 4; rb <= 5; ++rb) {
       const int64_t tiles_m = (T + 16 * rb - 1) / (16 * rb);
-      for (int s = 1; s <= 4; s *= 2) {
+      for (int s = 1; s <= max_split; s *= 2) {
         const int64_t wgs = tiles_m * tiles_n * s;
         if (s > 1 && (wgs > MID_SPLIT_WGS || ktiles < 4 * s)) continue;
         const double t1 = tile_us[rb - 4][wn == 4] * stretch * (double)((ktiles + s - 1) / s), t2 = 2.5 * t1;
