@@ -146,9 +146,11 @@ void marlaas_segmap_destroy(marlaas_segmap* map);
  * batch every step: marlaas_segmap_create allocates a map object able to hold
  * any batch of up to T_max tokens over up to n_adapters_max adapters (device
  * buffers and one pinned host buffer, holding no map yet); marlaas_segmap_update
- * regroups a batch into it without allocating: five small kernels, one
- * device-to-host copy of the n_adapters + 2 offsets and one wait on `stream` (the
- * host plans launch grids from the segment sizes).  Sizes beyond the capacity
+ * regroups a batch into it without allocating: up to 32768 tokens and 800
+ * adapters one kernel, which also writes the n_adapters + 2 offsets to the pinned
+ * buffer, where the host watches for them (it plans launch grids from the segment
+ * sizes); beyond that several kernels, two device-to-host copies and a wait on
+ * `stream`.  Sizes beyond the capacity
  * give MARLAAS_ESHAPE, ids outside [-1, n_adapters) MARLAAS_EINVAL (the object
  * then holds no map until the next successful update), a capturing stream
  * MARLAAS_EUNSUPPORTED.  marlaas_segmap_build = create(T, n_adapters) + update.

@@ -25,17 +25,22 @@
 // 128 rows x 32 columns; the two halves are added through LDS once, at the end.  Two waves per
 // SIMD, one from each half, so one wave's LDS and memory latency is covered by the other's MFMAs.
 //
-// Who finishes the call (adds the splits, adds the expand, rounds, scatters the rows):
-//   fin_in_kernel = 0 (default): splitk_finish_kernel, a second launch; partial sums as fp32 rows.
-//   fin_in_kernel = 1: this kernel.  The splits of a tile share out its 32 units (16 rows x 32
-//     columns) and meet through counters in device memory; the column tiles that carry extended
-//     columns publish their partial u the same way.  Everything that crosses workgroups is
-//     written and read with the agent-scope policy on the instruction itself.  There is one
-//     bounded wait; a split that does not see the others in time leaves its share to whichever
-//     split is through with the tile last, and u that does not show up in time is recomputed, so
-//     no workgroup ever depends on another one being scheduled.  On MI355X every fabric round
-//     trip in that tail costs 1 - 1.5 us and the whole comes out slower than the second launch,
-//     which is why it is not the default.
+// Most calls on packed weights run in one launch of other kernels (gemm_thin.hip, gemm_mid.hip); this one
+// serves more than 1024 rows whose tiles do not fill the chip, 65 to 256 rows against a long contraction with
+// few columns (mid_pays), and calls that have no area to exchange values through.
+//
+// Who finishes the call (adds the splits, adds the expand, rounds, scatters the rows), decode_finish_mode():
+//   generic: splitk_finish_kernel, a second launch; partial sums as fp32 rows.
+//   launch (where the contraction is split): a second launch of this kernel's own finish (PHASE 1), the expand
+//     on the matrix instructions.
+//   in the kernel (where it is not split: the sums never leave the registers).  Splits of a tile share out
+//     its 32 units (16 rows x 32 columns) and meet through counters in device memory; the column tiles that
+//     carry extended columns publish their partial u the same way.  Everything that crosses workgroups is
+//     written and read with the agent-scope policy on the instruction itself.  There is one bounded wait; a
+//     split that does not see the others in time leaves its share to whichever split is through with the
+//     tile last, and u that does not show up in time is recomputed, so no workgroup ever depends on another
+//     one being scheduled.  On MI355X every fabric round trip in that tail costs 1 - 1.5 us and with splits
+//     the whole comes out slower than the second launch.
 #include "gemm_args.h"
 #include "agent_memory.h"
 #include "lora_expand.h"

@@ -5,21 +5,24 @@
 // A workgroup owns a tile of 16 RB rows x 32 WN columns; its eight waves are WN column groups of 32 times
 // KG = 8 / WN contraction groups, so a weight fragment is read once, by the one wave that multiplies it,
 // and the sums of the contraction groups meet in LDS.  x goes through LDS by DMA in a ring of 128-deep
-// tiles, because every column group needs all of it.  What bounds it: the fabric delivers 28 GB/s to each
-// of the 256 compute units (7.3 TB/s in all, the weight once, x once per XCD), an XCD's L2 four times
-// that; below those a call pays for every dependent trip through the fabric, 1 to 1.5 us each, and for
+// tiles, because every column group needs all of it.  What bounds it: the fabric between the memory and the
+// eight L2s (256 rows of 4096 x 4096 fetch 66.7 MB by the counters: the weight 33.5, x 2.1 for each XCD, the
+// factors and what is read again), and below its rate every dependent trip through it, 1 to 1.5 us each, and
 // every launch, about 4 us.  So: no second launch, few contraction splits, tiles small enough that two
 // workgroups share a compute unit (128 registers, 80 KB of LDS).
 //
-// Measured (microseconds, before: extended columns through the split kernel and a second launch):
-// 256 rows 4096 x 4096 30 -> 26; 157 rows 4096 x 28672 127 -> 82, 4096 x 14336 63 -> 45; 512 rows of 64 adapters
-// of ranks 8 to 64, 5120 x 5120 105 -> 68.
+// Measured (microseconds, before: extended columns through the split kernel and a second launch): 256 rows
+// 4096 x 4096 with 32 adapters of rank 16 28.4 -> 24.3, q/k/v of 4096 + 1024 + 1024 columns 42.0 -> 33.1, the
+// four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 209, 512 rows of 64 adapters of ranks 8
+// to 64, 5120 x 5120, with their regrouping 146 -> 94.
 //
 // Whatever crosses workgroups carries its own flag: it travels through areas of the context that are all
 // zero bits between launches, no value is stored as zero bits (+0 becomes -0), and a reader reads until
 // nothing is zero bits any more.
 //   u: workgroups before the others ("producers") compute it, one per 16 ranks of an adapter and pair of
-//     its 16-row blocks in a row tile.  The workgroup that is last through with a row tile clears it.
+//     16-row blocks of a row tile (and half of a long contraction).  There are as many as any grouping of the
+//     rows needs and each finds its share in the segment map, so that a captured call serves the groupings
+//     that the map object gets later.  The workgroup that is last through with a row tile clears its u.
 //   partial sums: with ksplit > 1 the splits of a tile share out its 16 x 16 units; a split hands the
 //     others' units over, reads its own ones' missing sums and clears them.
 // The reading is bounded (MID_POLLS).  u that does not come in time is computed by the reader; so are missing
@@ -688,11 +691,11 @@ hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream
   return p.rb == 4 ? launch_mid<4, 2>(a, cu_count, stream) : launch_mid<5, 2>(a, cu_count, stream);
 }
 
-// Estimated run time of a tiling in microseconds, fitted to 3500 runs over 5 to 1024 rows, contractions of
-// 1024 to 14336 and 1024 to 28672 columns (a tenth off as a rule; the tiling it picks is 2 % slower than
-// the best one in the mean).  A k-tile's time when a workgroup has its compute unit to itself, which
-// two on one unit take 2.5 times as long for; longer rows of x and W cost a little more; against it what the
-// fabric delivers; splits pay for the exchange.
+// Estimated run time of a tiling in microseconds; the constants are a fit to timed runs over 5 to 1024 rows,
+// contractions of 1024 to 14336 and 1024 to 28672 columns, and only the order of the tilings matters.  A
+// k-tile's time when a workgroup has its compute unit to itself, which two on one unit take 2.5 times as long
+// for; longer rows of x and W cost a little more; against it what the fabric delivers; splits pay for the
+// exchange.
 MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool lora, int max_split) {
   static const double tile_us[2][2] = {{0.29, 0.25}, {0.38, 0.31}};       // [rb - 4][wn == 4]
   MidPlan best;

@@ -1,5 +1,5 @@
 // Token grouping by adapter: a stable counting sort, one launch of one block for the batches of a
-// serving step (segmap_small), three small kernels for very large ones.
+// serving step (segmap_small), several small kernels for very large ones.
 // The mixed-tenant batch carries one adapter id per token (paper Sec. 4.5,
 // cross-task batching of rollouts); every later kernel works on tokens grouped
 // by adapter, so this map is built once per batch and reused by all layers.
