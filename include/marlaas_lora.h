@@ -43,9 +43,9 @@
  *    second launch of the decode kernel's own finish, or (default, 3) the second for an unsplit
  *    contraction and the third otherwise.  With 0 and 2 the forwards of few rows, which run in one
  *    launch of other kernels, go through the decode kernel as well.  MARLAAS_SPIN_LIMIT = n: the
- *    most readings of a workgroup that waits for another one's values (default: 256 in the
- *    one-launch kernels, 2^20 in the decode kernel's in-kernel finish; 0: none) before it goes on
- *    without them.  The work is then done by whoever wants the values; in the one-launch kernels
+ *    most readings of a workgroup that waits for another one's values (default, and at most, 256
+ *    in the one-launch kernels; default 2^20 in the decode kernel's in-kernel finish; 0: none)
+ *    before it goes on without them.  The work is then done by whoever wants the values; in the one-launch kernels
  *    in the same order of sums.
  */
 #ifndef MARLAAS_LORA_H
