@@ -180,14 +180,14 @@ static constexpr int DECODE_SYNC_INTS = 4096;
 static constexpr int THIN_ROWS = 32;                              // rows of the few-row kernel (gemm_thin.hip)
 static constexpr int THIN_SPLITS = 4;
 // One launch for up to MID_ROWS rows (gemm_mid.hip): rows of a tile, columns of a tile / 32, contraction
-// splits.  u travels where the few-row kernel's does ([MAX_PROJ][MID_SPLITS][MID_ROWS][128]), the partial
+// splits.  u travels where the few-row kernel's does ([projection][piece of the contraction][T][r_stride], two pieces always fit), the partial
 // sums of at most MID_SPLIT_WGS workgroups behind it.
-static constexpr int MID_ROWS = 1024, MID_SPLITS = 2, MID_SPLIT_WGS = 512;
-static constexpr int MID_U_FLOATS = MAX_PROJ * MID_SPLITS * MID_ROWS * 128;
+static constexpr int MID_ROWS = 1024, MID_SPLITS = 4, MID_SPLIT_WGS = 512;
+static constexpr int MID_U_FLOATS = MAX_PROJ * 2 * MID_ROWS * 128;
 static constexpr int MID_PART_FLOATS = MID_SPLIT_WGS * 96 * 128;
 static constexpr int SYNC_INTS = DECODE_SYNC_INTS + MID_U_FLOATS + MID_PART_FLOATS;
 // (the counter of a row tile holds its consumers and MID_JOBS, more than the shrink jobs it can have, in 16 bits)
-static constexpr int MID_JOBS = 2048, MID_CONSUMERS = 65535 - MID_JOBS;
+static constexpr int MID_JOBS = 4096, MID_CONSUMERS = 65535 - MID_JOBS;
 static_assert(80 * 8 * MID_SPLITS < MID_JOBS, "every row its own adapter of rank 128");
 // Readings of a bounded wait, a round trip through the fabric each (1 to 1.5 us under load): what is waited for
 // takes a tenth of it where its workgroups are on the chip, and doing without costs a few hundred microseconds.

@@ -12,15 +12,16 @@
 // workgroups share a compute unit (128 registers, 80 KB of LDS).
 //
 // Measured (microseconds, before: extended columns through the split kernel and a second launch): 256 rows
-// 4096 x 4096 with 32 adapters of rank 16 28.4 -> 24.3, q/k/v of 4096 + 1024 + 1024 columns 42.0 -> 33.1, the
-// four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 209, 512 rows of 64 adapters of ranks 8
-// to 64, 5120 x 5120, with their regrouping 146 -> 94.
+// 4096 x 4096 with 32 adapters of rank 16 28.4 -> 22.4, q/k/v of 4096 + 1024 + 1024 columns 42.0 -> 33.1, the
+// four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 195, 512 rows of 64 adapters of ranks 8
+// to 64, 5120 x 5120, 60.  Stamps in the 256 rows: indices 1.8, first tile 3.8, loop done 15.4 (17.5 where a
+// producer shares the unit; 14.6 without adapters), sums and u 17.4, expand 18.5, stored 19.1.
 //
 // Whatever crosses workgroups carries its own flag: it travels through areas of the context that are all
 // zero bits between launches, no value is stored as zero bits (+0 becomes -0), and a reader reads until
 // nothing is zero bits any more.
 //   u: workgroups before the others ("producers") compute it, one per 16 ranks of an adapter and pair of
-//     16-row blocks of a row tile (and half of a long contraction).  There are as many as any grouping of the
+//     16-row blocks of a row tile (and piece of a long contraction).  There are as many as any grouping of the
 //     rows needs and each finds its share in the segment map, so that a captured call serves the groupings
 //     that the map object gets later.  The workgroup that is last through with a row tile clears its u.
 //   partial sums: with ksplit > 1 the splits of a tile share out its 16 x 16 units; a split hands the
@@ -57,7 +58,7 @@ struct MidShape {
   static constexpr int NS = RB == 4 || WN == 4 ? 4 : 3; // ring slots = k-tiles on the way (registers, LDS)
   static constexpr int SLOT = RB * 16 * K * 2;
   static constexpr int RED = RB * WN * 2 * (KG - 1) * 1024;       // exchange of the contraction groups
-  static constexpr int BASE = NS * SLOT > RED ? NS * SLOT : RED;
+  
 };
 
 // Job `job` of a projection's shrink, counted over all row tiles (16 RB rows each): 16 ranks of an adapter for its
@@ -131,9 +132,9 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   constexpr int KG = S_::KG, MD_K = S_::K, UR = MD_K / 8, NS = S_::NS, SLOT = S_::SLOT, BM = 16 * RB, NR = (RB + KG - 1) / KG;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int us = a.r_stride + 4, oct_max = 2 * a.r_stride;       // (octet: 8 ranks of one adapter; so many can a 16-row block have)
-  const int base_bytes = S_::BASE > BM * us * 4 ? S_::BASE : BM * us * 4;
+  const int base_bytes = NS * SLOT > S_::RED + BM * us * 4 ? NS * SLOT : S_::RED + BM * us * 4;
   f32x4* red = (f32x4*)smem;
-  float* u_s = (float*)smem;                                     // [BM][us], once the sums have met
+  float* u_s = (float*)(smem + S_::RED);                         // [BM][us]: the rows' u, behind the exchange of the sums
   uint64_t* rL_s = (uint64_t*)(smem + base_bytes);               // per row: expand factor,
   int32_t* tok_s = (int32_t*)(rL_s + BM);                        // token (-1: past the end),
   int32_t* t_s = tok_s + BM;                                     // adapter (-1: none),
@@ -147,24 +148,27 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   const int li = lane & 15, lg = lane >> 4;
   const bool lora = a.n_adapters > 0 && a.table != nullptr;
   const int b = (int)blockIdx.x - a.prod0, S = a.n_split;        // the producers are workgroups prod0 ..
-  const int64_t u_n = a.T * a.r_stride;                          // u of a projection: [split][T][r_stride], scaled
+  const int64_t u_n = a.T * a.r_stride;                          // u: [projection][split][T][r_stride], scaled
   constexpr int UNITS = 2 * WN * RB;
   // Workgroups through with row tile tm of projection p (bits 16 ..: those that gave up waiting for sums).  Only
   // a consumer knows how many producers the tile has: the one of the first column tile and split counts for
   // MID_JOBS less those, so that the count is the same, consumers + MID_JOBS, for every grouping.
-  // Called by one whole wave, when the workgroup's requests are performed.
+  // Called by one whole wave, when the workgroup's requests are performed; the count's answer is a trip through
+  // the fabric, and what it is needed for can wait.
   auto leave = [&](int p, int tm, int mine) {
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(a.sync + p * a.tiles_m + tm, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return old;
+  };
+  auto left = [&](int p, int tm, int mine, int old) {
     const int p_tiles = (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
     const int64_t m0 = (int64_t)tm * BM;
-    int32_t* done = a.sync + p * a.tiles_m + tm;
-    int old = 0;
-    if (lane == 0) old = __hip_atomic_fetch_add(done, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     old = __builtin_amdgcn_readfirstlane(old) + mine;
     if ((old & 0xffff) != p_tiles * a.ksplit + MID_JOBS) return;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     if (lora) {
       const int64_t rows = a.T - m0 < BM ? a.T - m0 : BM;
-      float* u = a.thin_u + p * (MID_SPLITS * MID_ROWS * 128) + m0 * a.r_stride;
+      float* u = a.thin_u + p * S * u_n + m0 * a.r_stride;
       for (int s = 0; s < S; ++s)
         for (int64_t i = lane; i < rows * a.r_stride / 4; i += 64) store4_agent(u + s * u_n + i * 4, zero);
     }
@@ -172,7 +176,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       float* part = a.partials + ((int64_t)tm * a.tiles_n + a.proj[p].tile0) * (UNITS * 256) * a.ksplit;
       for (int64_t i = lane, n = (int64_t)p_tiles * UNITS * 64 * a.ksplit; i < n; i += 64) store4_agent(part + i * 4, zero);
     }
-    if (lane == 0) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) __hip_atomic_store(a.sync + p * a.tiles_m + tm, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
 
   if (b >= 0 && b < a.n_prod) {
@@ -186,10 +190,10 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     const int64_t r0 = (int64_t)tile * BM + (job.row0 & ~15) + li, last = a.T - 1;
     const int64_t i0 = r0 < last ? r0 : last, i1 = r0 + 16 < last ? r0 + 16 : last;
     const int32_t tok0 = a.perm ? a.perm[i0] : (int32_t)i0, tok1 = a.perm ? a.perm[i1] : (int32_t)i1;
-    shrink_job<3, 2>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, a.thin_u + pp * (MID_SPLITS * MID_ROWS * 128) + job.split * u_n + (int64_t)tile * BM * a.r_stride,
+    shrink_job<3, 2>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, a.thin_u + (pp * S + job.split) * u_n + (int64_t)tile * BM * a.r_stride,
                      a.r_stride, wave, lane);
     __syncthreads();
-    if (wave == 0) leave(pp, tile, 1);
+    if (wave == 0) left(pp, tile, 1, leave(pp, tile, 1));
     return;
   }
 
@@ -204,7 +208,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   const int64_t m0 = (int64_t)tm * BM;
   const int64_t Nout = a.proj[p].Nout, ldb = a.proj[p].ldw;
   const AdapterEntry* table = a.table + a.proj[p].tab0;
-  float* u_p = a.thin_u + p * (MID_SPLITS * MID_ROWS * 128);
+  const float* u_p = a.thin_u + p * S * u_n;
   float* parts = a.partials + (int64_t)(tm * a.tiles_n) * (UNITS * 256) * a.ksplit;    // [tile][unit][split][lane] x 4
   const int steps = (int)((a.Kc + 31) >> 5);
   const bool lead = ks0 == 0 && tn == a.proj[p].tile0;
@@ -283,6 +287,68 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   f32x4 y[NR][2];
   const int cbo = ks0 & 1;                                       // with several splits this wave's own units are its
   const bool own = a.ksplit == 1 || ((g * WN * 2 + wn * 2 + cbo) & (a.ksplit - 1)) == ks0;   // column block cbo, if any
+  // eight ranks of an octet of row block rb in column lane % 16 of column block cb
+  auto factor = [&](int rb, int i, int cb) {
+    const int o = oct_s[rb * oct_max + i], row = o >> 8;
+    const int64_t n = n0 + cb * 16 + li;
+    if (n >= Nout || (a.ksplit > 1 && cb != cbo)) return make_uint4(0, 0, 0, 0);
+    return *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[row] + (o & 255) + n * rank_s[row]);
+  };
+  constexpr bool EARLY = NR == 1;
+  constexpr int PD = EARLY ? 2 : 1;                            // groups of four octets requested ahead
+  uint4 pre[NR][PD][2];
+  uint64_t uw[MID_SPLITS][2];                                    // first reading of the first four values of u this thread fetches
+  const int urow = tid / (a.r_stride >> 2), uq0 = (tid - urow * (a.r_stride >> 2)) * 4;
+  // u and the first octets' factors, a trip through the fabric each: on the way while the sums meet
+  auto request_u = [&]() {
+#pragma unroll
+    for (int q = 0; q < MID_SPLITS; ++q) uw[q][0] = uw[q][1] = 0;
+    if (urow < BM && uq0 < rank_s[urow])
+#pragma unroll
+      for (int q = 0; q < MID_SPLITS; ++q)
+        if (q < S) {
+          const uint64_t* from = (const uint64_t*)(u_p + q * u_n + (m0 + urow) * a.r_stride + uq0);
+          uw[q][0] = __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          uw[q][1] = __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+  };
+  auto request_factors = [&](int j) {
+    const int rb = j * KG + g, cnt = rb < RB ? cnt_s[rb] : 0;
+#pragma unroll
+    for (int d = 0; d < PD; ++d)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        pre[j][d][cb] = make_uint4(0, 0, 0, 0);
+        if (4 * d + lg < cnt) pre[j][d][cb] = factor(rb, 4 * d + lg, cb);
+      }
+  };
+  auto take_u = [&]() {
+    const int uq = a.r_stride >> 2;
+    for (int i = tid, row = urow, q = uq0; i < BM * uq; i += MD_THREADS, row = i / uq, q = (i - row * uq) * 4) {   // (whole waves)
+      const int rank = rank_s[row];
+      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+      bool ok = true;
+      if (q < rank) {
+        ok = i == tid && a.spin_limit > 0;
+#pragma unroll
+        for (int k = 0; k < MID_SPLITS; ++k)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t w = (uint32_t)(uw[k][j >> 1] >> (32 * (j & 1)));
+            ok &= k >= S || w != 0u;
+            v[j] = k == 0 ? __uint_as_float(w) : k < S ? v[j] + __uint_as_float(w) : v[j];
+          }
+        if (!ok) ok = read_u<MID_SPLITS>(u_p + (m0 + row) * a.r_stride + q, u_n, S, a.spin_limit, v);
+      }
+      if (__builtin_expect(__ballot(!ok) != 0, 0))               // (not reached in practice)
+        u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
+      *(f32x4*)(u_s + row * us + q) = v;
+      if (a.u_out && lead && m0 + row < a.T && q < ((rank + 15) & ~15))
+        *(f32x4*)(a.u_out + (m0 + row) * a.r_stride + q) = v;
+    }
+  };
   if (tid == 0) gave_s[0] = 0;
   {
     const int kt_b = ks0 * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;
@@ -416,7 +482,12 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     for (; i0 + 2 * NS <= nt; i0 += NS) MD_ROUND(MD_STEADY);
 #pragma unroll 1
     for (; i0 < nt; i0 += NS) MD_ROUND(MD_ITER);
+    // (the last reads are not used, but until they are there their registers must not look free)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < RB; ++i) if (nt > 0) asm volatile("" : "+v"(xf[i]));
+    if (lora && a.ksplit == 1) request_u();
+    if (EARLY && lora && a.ksplit == 1) request_factors(0);
     __syncthreads();                                             // the ring is free
     // ---- the contraction groups' sums: row block i is finished by group i mod KG
 #pragma unroll
@@ -426,6 +497,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) red[(((i * WN + wn) * 2 + cb) * (KG - 1) + d) * 64 + lane] = acc[i][cb];
       }
+    if (lora && a.ksplit == 1) take_u();
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RB; ++i)
@@ -554,40 +626,18 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     }
   }
 
+  int old = 0, mine = 0;
   if (lora) {
-    // the first octets' factor fragments depend on nothing that has to be waited for
-    uint4 pre[NR][2];
+    if (!EARLY || a.ksplit > 1)                                  // (earlier there are no registers for them)
 #pragma unroll
-    for (int j = 0; j < NR; ++j)
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
-        const int rb = j * KG + g;
-        pre[j][cb] = make_uint4(0, 0, 0, 0);
-        if (rb < RB && lg < cnt_s[rb]) {
-          const int o = oct_s[rb * oct_max + lg];
-          const int64_t n = n0 + cb * 16 + li;
-          if (n < Nout) pre[j][cb] = *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[o >> 8] + (o & 255) + n * rank_s[o >> 8]);
-        }
-      }
-    __syncthreads();                                             // the sums have met: their place is u's now
-    const int uq = a.r_stride >> 2;
-    for (int i = tid; i < BM * uq; i += MD_THREADS) {            // (whole waves)
-      const int row = i / uq, q = (i - row * uq) * 4;
-      const int rank = t_s[row] >= 0 ? rank_s[row] : 0;
-      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-      bool ok = true;
-      if (q < rank) ok = read_u<MID_SPLITS>(u_p + (m0 + row) * a.r_stride + q, u_n, S, a.spin_limit, v);
-      if (__builtin_expect(__ballot(!ok) != 0, 0))               // (not reached in practice)
-        u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
-      *(f32x4*)(u_s + row * us + q) = v;
-      if (a.u_out && lead && m0 + row < a.T && q < ((rank + 15) & ~15))
-        *(f32x4*)(a.u_out + (m0 + row) * a.r_stride + q) = v;
+      for (int j = 0; j < NR; ++j) request_factors(j);
+    if (a.ksplit > 1) {                                          // (u after the sums, which other workgroups wait for)
+      request_u();
+      take_u();
+      __syncthreads();
     }
-    __syncthreads();
-    if (wave == MD_WAVES - 1)
-      leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS - (gave_s[2] + (RB > 4 ? gave_s[3] : 0)) * S : 0));
+    mine = 1 + (gave_s[0] << 16) + (lead ? MID_JOBS - (gave_s[2] + (RB > 4 ? gave_s[3] : 0)) * S : 0);
+    if (wave == MD_WAVES - 1) old = leave(p, tm, mine);
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const int rb = j * KG + g;
@@ -596,11 +646,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       if (cnt >= 0) {
         expand_octets(y[j], pre[j], cnt, lg, t_s[row], u_s + row * us,
                       [&](int i) { const int o = oct_s[rb * oct_max + i]; return t_s[o >> 8] << 8 | (o & 255); },
-                      [&](int i, int cb) {
-                        const int o = oct_s[rb * oct_max + i], orow = o >> 8;
-                        const int64_t n = n0 + cb * 16 + li;
-                        return n < Nout ? *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[orow] + (o & 255) + n * rank_s[orow]) : make_uint4(0, 0, 0, 0);
-                      });
+                      [&](int i, int cb) { return factor(rb, i, cb); });
       } else if (t_s[row] >= 0) {
         // ranks that are no multiples of 8, or factors stored rank-major: plain fp32 expand of this lane's row
         const int rank = rank_s[row];
@@ -620,12 +666,12 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     }
   } else if (a.ksplit > 1) {
     __syncthreads();
-    if (wave == MD_WAVES - 1) leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS : 0));
+    mine = 1 + (gave_s[0] << 16) + (lead ? MID_JOBS : 0);
+    if (wave == MD_WAVES - 1) old = leave(p, tm, mine);
   }
-  if (!own) return;
 #pragma unroll
   for (int j = 0; j < NR; ++j) {
-    if (j * KG + g >= RB) break;
+    if (j * KG + g >= RB || !own) break;
     const int32_t otok = tok_s[(j * KG + g) * 16 + li];
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
@@ -641,12 +687,13 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       }
     }
   }
+  if (mine && wave == MD_WAVES - 1) left(p, tm, mine, old);
 }
 
 template <int RB, int WN>
 static hipError_t launch_mid(const GemmArgs& a, int cu_count, hipStream_t stream) {
   constexpr int BM = 16 * RB;
-  const size_t u_bytes = (size_t)BM * (a.r_stride + 4) * sizeof(float), base = MidShape<RB, WN>::BASE;
+  const size_t u_bytes = MidShape<RB, WN>::RED + (size_t)BM * (a.r_stride + 4) * sizeof(float), base = MidShape<RB, WN>::NS * MidShape<RB, WN>::SLOT;
   const size_t lds = (base > u_bytes ? base : u_bytes) + BM * 20 + RB * 4 + 16 + (size_t)RB * 2 * a.r_stride * sizeof(uint16_t);
   static std::atomic<uint64_t> done_dev{0};
   int dev = 0;
@@ -671,22 +718,39 @@ static hipError_t launch_mid(const GemmArgs& a, int cu_count, hipStream_t stream
   return hipGetLastError();
 }
 
+// Pieces of a producer's contraction.  A compute unit that has a producer besides its consumer is behind the
+// others by what the producer reads (256 rows, 4096 x 4096: first tile after 9 us instead of 4 with two pieces,
+// 6 with four), and a last wave of workgroups costs more than that.
+//   Whole (up to 16 steps a wave), where every workgroup has a unit of its own: 157 rows 22.7 -> 19.9 us.
+//   Else four pieces, if all workgroups are on the chip at once: 256 rows 23.8 -> 22.4, 157 rows 14336 x 4096
+//   51 -> 43; two, if only those are (q/k/v of 256 rows: four pieces 47 us, two 33).
+//   Else as few as steps allow (512 rows, 5120 x 5120, 64 adapters: 75 -> 68).
+// Few steps are not cut: a value of u is read once for each piece.
+static int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t consumers, int64_t jobs, int cu_count) {
+  const int64_t steps = ((Kc + 31) / 32 + MD_WAVES - 1) / MD_WAVES;      // 32-deep steps of a wave
+  if (steps <= 8 || (steps <= 16 && consumers + jobs <= cu_count)) return 1;
+  int s = MID_SPLITS;
+  while (s > 1 && (consumers + jobs * s > 2 * cu_count || u_floats * s > MID_U_FLOATS)) s /= 2;
+  if (s == 1 && steps > 24 && 2 * u_floats <= MID_U_FLOATS) s = 2;
+  return s;
+}
+
 hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream_t stream) {
   // How far apart neighbouring column tiles start (see MD_T): eight of them over the whole contraction, as long
   // as the part of x between the first and the last stays in an XCD's L2 (256 rows, 14336 x 4096 in one
   // split: 81 us over 1.4 MB of x, 91 over all of it).
   const int64_t kt = 32 * (MD_WAVES / p.wn), nt = ((a.Kc + kt - 1) / kt + p.ksplit - 1) / p.ksplit, window = (1400 << 10) / (a.T * kt * 2);
   a.rot = (int)((nt < window ? nt : window) / 8);
-  // a producer's contraction in two pieces unless a wave has few steps of it
-  a.n_split = (a.Kc + 31) / 32 <= 8 * MD_WAVES ? 1 : MID_SPLITS;
   a.ksplit = p.ksplit;
   a.tiles_m = p.tiles_m;
-  a.n_prod = (a.n_proj * a.proj_jobs * a.n_split + 7) / 8 * 8;
   a.tiles_n = 0;
   for (int q = 0; q < a.n_proj; ++q) {
     a.proj[q].tile0 = a.tiles_n;
     a.tiles_n += (int)((a.proj[q].Nout + 32 * p.wn - 1) / (32 * p.wn));
   }
+  const int64_t consumers = (int64_t)p.tiles_m * a.tiles_n * p.ksplit, jobs = (int64_t)a.n_proj * a.proj_jobs;
+  a.n_split = mid_u_splits(a.Kc, a.T * a.r_stride * a.n_proj, consumers, jobs, cu_count);
+  a.n_prod = (int)((jobs * a.n_split + 7) / 8 * 8);
   if (p.wn == 4) return p.rb == 4 ? launch_mid<4, 4>(a, cu_count, stream) : launch_mid<5, 4>(a, cu_count, stream);
   return p.rb == 4 ? launch_mid<4, 2>(a, cu_count, stream) : launch_mid<5, 2>(a, cu_count, stream);
 }

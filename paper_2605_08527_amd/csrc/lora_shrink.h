@@ -28,7 +28,13 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
   const int per = (part + WAVES - 1) / WAVES;
   const int s0 = k0 + wave * per, s1 = s0 + per < k1 ? s0 + per : k1;
   const int blk = j.row0 >> 4;
-  const bool two = (j.row1 - 1) >> 4 > blk, row_in = j.q0 + li < j.rank;
+  const bool row_in = j.q0 + li < j.rank;
+  const bool two = (j.row1 - 1) >> 4 > blk;
+  // (rows of others read the job's first row in the block, in a tile of many adapters most of it, and are not stored)
+  const int r0 = blk * 16 + li, r1 = r0 + 16;
+  const int32_t first0 = __shfl(tok0, j.row0 & 15), first1 = __shfl(tok1, 0);
+  if (r0 < j.row0 || r0 >= j.row1) tok0 = first0;
+  if (r1 >= j.row1) tok1 = first1;
   const bf16_t* lrow = j.L + (int64_t)(row_in ? j.q0 + li : 0) * Kc;
   const bf16_t* xrow[2] = {X + (int64_t)tok0 * lda, X + (int64_t)tok1 * lda};
   f32x4 acc[NB];
@@ -39,12 +45,13 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
 #pragma unroll
     for (int i = 0; i < UP; ++i) {
       const int64_t k = (int64_t)(s + i) * 32 + 8 * lg;
-      const bool in = s + i < s1 && k < Kc;
 #pragma unroll
       for (int b = 0; b <= NB; ++b) f[i][b].u = make_uint4(0, 0, 0, 0);
-      if (in && row_in) f[i][NB].u = *(const uint4*)(lrow + k);
-      if (in) f[i][0].u = *(const uint4*)(xrow[0] + k);
-      if (NB > 1 && in && two) f[i][NB - 1].u = *(const uint4*)(xrow[1] + k);
+      if (s + i < s1 && k < Kc) {
+        if (row_in) f[i][NB].u = *(const uint4*)(lrow + k);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) if (b == 0 || two) f[i][b].u = *(const uint4*)(xrow[b] + k);
+      }
     }
   };
   auto multiply = [&](Frag (&f)[UP][NB + 1]) {

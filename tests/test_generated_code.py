@@ -93,6 +93,44 @@ def early_moves(blocks):
     return found
 
 
+def overwritten_reads(blocks):
+    """Writes into a register that an inline-assembly LDS read is still to fill: a read whose value nobody uses
+    looks done to the compiler as soon as it is issued, and its registers free."""
+    order = list(blocks)
+    after = dict(zip(order, order[1:]))
+    seen, work, found = set(), [("", ())], []
+
+    def reach(label, pending):
+        if label is not None and (label, pending) not in seen:
+            seen.add((label, pending))
+            work.append((label, pending))
+
+    while work:
+        label, pending = work.pop()                  # registers of the LDS requests under way, oldest first
+        for s, op, operands, asm in blocks[label]:
+            if op == "s_waitcnt":
+                m = re.search(r"lgkmcnt\((\d+)\)", s)
+                if m:
+                    pending = pending[max(0, len(pending) - int(m.group(1))):]
+                continue
+            if op == "s_branch":
+                reach(operands[0], pending)
+                break
+            if op.startswith("s_cbranch"):
+                reach(operands[0], pending)
+            if op == "s_endpgm":
+                break
+            read = asm and op.startswith("ds_read")
+            if not read and "store" not in op and not op.startswith(("ds_write", "s_")):
+                if any(r in p for r in _registers(operands[0]) for p in pending):
+                    found.append(s)
+            if op.startswith("ds_"):
+                pending = (pending + (tuple(_registers(operands[0])) if read else (),))[-16:]
+        else:
+            reach(after.get(label), pending)
+    return found
+
+
 @pytest.fixture(scope="module")
 def listings(tmp_path_factory):
     out = tmp_path_factory.mktemp("listings")
@@ -111,6 +149,31 @@ def test_no_move_of_a_load_before_a_wait(listings, f):
         seen += 1
         assert not early_moves(blocks), name
     assert seen > 0
+
+
+@pytest.mark.parametrize("f", ["gemm_mid", "gemm_decode"])
+def test_no_write_over_a_pending_lds_read(listings, f):
+    for name, blocks in _functions(listings[f]):
+        assert not overwritten_reads(blocks), name
+
+
+def test_overwritten_read_is_seen():
+    text = """_Zk:
+\t;;#ASMSTART
+\tds_read_b128 v[4:7], v0
+\t;;#ASMEND
+\t;;#ASMSTART
+\tds_read_b128 v[8:11], v0
+\t;;#ASMEND
+%s
+\tv_add_u32_e32 v6, v1, v2
+.LBB0_1:
+\ts_endpgm
+.Lfunc_end0:
+"""
+    for wait, seen in {"": 1, "\ts_waitcnt lgkmcnt(1)": 0, "\ts_waitcnt lgkmcnt(2)": 1, "\ts_waitcnt vmcnt(0)": 1}.items():
+        (_, blocks), = _functions(text % wait)
+        assert len(overwritten_reads(blocks)) == seen, wait
 
 
 def test_early_move_is_seen():

@@ -180,6 +180,17 @@ def test_some_rows_short_last_split(oracle, T, K, N):
     _check_layer(oracle, w, bwd=False, tag="short last split", table="table+packed")
 
 
+# u in one, two and four pieces of the contraction (the last of them shorter), rows of several adapters in a
+# pair of row blocks, rank tiles that are not whole.
+@pytest.mark.parametrize("T,K,N,ranks", [(66, 4096, 1032, [16, 24]), (300, 4616, 1032, [32] * 64), (130, 4616, 520, [40, 8, 16] * 4)])
+def test_some_rows_u_pieces(oracle, T, K, N, ranks):
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    w = wl.make_layer(T + N, T, K, N, ranks, [0.5 + t % 3 for t in range(len(ranks))], ids, dtype="bf16", layout=wl.TORCH)
+    for rep in range(2):
+        _check_layer(oracle, w, bwd=False, tag="u in pieces", table="table+packed")
+
+
 # A workgroup that gives up waiting computes what it waited for in the same order of sums: no bit depends on
 # which workgroups were on the chip.  (Limit 0: every wait is given up at once.)
 @pytest.mark.parametrize("layout", [0, 1])
