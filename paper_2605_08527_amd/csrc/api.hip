@@ -708,12 +708,14 @@ struct Bank {
   int n_ext = 0;                           // this call's extended columns (sum of its ranks)
   bool mult8 = true;
   bool in_ws = false;                      // tables are a per-call copy in the workspace
+  SideWork side;                           // side.n_inl > 0: that copy is still to be written (the next shrink's launch can)
 };
 
 // Resolve a descriptor's tables.  Without a table object the entries are written into the
 // workspace slice `ws_tab` by a small kernel launch on the caller's stream (payload in the kernel
-// arguments); with one, nothing is enqueued.
-static int resolve_bank(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* ws_tab, size_t ws_tab_bytes,
+// arguments); with one, nothing is enqueued.  put_off: the entries of few adapters stay in b->side, for
+// a shrink's launch or flush_bank.
+static int resolve_bank(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* ws_tab, size_t ws_tab_bytes, bool put_off,
                         hipStream_t st, Bank* b) {
   *b = Bank();
   if (d->n_adapters == 0) return MARLAAS_OK;
@@ -741,8 +743,34 @@ static int resolve_bank(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* ws_t
   for (int t = 0; t < d->n_adapters; ++t) {
     host[t].A = d->A[t]; host[t].B = d->B[t]; host[t].rank = d->ranks[t]; host[t].scale = d->scales[t];
   }
+  if (put_off && d->n_adapters <= SIDE_INLINE) {
+    b->side.n_inl = d->n_adapters;
+    b->side.entries_out = b->all.entries;
+    std::copy(host.begin(), host.end(), b->side.entry);
+    return MARLAAS_OK;
+  }
   HIP_TRY(ctx, enqueue_write_entries(b->all, 0, d->n_adapters, host.data(), st));
   return MARLAAS_OK;
+}
+
+static int flush_bank(marlaas_ctx* ctx, Bank* b, hipStream_t st) {
+  const int n = b->side.n_inl;
+  if (n == 0) return MARLAAS_OK;
+  b->side.n_inl = 0;
+  HIP_TRY(ctx, enqueue_write_entries(b->all, 0, n, b->side.entry, st));
+  if (b->side.grads_out) HIP_TRY(ctx, enqueue_write_grads(b->all, 0, n, b->side.grad, st));
+  return MARLAAS_OK;
+}
+
+// Has the shrink's launch write the lists of the large-batch GEMM behind it, where that is the kernel, the lists
+// have room and every 16-byte piece of a factor row stays inside the row.
+static void lists_in_shrink(SideWork* side, LoraDma* dma, int form, bool mult8, void* scratch, size_t bytes, int64_t T, int64_t Kc, int64_t Nout, int need,
+                            bool packed, size_t partial_bytes, bool has_chunks) {
+  if (!scratch || bytes < lora_tiles_bytes(T) || (form == FORM_NT && !mult8)) return;
+  const int rows = gemm_tile_rows(T, Kc, Nout, need, packed, partial_bytes, has_chunks);
+  if (rows == 0) return;
+  side->lists = (int32_t*)scratch; side->list_rows = rows; side->list_tiles = (int)((T + rows - 1) / rows);
+  dma->tiles = side->lists; dma->list_rows = rows;
 }
 
 static bool inline_f32(const marlaas_lora_desc* d) { return d->in_dtype == MARLAAS_F32 && !d->table && d->n_adapters <= F32_INLINE; }
@@ -945,7 +973,8 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
   float* part = (have_ws && p.part_bytes) ? (float*)((char*)ws + p.part_off) : nullptr;
   Bank bank;
   // (small fp32 calls carry their pointer lists in the kernel arguments)
-  if (lora && !inline_f32(d) && (rc = resolve_bank(ctx, d, have_ws ? (char*)ws + p.tab_off : nullptr, p.tab_bytes, st, &bank)) != MARLAAS_OK) return rc;
+  const bool put_off = d->in_dtype == MARLAAS_BF16 && !d->W_packed_fwd;
+  if (lora && !inline_f32(d) && (rc = resolve_bank(ctx, d, have_ws ? (char*)ws + p.tab_off : nullptr, p.tab_bytes, put_off, st, &bank)) != MARLAAS_OK) return rc;
   const AdapterEntry* table = bank.entries;
   const int32_t* perm = map->identity ? nullptr : map->perm_dev;
   // forward contracts over d_in: math W[d_in,d_out] is [contraction, output] (NN), torch is NT;
@@ -973,22 +1002,23 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
       fused = gemm_can_fuse_shrink(form, d->T, d->d_in, d->d_out, need, bank.mult8, use_packed && d->W_packed_fwd, p.part_bytes);
       if (fused) {
         fuse.need = need;
+        if ((rc = flush_bank(ctx, &bank, st)) != MARLAAS_OK) return rc;
         if ((rc = bank_fuse(ctx, bank, d->n_adapters, st, &fuse)) != MARLAAS_OK) return rc;
         fuse.u_out = u;
       }
     }
     bool have_u2 = false;
     bf16_t* u2 = (have_ws && p.uv2_bytes) ? (bf16_t*)((char*)ws + p.u2_off) : nullptr;
+    LoraDma dma;
+    dma.zero_line = (const bf16_t*)ctx->zero_dev;
+    if (lora && !fused && u2)
+      lists_in_shrink(&bank.side, &dma, form, bank.mult8, p.lt_bytes ? (char*)ws + p.lt_off : nullptr, p.lt_bytes, d->T, d->d_in, d->d_out, need,
+                      use_packed && d->W_packed_fwd, part ? p.part_bytes : 0, map->chunks_dev != nullptr);
     if (lora && !fused)
       PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_bf16((const bf16_t*)d->x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters,
                                       map->max_seg, table, 0, form, u, rs, map->T_lora, part, part ? p.part_bytes : 0, u2,
-                                      &have_u2, (const bf16_t*)ctx->zero_dev, bank.mult8, st));
-    LoraDma dma;
-    dma.zero_line = (const bf16_t*)ctx->zero_dev;
-    if (have_u2 && have_ws && p.lt_bytes) {
-      dma.u2 = u2; dma.tiles = (int32_t*)((char*)ws + p.lt_off); dma.tiles_bytes = p.lt_bytes;
-      dma.ranks_mult8 = bank.mult8;
-    }
+                                      &have_u2, (const bf16_t*)ctx->zero_dev, bank.mult8, bank.side, st));
+    if (have_u2) dma.u2 = u2;
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16((const bf16_t*)d->x, d->ldx, (const bf16_t*)d->W, d->ldw, form, d->T, d->d_in,
                                   d->d_out, perm, map->seg_off_dev, d->n_adapters, table, 1, lora ? u : nullptr,
                                   rs, y, ldy, out_f32, part, part ? p.part_bytes : 0, map->chunks_dev, map->n_chunks,
@@ -1237,7 +1267,8 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
   const bool need_u = lora && want_grads && !u;
   if (need_u) u = (float*)((char*)ctx->ws + p.u_off);
   Bank bank;
-  if (d->n_adapters > 0 && !inline_f32(d) && (rc = resolve_bank(ctx, d, (char*)ctx->ws + p.tab_off, p.tab_bytes, st, &bank)) != MARLAAS_OK) return rc;
+  const bool put_off = d->in_dtype == MARLAAS_BF16 && !d->W_packed_bwd;
+  if (d->n_adapters > 0 && !inline_f32(d) && (rc = resolve_bank(ctx, d, (char*)ctx->ws + p.tab_off, p.tab_bytes, put_off, st, &bank)) != MARLAAS_OK) return rc;
   const AdapterEntry* table = bank.entries;
   const GradEntry* grads = bank.grads;
   if (want_grads && !opt && !grads_in_table && d->n_adapters > 0) {
@@ -1248,7 +1279,12 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
     if (bank.in_ws) {
       std::vector<GradEntry> host((size_t)d->n_adapters);
       for (int t = 0; t < d->n_adapters; ++t) { host[t].dA = (float*)dA[t]; host[t].dB = (float*)dB[t]; }
-      HIP_TRY(ctx, enqueue_write_grads(bank.all, 0, d->n_adapters, host.data(), st));
+      if (bank.side.n_inl) {
+        bank.side.grads_out = bank.all.grads;
+        std::copy(host.begin(), host.end(), bank.side.grad);
+      } else {
+        HIP_TRY(ctx, enqueue_write_grads(bank.all, 0, d->n_adapters, host.data(), st));
+      }
     }
   }
   const int32_t* perm = map->identity ? nullptr : map->perm_dev;
@@ -1267,9 +1303,11 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
   if (d->in_dtype == MARLAAS_BF16) {
     const bf16_t* x = (const bf16_t*)d->x;
     const bf16_t* dy = (const bf16_t*)dY;
-    if (need_u)
+    if (need_u) {
       PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_bf16(x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
-                                      table, 0, fform, u, rs, map->T_lora, part, part ? p.part_bytes : 0, nullptr, nullptr, (const bf16_t*)ctx->zero_dev, bank.mult8, st));
+                                      table, 0, fform, u, rs, map->T_lora, part, part ? p.part_bytes : 0, nullptr, nullptr, (const bf16_t*)ctx->zero_dev, bank.mult8, bank.side, st));
+      bank.side.n_inl = 0;
+    }
     // small batches: the dX GEMM computes v itself (and leaves it in `v` for the dA reduction)
     GemmFuse fuse;
     bool fused = false;
@@ -1286,21 +1324,25 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
       fused = gemm_can_fuse_shrink(bform, d->T, d->d_out, d->d_in, need, bank.mult8, use_packed && d->W_packed_bwd, p.part_bytes);
       if (fused) {
         fuse.need = need;
+        if ((rc = flush_bank(ctx, &bank, st)) != MARLAAS_OK) return rc;
         if ((rc = bank_fuse(ctx, bank, d->n_adapters, st, &fuse)) != MARLAAS_OK) return rc;
         fuse.u_out = v;
       }
     }
     bool have_v2 = false;
     bf16_t* v2 = (have_ws && p.uv2_bytes && dX) ? (bf16_t*)((char*)ctx->ws + p.v2_off) : nullptr;
-    if (lora && (dX || want_grads) && !fused && !done)
-      PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_bf16(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
-                                      table, 1, bform, v, rs, map->T_lora, part, part ? p.part_bytes : 0, v2, &have_v2, (const bf16_t*)ctx->zero_dev, bank.mult8, st));
     LoraDma dma;
     dma.zero_line = (const bf16_t*)ctx->zero_dev;
-    if (have_v2 && p.lt_bytes) {
-      dma.u2 = v2; dma.tiles = (int32_t*)((char*)ctx->ws + p.lt_off); dma.tiles_bytes = p.lt_bytes;
-      dma.ranks_mult8 = bank.mult8;
+    if (lora && (dX || want_grads) && !fused && !done) {
+      if (v2)
+        lists_in_shrink(&bank.side, &dma, bform, bank.mult8, p.lt_bytes ? (char*)ctx->ws + p.lt_off : nullptr, p.lt_bytes, d->T, d->d_out, d->d_in, need,
+                        use_packed && d->W_packed_bwd, part ? p.part_bytes : 0, map->chunks_dev != nullptr);
+      PROFILED(ctx, MARLAAS_KERNEL_SHRINK, st, launch_shrink_bf16(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
+                                      table, 1, bform, v, rs, map->T_lora, part, part ? p.part_bytes : 0, v2, &have_v2, (const bf16_t*)ctx->zero_dev, bank.mult8, bank.side, st));
+      bank.side.n_inl = 0;
     }
+    if (have_v2) dma.u2 = v2;
+    if ((rc = flush_bank(ctx, &bank, st)) != MARLAAS_OK) return rc;
     if (dX && d->T > 0 && !done)
       PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16(dy, lddy, (const bf16_t*)d->W, d->ldw, bform, d->T, d->d_out, d->d_in, perm,
                                     map->seg_off_dev, d->n_adapters, table, 0, lora ? v : nullptr, rs, dX, lddx,

@@ -150,6 +150,18 @@ int64_t segmap_chunk_count(const int32_t* seg_off, int n);
 // Upper bound of that count for any map of T tokens and n adapters.
 int64_t segmap_chunk_bound(int64_t T, int n);
 
+// What a shrink's launch does besides, in workgroups behind its own: the row tiles' lists for the large-batch
+// GEMM behind it, and the tables of a call that brings pointer lists of few adapters, which then travel in
+// the kernel arguments (the shrink reads them there).  A launch of its own takes 5 us for either.
+static constexpr int SIDE_INLINE = 16;
+struct SideWork {
+  int32_t* lists = nullptr; int list_rows = 0, list_tiles = 0;     // scratch (lora_tiles_bytes), rows of a tile, tiles
+  int n_inl = 0;                                                   // entries below (0: none)
+  AdapterEntry* entries_out = nullptr; GradEntry* grads_out = nullptr;   // where they go (grads_out may be null)
+  AdapterEntry entry[SIDE_INLINE];
+  GradEntry grad[SIDE_INLINE];
+};
+
 // u[m, 0..r_stride) = scale_t * sum_c X[perm[m], c] * L_t(c, q), grouped order m.
 // which = 0 uses AdapterEntry::A as L_t, 1 uses ::B.  lora_form: FORM_NN when
 // L_t is stored [C, r_t] (q contiguous), FORM_NT when stored [r_t, C].
@@ -157,7 +169,7 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
                               const int32_t* seg_off, int n_adapters, int max_seg,
                               const AdapterEntry* table, int which, int lora_form, float* u,
                               int r_stride, int64_t T_lora, float* partials, size_t partial_bytes,
-                              bf16_t* u2, bool* wrote_u2, const bf16_t* zero_line, bool ranks_mult8, hipStream_t stream);
+                              bf16_t* u2, bool* wrote_u2, const bf16_t* zero_line, bool ranks_mult8, const SideWork& side, hipStream_t stream);
 // scratch for the sums of a shrink whose contraction is split (0: it is not)
 size_t shrink_partial_bytes(int64_t C, int64_t T_lora, int n_adapters, int r_stride);
 
@@ -195,16 +207,17 @@ static constexpr int MID_POLLS = 256;
 struct MidPlan { int rb = 0, wn = 2, ksplit = 1, tiles_m = 0; double us = 0.0; };     // rb = rows / 16; 0: none
 
 // What lets the large-batch GEMM fetch the expand's operands by DMA: u (or v) as a two-term bf16
-// split written by the shrink, scratch for the row tiles' lists of extra contraction tiles
-// (lora_tiles_bytes(T) bytes), and whether every rank is a multiple of 8; zero_line: 16 zero bytes in
-// device memory (always given).
+// split and the row tiles' lists of extra contraction tiles, both written by the shrink's launch
+// (list_rows: rows of a tile, 0: no lists); zero_line: 16 zero bytes in device memory (always given).
 struct LoraDma {
   const bf16_t* u2 = nullptr;
-  int32_t* tiles = nullptr; size_t tiles_bytes = 0;
+  const int32_t* tiles = nullptr; int list_rows = 0;
   const bf16_t* zero_line = nullptr;
-  bool ranks_mult8 = false;
 };
 size_t lora_tiles_bytes(int64_t T);
+// Rows of the large-batch GEMM's tiles for a call that launch_gemm_bf16 gets with these sizes and no fused
+// shrink; 0: another kernel runs.
+int gemm_tile_rows(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, size_t partial_bytes, bool has_chunks);
 
 struct GemmFuse {
   const ExtCol* cols;      // [n_ext] device

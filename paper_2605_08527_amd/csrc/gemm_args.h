@@ -88,7 +88,7 @@ struct WidePlan {
   double us = 0.0;                   // estimated run time
 };
 WidePlan wide_plan(int64_t T, int64_t Kc, int64_t Nout, size_t max_bytes);    // (of partial sums; 0: nothing is split)
-hipError_t launch_gemm_wide(WideArgs a, const WidePlan& p, int form, int lform, int out_is_f32, LoraTile* lists, hipStream_t stream);
+hipError_t launch_gemm_wide(WideArgs a, const WidePlan& p, int form, int lform, int out_is_f32, hipStream_t stream);
 // Tile t in walking order -> its column tile (and row tile *tm): groups of 2048 rows share their column tiles.
 __host__ __device__ inline int wide_tile(int t, int mt, int tiles_m, int tiles_n, int* tm) {
   const int GM = 64 / mt;

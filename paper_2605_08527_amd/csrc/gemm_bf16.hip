@@ -838,6 +838,22 @@ static GemmPlan gemm_plan(int64_t T, int64_t Kc, int64_t Nout, int need, bool pa
   return best;
 }
 
+// The plan of a call (the 128 x 128 kernels need the map's row chunks).
+static GemmPlan call_plan(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, size_t max_bytes, bool has_chunks) {
+  GemmPlan p = gemm_plan(T, Kc, Nout, need, packed, max_bytes);
+  if (!p.wide && !has_chunks) {
+    p.wide = true;
+    p.w = wide_plan(T, Kc, Nout, max_bytes);
+  }
+  return p;
+}
+
+int gemm_tile_rows(int64_t T, int64_t Kc, int64_t Nout, int need, bool packed, size_t partial_bytes, bool has_chunks) {
+  if (T <= 0 || Nout <= 0) return 0;
+  const GemmPlan p = call_plan(T, Kc, Nout, need, packed, partial_bytes, has_chunks);
+  return p.wide ? 32 * p.w.mt : 0;
+}
+
 int gemm_ext_room(int64_t Nout) { return (int)((Nout + SK_BN - 1) / SK_BN) * SK_BX; }
 
 static int ext_carried_at_most(int64_t Nout, int n_ext) { return n_ext < gemm_ext_room(Nout) ? n_ext : gemm_ext_room(Nout); }
@@ -916,25 +932,20 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
   if (ldb > (1 << 22)) return hipErrorInvalidValue;      // 32-bit byte offsets inside a weight tile
   const bool packed = Bpacked != nullptr && use_packed;
   if (partials == nullptr) partial_bytes = 0;
-  GemmPlan p = gemm_plan(T, Kc, Nout, fuse ? fuse->need : n_adapters > 0 ? need_unfused : 0, packed, partial_bytes);
+  GemmPlan p = call_plan(T, Kc, Nout, fuse ? fuse->need : n_adapters > 0 ? need_unfused : 0, packed, partial_bytes, chunks != nullptr);
   // the caller skipped the shrink: the conditions of gemm_can_fuse_shrink() must hold
   if (fuse && (!gemm_can_fuse_shrink(form, T, Kc, Nout, fuse->need, fuse->ranks_mult8, packed, partial_bytes) || chunks == nullptr))
     return hipErrorInvalidValue;
-  if (!p.wide && chunks == nullptr) {
-    p.wide = true;
-    p.w = wide_plan(T, Kc, Nout, partial_bytes);
-  }
   if (p.wide) {
     WideArgs w;
     w.A = Aop; w.lda = lda; w.B = Bop; w.ldb = ldb; w.T = T; w.Kc = Kc; w.Nout = Nout;
     w.perm = perm; w.seg_off = seg_off; w.n_adapters = n_adapters; w.table = table; w.which = which;
     w.U = U; w.r_stride = r_stride; w.U2 = nullptr; w.lora_tiles = nullptr; w.zero_line = dma->zero_line;
     w.out = out; w.ldo = ldo; w.partials = partials;
-    // the expand's operands by DMA when the shrink left u as a bf16 split, the lists have room, and
-    // every 16-byte piece of a factor row stays inside the row
+    // the expand's operands by DMA when the shrink's launch left u as a bf16 split and the lists
     w.lora = n_adapters > 0 && U != nullptr ? WIDE_LORA_STAGED : WIDE_LORA_NONE;
-    if (w.lora && dma->u2 && dma->tiles && (form == FORM_NN || dma->ranks_mult8) && dma->tiles_bytes >= lora_tiles_bytes(T)) {
-      w.U2 = dma->u2; w.lora = WIDE_LORA_LISTS;
+    if (w.lora && dma->u2 && dma->tiles && dma->list_rows == 32 * p.w.mt) {
+      w.U2 = dma->u2; w.lora_tiles = (const LoraTile*)dma->tiles; w.lora = WIDE_LORA_LISTS;
     }
     int wform = form;
     if (form == FORM_NN && Bt_kept != nullptr) {
@@ -947,7 +958,7 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
       if (e != hipSuccess) return e;
       w.B = wt_scratch; w.ldb = Kc; wform = FORM_NT;
     }
-    return launch_gemm_wide(w, p.w, wform, form, out_is_f32, (LoraTile*)dma->tiles, stream);
+    return launch_gemm_wide(w, p.w, wform, form, out_is_f32, stream);
   }
   GemmArgs a;
   a.Aop = Aop; a.lda = lda; a.Bop = Bop; a.ldb = ldb; a.T = T; a.Kc = Kc; a.Nout = Nout;

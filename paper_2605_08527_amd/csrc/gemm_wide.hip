@@ -639,53 +639,6 @@ __global__ __launch_bounds__(W_THREADS) void wide_finish_kernel(WideArgs a, int 
   }
 }
 
-// The row tiles' lists of extra contraction tiles: one wave per row tile, a lane per adapter.  The
-// rows are grouped by adapter, so the segments that intersect a tile belong to consecutive adapters;
-// each is cut into 64-wide pieces of its 2 r_pad extra contraction values.  Record 0 holds the count
-// (-1: more than the list holds).
-__global__ __launch_bounds__(64) void lora_tile_list_kernel(const int32_t* __restrict__ seg_off, int n_adapters,
-                                                            const AdapterEntry* __restrict__ table, int which, int rows,
-                                                            LoraTile* __restrict__ out) {
-  const int lane = threadIdx.x;
-  LoraTile* o = out + (int64_t)blockIdx.x * (LT_MAX + 1);
-  const int64_t m0 = (int64_t)blockIdx.x * rows;
-  const int64_t T_lora = seg_off[n_adapters];
-  const int64_t m_end = m0 + rows < T_lora ? m0 + rows : T_lora;
-  int cnt = 0;
-  if (m0 < m_end) {
-    for (int t0 = segment_of(seg_off, n_adapters, (int)m0); t0 < n_adapters; t0 += 64) {
-      const int t = t0 + lane;
-      int64_t lo = 0, hi = 0;
-      int pieces = 0;
-      AdapterEntry e;
-      e.rank = 0;
-      if (t < n_adapters) {
-        lo = seg_off[t]; hi = seg_off[t + 1];
-        if (lo < m0) lo = m0;
-        if (hi > m_end) hi = m_end;
-        e = table[t];
-        if (hi > lo) pieces = (2 * ((e.rank + 15) & ~15) + 63) / 64;
-      }
-      int inc = pieces;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
-      for (int p = 0, at = cnt + inc - pieces; p < pieces && at < LT_MAX; ++p, ++at) {
-        LoraTile r;
-        r.L = (uint64_t)(uintptr_t)(which ? e.B : e.A);
-        r.lo = (int32_t)lo; r.hi = (int32_t)hi; r.kc = p * 64; r.rank = e.rank; r.pad[0] = r.pad[1] = 0;
-        o[1 + at] = r;
-      }
-      cnt += __shfl(inc, 63);
-      if (__ballot(t < n_adapters && (int64_t)seg_off[t + 1] < m_end) != ~0ull) break;   // the tile ends inside these
-    }
-  }
-  if (lane == 0) {
-    LoraTile r;
-    r.L = 0; r.lo = cnt > LT_MAX ? -1 : cnt; r.hi = r.kc = r.rank = 0; r.pad[0] = r.pad[1] = 0;
-    o[0] = r;
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Plan: the tile height and the split of the last round.  256 workgroups take the tiles in rounds;
 // tiles that do not fill the last round are cut along the contraction into as many pieces as keep
@@ -749,16 +702,9 @@ static hipError_t launch_wide_mt(const WideArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_wide(WideArgs a, const WidePlan& p, int form, int lform, int out_is_f32, LoraTile* lists, hipStream_t stream) {
+hipError_t launch_gemm_wide(WideArgs a, const WidePlan& p, int form, int lform, int out_is_f32, hipStream_t stream) {
   a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.rounds = p.rounds;
   a.tail_tiles = p.tail_tiles; a.tail_split = p.tail_split; a.tail_kchunk = p.tail_kchunk;
-  if (a.lora == WIDE_LORA_LISTS) {
-    hipLaunchKernelGGL(lora_tile_list_kernel, dim3(p.tiles_m), dim3(64), 0, stream, a.seg_off, a.n_adapters, a.table, a.which,
-                       32 * p.mt, lists);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    a.lora_tiles = lists;
-  }
   hipError_t e;
 #define W_PICK2(MT_, F_, L_) (out_is_f32 ? launch_wide_mt<MT_, F_, true, L_>(a, stream) : launch_wide_mt<MT_, F_, false, L_>(a, stream))
 #define W_PICK(MT_) (form == FORM_NN ? W_PICK2(MT_, FORM_NN, FORM_NN) : lform == FORM_NN ? W_PICK2(MT_, FORM_NT, FORM_NN) : W_PICK2(MT_, FORM_NT, FORM_NT))

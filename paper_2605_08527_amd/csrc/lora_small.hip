@@ -4,7 +4,7 @@
 // LoRA parameters are trained (paper Sec. 4.2), so these are the only weight
 // gradients of the layer.  Both kernels read their big operand (x or dY) once
 // and are bound by HBM; the small operand stays in LDS.
-#include "gemm_args.h"
+#include "lora_lists.h"
 
 #include <atomic>
 
@@ -43,7 +43,31 @@ struct ShrinkArgs {
   // of its adapter in bf16, u_hi = bf16(u), u_lo = bf16(u - u_hi); row stride 2 * r_stride
   bf16_t* u2;
   const bf16_t* zero_line;  // 16 readable zero bytes (what masked DMA lanes of shrink_ring_kernel fetch)
+  int n_adapters;           // workgroups with blockIdx.y from here on do the side work
+  SideWork side;
 };
+
+__device__ __forceinline__ AdapterEntry entry_of(const ShrinkArgs& a, int t) { return a.side.n_inl ? a.side.entry[t] : a.table[t]; }
+
+// A workgroup's share of the side work: a row tile's list for each of its waves, and the first one's copy of
+// the tables; false: it has none.
+__device__ __forceinline__ bool side_work(const ShrinkArgs& a) {
+  if ((int)blockIdx.y < a.n_adapters) return false;
+  const int wg = (blockIdx.y - a.n_adapters) * gridDim.x + blockIdx.x;
+  const int tile = wg * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (tile < a.side.list_tiles)
+    lora_tile_list(a.seg_off, a.n_adapters, a.side.n_inl ? a.side.entry : a.table, 1 - a.which, a.side.list_rows, tile, threadIdx.x & 63,
+                   (LoraTile*)a.side.lists);
+  if (wg == 0 && (int)threadIdx.x < a.side.n_inl) {
+    a.side.entries_out[threadIdx.x] = a.side.entry[threadIdx.x];
+    if (a.side.grads_out) a.side.grads_out[threadIdx.x] = a.side.grad[threadIdx.x];
+  }
+  return true;
+}
+static dim3 side_grid(const ShrinkArgs& a, int x, int waves) {
+  const int wgs = (a.side.list_tiles + waves - 1) / waves, need = wgs > 0 || a.side.n_inl == 0 ? wgs : 1;
+  return dim3(x, a.n_adapters + (need + x - 1) / x);
+}
 
 // u (scaled, fp32) and its two-term bf16 split for row m, rank index q of an adapter with padded rank r_pad
 __device__ __forceinline__ void shrink_store(const ShrinkArgs& a, int64_t m, int q, int r_pad, float val) {
@@ -64,12 +88,13 @@ __device__ __forceinline__ void shrink_store(const ShrinkArgs& a, int64_t m, int
 template <int LFORM, int NQT>
 __global__ __launch_bounds__(SH_THREADS, (NQT >= 8 ? 1 : 2)) void shrink_bf16_kernel(ShrinkArgs a) {
   extern __shared__ __attribute__((aligned(16))) char Ls[];   // [r_pad][SH_PITCH]
+  if (side_work(a)) return;
   const int t = blockIdx.y;
   const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int rb = blockIdx.x / a.ksplit, ks = blockIdx.x - rb * a.ksplit;
   const int row0 = lo + rb * SH_ROWS;
   if (row0 >= hi) return;
-  const AdapterEntry e = a.table[t];
+  const AdapterEntry e = entry_of(a, t);
   const bf16_t* L = (const bf16_t*)(a.which ? e.B : e.A);
   const int r = e.rank;
   const int r_pad = (r + 15) & ~15;
@@ -220,12 +245,13 @@ template <int LFORM, int NQT, int RT>
 __global__ __launch_bounds__(256) void shrink_ring_kernel(ShrinkArgs a) {
   constexpr int SR_ROWS = 64 * RT, SR_X_BYTES = SR_ROWS * 64 * 2, XI = 2 * RT;   // rows, x part of a slot, x instructions per wave and k-tile
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (side_work(a)) return;
   const int t = blockIdx.y;
   const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int rb = blockIdx.x / a.ksplit, ks = blockIdx.x - rb * a.ksplit;
   const int row0 = lo + rb * SR_ROWS;
   if (row0 >= hi) return;
-  const AdapterEntry e = a.table[t];
+  const AdapterEntry e = entry_of(a, t);
   const bf16_t* L = (const bf16_t*)(a.which ? e.B : e.A);
   const int r = e.rank;
   const int r_pad = (r + 15) & ~15;
@@ -360,19 +386,23 @@ __global__ __launch_bounds__(256) void shrink_ring_kernel(ShrinkArgs a) {
         }
 }
 
-// Small batches (decode): one block per (adapter, 16 grouped rows); its 8 waves split the
+// Batches of few rows a compute unit: one block per (adapter, 16 grouped rows); its 8 waves split the
 // contraction, take both operands straight from global memory (L_t stored [r_t, C], so a lane's 8
 // contraction values are one 16-byte load) and add their partial tiles through LDS in wave order,
-// so the result does not depend on timing.
+// so the result does not depend on timing.  Bound by latency: a wave has U steps of 32 contraction values
+// under way while U others are multiplied, and the four lanes of a row read 64 bytes in a row.
 static constexpr int SS_WAVES = 8;
-template <int DUMMY>
+template <int NQT>
 __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkArgs a) {
+  constexpr int U = NQT == 1 ? 4 : NQT == 2 ? 3 : NQT == 4 ? 2 : 1;
+  union Frag { uint4 u; bf16x8 v; };
   extern __shared__ __attribute__((aligned(16))) char red[];   // [SS_WAVES][nqt][64] f32x4
+  if (side_work(a)) return;
   const int t = blockIdx.y;
   const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int row0 = lo + blockIdx.x * 16;
   if (row0 >= hi) return;
-  const AdapterEntry e = a.table[t];
+  const AdapterEntry e = entry_of(a, t);
   const bf16_t* L = (const bf16_t*)(a.which ? e.B : e.A);
   const int r = e.rank, r_pad = (r + 15) & ~15, nqt = r_pad >> 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -380,42 +410,46 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
   int m = row0 + li;
   if (m >= hi) m = hi - 1;
   const int64_t tok = a.perm ? a.perm[m] : m;
-  const bf16_t* xrow = a.X + tok * a.ldx;
-  const int64_t kw = ((a.C + SS_WAVES * 128 - 1) / (SS_WAVES * 128)) * 128;   // per wave, multiple of 128
-  const int64_t kbeg = wave * kw;
-  const int64_t kend = (kbeg + kw) < a.C ? (kbeg + kw) : a.C;
-  f32x4 acc[8];
-  for (int q = 0; q < 8; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const uint4 zero4 = make_uint4(0, 0, 0, 0);
-  for (int64_t k0 = kbeg; k0 < kend; k0 += 128) {
-    uint4 xf[4];
+  const bf16_t* xrow = a.X + tok * a.ldx + 8 * g;
+  const int steps = (int)((a.C + 31) >> 5), per = (steps + SS_WAVES - 1) / SS_WAVES;
+  const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
+  f32x4 acc[NQT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t k = k0 + g * 32 + j * 8;
-      xf[j] = zero4;
-      if (k < kend) xf[j] = *(const uint4*)(xrow + k);
+  for (int q = 0; q < NQT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Frag fa[U][NQT + 1], fb[U][NQT + 1];
+  auto request = [&](Frag (&f)[U][NQT + 1], int s) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int64_t k = (int64_t)(s + i) * 32;
+      const bool in = s + i < s1 && k + 8 * g < a.C;
+#pragma unroll
+      for (int q = 0; q <= NQT; ++q) f[i][q].u = make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < NQT; ++q)
+        if (in && q * 16 + li < r) f[i][q].u = *(const uint4*)(L + (int64_t)(q * 16 + li) * a.C + k + 8 * g);
+      if (in) f[i][NQT].u = *(const uint4*)(xrow + k);
     }
+  };
+  auto multiply = [&](Frag (&f)[U][NQT + 1]) {
 #pragma unroll
-    for (int qt = 0; qt < 8; ++qt)
-      if (qt < nqt) {
-        const int q = qt * 16 + li;
-        uint4 lf[4];
+    for (int i = 0; i < U; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int64_t k = k0 + g * 32 + j * 8;
-          lf[j] = zero4;
-          if (q < r && k < kend) lf[j] = *(const uint4*)(L + (int64_t)q * a.C + k);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          union { uint4 u; bf16x8 v; } xa, lb; xa.u = xf[j]; lb.u = lf[j];
-          acc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa.v, lb.v, acc[qt], 0, 0, 0);
-        }
-      }
+      for (int q = 0; q < NQT; ++q)
+        if (q < nqt) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i][NQT].v, f[i][q].v, acc[q], 0, 0, 0);
+  };
+  request(fa, s0);
+#pragma unroll 1
+  for (int s = s0; s < s1; s += 2 * U) {
+    if (s + U < s1) request(fb, s + U);
+    multiply(fa);
+    if (s + U < s1) {
+      if (s + 2 * U < s1) request(fa, s + 2 * U);
+      multiply(fb);
+    }
   }
   f32x4* rp = (f32x4*)red;
 #pragma unroll
-  for (int qt = 0; qt < 8; ++qt)
+  for (int qt = 0; qt < NQT; ++qt)
     if (qt < nqt) rp[(wave * nqt + qt) * 64 + lane] = acc[qt];
   __syncthreads();
   // wave w finishes q-tiles w, w + 8, ...
@@ -439,7 +473,7 @@ __global__ __launch_bounds__(256) void shrink_finalize_kernel(ShrinkArgs a) {
   const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int64_t m = lo + (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   if (m >= hi) return;
-  const AdapterEntry e = a.table[t];
+  const AdapterEntry e = entry_of(a, t);
   const int r_pad = (e.rank + 15) & ~15;
   for (int q = threadIdx.x & 15; q < r_pad; q += 16) {
     float sum = 0.f;
@@ -471,20 +505,22 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
                               const int32_t* seg_off, int n_adapters, int max_seg,
                               const AdapterEntry* table, int which, int lora_form, float* u,
                               int r_stride, int64_t T_lora, float* partials, size_t partial_bytes,
-                              bf16_t* u2, bool* wrote_u2, const bf16_t* zero_line, bool ranks_mult8, hipStream_t stream) {
+                              bf16_t* u2, bool* wrote_u2, const bf16_t* zero_line, bool ranks_mult8, const SideWork& side, hipStream_t stream) {
   if (wrote_u2) *wrote_u2 = false;
   if (n_adapters <= 0 || max_seg <= 0 || T_lora <= 0) return hipSuccess;
   ShrinkArgs a;
   a.X = X; a.ldx = ldx; a.C = C; a.perm = perm; a.seg_off = seg_off; a.table = table;
   a.which = which; a.u = u; a.r_stride = r_stride;
   a.partials = nullptr; a.T_lora = T_lora; a.u2 = nullptr; a.zero_line = zero_line;
+  a.n_adapters = n_adapters; a.side = side;
   const int64_t real_blocks = (T_lora + SH_ROWS - 1) / SH_ROWS + n_adapters;
   if (lora_form == FORM_NT && real_blocks <= 96) {
     a.ksplit = 1; a.kchunk = 0; a.u2 = u2;
     if (wrote_u2) *wrote_u2 = u2 != nullptr;
     const size_t lds = (size_t)SS_WAVES * (r_stride / 16) * 64 * sizeof(f32x4);
-    hipLaunchKernelGGL(shrink_small_nt_kernel<0>, dim3((max_seg + 15) / 16, n_adapters), dim3(64 * SS_WAVES), lds,
-                       stream, a);
+    const int nq = r_stride / 16;
+    auto kern = nq <= 1 ? shrink_small_nt_kernel<1> : nq <= 2 ? shrink_small_nt_kernel<2> : nq <= 4 ? shrink_small_nt_kernel<4> : shrink_small_nt_kernel<8>;
+    hipLaunchKernelGGL(kern, side_grid(a, (max_seg + 15) / 16, SS_WAVES), dim3(64 * SS_WAVES), lds, stream, a);
     return hipGetLastError();
   }
   // both operands by DMA where every piece of a factor row stays inside the row; 128 rows per
@@ -530,7 +566,7 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
     hipError_t e = allow_big_lds((const void*)kern, (lora_form == FORM_NT ? 0 : 4) + (nq <= 1 ? 0 : nq <= 2 ? 1 : nq <= 4 ? 2 : 3));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3(rb_max * ksplit, n_adapters), dim3(SH_THREADS), lds, stream, a);
+  hipLaunchKernelGGL(kern, side_grid(a, rb_max * ksplit, SH_THREADS / 64), dim3(SH_THREADS), lds, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || ksplit == 1) return e;
   hipLaunchKernelGGL(shrink_finalize_kernel, dim3((max_seg + 15) / 16, n_adapters), dim3(256), 0, stream, a);

@@ -180,6 +180,18 @@ def test_some_rows_short_last_split(oracle, T, K, N):
     _check_layer(oracle, w, bwd=False, tag="short last split", table="table+packed")
 
 
+# Pointer lists of as many adapters as travel in the shrink's arguments, and of one more; no row with an adapter (no
+# shrink at all); row tiles of 128 rows and a few rows in the last one; more row tiles than shrink workgroups.
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,K,N,n,base", [(1030, 264, 8200, 16, 0.3), (1030, 264, 8200, 17, 0.3), (1030, 264, 8200, 16, 1.0), (4100, 72, 2056, 1, 0.98)])
+def test_lists_with_the_shrink(oracle, T, K, N, n, base, layout):
+    rng = np.random.default_rng(T + n)
+    ids = rng.integers(0, n, size=T).astype(np.int32)
+    ids[rng.random(T) < base] = -1
+    w = wl.make_layer(T + n, T, K, N, [8 + 8 * (t % 4) for t in range(n)], [0.5 + t % 3 for t in range(n)], ids, dtype="bf16", layout=layout, want_dY=True)
+    _check_layer(oracle, w, bwd=True, tag="lists", table="lists")
+
+
 # u in one, two and four pieces of the contraction (the last of them shorter), rows of several adapters in a
 # pair of row blocks, rank tiles that are not whole.
 @pytest.mark.parametrize("T,K,N,ranks", [(66, 4096, 1032, [16, 24]), (300, 4616, 1032, [32] * 64), (130, 4616, 520, [40, 8, 16] * 4)])
