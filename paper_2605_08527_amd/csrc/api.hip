@@ -612,8 +612,7 @@ static WsPlan plan_workspace(const marlaas_lora_desc* d, int want_bwd, size_t ws
       const bool always = d->n_adapters <= OPT_MAX_ADAPTERS;
       const size_t pa = reduce_partial_bytes(d->d_in, d->n_adapters, d->map->max_seg, (int)rs, always, d->map->ragged_chunk, d->map->ragged_slots);
       const size_t pb = reduce_partial_bytes(d->d_out, d->n_adapters, d->map->max_seg, (int)rs, always, d->map->ragged_chunk, d->map->ragged_slots);
-      needs(pa, pa);
-      needs(pb, pb);
+      needs(align_up(pa, WS_ALIGN) + pb, std::max(pa, pb));      // (one launch for both; with less room one after the other)
       needs(gemm_splitk_bytes(d->T, d->d_out, d->d_in, n_ext), gemm_splitk_min_bytes(d->T, d->d_out, d->d_in, n_ext));
     }
   }
@@ -1350,12 +1349,10 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
                                     fused ? &fuse : nullptr, need, (have_ws && p.wt_bytes) ? (bf16_t*)((char*)ctx->ws + p.wt_off) : nullptr,
                                     p.wt_bytes, d->layout == MARLAAS_LAYOUT_TORCH ? (const bf16_t*)d->W_t : nullptr, &dma, (const bf16_t*)d->W_packed_bwd, use_packed, &dsync, st));
     if (want_grads && d->n_adapters > 0) {
-      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_bf16(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
-                                      table, grads, 1, db_form, u, rs, accumulate, part, part ? p.part_bytes : 0, opt ? &opt[1] : nullptr, map->order_dev, map->chunk_base_dev,
-                                      map->ragged_chunk, map->ragged_slots, map->ragged_adapters, st));
-      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_bf16(x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters, map->max_seg,
-                                      table, grads, 0, da_form, v, rs, accumulate, part, part ? p.part_bytes : 0, opt ? &opt[0] : nullptr, map->order_dev, map->chunk_base_dev,
-                                      map->ragged_chunk, map->ragged_slots, map->ragged_adapters, st));
+      const ReduceJob jobs[2] = {{dy, lddy, d->d_out, u, 1, db_form, opt ? &opt[1] : nullptr}, {x, d->ldx, d->d_in, v, 0, da_form, opt ? &opt[0] : nullptr}};
+      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_bf16(jobs, perm, map->seg_off_dev, d->n_adapters, map->max_seg, table, grads, rs, accumulate,
+                                      part, part ? p.part_bytes : 0, map->order_dev, map->chunk_base_dev, map->ragged_chunk, map->ragged_slots,
+                                      map->ragged_adapters, st));
     }
   } else {
     if (opt) return fail(ctx, MARLAAS_EUNSUPPORTED, "the optimizer step is attached to the bf16 backward only");

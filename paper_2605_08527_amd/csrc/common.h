@@ -316,12 +316,16 @@ struct ReduceOpt {
   float lr, beta1, beta2, eps, wd, inv_c1, inv_c2;   // inv_c: 1 / (1 - beta^step)
   OptFactor f[OPT_MAX_ADAPTERS];
 };
-hipError_t launch_reduce_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int32_t* perm,
-                              const int32_t* seg_off, int n_adapters, int max_seg,
-                              const AdapterEntry* table, const GradEntry* grads, int which,
-                              int out_form, const float* V, int r_stride, int accumulate,
-                              float* partials, size_t partial_bytes, const ReduceOpt* opt, const int32_t* order,
-                              const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters,
+// Both weight gradients of a backward; a job: X [T, C] and V [T, r_stride] of one of them.
+struct ReduceJob {
+  const bf16_t* X; int64_t ldx; int64_t C;
+  const float* V;
+  int which, form;          // 0: dA, 1: dB; storage of the gradient
+  const ReduceOpt* opt;     // or null
+};
+hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, const int32_t* seg_off, int n_adapters, int max_seg,
+                              const AdapterEntry* table, const GradEntry* grads, int r_stride, int accumulate, float* partials, size_t partial_bytes,
+                              const int32_t* order, const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters,
                               hipStream_t stream);
 size_t reduce_partial_bytes(int64_t C, int n_adapters, int max_seg, int max_rank, bool always = false,
                             int ragged_chunk = 0, int ragged_slots = 0);

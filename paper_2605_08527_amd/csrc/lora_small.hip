@@ -6,6 +6,7 @@
 // and are bound by HBM; the small operand stays in LDS.
 #include "lora_lists.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace marlaas {
@@ -589,9 +590,17 @@ struct ReduceArgs {
   // ragged = 1: only segments longer than tchunk are cut; adapter t's pieces use partial-sum slots
   // chunk_base[t] .. ([slot][C][r_stride]), every other adapter's block writes its result itself
   int ragged; const int32_t* chunk_base;
-  float* partials;                         // [adapter][chunk][C][r_stride] when to_partials
-  int to_partials;                         // 1: the chunks' sums go to `partials`, reduce_finalize_kernel completes
+  float* partials;                         // [adapter][chunk] slots when to_partials
+  int to_partials;                         // 1: the chunks' sums go to `partials`, reduce_finalize_kernel completes;
+                                           // a slot is laid out like the gradient, [C][r_stride] or [r_stride][C]
+  int form;                                // of the gradient: FORM_NN [C, r], FORM_NT [r, C]
   ReduceOpt opt;                           // (finalize) optimizer step on every completed gradient element
+};
+// dB_t from (dY, u) and dA_t from (x, v) are independent: one launch, the first job's workgroups of an adapter
+// beside the second's (3000 rows of 4 adapters fill a quarter of the chip each).
+struct ReducePair {
+  ReduceArgs a[2];
+  int n0;                                  // workgroups of the first job in x
 };
 
 // LDS byte offset of 16-byte unit `unit` (of 32) of token row `tk` in the [64][256] X tile.
@@ -600,17 +609,17 @@ __device__ __forceinline__ int swz_tokc(int tk, int unit) {
   return tk * 512 + ((unit ^ (f << 1)) << 4);
 }
 
-// grid: x = slabs * chunks_max, y = adapter.  The kernel is bound by the one pass over X, so the
+// grid: x = slabs * chunks_max of both jobs, y = adapter.  The kernel is bound by the one pass over X, so the
 // loop is software-pipelined through registers: while a 64-token step is multiplied out of LDS,
 // the X rows and V rows of the next step are already requested (and the gather indices of the
-// step after that), and only the LDS hand-over sits between two barriers.
+// step after that), and only the LDS hand-over sits between two barriers.  The operand order of the matrix
+// instructions follows the gradient's storage: a lane ends up with four values that are neighbours there.
 template <int OFORM, int NQT>
-__global__ __launch_bounds__(RD_THREADS, NQT >= 8 ? 1 : 2) void reduce_bf16_kernel(ReduceArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char rsm[];
+__device__ __forceinline__ void reduce_block(const ReduceArgs& a, int bx, int by, char* rsm) {
   char* Xs = rsm;                               // [RD_TOK][RD_COLS] bf16, swizzled
   char* Vh = rsm + RD_TOK * RD_COLS * 2;        // [RD_TOK][r_pad] bf16: leading halves of V
-  const int t = a.order ? a.order[blockIdx.y] : blockIdx.y;
-  const int slab = blockIdx.x % a.slabs, ch = blockIdx.x / a.slabs;
+  const int t = a.order ? a.order[by] : by;
+  const int slab = bx % a.slabs, ch = bx / a.slabs;
   const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int beg = lo + ch * a.tchunk;
   const bool empty = beg >= hi;
@@ -729,34 +738,52 @@ __global__ __launch_bounds__(RD_THREADS, NQT >= 8 ? 1 : 2) void reduce_bf16_kern
           }
 #pragma unroll
           for (int ct = 0; ct < 4; ++ct) {
-            acc[ct][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ct], vh, acc[ct][qt], 0, 0, 0);
-            acc[ct][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ct], vl, acc[ct][qt], 0, 0, 0);
+            if (OFORM == FORM_NT) {
+              acc[ct][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ct], vh, acc[ct][qt], 0, 0, 0);
+              acc[ct][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ct], vl, acc[ct][qt], 0, 0, 0);
+            } else {
+              acc[ct][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vh, xa[ct], acc[ct][qt], 0, 0, 0);
+              acc[ct][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vl, xa[ct], acc[ct][qt], 0, 0, 0);
+            }
           }
         }
     }
   }
-  // D layout: row (column c of X) = 4 * (lane / 16) + v, column (q) = lane % 16
+  // D layout: 4 * (lane / 16) + v counts columns c of X (FORM_NT) or ranks (FORM_NN), lane % 16 the other
   const bool via_part = a.ragged ? nch_t > 1 : a.to_partials != 0;
-  float* outp = via_part ? nullptr : (a.which ? a.grads[t].dB : a.grads[t].dA);
-  float* part = !via_part ? nullptr
-                : a.partials + (a.ragged ? (int64_t)a.chunk_base[t] + ch : (int64_t)t * a.chunks_max + ch) * a.C * a.r_stride;
+  float* out = via_part ? a.partials + (a.ragged ? (int64_t)a.chunk_base[t] + ch : (int64_t)t * a.chunks_max + ch) * a.C * a.r_stride
+                        : a.which ? a.grads[t].dB : a.grads[t].dA;
+  const int64_t pitch = OFORM == FORM_NT ? a.C : via_part ? a.r_stride : r;
+  const int q_end = via_part ? r_pad : r;      // (a slot's padding ranks hold zeros and are not read)
+  const bool add = !via_part && a.accumulate, whole = OFORM == FORM_NT || via_part || (r & 3) == 0;
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt)
-      if (qt < nqt)
-        for (int v = 0; v < 4; ++v) {
-          const int64_t c = c0 + wave * 64 + ct * 16 + 4 * g + v;
-          const int q = qt * 16 + li;
-          if (c < a.C && q < r) {
-            if (part) {
-              part[c * a.r_stride + q] = acc[ct][qt][v];
-            } else {
-              float* o = outp + (OFORM == FORM_NN ? c * r + q : (int64_t)q * a.C + c);
-              *o = a.accumulate ? *o + acc[ct][qt][v] : acc[ct][qt][v];
-            }
-          }
+      if (qt < nqt) {
+        const int64_t c = c0 + wave * 64 + ct * 16 + (OFORM == FORM_NT ? 4 * g : li);
+        const int q = qt * 16 + (OFORM == FORM_NT ? li : 4 * g);
+        if (c >= a.C || q >= q_end) continue;  // (C is a multiple of 8: four columns are in or out together)
+        float* o = out + (OFORM == FORM_NT ? q * pitch + c : c * pitch + q);
+        f32x4 s = acc[ct][qt];
+        if (whole) {
+          if (add) { const f32x4 was = *(const f32x4*)o; s[0] += was[0]; s[1] += was[1]; s[2] += was[2]; s[3] += was[3]; }
+          *(f32x4*)o = s;
+        } else {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) if (q + v < q_end) o[v] = add ? o[v] + s[v] : s[v];
         }
+      }
+}
+
+template <int NQT>
+__global__ __launch_bounds__(RD_THREADS, NQT >= 8 ? 1 : 2) void reduce_bf16_kernel(ReducePair p) {
+  extern __shared__ __attribute__((aligned(16))) char rsm[];
+  const bool second = (int)blockIdx.x >= p.n0;
+  const ReduceArgs& a = second ? p.a[1] : p.a[0];
+  const int bx = blockIdx.x - (second ? p.n0 : 0);
+  if (a.form == FORM_NT) reduce_block<FORM_NT, NQT>(a, bx, blockIdx.y, rsm);
+  else reduce_block<FORM_NN, NQT>(a, bx, blockIdx.y, rsm);
 }
 
 // out_t (+)= sum over the chunks of adapter t, in chunk order.  With an optimizer step attached
@@ -764,58 +791,45 @@ __global__ __launch_bounds__(RD_THREADS, NQT >= 8 ? 1 : 2) void reduce_bf16_kern
 // (Adam with decoupled weight decay; the policy update of the task being trained, paper Sec. 4.2
 // and Alg. 1, whose optimizer state is kept per task) of the fp32 master value and its two
 // moments, and the bf16 value of the next version of the factor.  Adapters without tokens in the
-// batch are not trained by it and are left alone.
-template <int OFORM>
-__global__ __launch_bounds__(256) void reduce_finalize_kernel(ReduceArgs a) {
-  // block = 32 columns x 32 rank indices of one adapter.  The chunks' sums are read with the rank
-  // index fastest (their storage order) and handed over through LDS, so that the gradient and the
-  // optimizer state are touched in THEIR storage order: rank fastest for [C, r] outputs, column
-  // fastest for [r, C] outputs.
-  __shared__ float tile[32][33];
+// batch are not trained by it and are left alone.  A thread owns one element; the slots are laid out like the
+// gradient, so every access is whole lines, and eight slots are read at a time.
+__global__ __launch_bounds__(256) void reduce_finalize_kernel(ReducePair p) {
+  const bool second = (int)blockIdx.x >= p.n0;
+  const ReduceArgs& a = second ? p.a[1] : p.a[0];
+  if (!a.to_partials) return;
   // (ragged: the grid covers the adapters that are cut, the longest ones, first in `order`)
   const int t = a.ragged ? a.order[blockIdx.y] : blockIdx.y;
-  const AdapterEntry e = a.table[t];
-  const int r = e.rank;
-  const int qtiles = (a.r_stride + 31) / 32;
-  const int64_t c0 = (int64_t)(blockIdx.x / qtiles) * 32;
-  const int q0 = (int)(blockIdx.x % qtiles) * 32;
-  if (q0 >= r) return;
+  const int r = a.table[t].rank;
+  const int64_t off = (int64_t)(blockIdx.x - (second ? p.n0 : 0)) * 256 + threadIdx.x;
+  if (off >= a.C * r) return;
   const int len = a.seg_off[t + 1] - a.seg_off[t];
   if (a.opt.on && len == 0) return;
   const int nch = (len + a.tchunk - 1) / a.tchunk;
   if (a.ragged && nch <= 1) return;      // (written by its one block)
-  const int64_t slot0 = a.ragged ? (int64_t)a.chunk_base[t] : (int64_t)t * a.chunks_max;
-  for (int i = threadIdx.x; i < 1024; i += 256) {
-    const int cc = i >> 5, qq = i & 31;
-    const int64_t c = c0 + cc;
-    const int q = q0 + qq;
-    float sum = 0.f;
-    if (c < a.C && q < r)
-      for (int ch = 0; ch < nch; ++ch)
-        sum += a.partials[((slot0 + ch) * a.C + c) * a.r_stride + q];
-    tile[cc][qq] = sum;
+  const int64_t slot0 = a.ragged ? (int64_t)a.chunk_base[t] : (int64_t)t * a.chunks_max, slot = a.C * a.r_stride;
+  const float* from = a.partials + slot0 * slot + (a.form == FORM_NT ? off : off / r * a.r_stride + off % r);
+  float sum = 0.f;
+  int ch = 0;
+  for (; ch + 8 <= nch; ch += 8) {
+    float s[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = from[(ch + i) * slot];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += s[i];
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 1024; i += 256) {
-    const int cc = OFORM == FORM_NN ? i >> 5 : i & 31, qq = OFORM == FORM_NN ? i & 31 : i >> 5;
-    const int64_t c = c0 + cc;
-    const int q = q0 + qq;
-    if (c >= a.C || q >= r) continue;
-    const float sum = tile[cc][qq];
-    const int64_t off = OFORM == FORM_NN ? c * r + q : (int64_t)q * a.C + c;
-    if (a.opt.on) {
-      const OptFactor f = a.opt.f[t];
-      float p = f.master[off];
-      p -= a.opt.lr * a.opt.wd * p;
-      const float m = a.opt.beta1 * f.m[off] + (1.f - a.opt.beta1) * sum;
-      const float v = a.opt.beta2 * f.v[off] + (1.f - a.opt.beta2) * sum * sum;
-      p -= a.opt.lr * (m * a.opt.inv_c1) / (sqrtf(v * a.opt.inv_c2) + a.opt.eps);
-      f.master[off] = p; f.m[off] = m; f.v[off] = v;
-      f.out[off] = float_to_bf16_bits(p);
-    } else {
-      float* o = (a.which ? a.grads[t].dB : a.grads[t].dA) + off;
-      *o = a.accumulate ? *o + sum : sum;
-    }
+  for (; ch < nch; ++ch) sum += from[ch * slot];
+  if (a.opt.on) {
+    const OptFactor f = a.opt.f[t];
+    float p1 = f.master[off];
+    p1 -= a.opt.lr * a.opt.wd * p1;
+    const float m = a.opt.beta1 * f.m[off] + (1.f - a.opt.beta1) * sum;
+    const float v = a.opt.beta2 * f.v[off] + (1.f - a.opt.beta2) * sum * sum;
+    p1 -= a.opt.lr * (m * a.opt.inv_c1) / (sqrtf(v * a.opt.inv_c2) + a.opt.eps);
+    f.master[off] = p1; f.m[off] = m; f.v[off] = v;
+    f.out[off] = float_to_bf16_bits(p1);
+  } else {
+    float* o = (a.which ? a.grads[t].dB : a.grads[t].dA) + off;
+    *o = a.accumulate ? *o + sum : sum;
   }
 }
 
@@ -853,71 +867,95 @@ size_t reduce_partial_bytes(int64_t C, int n_adapters, int max_seg, int r_stride
   return need;
 }
 
-hipError_t launch_reduce_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int32_t* perm,
-                              const int32_t* seg_off, int n_adapters, int max_seg,
-                              const AdapterEntry* table, const GradEntry* grads, int which,
-                              int out_form, const float* V, int r_stride, int accumulate,
-                              float* partials, size_t partial_bytes, const ReduceOpt* opt, const int32_t* order,
-                              const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters,
-                              hipStream_t stream) {
-  if (n_adapters <= 0) return hipSuccess;
+// One job's arguments: how its segments are cut, and the bytes of sums it leaves.
+static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int32_t* seg_off, int n_adapters, int max_seg, const AdapterEntry* table,
+                              const GradEntry* grads, int r_stride, int accumulate, size_t partial_bytes, const int32_t* order,
+                              const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters, ReduceArgs* out, size_t* bytes) {
   ReduceArgs a;
+  const size_t slot = (size_t)j.C * r_stride * sizeof(float);
   a.order = order;
   a.ragged = 0; a.chunk_base = nullptr;
-  a.X = X; a.ldx = ldx; a.C = C; a.perm = perm; a.seg_off = seg_off; a.table = table;
-  a.grads = grads; a.which = which; a.V = V; a.r_stride = r_stride; a.accumulate = accumulate;
-  a.slabs = (int)((C + RD_COLS - 1) / RD_COLS);
-  reduce_plan(C, n_adapters, max_seg, &a.tchunk, &a.chunks_max);
-  if (a.chunks_max > 1 &&
-      (partials == nullptr || partial_bytes < (size_t)n_adapters * a.chunks_max * C * r_stride * sizeof(float))) {
+  a.X = j.X; a.ldx = j.ldx; a.C = j.C; a.perm = perm; a.seg_off = seg_off; a.table = table;
+  a.grads = grads; a.which = j.which; a.form = j.form; a.V = j.V; a.r_stride = r_stride; a.accumulate = accumulate;
+  a.slabs = (int)((j.C + RD_COLS - 1) / RD_COLS);
+  a.partials = nullptr;
+  reduce_plan(j.C, n_adapters, max_seg, &a.tchunk, &a.chunks_max);
+  if (a.chunks_max > 1 && partial_bytes < n_adapters * a.chunks_max * slot) {
     a.chunks_max = 1;   // no room for partial sums: one block walks the whole segment
     a.tchunk = ((max_seg + RD_TOK - 1) / RD_TOK) * RD_TOK;
     if (a.tchunk < RD_TOK) a.tchunk = RD_TOK;
   }
-  a.partials = partials;
   a.to_partials = a.chunks_max > 1;
-  if (!(opt && opt->on) && a.chunks_max == 1 && chunk_base != nullptr && order != nullptr && partials != nullptr &&
-      ragged_adapters > 0 && ragged_adapters <= n_adapters &&
-      reduce_ragged(C, n_adapters, max_seg, ragged_chunk, ragged_slots) &&
-      partial_bytes >= (size_t)ragged_slots * C * r_stride * sizeof(float)) {
+  *bytes = a.to_partials ? n_adapters * a.chunks_max * slot : 0;
+  const bool opt = j.opt && j.opt->on;
+  if (!opt && a.chunks_max == 1 && chunk_base != nullptr && order != nullptr && ragged_adapters > 0 && ragged_adapters <= n_adapters &&
+      reduce_ragged(j.C, n_adapters, max_seg, ragged_chunk, ragged_slots) && partial_bytes >= ragged_slots * slot) {
     a.ragged = 1; a.chunk_base = chunk_base;
     a.tchunk = ragged_chunk;
     a.chunks_max = (max_seg + ragged_chunk - 1) / ragged_chunk;
     a.to_partials = 1;               // (the finalize kernel runs; it skips the adapters with one piece)
+    *bytes = ragged_slots * slot;
   }
   a.opt.on = 0;
-  if (opt && opt->on) {
+  if (opt) {
     // the optimizer step lives in the finalize kernel: the sums always go through `partials`
-    if (n_adapters > OPT_MAX_ADAPTERS || partials == nullptr ||
-        partial_bytes < (size_t)n_adapters * a.chunks_max * C * r_stride * sizeof(float))
-      return hipErrorInvalidValue;
-    a.opt = *opt;
+    *bytes = n_adapters * a.chunks_max * slot;
+    if (n_adapters > OPT_MAX_ADAPTERS || partial_bytes < *bytes) return hipErrorInvalidValue;
+    a.opt = *j.opt;
     a.to_partials = 1;
   }
+  *out = a;
+  return hipSuccess;
+}
+
+hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, const int32_t* seg_off, int n_adapters, int max_seg,
+                              const AdapterEntry* table, const GradEntry* grads, int r_stride, int accumulate, float* partials, size_t partial_bytes,
+                              const int32_t* order, const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters,
+                              hipStream_t stream) {
+  if (n_adapters <= 0) return hipSuccess;
+  if (partials == nullptr) partial_bytes = 0;
+  ReducePair p;
+  size_t bytes[2];
+  for (int j = 0; j < 2; ++j) {
+    const hipError_t e = reduce_args(jobs[j], perm, seg_off, n_adapters, max_seg, table, grads, r_stride, accumulate, partial_bytes, order, chunk_base,
+                                     ragged_chunk, ragged_slots, ragged_adapters, &p.a[j], &bytes[j]);
+    if (e != hipSuccess) return e;
+    bytes[j] = (bytes[j] + 255) / 256 * 256;
+    p.a[j].partials = partials;
+  }
+  // one launch where there is room for both jobs' sums
+  const bool both = bytes[0] == 0 || bytes[1] == 0 || bytes[0] + bytes[1] <= partial_bytes;
+  if (both && bytes[0]) p.a[1].partials = (float*)((char*)partials + bytes[0]);
   const size_t lds = (size_t)RD_TOK * RD_COLS * 2 + (size_t)2 * RD_TOK * (r_stride * 2 + 16);   // r_stride >= every r_pad
-  typedef void (*rkern_t)(ReduceArgs);
   const int nq = r_stride / 16;
-  rkern_t kern;
-  if (out_form == FORM_NN)
-    kern = nq <= 1 ? reduce_bf16_kernel<FORM_NN, 1> : nq <= 2 ? reduce_bf16_kernel<FORM_NN, 2>
-         : nq <= 4 ? reduce_bf16_kernel<FORM_NN, 4> : reduce_bf16_kernel<FORM_NN, 8>;
-  else
-    kern = nq <= 1 ? reduce_bf16_kernel<FORM_NT, 1> : nq <= 2 ? reduce_bf16_kernel<FORM_NT, 2>
-         : nq <= 4 ? reduce_bf16_kernel<FORM_NT, 4> : reduce_bf16_kernel<FORM_NT, 8>;
+  typedef void (*rkern_t)(ReducePair);
+  const rkern_t kern = nq <= 1 ? reduce_bf16_kernel<1> : nq <= 2 ? reduce_bf16_kernel<2> : nq <= 4 ? reduce_bf16_kernel<4> : reduce_bf16_kernel<8>;
   if (lds > 64 * 1024) {
-    hipError_t e = allow_big_lds((const void*)kern, 8 + (out_form == FORM_NT ? 0 : 4) + (nq <= 1 ? 0 : nq <= 2 ? 1 : nq <= 4 ? 2 : 3));
+    hipError_t e = allow_big_lds((const void*)kern, 8 + (nq <= 1 ? 0 : nq <= 2 ? 1 : nq <= 4 ? 2 : 3));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3(a.slabs * a.chunks_max, n_adapters), dim3(RD_THREADS), lds, stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.to_partials) {
-    auto fin = out_form == FORM_NN ? reduce_finalize_kernel<FORM_NN> : reduce_finalize_kernel<FORM_NT>;
-    hipLaunchKernelGGL(fin, dim3((unsigned)(((C + 31) / 32) * ((r_stride + 31) / 32)), a.ragged ? ragged_adapters : n_adapters),
-                       dim3(256), 0, stream, a);
+  for (int first = 0; first < 2; first += both ? 2 : 1) {
+    ReducePair q = p;
+    if (first == 1) q.a[0] = p.a[1];
+    const int x0 = q.a[0].slabs * q.a[0].chunks_max, x1 = both ? q.a[1].slabs * q.a[1].chunks_max : 0;
+    q.n0 = x0;
+    hipLaunchKernelGGL(kern, dim3(x0 + x1, n_adapters), dim3(RD_THREADS), lds, stream, q);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    int64_t blocks[2] = {0, 0};
+    int adapters = 0;
+    for (int j = 0; j < (both ? 2 : 1); ++j)
+      if (q.a[j].to_partials) {
+        blocks[j] = (q.a[j].C * r_stride + 255) / 256;
+        adapters = std::max(adapters, q.a[j].ragged ? ragged_adapters : n_adapters);
+      }
+    if (adapters == 0) continue;
+    q.n0 = (int)blocks[0];
+    hipLaunchKernelGGL(reduce_finalize_kernel, dim3((unsigned)(blocks[0] + blocks[1]), adapters), dim3(256), 0, stream, q);
     e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  return e;
+  return hipSuccess;
 }
 
 }  // namespace marlaas
