@@ -590,6 +590,7 @@ struct ReduceArgs {
   // ragged = 1: only segments longer than tchunk are cut; adapter t's pieces use partial-sum slots
   // chunk_base[t] .. ([slot][C][r_stride]), every other adapter's block writes its result itself
   int ragged; const int32_t* chunk_base;
+  int ragged_adapters, n_adapters;         // adapters that are cut (the first ones in `order`), all
   float* partials;                         // [adapter][chunk] slots when to_partials
   int to_partials;                         // 1: the chunks' sums go to `partials`, reduce_finalize_kernel completes;
                                            // a slot is laid out like the gradient, [C][r_stride] or [r_stride][C]
@@ -618,8 +619,12 @@ template <int OFORM, int NQT>
 __device__ __forceinline__ void reduce_block(const ReduceArgs& a, int bx, int by, char* rsm) {
   char* Xs = rsm;                               // [RD_TOK][RD_COLS] bf16, swizzled
   char* Vh = rsm + RD_TOK * RD_COLS * 2;        // [RD_TOK][r_pad] bf16: leading halves of V
-  const int t = a.order ? a.order[by] : by;
-  const int slab = bx % a.slabs, ch = bx / a.slabs;
+  // (ragged: the further chunks of the adapters that are cut, chunk after chunk, then every adapter's first one)
+  const int slab = bx % a.slabs, more = a.ragged ? (a.chunks_max - 1) * a.ragged_adapters : 0;
+  const int ch = !a.ragged ? bx / a.slabs : by < more ? by / a.ragged_adapters + 1 : 0;
+  const int k = !a.ragged ? by : by < more ? by % a.ragged_adapters : by - more;
+  if (k >= a.n_adapters) return;
+  const int t = a.order ? a.order[k] : k;
   const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int beg = lo + ch * a.tchunk;
   const bool empty = beg >= hi;
@@ -791,8 +796,8 @@ __global__ __launch_bounds__(RD_THREADS, NQT >= 8 ? 1 : 2) void reduce_bf16_kern
 // (Adam with decoupled weight decay; the policy update of the task being trained, paper Sec. 4.2
 // and Alg. 1, whose optimizer state is kept per task) of the fp32 master value and its two
 // moments, and the bf16 value of the next version of the factor.  Adapters without tokens in the
-// batch are not trained by it and are left alone.  A thread owns one element; the slots are laid out like the
-// gradient, so every access is whole lines, and eight slots are read at a time.
+// batch are not trained by it and are left alone.  A thread owns four elements; the slots are laid out
+// like the gradient, so every access is whole lines, and eight slots are read at a time.
 __global__ __launch_bounds__(256) void reduce_finalize_kernel(ReducePair p) {
   const bool second = (int)blockIdx.x >= p.n0;
   const ReduceArgs& a = second ? p.a[1] : p.a[0];
@@ -800,36 +805,52 @@ __global__ __launch_bounds__(256) void reduce_finalize_kernel(ReducePair p) {
   // (ragged: the grid covers the adapters that are cut, the longest ones, first in `order`)
   const int t = a.ragged ? a.order[blockIdx.y] : blockIdx.y;
   const int r = a.table[t].rank;
-  const int64_t off = (int64_t)(blockIdx.x - (second ? p.n0 : 0)) * 256 + threadIdx.x;
+  const int64_t off = ((int64_t)(blockIdx.x - (second ? p.n0 : 0)) * 256 + threadIdx.x) * 4;
   if (off >= a.C * r) return;
   const int len = a.seg_off[t + 1] - a.seg_off[t];
   if (a.opt.on && len == 0) return;
   const int nch = (len + a.tchunk - 1) / a.tchunk;
   if (a.ragged && nch <= 1) return;      // (written by its one block)
   const int64_t slot0 = a.ragged ? (int64_t)a.chunk_base[t] : (int64_t)t * a.chunks_max, slot = a.C * a.r_stride;
-  const float* from = a.partials + slot0 * slot + (a.form == FORM_NT ? off : off / r * a.r_stride + off % r);
-  float sum = 0.f;
+  // (C is a multiple of 8: only ranks that are no multiples of 4 leave an element's neighbours in another row)
+  const bool whole = a.form == FORM_NT || (r & 3) == 0;
+  const float* from[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) from[i] = a.partials + slot0 * slot + (a.form == FORM_NT ? off + i : (off + i) / r * a.r_stride + (off + i) % r);
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  auto read = [&](int ch) {
+    f32x4 s;
+    if (whole) s = *(const f32x4*)(from[0] + ch * slot);
+    else
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] = from[i][ch * slot];
+    return s;
+  };
   int ch = 0;
   for (; ch + 8 <= nch; ch += 8) {
-    float s[8];
+    f32x4 s[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = from[(ch + i) * slot];
+    for (int i = 0; i < 8; ++i) s[i] = read(ch + i);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sum += s[i];
+    for (int i = 0; i < 8; ++i) { sum[0] += s[i][0]; sum[1] += s[i][1]; sum[2] += s[i][2]; sum[3] += s[i][3]; }
   }
-  for (; ch < nch; ++ch) sum += from[ch * slot];
+  for (; ch < nch; ++ch) { const f32x4 s = read(ch); sum[0] += s[0]; sum[1] += s[1]; sum[2] += s[2]; sum[3] += s[3]; }
   if (a.opt.on) {
     const OptFactor f = a.opt.f[t];
-    float p1 = f.master[off];
-    p1 -= a.opt.lr * a.opt.wd * p1;
-    const float m = a.opt.beta1 * f.m[off] + (1.f - a.opt.beta1) * sum;
-    const float v = a.opt.beta2 * f.v[off] + (1.f - a.opt.beta2) * sum * sum;
-    p1 -= a.opt.lr * (m * a.opt.inv_c1) / (sqrtf(v * a.opt.inv_c2) + a.opt.eps);
-    f.master[off] = p1; f.m[off] = m; f.v[off] = v;
-    f.out[off] = float_to_bf16_bits(p1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {        // (nothing is asked of the state's alignment)
+      float p1 = f.master[off + i];
+      p1 -= a.opt.lr * a.opt.wd * p1;
+      const float m = a.opt.beta1 * f.m[off + i] + (1.f - a.opt.beta1) * sum[i];
+      const float v = a.opt.beta2 * f.v[off + i] + (1.f - a.opt.beta2) * sum[i] * sum[i];
+      p1 -= a.opt.lr * (m * a.opt.inv_c1) / (sqrtf(v * a.opt.inv_c2) + a.opt.eps);
+      f.master[off + i] = p1; f.m[off + i] = m; f.v[off + i] = v;
+      f.out[off + i] = float_to_bf16_bits(p1);
+    }
   } else {
-    float* o = (a.which ? a.grads[t].dB : a.grads[t].dA) + off;
-    *o = a.accumulate ? *o + sum : sum;
+    f32x4* out = (f32x4*)((a.which ? a.grads[t].dB : a.grads[t].dA) + off);
+    if (a.accumulate) { const f32x4 was = *out; sum[0] += was[0]; sum[1] += was[1]; sum[2] += was[2]; sum[3] += was[3]; }
+    *out = sum;
   }
 }
 
@@ -874,7 +895,7 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   ReduceArgs a;
   const size_t slot = (size_t)j.C * r_stride * sizeof(float);
   a.order = order;
-  a.ragged = 0; a.chunk_base = nullptr;
+  a.ragged = 0; a.chunk_base = nullptr; a.ragged_adapters = 0; a.n_adapters = n_adapters;
   a.X = j.X; a.ldx = j.ldx; a.C = j.C; a.perm = perm; a.seg_off = seg_off; a.table = table;
   a.grads = grads; a.which = j.which; a.form = j.form; a.V = j.V; a.r_stride = r_stride; a.accumulate = accumulate;
   a.slabs = (int)((j.C + RD_COLS - 1) / RD_COLS);
@@ -890,7 +911,7 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   const bool opt = j.opt && j.opt->on;
   if (!opt && a.chunks_max == 1 && chunk_base != nullptr && order != nullptr && ragged_adapters > 0 && ragged_adapters <= n_adapters &&
       reduce_ragged(j.C, n_adapters, max_seg, ragged_chunk, ragged_slots) && partial_bytes >= ragged_slots * slot) {
-    a.ragged = 1; a.chunk_base = chunk_base;
+    a.ragged = 1; a.chunk_base = chunk_base; a.ragged_adapters = ragged_adapters;
     a.tchunk = ragged_chunk;
     a.chunks_max = (max_seg + ragged_chunk - 1) / ragged_chunk;
     a.to_partials = 1;               // (the finalize kernel runs; it skips the adapters with one piece)
@@ -937,16 +958,21 @@ hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, c
   for (int first = 0; first < 2; first += both ? 2 : 1) {
     ReducePair q = p;
     if (first == 1) q.a[0] = p.a[1];
-    const int x0 = q.a[0].slabs * q.a[0].chunks_max, x1 = both ? q.a[1].slabs * q.a[1].chunks_max : 0;
-    q.n0 = x0;
-    hipLaunchKernelGGL(kern, dim3(x0 + x1, n_adapters), dim3(RD_THREADS), lds, stream, q);
+    int x[2] = {0, 0}, y = 0;
+    for (int j = 0; j < (both ? 2 : 1); ++j) {
+      const ReduceArgs& a = q.a[j];
+      x[j] = a.slabs * (a.ragged ? 1 : a.chunks_max);
+      y = std::max(y, n_adapters + (a.ragged ? (a.chunks_max - 1) * a.ragged_adapters : 0));
+    }
+    q.n0 = x[0];
+    hipLaunchKernelGGL(kern, dim3(x[0] + x[1], y), dim3(RD_THREADS), lds, stream, q);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int64_t blocks[2] = {0, 0};
     int adapters = 0;
     for (int j = 0; j < (both ? 2 : 1); ++j)
       if (q.a[j].to_partials) {
-        blocks[j] = (q.a[j].C * r_stride + 255) / 256;
+        blocks[j] = (q.a[j].C * r_stride + 1023) / 1024;
         adapters = std::max(adapters, q.a[j].ragged ? ragged_adapters : n_adapters);
       }
     if (adapters == 0) continue;
