@@ -44,7 +44,7 @@ struct ShrinkArgs {
   // of its adapter in bf16, u_hi = bf16(u), u_lo = bf16(u - u_hi); row stride 2 * r_stride
   bf16_t* u2;
   const bf16_t* zero_line;  // 16 readable zero bytes (what masked DMA lanes of shrink_ring_kernel fetch)
-  int n_adapters;           // workgroups with blockIdx.y from here on do the side work
+  int n_adapters, row_blocks;   // workgroups from row_blocks * ksplit on do the side work
   SideWork side;
 };
 
@@ -53,8 +53,8 @@ __device__ __forceinline__ AdapterEntry entry_of(const ShrinkArgs& a, int t) { r
 // A workgroup's share of the side work: a row tile's list for each of its waves, and the first one's copy of
 // the tables; false: it has none.
 __device__ __forceinline__ bool side_work(const ShrinkArgs& a) {
-  if ((int)blockIdx.y < a.n_adapters) return false;
-  const int wg = (blockIdx.y - a.n_adapters) * gridDim.x + blockIdx.x;
+  const int wg = (int)blockIdx.x - a.row_blocks * a.ksplit;
+  if (wg < 0) return false;
   const int tile = wg * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (tile < a.side.list_tiles)
     lora_tile_list(a.seg_off, a.n_adapters, a.side.n_inl ? a.side.entry : a.table, 1 - a.which, a.side.list_rows, tile, threadIdx.x & 63,
@@ -65,9 +65,34 @@ __device__ __forceinline__ bool side_work(const ShrinkArgs& a) {
   }
   return true;
 }
-static dim3 side_grid(const ShrinkArgs& a, int x, int waves) {
-  const int wgs = (a.side.list_tiles + waves - 1) / waves, need = wgs > 0 || a.side.n_inl == 0 ? wgs : 1;
-  return dim3(x, a.n_adapters + (need + x - 1) / x);
+static int side_blocks(const ShrinkArgs& a, int waves) {
+  const int wgs = (a.side.list_tiles + waves - 1) / waves;
+  return wgs > 0 || a.side.n_inl == 0 ? wgs : 1;
+}
+
+// The adapter that row block b belongs to, when every segment is cut into blocks of `rows` rows, and the block's
+// first row; -1: there are fewer blocks.  A lane per adapter, all lanes of a wave call it.  (A grid of the
+// longest segment's blocks for every adapter was mostly workgroups without rows: 6400 for 1312, 16896 rows of
+// 64 adapters.)
+__device__ __forceinline__ int row_block(const int32_t* __restrict__ seg_off, int n, int rows, int b, int* row0, int* end) {
+  const int lane = threadIdx.x & 63;
+  for (int t0 = 0; t0 < n; t0 += 64) {
+    const int t = t0 + lane;
+    const int lo = t < n ? seg_off[t] : 0, hi = t < n ? seg_off[t + 1] : 0;
+    const int blocks = (hi - lo + rows - 1) / rows;
+    int inc = blocks;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
+    const uint64_t hit = __ballot(b < inc);
+    if (hit) {
+      const int l = __ffsll((unsigned long long)hit) - 1;
+      *row0 = __builtin_amdgcn_readlane(lo, l) + (b - __builtin_amdgcn_readlane(inc - blocks, l)) * rows;
+      *end = __builtin_amdgcn_readlane(hi, l);
+      return t0 + l;
+    }
+    b -= __builtin_amdgcn_readlane(inc, 63);
+  }
+  return -1;
 }
 
 // u (scaled, fp32) and its two-term bf16 split for row m, rank index q of an adapter with padded rank r_pad
@@ -81,7 +106,7 @@ __device__ __forceinline__ void shrink_store(const ShrinkArgs& a, int64_t m, int
   }
 }
 
-// grid: x = row blocks of the largest segment * ksplit, y = adapter
+// grid: row blocks (T_lora / rows + adapters, at most) * ksplit, then the side work
 // NQT: 16-wide output tiles held per wave (covers the largest padded rank of the call)
 // The kernel is bound by the one pass over X, so the loop is software-pipelined through
 // registers: the x fragments and the factor tile of step s + 1 are requested before the MFMAs
@@ -90,11 +115,10 @@ template <int LFORM, int NQT>
 __global__ __launch_bounds__(SH_THREADS, (NQT >= 8 ? 1 : 2)) void shrink_bf16_kernel(ShrinkArgs a) {
   extern __shared__ __attribute__((aligned(16))) char Ls[];   // [r_pad][SH_PITCH]
   if (side_work(a)) return;
-  const int t = blockIdx.y;
-  const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int rb = blockIdx.x / a.ksplit, ks = blockIdx.x - rb * a.ksplit;
-  const int row0 = lo + rb * SH_ROWS;
-  if (row0 >= hi) return;
+  int row0, hi;
+  const int t = row_block(a.seg_off, a.n_adapters, SH_ROWS, rb, &row0, &hi);
+  if (t < 0) return;
   const AdapterEntry e = entry_of(a, t);
   const bf16_t* L = (const bf16_t*)(a.which ? e.B : e.A);
   const int r = e.rank;
@@ -247,11 +271,10 @@ __global__ __launch_bounds__(256) void shrink_ring_kernel(ShrinkArgs a) {
   constexpr int SR_ROWS = 64 * RT, SR_X_BYTES = SR_ROWS * 64 * 2, XI = 2 * RT;   // rows, x part of a slot, x instructions per wave and k-tile
   extern __shared__ __attribute__((aligned(16))) char smem[];
   if (side_work(a)) return;
-  const int t = blockIdx.y;
-  const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int rb = blockIdx.x / a.ksplit, ks = blockIdx.x - rb * a.ksplit;
-  const int row0 = lo + rb * SR_ROWS;
-  if (row0 >= hi) return;
+  int row0, hi;
+  const int t = row_block(a.seg_off, a.n_adapters, SR_ROWS, rb, &row0, &hi);
+  if (t < 0) return;
   const AdapterEntry e = entry_of(a, t);
   const bf16_t* L = (const bf16_t*)(a.which ? e.B : e.A);
   const int r = e.rank;
@@ -399,10 +422,9 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
   union Frag { uint4 u; bf16x8 v; };
   extern __shared__ __attribute__((aligned(16))) char red[];   // [SS_WAVES][nqt][64] f32x4
   if (side_work(a)) return;
-  const int t = blockIdx.y;
-  const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
-  const int row0 = lo + blockIdx.x * 16;
-  if (row0 >= hi) return;
+  int row0, hi;
+  const int t = row_block(a.seg_off, a.n_adapters, 16, blockIdx.x, &row0, &hi);
+  if (t < 0) return;
   const AdapterEntry e = entry_of(a, t);
   const bf16_t* L = (const bf16_t*)(a.which ? e.B : e.A);
   const int r = e.rank, r_pad = (r + 15) & ~15, nqt = r_pad >> 4;
@@ -467,13 +489,21 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
   }
 }
 
-// Second step of a shrink with a split contraction: block = (adapter, 16 grouped rows), thread =
-// (row, 16 rank indices apart); the splits are added in split order, then scaled.
+// Second step of a shrink with a split contraction: block = 16 grouped rows, thread = (row, 16 rank indices
+// apart); the splits are added in split order, then scaled.
 __global__ __launch_bounds__(256) void shrink_finalize_kernel(ShrinkArgs a) {
-  const int t = blockIdx.y;
-  const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
-  const int64_t m = lo + (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-  if (m >= hi) return;
+  const int lane = threadIdx.x & 63;
+  const int m0 = blockIdx.x * 16 + (threadIdx.x >> 6) * 4, m = m0 + (lane >> 4);     // (four rows a wave)
+  int t = 0;                                                     // segments that end at or before the row
+  for (int t0 = 0; t0 < a.n_adapters; t0 += 64) {
+    const int end = t0 + lane < a.n_adapters ? a.seg_off[t0 + lane + 1] : 0x7fffffff;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int before = __popcll(__ballot(end <= m0 + i));
+      if (lane >> 4 == i) t += before;
+    }
+  }
+  if (m >= a.T_lora) return;
   const AdapterEntry e = entry_of(a, t);
   const int r_pad = (e.rank + 15) & ~15;
   for (int q = threadIdx.x & 15; q < r_pad; q += 16) {
@@ -521,7 +551,8 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
     const size_t lds = (size_t)SS_WAVES * (r_stride / 16) * 64 * sizeof(f32x4);
     const int nq = r_stride / 16;
     auto kern = nq <= 1 ? shrink_small_nt_kernel<1> : nq <= 2 ? shrink_small_nt_kernel<2> : nq <= 4 ? shrink_small_nt_kernel<4> : shrink_small_nt_kernel<8>;
-    hipLaunchKernelGGL(kern, side_grid(a, (max_seg + 15) / 16, SS_WAVES), dim3(64 * SS_WAVES), lds, stream, a);
+    a.row_blocks = (int)((T_lora + 15) / 16) + n_adapters;
+    hipLaunchKernelGGL(kern, dim3(a.row_blocks + side_blocks(a, SS_WAVES)), dim3(64 * SS_WAVES), lds, stream, a);
     return hipGetLastError();
   }
   // both operands by DMA where every piece of a factor row stays inside the row; 128 rows per
@@ -529,7 +560,6 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
   const bool ring = zero_line != nullptr && (lora_form == FORM_NT || ranks_mult8);
   const bool long_seg = T_lora >= (int64_t)512 * n_adapters;
   const int rows = ring ? (long_seg ? 128 : 64) : SH_ROWS;
-  const int rb_max = (max_seg + rows - 1) / rows;
   const int kst = (int)((C + SH_KSTG - 1) / SH_KSTG);
   int ksplit = shrink_splits(C, T_lora, n_adapters, rows);
   // (no room for the splits' sums: fewer splits)
@@ -567,10 +597,11 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
     hipError_t e = allow_big_lds((const void*)kern, (lora_form == FORM_NT ? 0 : 4) + (nq <= 1 ? 0 : nq <= 2 ? 1 : nq <= 4 ? 2 : 3));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, side_grid(a, rb_max * ksplit, SH_THREADS / 64), dim3(SH_THREADS), lds, stream, a);
+  a.row_blocks = (int)((T_lora + rows - 1) / rows) + n_adapters;
+  hipLaunchKernelGGL(kern, dim3(a.row_blocks * ksplit + side_blocks(a, SH_THREADS / 64)), dim3(SH_THREADS), lds, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || ksplit == 1) return e;
-  hipLaunchKernelGGL(shrink_finalize_kernel, dim3((max_seg + 15) / 16, n_adapters), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(shrink_finalize_kernel, dim3((unsigned)((T_lora + 15) / 16)), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
