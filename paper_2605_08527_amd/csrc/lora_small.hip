@@ -229,10 +229,12 @@ __global__ __launch_bounds__(SH_THREADS, (NQT >= 8 ? 1 : 2)) void shrink_bf16_ke
       }
 }
 
-// The same shrink with both operands moved global -> LDS by DMA through a ring of four 64-wide
+// The same shrink with both operands moved global -> LDS by DMA through a ring of two or three 64-wide
 // k-tiles: every request of a wave covers whole 128-byte row segments (the register-staged kernel
-// above fetches 64-byte pieces and its factor tile through VGPRs) and three k-tiles are in flight
-// per block.  A block takes 128 rows of one adapter where the segments are long (half the factor
+// above fetches 64-byte pieces and its factor tile through VGPRs).  Few slots and more blocks on a compute
+// unit: with four slots two blocks fit, and while one looks up its rows or stores, little is under way
+// (16896 rows of 64 adapters, rank-major / contraction-major factors: four slots 43 / 56 us, three 35 / 46,
+// two 39 / 41; 128 rows a block, 262144 rows: 876 / 354, 874 / 358, 884 / 308).  A block takes 128 rows of one adapter where the segments are long (half the factor
 // traffic of 64-row blocks) and 64 where they are short.  Measured on MI355X against the
 // register-staged kernel: 10 - 15 % faster for factors stored rank-major, 3 - 10 % for
 // contraction-major ones.  x part of a slot: [128 rows][64 k], 16-byte units
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(SH_THREADS, (NQT >= 8 ? 1 : 2)) void shrink_bf16_ke
 // (LFORM NT), [64 k][r_pad] read with transposing LDS reads for factors stored [C][rank] (LFORM
 // NN, ranks multiples of 8).  Rows past the end of the segment repeat its last row (never stored),
 // rank rows past r and contraction units past the end fetch zeros.
-static constexpr int SR_NS = 4;
+static constexpr int sr_slots(int lform, int rt) { return lform == FORM_NT && rt == 1 ? 3 : 2; }
 
 __device__ __forceinline__ void sr_wait(int n) {      // at most n vector-memory requests outstanding (n <= 16)
   switch (n) {
@@ -268,6 +270,7 @@ __device__ __forceinline__ void sr_wait(int n) {      // at most n vector-memory
 // RT: 16-row tiles per wave (block = 64 RT rows)
 template <int LFORM, int NQT, int RT>
 __global__ __launch_bounds__(256) void shrink_ring_kernel(ShrinkArgs a) {
+  constexpr int SR_NS = sr_slots(LFORM, RT);
   constexpr int SR_ROWS = 64 * RT, SR_X_BYTES = SR_ROWS * 64 * 2, XI = 2 * RT;   // rows, x part of a slot, x instructions per wave and k-tile
   extern __shared__ __attribute__((aligned(16))) char smem[];
   if (side_work(a)) return;
@@ -579,7 +582,7 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
   kern_t kern;
   if (ring) {
     const int nqt_max = nq <= 1 ? 1 : nq <= 2 ? 2 : nq <= 4 ? 4 : 8;
-    lds = (size_t)SR_NS * (rows * 128 + nqt_max * 16 * 128);
+    lds = (size_t)sr_slots(lora_form, rows / 64) * (rows * 128 + nqt_max * 16 * 128);
 #define SR_PICK(F_, R_) (nq <= 1 ? shrink_ring_kernel<F_, 1, R_> : nq <= 2 ? shrink_ring_kernel<F_, 2, R_> \
                          : nq <= 4 ? shrink_ring_kernel<F_, 4, R_> : shrink_ring_kernel<F_, 8, R_>)
     if (lora_form == FORM_NT) kern = long_seg ? SR_PICK(FORM_NT, 2) : SR_PICK(FORM_NT, 1);
