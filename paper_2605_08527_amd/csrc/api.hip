@@ -1350,7 +1350,7 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
                                     p.wt_bytes, d->layout == MARLAAS_LAYOUT_TORCH ? (const bf16_t*)d->W_t : nullptr, &dma, (const bf16_t*)d->W_packed_bwd, use_packed, &dsync, st));
     if (want_grads && d->n_adapters > 0) {
       const ReduceJob jobs[2] = {{dy, lddy, d->d_out, u, 1, db_form, opt ? &opt[1] : nullptr}, {x, d->ldx, d->d_in, v, 0, da_form, opt ? &opt[0] : nullptr}};
-      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_bf16(jobs, perm, map->seg_off_dev, d->n_adapters, map->max_seg, table, grads, rs, accumulate,
+      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_bf16(jobs, perm, map->seg_off_dev, d->n_adapters, map->T_lora, map->max_seg, table, grads, rs, accumulate,
                                       part, part ? p.part_bytes : 0, map->order_dev, map->chunk_base_dev, map->ragged_chunk, map->ragged_slots,
                                       map->ragged_adapters, st));
     }

@@ -323,7 +323,7 @@ struct ReduceJob {
   int which, form;          // 0: dA, 1: dB; storage of the gradient
   const ReduceOpt* opt;     // or null
 };
-hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, const int32_t* seg_off, int n_adapters, int max_seg,
+hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, const int32_t* seg_off, int n_adapters, int64_t T_lora, int max_seg,
                               const AdapterEntry* table, const GradEntry* grads, int r_stride, int accumulate, float* partials, size_t partial_bytes,
                               const int32_t* order, const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters,
                               hipStream_t stream);

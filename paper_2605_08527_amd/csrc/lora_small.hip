@@ -925,7 +925,8 @@ size_t reduce_partial_bytes(int64_t C, int n_adapters, int max_seg, int r_stride
 // One job's arguments: how its segments are cut, and the bytes of sums it leaves.
 static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int32_t* seg_off, int n_adapters, int max_seg, const AdapterEntry* table,
                               const GradEntry* grads, int r_stride, int accumulate, size_t partial_bytes, const int32_t* order,
-                              const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters, ReduceArgs* out, size_t* bytes) {
+                              const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters, int64_t slot_rows, ReduceArgs* out,
+                              size_t* bytes) {
   ReduceArgs a;
   const size_t slot = (size_t)j.C * r_stride * sizeof(float);
   a.order = order;
@@ -946,8 +947,11 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   if (!opt && a.chunks_max == 1 && chunk_base != nullptr && order != nullptr && ragged_adapters > 0 && ragged_adapters <= n_adapters &&
       reduce_ragged(j.C, n_adapters, max_seg, ragged_chunk, ragged_slots) && partial_bytes >= ragged_slots * slot) {
     a.ragged = 1; a.chunk_base = chunk_base; a.ragged_adapters = ragged_adapters;
-    a.tchunk = ragged_chunk;
-    a.chunks_max = (max_seg + ragged_chunk - 1) / ragged_chunk;
+    // (every cut costs a sum written and read: pieces of twice the length where the rows that a place on the chip
+    // has to take, two workgroups a unit, are more than that.  16896 rows, 64 adapters, 5120 x 5120: pieces of
+    // 576 rows 117 + 18 us, 1088 rows 110 + 13, 1600 rows 115 + 10, whole segments 151.)
+    a.tchunk = slot_rows >= 2 * ragged_chunk ? 2 * ragged_chunk : ragged_chunk;
+    a.chunks_max = (max_seg + a.tchunk - 1) / a.tchunk;
     a.to_partials = 1;               // (the finalize kernel runs; it skips the adapters with one piece)
     *bytes = ragged_slots * slot;
   }
@@ -963,17 +967,18 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   return hipSuccess;
 }
 
-hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, const int32_t* seg_off, int n_adapters, int max_seg,
+hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, const int32_t* seg_off, int n_adapters, int64_t T_lora, int max_seg,
                               const AdapterEntry* table, const GradEntry* grads, int r_stride, int accumulate, float* partials, size_t partial_bytes,
                               const int32_t* order, const int32_t* chunk_base, int ragged_chunk, int ragged_slots, int ragged_adapters,
                               hipStream_t stream) {
   if (n_adapters <= 0) return hipSuccess;
   if (partials == nullptr) partial_bytes = 0;
+  const int64_t slot_rows = ((jobs[0].C + RD_COLS - 1) / RD_COLS + (jobs[1].C + RD_COLS - 1) / RD_COLS) * T_lora / 512;
   ReducePair p;
   size_t bytes[2];
   for (int j = 0; j < 2; ++j) {
     const hipError_t e = reduce_args(jobs[j], perm, seg_off, n_adapters, max_seg, table, grads, r_stride, accumulate, partial_bytes, order, chunk_base,
-                                     ragged_chunk, ragged_slots, ragged_adapters, &p.a[j], &bytes[j]);
+                                     ragged_chunk, ragged_slots, ragged_adapters, slot_rows, &p.a[j], &bytes[j]);
     if (e != hipSuccess) return e;
     bytes[j] = (bytes[j] + 255) / 256 * 256;
     p.a[j].partials = partials;
