@@ -126,15 +126,26 @@ __device__ __forceinline__ int find_job(const GemmArgs& a, const AdapterEntry* t
   return tm;
 }
 
+// LDS: the ring or, once it is free, the exchange of the sums and, behind it, the rows' u; in place of it where
+// two workgroups would not fit a compute unit otherwise (ranks above 48 or 112 by the tile); the rows' tables.
+template <int RB, int WN>
+__host__ __device__ inline int mid_tables(int r_stride) { return 16 * RB * 20 + RB * 4 + 16 + RB * 2 * r_stride * (int)sizeof(uint16_t); }
+template <int RB, int WN>
+__host__ __device__ inline int mid_sums(int r_stride) {
+  const int u = 16 * RB * (r_stride + 4) * (int)sizeof(float), red = MidShape<RB, WN>::RED;
+  return red + u + mid_tables<RB, WN>(r_stride) <= 80 * 1024 ? red + u : red > u ? red : u;
+}
+
 template <int RB, int WN>
 __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   typedef MidShape<RB, WN> S_;
   constexpr int KG = S_::KG, MD_K = S_::K, UR = MD_K / 8, NS = S_::NS, SLOT = S_::SLOT, BM = 16 * RB, NR = (RB + KG - 1) / KG;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int us = a.r_stride + 4, oct_max = 2 * a.r_stride;       // (octet: 8 ranks of one adapter; so many can a 16-row block have)
-  const int base_bytes = NS * SLOT > S_::RED + BM * us * 4 ? NS * SLOT : S_::RED + BM * us * 4;
+  const int sums = mid_sums<RB, WN>(a.r_stride), base_bytes = NS * SLOT > sums ? NS * SLOT : sums;
+  const bool apart = sums == S_::RED + BM * us * 4;
   f32x4* red = (f32x4*)smem;
-  float* u_s = (float*)(smem + S_::RED);                         // [BM][us]: the rows' u, behind the exchange of the sums
+  float* u_s = (float*)(smem + (apart ? S_::RED : 0));           // [BM][us]: the rows' u
   uint64_t* rL_s = (uint64_t*)(smem + base_bytes);               // per row: expand factor,
   int32_t* tok_s = (int32_t*)(rL_s + BM);                        // token (-1: past the end),
   int32_t* t_s = tok_s + BM;                                     // adapter (-1: none),
@@ -299,6 +310,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   uint4 pre[NR][PD][2];
   uint64_t uw[MID_SPLITS][2];                                    // first reading of the first four values of u this thread fetches
   const int urow = tid / (a.r_stride >> 2), uq0 = (tid - urow * (a.r_stride >> 2)) * 4;
+  const bool early = apart && a.ksplit == 1;
   // u and the first octets' factors, a trip through the fabric each: on the way while the sums meet
   auto request_u = [&]() {
 #pragma unroll
@@ -486,7 +498,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
     for (int i = 0; i < RB; ++i) if (nt > 0) asm volatile("" : "+v"(xf[i]));
-    if (lora && a.ksplit == 1) request_u();
+    if (early && lora) request_u();
     if (EARLY && lora && a.ksplit == 1) request_factors(0);
     __syncthreads();                                             // the ring is free
     // ---- the contraction groups' sums: row block i is finished by group i mod KG
@@ -497,7 +509,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) red[(((i * WN + wn) * 2 + cb) * (KG - 1) + d) * 64 + lane] = acc[i][cb];
       }
-    if (lora && a.ksplit == 1) take_u();
+    if (early && lora) take_u();
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RB; ++i)
@@ -631,8 +643,9 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     if (!EARLY || a.ksplit > 1)                                  // (earlier there are no registers for them)
 #pragma unroll
       for (int j = 0; j < NR; ++j) request_factors(j);
-    if (a.ksplit > 1) {                                          // (u after the sums, which other workgroups wait for)
+    if (!early) {                                                // (u after the sums, which other workgroups wait for)
       request_u();
+      if (!apart) __syncthreads();                               // (the sums have met: their place is u's)
       take_u();
       __syncthreads();
     }
@@ -692,9 +705,9 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
 
 template <int RB, int WN>
 static hipError_t launch_mid(const GemmArgs& a, int cu_count, hipStream_t stream) {
-  constexpr int BM = 16 * RB;
-  const size_t u_bytes = MidShape<RB, WN>::RED + (size_t)BM * (a.r_stride + 4) * sizeof(float), base = MidShape<RB, WN>::NS * MidShape<RB, WN>::SLOT;
-  const size_t lds = (base > u_bytes ? base : u_bytes) + BM * 20 + RB * 4 + 16 + (size_t)RB * 2 * a.r_stride * sizeof(uint16_t);
+  constexpr int ring = MidShape<RB, WN>::NS * MidShape<RB, WN>::SLOT;
+  const int sums = mid_sums<RB, WN>(a.r_stride);
+  const size_t lds = (size_t)(ring > sums ? ring : sums) + mid_tables<RB, WN>(a.r_stride);
   static std::atomic<uint64_t> done_dev{0};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -723,16 +736,17 @@ static hipError_t launch_mid(const GemmArgs& a, int cu_count, hipStream_t stream
 // 6 with four), and a last wave of workgroups costs more than that.
 //   Whole (up to 16 steps a wave), where every workgroup has a unit of its own: 157 rows 22.7 -> 19.9 us.
 //   Else four pieces, if all workgroups are on the chip at once: 256 rows 23.8 -> 22.4, 157 rows 14336 x 4096
-//   51 -> 43; two, if only those are (q/k/v of 256 rows: four pieces 47 us, two 33).
-//   Else as few as steps allow (512 rows, 5120 x 5120, 64 adapters: 75 -> 68).
+//   51 -> 43; two, if only those are, but for a few (q/k/v of 256 rows: four pieces 47 us, two 33; 256 rows of
+//   rank 64, 568 workgroups in two pieces at most: 33.3, whole 36.5).
+//   Else whole as far as the steps allow (300 rows of rank 128: 50 us, in two 62; 512 rows, 5120 x 5120, 64
+//   adapters, with their regrouping 82 and 88).
 // Few steps are not cut: a value of u is read once for each piece.
 static int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t consumers, int64_t jobs, int cu_count) {
   const int64_t steps = ((Kc + 31) / 32 + MD_WAVES - 1) / MD_WAVES;      // 32-deep steps of a wave
   if (steps <= 8 || (steps <= 16 && consumers + jobs <= cu_count)) return 1;
   int s = MID_SPLITS;
-  while (s > 1 && (consumers + jobs * s > 2 * cu_count || u_floats * s > MID_U_FLOATS)) s /= 2;
-  if (s == 1 && steps > 24 && 2 * u_floats <= MID_U_FLOATS) s = 2;
-  return s;
+  while (s > 1 && (consumers + jobs * s > (s == 2 ? 9 : 8) * cu_count / 4 || u_floats * s > MID_U_FLOATS)) s /= 2;
+  return s == 1 && steps > 24 && 2 * u_floats <= MID_U_FLOATS ? 2 : s;
 }
 
 hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream_t stream) {
