@@ -909,12 +909,17 @@ static int max_rank_tiles(const marlaas_lora_desc* d) {
   return tiles;
 }
 
-// The most shrink jobs of gemm_mid.hip that the adapters of T rows can have, however the rows are grouped: each
-// adapter's 16-rank tiles once, and again for every pair of row blocks that begins inside an adapter's rows.
-static int max_shrink_jobs(const marlaas_lora_desc* d, const MidPlan& plan) {
-  const int64_t rows = 16 * plan.rb;
-  const int64_t pairs = d->T / rows * ((plan.rb + 1) / 2) + (d->T % rows + 31) / 32;
-  return max_rank_tiles(d) + (int)(pairs - 1) * ((max_rank_of(d) + 15) / 16);
+static MidLora mid_lora_of(const marlaas_lora_desc* descs, int32_t n_proj, int rs) {
+  MidLora l;
+  l.n = descs[0].n_adapters; l.r_stride = rs;
+  for (int p = 0; p < n_proj; ++p) {
+    const int32_t* ranks = ranks_of(&descs[p]);
+    int sum = 0, tiles = 0;
+    for (int t = 0; t < l.n; ++t) { sum += ranks[t]; tiles += (ranks[t] + 15) / 16; l.tile_max = std::max(l.tile_max, (int)(ranks[t] + 15) / 16); }
+    l.ranks = std::max(l.ranks, sum); l.tiles = std::max(l.tiles, tiles);
+    l.tiles_max = std::max(l.tiles_max, max_rank_tiles(&descs[p]));
+  }
+  return l;
 }
 
 // A call on packed weights (W and ldw of `proj` filled in) that one of the one-launch kernels does best:
@@ -929,10 +934,10 @@ static int launch_packed(marlaas_ctx* ctx, int32_t* exchange, const marlaas_lora
   *done = false;
   int ext = 0;
   for (int t = 0; lora && t < d->n_adapters; ++t) if (map->seg_off[t + 1] > map->seg_off[t]) ext += ranks_of(d)[t];
-  const MidPlan mid = gemm_mid_plan(form, d->T, ldx, Kc, proj, n_proj, lora, ext, rs, &sync);
+  const MidLora ml = lora ? mid_lora_of(descs, n_proj, rs) : MidLora();
+  const MidPlan mid = gemm_mid_plan(form, d->T, ldx, Kc, proj, n_proj, ml, ext, &sync);
   if (mid.rb) {
-    int jobs = 0;
-    for (int p = 0; p < n_proj && lora; ++p) jobs = std::max(jobs, max_shrink_jobs(&descs[p], mid));
+    const int jobs = lora ? mid_max_jobs(d->T, mid.rb, ml) : 0;
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_mid(x, ldx, form, d->T, Kc, perm, map->seg_off_dev, n, table, which, proj, n_proj, out_f32, u, rs, mid,
                                       jobs, (const bf16_t*)ctx->zero_dev, &sync, st));
     *done = true;

@@ -204,6 +204,16 @@ static_assert(80 * 8 * MID_SPLITS < MID_JOBS, "every row its own adapter of rank
 // Readings of a bounded wait, a round trip through the fabric each (1 to 1.5 us under load): what is waited for
 // takes a tenth of it where its workgroups are on the chip, and doing without costs a few hundred microseconds.
 static constexpr int MID_POLLS = 256;
+// The adapters of a call as its plan takes them: how many (0: none), their ranks and 16-rank tiles in all (of a
+// projection, the largest), the largest adapter's tiles, and the most that the adapters of T rows can have.
+struct MidLora { int n = 0, ranks = 0, tiles = 0, tile_max = 0, tiles_max = 0, r_stride = 0; };
+// The most shrink jobs of gemm_mid.hip (a projection's) that the adapters of T rows can have in tiles of 16 rb rows,
+// however the rows are grouped: each adapter's 16-rank tiles once, and again for every pair of row blocks that
+// begins inside an adapter's rows.
+inline int mid_max_jobs(int64_t T, int rb, const MidLora& l) {
+  const int64_t rows = 16 * rb, pairs = T / rows * ((rb + 1) / 2) + (T % rows + 31) / 32;
+  return l.tiles_max + (int)(pairs - 1) * l.tile_max;
+}
 struct MidPlan { int rb = 0, wn = 2, ksplit = 1, tiles_m = 0; double us = 0.0; };     // rb = rows / 16; 0: none
 
 // What lets the large-batch GEMM fetch the expand's operands by DMA: u (or v) as a two-term bf16
@@ -256,7 +266,7 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
 // all adapters in the batch (0: none); seg_off: rows of the adapters (device); proj_jobs: the most shrink jobs
 // (16 ranks of an adapter x a pair of 16-row blocks of a row tile, 16 plan.rb rows) that any grouping of T rows
 // has in any projection.
-MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, bool lora, int ext, int r_stride, const DecodeSync* sync);
+MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, const MidLora& lora, int ext, const DecodeSync* sync);
 hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,
                                 const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
                                 float* u, int r_stride, const MidPlan& plan, int proj_jobs, const bf16_t* zero_line, const DecodeSync* sync,

@@ -1011,8 +1011,8 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
 }
 
 // ---- some more rows
-MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, bool lora, int ext, int r_stride, const DecodeSync* sync) {
-  if (T <= 0 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || (lora && (!sync->counters || form != FORM_NT || !sync->grp_ids || r_stride > 128)) ||
+MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, const MidLora& lora, int ext, const DecodeSync* sync) {
+  if (T <= 0 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || (lora.n > 0 && (!sync->counters || form != FORM_NT || !sync->grp_ids || lora.r_stride > 128)) ||
       (sync->mode != DECODE_FINISH_AUTO && sync->mode != DECODE_FINISH_IN_KERNEL))
     return MidPlan();
   int64_t cols = 0;

@@ -769,17 +769,20 @@ hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream
   return p.rb == 4 ? launch_mid<4, 2>(a, cu_count, stream) : launch_mid<5, 2>(a, cu_count, stream);
 }
 
-// Estimated run time of a tiling in microseconds; the constants are a fit to timed runs over 5 to 1024 rows,
-// contractions of 1024 to 14336 and 1024 to 28672 columns, and only the order of the tilings matters.  A
-// k-tile's time when a workgroup has its compute unit to itself, which two on one unit take 2.5 times as long
-// for; longer rows of x and W cost a little more; against it what the fabric delivers; splits pay for the
-// exchange.
-MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool lora, int max_split) {
-  static const double tile_us[2][2] = {{0.29, 0.25}, {0.38, 0.31}};       // [rb - 4][wn == 4]
+// Estimated run time of a tiling in microseconds.  The constants are a fit to timed runs of every tiling over 24
+// to 700 rows, contractions of 1024 to 14336 and 1024 to 28672 columns, without adapters, with 32 of rank 16 and
+// with 64 of ranks 8 to 64; only the order of the tilings matters (the one chosen takes 1.7 % longer than the best
+// of them on the average, 1.036 times as long with the constants of an earlier version of the kernel: 256 rows of
+// q/k/v 33.7 -> 31.5 us, 157 rows 29.6 -> 27.1, 512 rows of 64 adapters, 5120 x 5120, 60 -> 57).  A k-tile's time when
+// a workgroup has its compute unit to itself, which two on one unit take 1.8 times as long for; against it what
+// the fabric delivers; the expand by the ranks and row blocks of a wave; producers, where they share a unit with
+// a consumer or make a last wave of workgroups; the exchange of split contractions.
+MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora, int max_split) {
+  static const double tile_us[2][2] = {{0.306, 0.252}, {0.334, 0.282}};   // [rb - 4][wn == 4]
   MidPlan best;
   int64_t cols = 0;
   for (int q = 0; q < n_proj; ++q) cols += proj[q].Nout;
-  const double stretch = Kc > 4096 ? 1.0 + 0.12 * log2((double)Kc / 4096.0) : 1.0;
+  auto up_to_1 = [](double v) { return v < 0.0 ? 0.0 : v > 1.0 ? 1.0 : v; };
   for (int wn = 2; wn <= 4; wn += 2) {
     const int64_t kt = 32 * (MD_WAVES / wn), ktiles = (Kc + kt - 1) / kt;
     int64_t tiles_n = 0;
@@ -789,18 +792,27 @@ MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool 
       for (int s = 1; s <= max_split; s *= 2) {
         const int64_t wgs = tiles_m * tiles_n * s;
         if (s > 1 && (wgs > MID_SPLIT_WGS || ktiles < 4 * s)) continue;
-        const double t1 = tile_us[rb - 4][wn == 4] * stretch * (double)((ktiles + s - 1) / s), t2 = 2.5 * t1;
+        const double t1 = tile_us[rb - 4][wn == 4] * (double)((ktiles + s - 1) / s), t2 = 1.827 * t1;
         double fill;
         if (wgs <= 256) {
-          fill = t1 * (wgs > 128 ? 1.0 + 0.58 * (double)(wgs - 128) / 128.0 : 1.0);
+          fill = t1 * (wgs > 128 ? 1.0 + 0.066 * (double)(wgs - 128) / 128.0 : 1.0);
         } else {
-          const double left = (double)(wgs % 512);
-          fill = (double)(wgs / 512) * (t2 + 2.3);
-          if (left > 0.0) fill += 2.3 + t1 + (left > 256.0 ? (t2 - t1) * (left - 256.0 < 82.0 ? (left - 256.0) / 82.0 : 1.0) : 0.0);
+          const int64_t left = wgs % 512;
+          fill = (double)(wgs / 512) * (t2 + 2.172);
+          if (left > 0) fill += 2.172 + 1.066 * t1 + (t2 - 1.066 * t1) * up_to_1((double)(left - 256) / 11.767);
         }
-        const double fabric = (2.0 * cols * Kc + 16.0 * T * Kc / s) / 6.4e6;
-        double us = 4.1 + cbrt(fill * fill * fill + fabric * fabric * fabric) + (lora ? 6.2 + T / 300.0 : 0.0);
-        if (s > 1) us += (s > 2 ? 4.1 : 2.1) + (wgs > 192 ? 0.9 * (double)(wgs - 192) / 64.0 : 0.0);
+        const double fabric = (2.0 * cols * Kc + 16.0 * T * Kc / s) / 11.6e6;
+        double us = 7.687 + cbrt(fill * fill * fill + fabric * fabric * fabric);
+        if (lora.n > 0) {
+          const int pieces = mid_u_splits(Kc, T * lora.r_stride * n_proj, wgs, (int64_t)n_proj * mid_max_jobs(T, rb, lora), 256);
+          const int64_t with_rows = (int64_t)(0.6 * T) + 1 < lora.n ? (int64_t)(0.6 * T) + 1 : lora.n;      // (adapters, about)
+          const int64_t prods = n_proj * pieces * (with_rows * (lora.tiles / lora.n > 1 ? lora.tiles / lora.n : 1) + T / (16 * rb) * ((rb + 1) / 2));
+          const double prod_us = 10.735 * Kc / 4096.0 / pieces + 0.498;
+          us += 0.562 + 2.009 * ((rb * wn + 7) / 8) * lora.ranks / (16.0 * lora.n);
+          us += prod_us * (wgs <= 256 ? 0.574 * up_to_1((double)(wgs + prods - 256) / 17.45) : 0.289 * up_to_1((double)prods / 256.0));
+          us += prod_us * 0.918 * up_to_1((double)((wgs < 512 ? wgs : 512) + prods - 512) / 17.45);
+        }
+        if (s > 1) us += (s > 2 ? 2.442 : 2.257) * (0.5 + rb * wn / 32.0) + (wgs > 192 ? 0.186 * (double)(wgs - 192) / 64.0 : 0.0);
         if (best.rb == 0 || us < best.us) { best.us = us; best.rb = rb; best.wn = wn; best.ksplit = s; best.tiles_m = (int)tiles_m; }
       }
     }
@@ -810,17 +822,21 @@ MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, bool 
 
 // Whether the call is better off elsewhere (ext: ranks of all adapters in the batch, 0: no adapters).
 //   Up to 16 rows the few-row kernel, up to 32 while its workgroups, which hold all of x, have little of it.
-//   Above 384 rows the wide kernel as soon as its rate makes up for its shrink's launches and its ext
-//   columns: mostly few adapters on large weights (512 rows, 4096 x 14336: no adapter 55 against 88 us, one
-//   66 / 93, 32 adapters of rank 16 107 / 100, 64 of mixed ranks 145 / 123).
-//   Up to 256 rows the split kernel with its separate finish on a long contraction and few columns, where
-//   the row tiles here are few and their splits expensive (200 rows, 14336 x 4096, rank 16: 61 / 72).
+//   Above 384 rows the wide kernel where its plan, without adapters, or its rate, which has to make up for its
+//   shrink's launch and its ext columns, says so (400 rows, 4096 x 14336, no adapter: 48 against 63 us, 32 adapters
+//   of rank 16 86 / 75; 4096 x 4096, no adapter, 27 / 23; 14336 x 4096, 32 adapters, 109 / 75).
+//   Up to 256 rows the split kernel with its separate finish on a long contraction and few columns, where the row
+//   tiles here are few and their splits expensive (256 rows, 14336 x 4096, no adapter: 36 / 41, 157 rows 37 / 31;
+//   200 rows, 20480 x 2048, 32 adapters of rank 16: 44 / 52, 14336 x 4096 54 / 49; up to 128 rows with adapters
+//   never: 100 rows 45 / 35 and 37 / 36).
 bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext) {
   if (T <= 16) return false;
   if (T <= 32) return T * Kc > 140000 || Kc * cols > 50000000;
-  if (T > 384) return p.us < 14.0 + 2.0 * T * Kc * cols / 1.25e9 + (ext > 0 ? 6.0 + 0.1 * ext : 0.0);
-  if (T > 64 && T <= 256 && ext <= 512 && Kc >= 2 * cols && Kc * cols >= 40000000)
-    return 1.1 * p.us < 15.0 + Kc * cols * (T <= 128 ? 0.57e-6 : 0.82e-6);
+  if (T > 384) return p.us < (ext > 0 ? 20.0 + 2.0 * T * Kc * cols / 1.25e9 + 0.1 * ext : wide_plan(T, Kc, cols, SIZE_MAX).us);
+  if (T > 64 && T <= 256 && Kc >= 2 * cols && Kc * cols >= 40000000) {
+    if (ext == 0) return p.us < 15.0 + Kc * cols * (T <= 128 ? 0.29e-6 : 0.365e-6);
+    if (T > 128 && ext <= 512) return 1.05 * p.us < 15.0 + Kc * cols * 0.67e-6;
+  }
   return true;
 }
 

@@ -203,6 +203,18 @@ def test_some_rows_u_pieces(oracle, T, K, N, ranks):
         _check_layer(oracle, w, bwd=False, tag="u in pieces", table="table+packed")
 
 
+# Both sides of the lines between the kernel for some rows and its neighbours: 384 rows with and without
+# adapters, the long contractions of 65 to 256 rows, many small tiles and few large ones.
+@pytest.mark.parametrize("T,K,N,ranks", [(384, 1032, 2056, [16] * 8), (385, 1032, 2056, [16] * 8), (385, 1032, 2056, []), (400, 264, 9224, [64, 8, 24]), (700, 520, 1032, []),
+                                         (65, 10248, 4104, [16, 8]), (65, 10248, 4104, []), (256, 10248, 4104, []), (257, 10248, 4104, [24] * 3)])
+def test_some_rows_route_lines(oracle, T, K, N, ranks):
+    rng = np.random.default_rng(T + K)
+    n = max(len(ranks), 1)
+    ids = rng.integers(-1, n, size=T).astype(np.int32) if ranks else np.full(T, -1, np.int32)
+    w = wl.make_layer(T + N, T, K, N, ranks or [8], [0.5 + t % 3 for t in range(n)], ids, dtype="bf16", layout=wl.TORCH)
+    _check_layer(oracle, w, bwd=False, tag="route lines", table="table+packed")
+
+
 # A workgroup that gives up waiting computes what it waited for in the same order of sums: no bit depends on
 # which workgroups were on the chip.  (Limit 0: every wait is given up at once.)
 @pytest.mark.parametrize("layout", [0, 1])
