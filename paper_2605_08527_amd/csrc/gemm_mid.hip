@@ -776,7 +776,10 @@ hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream
 // q/k/v 33.7 -> 31.5 us, 157 rows 29.6 -> 27.1, 512 rows of 64 adapters, 5120 x 5120, 60 -> 57).  A k-tile's time when
 // a workgroup has its compute unit to itself, which two on one unit take 1.8 times as long for; against it what
 // the fabric delivers; the expand by the ranks and row blocks of a wave; producers, where they share a unit with
-// a consumer or make a last wave of workgroups; the exchange of split contractions.
+// a consumer or make a last wave of workgroups; the exchange of split contractions.  The timed runs had one weight,
+// from the memory-side cache; with eight in turn few units with two workgroups are worth more (512 rows, 5120 x
+// 5120, 64 adapters of rank 16: 280 workgroups of 80 rows 56 us, 320 of 64 rows 69; from the cache 51.5 and 50.8),
+// hence the 64 units over which a second workgroup comes to count in full.
 MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora, int max_split) {
   static const double tile_us[2][2] = {{0.306, 0.252}, {0.334, 0.282}};   // [rb - 4][wn == 4]
   MidPlan best;
@@ -799,7 +802,7 @@ MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const
         } else {
           const int64_t left = wgs % 512;
           fill = (double)(wgs / 512) * (t2 + 2.172);
-          if (left > 0) fill += 2.172 + 1.066 * t1 + (t2 - 1.066 * t1) * up_to_1((double)(left - 256) / 11.767);
+          if (left > 0) fill += 2.172 + 1.066 * t1 + (t2 - 1.066 * t1) * up_to_1((double)(left - 256) / 64.0);
         }
         const double fabric = (2.0 * cols * Kc + 16.0 * T * Kc / s) / 11.6e6;
         double us = 7.687 + cbrt(fill * fill * fill + fabric * fabric * fabric);
@@ -827,15 +830,15 @@ MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const
 //   of rank 16 86 / 75; 4096 x 4096, no adapter, 27 / 23; 14336 x 4096, 32 adapters, 109 / 75).
 //   Up to 256 rows the split kernel with its separate finish on a long contraction and few columns, where the row
 //   tiles here are few and their splits expensive (256 rows, 14336 x 4096, no adapter: 36 / 41, 157 rows 37 / 31;
-//   200 rows, 20480 x 2048, 32 adapters of rank 16: 44 / 52, 14336 x 4096 54 / 49; up to 128 rows with adapters
-//   never: 100 rows 45 / 35 and 37 / 36).
+//   200 rows, 20480 x 2048, 32 adapters of rank 16: 44 / 52; 256 rows, 14336 x 4096 from memory 63 / 70; up to 128
+//   rows with adapters never: 100 rows 45 / 35 and 37 / 36).
 bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext) {
   if (T <= 16) return false;
   if (T <= 32) return T * Kc > 140000 || Kc * cols > 50000000;
   if (T > 384) return p.us < (ext > 0 ? 20.0 + 2.0 * T * Kc * cols / 1.25e9 + 0.1 * ext : wide_plan(T, Kc, cols, SIZE_MAX).us);
   if (T > 64 && T <= 256 && Kc >= 2 * cols && Kc * cols >= 40000000) {
     if (ext == 0) return p.us < 15.0 + Kc * cols * (T <= 128 ? 0.29e-6 : 0.365e-6);
-    if (T > 128 && ext <= 512) return 1.05 * p.us < 15.0 + Kc * cols * 0.67e-6;
+    if (T > 128 && ext <= 512) return 1.15 * p.us < 15.0 + Kc * cols * 0.67e-6;
   }
   return true;
 }
