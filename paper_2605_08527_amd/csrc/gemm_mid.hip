@@ -34,6 +34,7 @@
 #include "lora_expand.h"
 #include "lora_shrink.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 
@@ -810,8 +811,12 @@ MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const
           const int pieces = mid_u_splits(Kc, T * lora.r_stride * n_proj, wgs, (int64_t)n_proj * mid_max_jobs(T, rb, lora), 256);
           const int64_t with_rows = (int64_t)(0.6 * T) + 1 < lora.n ? (int64_t)(0.6 * T) + 1 : lora.n;      // (adapters, about)
           const int64_t prods = n_proj * pieces * (with_rows * (lora.tiles / lora.n > 1 ? lora.tiles / lora.n : 1) + T / (16 * rb) * ((rb + 1) / 2));
+          // (the expand of more ranks is not proportionally more: 184 rows, 1872 x 8368, rank 32, 23.1 -> 22.1 us
+          // in tiles of 128 columns; a split makes every rank's u travel to more readers: 277 rows, 2144 x 1048, rank 64,
+          // 20.0 -> 18.4 unsplit)
+          const double rank = std::min(16.0, (double)lora.ranks / lora.n);
           const double prod_us = 10.735 * Kc / 4096.0 / pieces + 0.498;
-          us += 0.562 + 2.009 * ((rb * wn + 7) / 8) * lora.ranks / (16.0 * lora.n);
+          us += 0.562 + 2.009 * ((rb * wn + 7) / 8) * rank / 16.0 + (s > 1 ? 0.02 * lora.ranks / lora.n : 0.0);
           us += prod_us * (wgs <= 256 ? 0.574 * up_to_1((double)(wgs + prods - 256) / 17.45) : 0.289 * up_to_1((double)prods / 256.0));
           us += prod_us * 0.918 * up_to_1((double)((wgs < 512 ? wgs : 512) + prods - 512) / 17.45);
         }
