@@ -119,6 +119,16 @@ __device__ __forceinline__ int segment_of(const int32_t* __restrict__ seg_off, i
   return lo;
 }
 
+// The last index t of 0 .. n - 1 with le(t), for le true up to some index of 0 .. n - 1 and false behind it.
+// All lanes of a wave call it: a ballot over 64 indices, and for n above 64 (up to 4096) one inside the piece found.
+template <typename Le>
+__device__ __forceinline__ int wave_last(int n, Le le) {
+  const int lane = threadIdx.x & 63, step = (n + 63) >> 6;
+  int t = (__popcll(__ballot(lane * step < n && le(lane * step))) - 1) * step;
+  if (step > 1) t += __popcll(__ballot(lane < step && t + lane < n && le(t + lane))) - 1;
+  return t;
+}
+
 // ---- launchers (implemented in the .hip files; all enqueue on `stream`) ----
 
 struct SegmapDev {
@@ -139,6 +149,10 @@ __host__ __device__ inline int reduce_ragged_chunk(int64_t T_lora, int n) {
   if (c < 512) c = 512;
   return (int)((c + 63) / 64 * 64);
 }
+// Workgroups that such a cut takes per slab of columns: one for every slot, one for every adapter without.  A
+// chunk is at least twice the mean segment, so there are at most n / 2 whole ones and n remainders: less than
+// 3 n, and a grid's y holds 65535.
+inline int reduce_ragged_rows(int n, int ragged_slots, int ragged_adapters) { return ragged_slots + n - ragged_adapters; }
 // The same in one launch (T <= 32768, n <= 800); host: pinned, receives seg_off[n + 2], the two
 // flags and then `seq`, in this order (n + 5 values).
 bool segmap_is_small(int64_t T, int n);

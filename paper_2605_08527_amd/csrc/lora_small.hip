@@ -624,7 +624,8 @@ struct ReduceArgs {
   // ragged = 1: only segments longer than tchunk are cut; adapter t's pieces use partial-sum slots
   // chunk_base[t] .. ([slot][C][r_stride]), every other adapter's block writes its result itself
   int ragged; const int32_t* chunk_base;
-  int ragged_adapters, n_adapters;         // adapters that are cut (the first ones in `order`), all
+  int ragged_slots, ragged_adapters;       // slots, adapters that have some (the first ones in `order`)
+  int n_adapters;
   float* partials;                         // [adapter][chunk] slots when to_partials
   int to_partials;                         // 1: the chunks' sums go to `partials`, reduce_finalize_kernel completes;
                                            // a slot is laid out like the gradient, [C][r_stride] or [r_stride][C]
@@ -644,7 +645,9 @@ __device__ __forceinline__ int swz_tokc(int tk, int unit) {
   return tk * 512 + ((unit ^ (f << 1)) << 4);
 }
 
-// grid: x = slabs * chunks_max of both jobs, y = adapter.  The kernel is bound by the one pass over X, so the
+// grid: x = slabs * chunks_max of both jobs, y = adapter; ragged: x = slabs, y = the slots, then the adapters that
+// have none (a rectangle of the longest segment's chunks for every adapter that is cut was mostly workgroups
+// without rows, and above 65535 rows of them where one of many adapters has most tokens).  The kernel is bound by the one pass over X, so the
 // loop is software-pipelined through registers: while a 64-token step is multiplied out of LDS,
 // the X rows and V rows of the next step are already requested (and the gather indices of the
 // step after that), and only the LDS hand-over sits between two barriers.  The operand order of the matrix
@@ -653,12 +656,17 @@ template <int OFORM, int NQT>
 __device__ __forceinline__ void reduce_block(const ReduceArgs& a, int bx, int by, char* rsm) {
   char* Xs = rsm;                               // [RD_TOK][RD_COLS] bf16, swizzled
   char* Vh = rsm + RD_TOK * RD_COLS * 2;        // [RD_TOK][r_pad] bf16: leading halves of V
-  // (ragged: the further chunks of the adapters that are cut, chunk after chunk, then every adapter's first one)
-  const int slab = bx % a.slabs, more = a.ragged ? (a.chunks_max - 1) * a.ragged_adapters : 0;
-  const int ch = !a.ragged ? bx / a.slabs : by < more ? by / a.ragged_adapters + 1 : 0;
-  const int k = !a.ragged ? by : by < more ? by % a.ragged_adapters : by - more;
-  if (k >= a.n_adapters) return;
-  const int t = a.order ? a.order[k] : k;
+  const int slab = bx % a.slabs;
+  int t, ch = 0;
+  if (a.ragged && by < a.ragged_slots) {
+    t = wave_last(a.n_adapters, [&](int i) { return a.chunk_base[i] <= by; });
+    ch = by - a.chunk_base[t];                  // (a chunk of twice the length has no rows for the second half of the slots)
+  } else {
+    if (!a.ragged) ch = bx / a.slabs;
+    const int k = a.ragged ? by - a.ragged_slots + a.ragged_adapters : by;
+    if (k >= a.n_adapters) return;
+    t = a.order ? a.order[k] : k;
+  }
   const int lo = a.seg_off[t], hi = a.seg_off[t + 1];
   const int beg = lo + ch * a.tchunk;
   const bool empty = beg >= hi;
@@ -930,7 +938,7 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   ReduceArgs a;
   const size_t slot = (size_t)j.C * r_stride * sizeof(float);
   a.order = order;
-  a.ragged = 0; a.chunk_base = nullptr; a.ragged_adapters = 0; a.n_adapters = n_adapters;
+  a.ragged = 0; a.chunk_base = nullptr; a.ragged_slots = a.ragged_adapters = 0; a.n_adapters = n_adapters;
   a.X = j.X; a.ldx = j.ldx; a.C = j.C; a.perm = perm; a.seg_off = seg_off; a.table = table;
   a.grads = grads; a.which = j.which; a.form = j.form; a.V = j.V; a.r_stride = r_stride; a.accumulate = accumulate;
   a.slabs = (int)((j.C + RD_COLS - 1) / RD_COLS);
@@ -946,7 +954,7 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   const bool opt = j.opt && j.opt->on;
   if (!opt && a.chunks_max == 1 && chunk_base != nullptr && order != nullptr && ragged_adapters > 0 && ragged_adapters <= n_adapters &&
       reduce_ragged(j.C, n_adapters, max_seg, ragged_chunk, ragged_slots) && partial_bytes >= ragged_slots * slot) {
-    a.ragged = 1; a.chunk_base = chunk_base; a.ragged_adapters = ragged_adapters;
+    a.ragged = 1; a.chunk_base = chunk_base; a.ragged_slots = ragged_slots; a.ragged_adapters = ragged_adapters;
     // (every cut costs a sum written and read: pieces of twice the length where the rows that a place on the chip
     // has to take, two workgroups a unit, are more than that.  16896 rows, 64 adapters, 5120 x 5120: pieces of
     // 576 rows 117 + 18 us, 1088 rows 110 + 13, 1600 rows 115 + 10, whole segments 151.)
@@ -1001,7 +1009,7 @@ hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, c
     for (int j = 0; j < (both ? 2 : 1); ++j) {
       const ReduceArgs& a = q.a[j];
       x[j] = a.slabs * (a.ragged ? 1 : a.chunks_max);
-      y = std::max(y, n_adapters + (a.ragged ? (a.chunks_max - 1) * a.ragged_adapters : 0));
+      y = std::max(y, a.ragged ? reduce_ragged_rows(n_adapters, ragged_slots, ragged_adapters) : n_adapters);
     }
     q.n0 = x[0];
     hipLaunchKernelGGL(kern, dim3(x[0] + x[1], y), dim3(RD_THREADS), lds, stream, q);

@@ -236,3 +236,18 @@ def test_waits_given_up_keep_the_bits(monkeypatch, T, K, N, ranks, layout):
     for other in out[1:]:
         for a, b in zip(out[0], other):
             assert torch.equal(a, b)
+
+
+# The reductions of very unequal segments: one adapter with half of the rows among hundreds that are just cut (a
+# rectangle of the longest one's chunks for each of them would be 130000 workgroups high), pieces of once and of
+# twice the chunk, adapters without rows in between, and one gradient cut by length beside one in even chunks in
+# the same launch (56 slabs of columns and 4).
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("K,N,lens", [(8, 8, [3, 0, 262144] + [513] * 500 + [3] * 1545), (264, 520, [0, 7, 3000, 0, 1100, 513, 512] + [5] * 693),
+                                      (14336, 1024, [1500, 3, 1300, 0, 40, 7, 9, 900])])
+def test_reductions_of_unequal_segments(oracle, K, N, lens, layout):
+    n = len(lens)
+    rng = np.random.default_rng(K + n)
+    ids = rng.permutation(np.repeat(np.arange(n), lens)).astype(np.int32)
+    w = wl.make_layer(K + n, len(ids), K, N, [8 + 8 * (t % 2) for t in range(n)], [0.5 + t % 3 for t in range(n)], ids, dtype="bf16", layout=layout, want_dY=True)
+    _check_layer(oracle, w, bwd=True, tag="unequal segments", table="table")
