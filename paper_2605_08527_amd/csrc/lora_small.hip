@@ -506,7 +506,8 @@ __global__ __launch_bounds__(256) void shrink_finalize_kernel(ShrinkArgs a) {
       if (lane >> 4 == i) t += before;
     }
   }
-  if (m >= a.T_lora) return;
+  // (the map of a pass that is replayed can hold fewer rows than it did: there is no adapter t = n_adapters)
+  if (m >= a.T_lora || t >= a.n_adapters) return;
   const AdapterEntry e = entry_of(a, t);
   const int r_pad = (e.rank + 15) & ~15;
   for (int q = threadIdx.x & 15; q < r_pad; q += 16) {

@@ -49,3 +49,31 @@ def test_replay_after_regroup(oracle, T, K, N, ranks, first):
             assert beg.elapsed_time(end) < 50.0              # (a wait given up costs as many milliseconds and more)
         eager, _ = L.fwd()                                   # the program's own work between the replays
         assert torch.equal(eager, y) or np.allclose(to_host(eager), to_host(y), rtol=1e-4, atol=1e-4)
+
+
+# A pass of many rows is captured again after an update; where it is not, and the map has fewer rows with adapters
+# than it had, the shrink whose contraction is split writes none of the rows that have no adapter any more.
+@pytest.mark.parametrize("layout", [0, 1])
+def test_split_shrink_replayed_with_fewer_rows(layout):
+    T, K, N, n = 4200, 264, 4104, 40
+    rng = np.random.default_rng(layout)
+    ids = rng.integers(0, n, size=T).astype(np.int32)
+    w = wl.make_layer(T, T, K, N, [8 + 8 * (t % 4) for t in range(n)], [1.0] * n, ids, dtype="bf16", layout=layout)
+    L = HipLayer(w, table=True)
+    y = torch.empty((T, N), dtype=torch.float32, device="cuda")
+    u = torch.empty((T, api.marlaas_u_stride(L.desc)), dtype=torch.float32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        api.marlaas_lora_fwd(L.ctx, L.desc, y, u_save=u)
+    for rows in (4200, 3997, 64, 1):
+        ids[rng.permutation(T)[:T - rows]] = -1
+        left = int((ids >= 0).sum())
+        api.marlaas_segmap_update(L.ctx, L.map, torch.from_numpy(ids).cuda(), n)
+        u.fill_(7.0)
+        graph.replay()
+        got = u.clone()
+        u.fill_(7.0)
+        api.marlaas_lora_fwd(L.ctx, L.desc, y, u_save=u)
+        torch.cuda.synchronize()
+        assert bool((got[left:] == 7.0).all())
+        assert_close(to_host(got[:left]), to_host(u[:left]), "u of the rows left", tol_max=1e-3, tol_mean=2e-5)
