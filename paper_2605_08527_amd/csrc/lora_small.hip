@@ -71,28 +71,18 @@ static int side_blocks(const ShrinkArgs& a, int waves) {
 }
 
 // The adapter that row block b belongs to, when every segment is cut into blocks of `rows` rows, and the block's
-// first row; -1: there are fewer blocks.  A lane per adapter, all lanes of a wave call it.  (A grid of the
-// longest segment's blocks for every adapter was mostly workgroups without rows: 6400 for 1312, 16896 rows of
-// 64 adapters.)
+// first row; -1: no row.  The blocks of adapter t are numbered from seg_off[t] / rows + t on: a segment has at
+// most one block more than it adds whole ones to that, so the numbers are apart, and the last is below T_lora /
+// rows + n, which the grid covers.  A wave finds the adapter with a ballot over 64 of them, two above 64 adapters.
+// (A grid of the longest segment's blocks for every adapter was mostly workgroups without rows, 6400 for 1312 in
+// 16896 rows of 64 adapters; numbers without gaps take a scan over all adapters in every workgroup: 2011 rows,
+// 4096 x 4096, 4096 adapters, the whole call 314 us against 253.)
 __device__ __forceinline__ int row_block(const int32_t* __restrict__ seg_off, int n, int rows, int b, int* row0, int* end) {
-  const int lane = threadIdx.x & 63;
-  for (int t0 = 0; t0 < n; t0 += 64) {
-    const int t = t0 + lane;
-    const int lo = t < n ? seg_off[t] : 0, hi = t < n ? seg_off[t + 1] : 0;
-    const int blocks = (hi - lo + rows - 1) / rows;
-    int inc = blocks;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(inc, d); if (lane >= d) inc += v; }
-    const uint64_t hit = __ballot(b < inc);
-    if (hit) {
-      const int l = __ffsll((unsigned long long)hit) - 1;
-      *row0 = __builtin_amdgcn_readlane(lo, l) + (b - __builtin_amdgcn_readlane(inc - blocks, l)) * rows;
-      *end = __builtin_amdgcn_readlane(hi, l);
-      return t0 + l;
-    }
-    b -= __builtin_amdgcn_readlane(inc, 63);
-  }
-  return -1;
+  const int t = wave_last(n, [&](int i) { return (uint32_t)seg_off[i] / (uint32_t)rows + i <= (uint32_t)b; });
+  const int lo = seg_off[t], hi = seg_off[t + 1];
+  *row0 = lo + (b - (int)((uint32_t)lo / (uint32_t)rows) - t) * rows;
+  *end = hi;
+  return *row0 < hi ? t : -1;
 }
 
 // u (scaled, fp32) and its two-term bf16 split for row m, rank index q of an adapter with padded rank r_pad
@@ -497,17 +487,14 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
 __global__ __launch_bounds__(256) void shrink_finalize_kernel(ShrinkArgs a) {
   const int lane = threadIdx.x & 63;
   const int m0 = blockIdx.x * 16 + (threadIdx.x >> 6) * 4, m = m0 + (lane >> 4);     // (four rows a wave)
-  int t = 0;                                                     // segments that end at or before the row
-  for (int t0 = 0; t0 < a.n_adapters; t0 += 64) {
-    const int end = t0 + lane < a.n_adapters ? a.seg_off[t0 + lane + 1] : 0x7fffffff;
+  int t = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int before = __popcll(__ballot(end <= m0 + i));
-      if (lane >> 4 == i) t += before;
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int ti = wave_last(a.n_adapters, [&](int k) { return a.seg_off[k] <= m0 + i; });
+    if (lane >> 4 == i) t = ti;
   }
-  // (the map of a pass that is replayed can hold fewer rows than it did: there is no adapter t = n_adapters)
-  if (m >= a.T_lora || t >= a.n_adapters) return;
+  // (the map of a pass that is replayed can hold fewer rows than it did)
+  if (m >= a.T_lora || m >= a.seg_off[a.n_adapters]) return;
   const AdapterEntry e = entry_of(a, t);
   const int r_pad = (e.rank + 15) & ~15;
   for (int q = threadIdx.x & 15; q < r_pad; q += 16) {

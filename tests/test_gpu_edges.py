@@ -251,3 +251,16 @@ def test_reductions_of_unequal_segments(oracle, K, N, lens, layout):
     ids = rng.permutation(np.repeat(np.arange(n), lens)).astype(np.int32)
     w = wl.make_layer(K + n, len(ids), K, N, [8 + 8 * (t % 2) for t in range(n)], [0.5 + t % 3 for t in range(n)], ids, dtype="bf16", layout=layout, want_dY=True)
     _check_layer(oracle, w, bwd=True, tag="unequal segments", table="table")
+
+
+# Many adapters, most of them with few rows or none: the adapter of a row block or of a row is looked up over one
+# ballot's worth of adapters, one more, pieces of two to 64, the last of them short.
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("T,n", [(4200, 64), (4200, 65), (3000, 129), (1500, 1000), (3000, 4095), (2011, 4096)])
+def test_many_adapters(oracle, T, n, layout):
+    rng = np.random.default_rng(T + n)
+    p = rng.random(n) ** 6
+    ids = rng.choice(n, size=T, p=p / p.sum()).astype(np.int32)
+    ids[rng.random(T) < 0.1] = -1
+    w = wl.make_layer(T + n, T, 264, 1032, [8 + 8 * (t % 2) for t in range(n)], [0.5 + t % 3 for t in range(n)], ids, dtype="bf16", layout=layout, want_dY=True)
+    _check_layer(oracle, w, bwd=n <= 129, tag="many adapters", table="table")
