@@ -12,7 +12,7 @@ import pytest
 
 from paper_2605_08527_amd import build
 
-FILES = ["gemm_mid", "gemm_decode", "gemm_bf16"]
+FILES = ["gemm_mid", "gemm_decode", "gemm_bf16", "lora_small"]
 
 
 def _registers(operand):
@@ -131,6 +131,13 @@ def overwritten_reads(blocks):
     return found
 
 
+def masked_waits(blocks):
+    """Waits for a part of the requests under way behind a branch on the exec mask: the lanes' own values decide."""
+    text = [i for instructions in blocks.values() for i in instructions]
+    return [s for (_, before, _, _), (s, op, _, _) in zip(text, text[1:])
+            if before in ("s_cbranch_execz", "s_cbranch_execnz") and op == "s_waitcnt" and re.search(r"vmcnt\([1-9]", s)]
+
+
 @pytest.fixture(scope="module")
 def listings(tmp_path_factory):
     out = tmp_path_factory.mktemp("listings")
@@ -155,6 +162,15 @@ def test_no_move_of_a_load_before_a_wait(listings, f):
 def test_no_write_over_a_pending_lds_read(listings, f):
     for name, blocks in _functions(listings[f]):
         assert not overwritten_reads(blocks), name
+
+
+# The rank of a workgroup's adapter is one value for all its lanes: how many requests its ring waits for is no
+# matter of masks.
+def test_ring_waits_are_uniform(listings):
+    rings = [(name, blocks) for name, blocks in _functions(listings["lora_small"]) if "shrink_ring_kernel" in name]
+    assert len(rings) == 16
+    for name, blocks in rings:
+        assert not masked_waits(blocks), name
 
 
 def test_overwritten_read_is_seen():
