@@ -128,7 +128,8 @@ __device__ __forceinline__ int find_job(const GemmArgs& a, const AdapterEntry* t
 }
 
 // LDS: the ring or, once it is free, the exchange of the sums and, behind it, the rows' u; in place of it where
-// two workgroups would not fit a compute unit otherwise (ranks above 48 or 112 by the tile); the rows' tables.
+// two workgroups would not fit a compute unit otherwise (80-row tiles of 64 columns: ranks above 48; 64 x 64 and 80 x
+// 128: above 96); the rows' tables.
 template <int RB, int WN>
 __host__ __device__ inline int mid_tables(int r_stride) { return 16 * RB * 20 + RB * 4 + 16 + RB * 2 * r_stride * (int)sizeof(uint16_t); }
 template <int RB, int WN>
@@ -165,16 +166,15 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   // Workgroups through with row tile tm of projection p (bits 16 ..: those that gave up waiting for sums).  Only
   // a consumer knows how many producers the tile has: the one of the first column tile and split counts for
   // MID_JOBS less those, so that the count is the same, consumers + MID_JOBS, for every grouping.
-  // Called by one whole wave, when the workgroup's requests are performed; the count's answer is a trip through
-  // the fabric, and what it is needed for can wait.
+  // Called by one whole wave, when the workgroup's requests are performed.  (The count's answer is a trip through
+  // the fabric; put off until the workgroup's stores are out, it has to wait for those: 60 sizes of up to 384 rows and
+  // contractions of up to 2560 1 % longer.)
   auto leave = [&](int p, int tm, int mine) {
-    int old = 0;
-    if (lane == 0) old = __hip_atomic_fetch_add(a.sync + p * a.tiles_m + tm, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return old;
-  };
-  auto left = [&](int p, int tm, int mine, int old) {
     const int p_tiles = (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
     const int64_t m0 = (int64_t)tm * BM;
+    int32_t* done = a.sync + p * a.tiles_m + tm;
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(done, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     old = __builtin_amdgcn_readfirstlane(old) + mine;
     if ((old & 0xffff) != p_tiles * a.ksplit + MID_JOBS) return;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       float* part = a.partials + ((int64_t)tm * a.tiles_n + a.proj[p].tile0) * (UNITS * 256) * a.ksplit;
       for (int64_t i = lane, n = (int64_t)p_tiles * UNITS * 64 * a.ksplit; i < n; i += 64) store4_agent(part + i * 4, zero);
     }
-    if (lane == 0) __hip_atomic_store(a.sync + p * a.tiles_m + tm, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
 
   if (b >= 0 && b < a.n_prod) {
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     shrink_job<3, 2>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, a.thin_u + (pp * S + job.split) * u_n + (int64_t)tile * BM * a.r_stride,
                      a.r_stride, wave, lane);
     __syncthreads();
-    if (wave == 0) left(pp, tile, 1, leave(pp, tile, 1));
+    if (wave == 0) leave(pp, tile, 1);
     return;
   }
 
@@ -303,64 +303,8 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   auto factor = [&](int rb, int i, int cb) {
     const int o = oct_s[rb * oct_max + i], row = o >> 8;
     const int64_t n = n0 + cb * 16 + li;
-    if (n >= Nout || (a.ksplit > 1 && cb != cbo)) return make_uint4(0, 0, 0, 0);
+    if (n >= Nout) return make_uint4(0, 0, 0, 0);
     return *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[row] + (o & 255) + n * rank_s[row]);
-  };
-  constexpr bool EARLY = NR == 1;
-  constexpr int PD = EARLY ? 2 : 1;                            // groups of four octets requested ahead
-  uint4 pre[NR][PD][2];
-  uint64_t uw[MID_SPLITS][2];                                    // first reading of the first four values of u this thread fetches
-  const int urow = tid / (a.r_stride >> 2), uq0 = (tid - urow * (a.r_stride >> 2)) * 4;
-  const bool early = apart && a.ksplit == 1;
-  // u and the first octets' factors, a trip through the fabric each: on the way while the sums meet
-  auto request_u = [&]() {
-#pragma unroll
-    for (int q = 0; q < MID_SPLITS; ++q) uw[q][0] = uw[q][1] = 0;
-    if (urow < BM && uq0 < rank_s[urow])
-#pragma unroll
-      for (int q = 0; q < MID_SPLITS; ++q)
-        if (q < S) {
-          const uint64_t* from = (const uint64_t*)(u_p + q * u_n + (m0 + urow) * a.r_stride + uq0);
-          uw[q][0] = __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          uw[q][1] = __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-  };
-  auto request_factors = [&](int j) {
-    const int rb = j * KG + g, cnt = rb < RB ? cnt_s[rb] : 0;
-#pragma unroll
-    for (int d = 0; d < PD; ++d)
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
-        pre[j][d][cb] = make_uint4(0, 0, 0, 0);
-        if (4 * d + lg < cnt) pre[j][d][cb] = factor(rb, 4 * d + lg, cb);
-      }
-  };
-  auto take_u = [&]() {
-    const int uq = a.r_stride >> 2;
-    for (int i = tid, row = urow, q = uq0; i < BM * uq; i += MD_THREADS, row = i / uq, q = (i - row * uq) * 4) {   // (whole waves)
-      const int rank = rank_s[row];
-      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-      bool ok = true;
-      if (q < rank) {
-        ok = i == tid && a.spin_limit > 0;
-#pragma unroll
-        for (int k = 0; k < MID_SPLITS; ++k)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t w = (uint32_t)(uw[k][j >> 1] >> (32 * (j & 1)));
-            ok &= k >= S || w != 0u;
-            v[j] = k == 0 ? __uint_as_float(w) : k < S ? v[j] + __uint_as_float(w) : v[j];
-          }
-        if (!ok) ok = read_u<MID_SPLITS>(u_p + (m0 + row) * a.r_stride + q, u_n, S, a.spin_limit, v);
-      }
-      if (__builtin_expect(__ballot(!ok) != 0, 0))               // (not reached in practice)
-        u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
-      *(f32x4*)(u_s + row * us + q) = v;
-      if (a.u_out && lead && m0 + row < a.T && q < ((rank + 15) & ~15))
-        *(f32x4*)(a.u_out + (m0 + row) * a.r_stride + q) = v;
-    }
   };
   if (tid == 0) gave_s[0] = 0;
   {
@@ -499,8 +443,6 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
     for (int i = 0; i < RB; ++i) if (nt > 0) asm volatile("" : "+v"(xf[i]));
-    if (early && lora) request_u();
-    if (EARLY && lora && a.ksplit == 1) request_factors(0);
     __syncthreads();                                             // the ring is free
     // ---- the contraction groups' sums: row block i is finished by group i mod KG
 #pragma unroll
@@ -510,7 +452,6 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) red[(((i * WN + wn) * 2 + cb) * (KG - 1) + d) * 64 + lane] = acc[i][cb];
       }
-    if (early && lora) take_u();
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RB; ++i)
@@ -639,19 +580,39 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     }
   }
 
-  int old = 0, mine = 0;
   if (lora) {
-    if (!EARLY || a.ksplit > 1)                                  // (earlier there are no registers for them)
+    // the first octets' factor fragments depend on nothing that has to be waited for
+    uint4 pre[NR][2];
 #pragma unroll
-      for (int j = 0; j < NR; ++j) request_factors(j);
-    if (!early) {                                                // (u after the sums, which other workgroups wait for)
-      request_u();
-      if (!apart) __syncthreads();                               // (the sums have met: their place is u's)
-      take_u();
-      __syncthreads();
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        const int rb = j * KG + g;
+        pre[j][cb] = make_uint4(0, 0, 0, 0);
+        if (rb < RB && lg < cnt_s[rb]) pre[j][cb] = factor(rb, lg, cb);
+      }
+    // (A reading of u and the factors of eight octets requested before the sums meet, with four requests a reading and the
+    // count's answer put off, took 2.8 % longer over 190 sizes in every tiling, all of a thread's readings at once 1.4 %:
+    // the code around them costs every wave more than the trips it saves, but for ranks of 128, 1 % shorter with the second.)
+    if (!apart) __syncthreads();                                 // (the sums have met: their place is u's)
+    const int uq = a.r_stride >> 2;
+    for (int i = tid; i < BM * uq; i += MD_THREADS) {            // (whole waves)
+      const int row = i / uq, q = (i - row * uq) * 4;
+      const int rank = rank_s[row];
+      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+      bool ok = true;
+      if (q < rank) ok = read_u(u_p + (m0 + row) * a.r_stride + q, u_n, S, a.spin_limit, v);
+      if (__builtin_expect(__ballot(!ok) != 0, 0))               // (not reached in practice)
+        u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
+      *(f32x4*)(u_s + row * us + q) = v;
+      if (a.u_out && lead && m0 + row < a.T && q < ((rank + 15) & ~15))
+        *(f32x4*)(a.u_out + (m0 + row) * a.r_stride + q) = v;
     }
-    mine = 1 + (gave_s[0] << 16) + (lead ? MID_JOBS - (gave_s[2] + (RB > 4 ? gave_s[3] : 0)) * S : 0);
-    if (wave == MD_WAVES - 1) old = leave(p, tm, mine);
+    __syncthreads();
+    if (wave == MD_WAVES - 1)
+      leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS - (gave_s[2] + (RB > 4 ? gave_s[3] : 0)) * S : 0));
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const int rb = j * KG + g;
@@ -680,8 +641,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     }
   } else if (a.ksplit > 1) {
     __syncthreads();
-    mine = 1 + (gave_s[0] << 16) + (lead ? MID_JOBS : 0);
-    if (wave == MD_WAVES - 1) old = leave(p, tm, mine);
+    if (wave == MD_WAVES - 1) leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS : 0));
   }
 #pragma unroll
   for (int j = 0; j < NR; ++j) {
@@ -701,7 +661,6 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       }
     }
   }
-  if (mine && wave == MD_WAVES - 1) left(p, tm, mine, old);
 }
 
 template <int RB, int WN>

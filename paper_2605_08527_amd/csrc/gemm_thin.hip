@@ -232,15 +232,15 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
 
   if (lora) {
     // the first octets' factor fragments depend on nothing that has to be waited for
-    uint4 pre[MINE][1][1];
+    uint4 pre[MINE][1];
 #pragma unroll
     for (int k = 0; k < MINE; ++k) {
       const int tile = wave + k * TH_WAVES, rb = tile / NC, c = tile - rb * NC;
-      pre[k][0][0] = make_uint4(0, 0, 0, 0);
+      pre[k][0] = make_uint4(0, 0, 0, 0);
       if (tile < TILES && lg < cnt_s[rb]) {
         const int64_t n = n0 + c * 16 + li;
         const int o = rb * oct_max + lg;
-        if (n < Nout) pre[k][0][0] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
+        if (n < Nout) pre[k][0] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
       }
     }
     for (int i = tid; i < 16 * R * (a.r_stride >> 2); i += TH_THREADS) {      // (whole waves)
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
       const int rank = t_s[row] >= 0 ? rank_s[row] : 0;
       f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
       bool ok = true;
-      if (q < rank) ok = read_u<THIN_SPLITS>(u_p + row * a.r_stride + q, u_n, S, a.spin_limit, v);
+      if (q < rank) ok = read_u(u_p + row * a.r_stride + q, u_n, S, a.spin_limit, v);
       if (__builtin_expect(__ballot(!ok) != 0, 0))               // (not reached in practice)
         u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
 #pragma unroll

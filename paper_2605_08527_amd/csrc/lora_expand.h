@@ -25,63 +25,33 @@ __device__ __forceinline__ void split_u(const float* u, bool mine, bf16x8& hi, b
 //   t_row    adapter of this lane's row; u_row: its u (LDS, 16-byte aligned)
 //   oct(i)   adapter << 8 | first rank of octet i
 //   load(i, cb)  8 ranks of octet i in column lane % 16 of block cb (zeros beyond the last column)
-//   pre      load(4 d + lg, cb) where 4 d + lg < cnt, requested before (a trip through the fabric each; D > 1: so
-//            many of them stay under way)
+//   pre      load(lg, cb) where lg < cnt, requested before
 // One product takes four octets, whose adapters may differ: the others' u is 0.  0 times a factor that is
 // infinite or not a number is not 0, so where a sum comes out like that the block is done again, one
 // adapter at a time, and a row takes its own adapter's products only: the same bits as with finite factors
 // for everyone else.  The test costs eight fused multiply-adds a call.
-template <int NCB, int D, typename Oct, typename Load>
-__device__ __forceinline__ void expand_octets(f32x4 (&y)[NCB], const uint4 (&pre)[D][NCB], int cnt, int lg, int t_row, const float* u_row, Oct oct, Load load) {
+template <int NCB, typename Oct, typename Load>
+__device__ __forceinline__ void expand_octets(f32x4 (&y)[NCB], const uint4 (&pre)[NCB], int cnt, int lg, int t_row, const float* u_row, Oct oct, Load load) {
   union Frag { uint4 u; bf16x8 v; };
   f32x4 was[NCB];
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) was[cb] = y[cb];
-  auto request = [&](uint4 (&f)[NCB], int k0) {
+  for (int k0 = 0; k0 < cnt; k0 += 4) {
     const bool valid = k0 + lg < cnt;
+    const int i = valid ? k0 + lg : 0;
+    Frag f[NCB];
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) f[cb] = valid ? load(k0 + lg, cb) : make_uint4(0, 0, 0, 0);
-  };
-  auto multiply = [&](const uint4 (&f)[NCB], int k0) {
-    const bool valid = k0 + lg < cnt;
-    const int o = oct(valid ? k0 + lg : 0);
+    for (int cb = 0; cb < NCB; ++cb) {
+      f[cb].u = pre[cb];
+      if (k0 > 0) f[cb].u = valid ? load(i, cb) : make_uint4(0, 0, 0, 0);
+    }
+    const int o = oct(i);
     bf16x8 hi, lo;
     split_u(u_row + (o & 255), valid && t_row == o >> 8, hi, lo);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
-      Frag w;
-      w.u = f[cb];
-      y[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.v, lo, y[cb], 0, 0, 0);
-      y[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.v, hi, y[cb], 0, 0, 0);
-    }
-  };
-  if constexpr (D == 1) {
-    // (requests ahead were measured here too: 6 rows of 4096 x 4096 10.1 -> 10.3 us, q/k/v of 256 rows 33.1 -> 33.6)
-    for (int k0 = 0; k0 < cnt; k0 += 4) {
-      uint4 f[NCB];
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) f[cb] = pre[0][cb];
-      if (k0 > 0) request(f, k0);
-      multiply(f, k0);
-    }
-  } else {
-    uint4 next[D][NCB];
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) next[d][cb] = pre[d][cb];
-#pragma unroll 1
-    for (int k0 = 0; k0 < cnt; k0 += 4 * D) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const int k = k0 + 4 * d;
-        if (k >= cnt) break;
-        uint4 f[NCB];
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) f[cb] = next[d][cb];
-        if (k + 4 * D < cnt) request(next[d], k + 4 * D);
-        multiply(f, k);
-      }
+      y[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[cb].v, lo, y[cb], 0, 0, 0);
+      y[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[cb].v, hi, y[cb], 0, 0, 0);
     }
   }
   float z = 0.f;                                                 // (0 unless a sum is infinite or not a number)

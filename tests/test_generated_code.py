@@ -158,6 +158,12 @@ def test_no_move_of_a_load_before_a_wait(listings, f):
     assert seen > 0
 
 
+# A value kept in memory between the loop and the end of the some-rows kernel is a trip for every wave.
+def test_some_rows_keep_their_registers(listings):
+    spills = re.findall(r"\.vgpr_spill_count: +(\d+)", listings["gemm_mid"])
+    assert len(spills) == 4 and all(n == "0" for n in spills)
+
+
 @pytest.mark.parametrize("f", ["gemm_mid", "gemm_decode"])
 def test_no_write_over_a_pending_lds_read(listings, f):
     for name, blocks in _functions(listings[f]):

@@ -203,6 +203,18 @@ def test_some_rows_u_pieces(oracle, T, K, N, ranks):
         _check_layer(oracle, w, bwd=False, tag="u in pieces", table="table+packed")
 
 
+# Several readings of u for every thread (ranks of 64 and more, 64- and 80-row tiles), u in one, two and four pieces and
+# saved, ranks that are no multiples of 4 beside them.
+@pytest.mark.parametrize("T,K,N,ranks", [(70, 1032, 2056, [64, 128]), (80, 1032, 1032, [13, 100, 128]), (66, 4616, 1032, [128, 72]), (300, 4616, 1032, [128] * 8),
+                                         (157, 9224, 2056, [64] * 3)])
+def test_some_rows_large_ranks(oracle, T, K, N, ranks):
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(-1, len(ranks), size=T).astype(np.int32)
+    w = wl.make_layer(T + N, T, K, N, ranks, [0.5 + t % 3 for t in range(len(ranks))], ids, dtype="bf16", layout=wl.TORCH, want_dY=True)
+    for rep in range(2):
+        _check_layer(oracle, w, bwd=True, tag="large ranks", table="table+packed")
+
+
 # Both sides of the lines between the kernel for some rows and its neighbours: 384 rows with and without
 # adapters, the long contractions of 65 to 256 rows, many small tiles and few large ones.
 @pytest.mark.parametrize("T,K,N,ranks", [(384, 1032, 2056, [16] * 8), (385, 1032, 2056, [16] * 8), (385, 1032, 2056, []), (400, 264, 9224, [64, 8, 24]), (700, 520, 1032, []),
