@@ -627,14 +627,14 @@ struct ReduceArgs {
   float* partials;                         // [adapter][chunk] slots when to_partials
   int to_partials;                         // 1: the chunks' sums go to `partials`, reduce_finalize_kernel completes;
                                            // a slot is laid out like the gradient, [C][r_stride] or [r_stride][C]
-  int form;                                // of the gradient: FORM_NN [C, r], FORM_NT [r, C]
   ReduceOpt opt;                           // (finalize) optimizer step on every completed gradient element
 };
 // dB_t from (dY, u) and dA_t from (x, v) are independent: one launch, the first job's workgroups of an adapter
 // beside the second's (3000 rows of 4 adapters fill a quarter of the chip each).
 struct ReducePair {
-  ReduceArgs a[2];
-  int n0;                                  // workgroups of the first job in x
+  ReduceArgs a[2];                         // of the gradient stored [C, r], of the one stored [r, C]: each form has its own
+                                           // arguments (picked at run time they cost up to 179 scalar spills)
+  int n0;                                  // workgroups of the first in x
 };
 
 // LDS byte offset of 16-byte unit `unit` (of 32) of token row `tk` in the [64][256] X tile.
@@ -824,11 +824,8 @@ __device__ __forceinline__ void reduce_block(const ReduceArgs& a, int bx, int by
 template <int NQT>
 __global__ __launch_bounds__(RD_THREADS, NQT >= 8 ? 1 : 2) void reduce_bf16_kernel(ReducePair p) {
   extern __shared__ __attribute__((aligned(16))) char rsm[];
-  const bool second = (int)blockIdx.x >= p.n0;
-  const ReduceArgs& a = second ? p.a[1] : p.a[0];
-  const int bx = blockIdx.x - (second ? p.n0 : 0);
-  if (a.form == FORM_NT) reduce_block<FORM_NT, NQT>(a, bx, blockIdx.y, rsm);
-  else reduce_block<FORM_NN, NQT>(a, bx, blockIdx.y, rsm);
+  if ((int)blockIdx.x < p.n0) reduce_block<FORM_NN, NQT>(p.a[0], blockIdx.x, blockIdx.y, rsm);
+  else reduce_block<FORM_NT, NQT>(p.a[1], blockIdx.x - p.n0, blockIdx.y, rsm);
 }
 
 // out_t (+)= sum over the chunks of adapter t, in chunk order.  With an optimizer step attached
@@ -838,32 +835,35 @@ __global__ __launch_bounds__(RD_THREADS, NQT >= 8 ? 1 : 2) void reduce_bf16_kern
 // moments, and the bf16 value of the next version of the factor.  Adapters without tokens in the
 // batch are not trained by it and are left alone.  A thread owns four elements; the slots are laid out
 // like the gradient, so every access is whole lines, and eight slots are read at a time.
-__global__ __launch_bounds__(256) void reduce_finalize_kernel(ReducePair p) {
-  const bool second = (int)blockIdx.x >= p.n0;
-  const ReduceArgs& a = second ? p.a[1] : p.a[0];
+template <int FORM>
+__device__ __forceinline__ void reduce_finalize(const ReduceArgs& a, int bx) {
   if (!a.to_partials) return;
   // (ragged: the grid covers the adapters that are cut, the longest ones, first in `order`)
   const int t = a.ragged ? a.order[blockIdx.y] : blockIdx.y;
   const int r = a.table[t].rank;
-  const int64_t off = ((int64_t)(blockIdx.x - (second ? p.n0 : 0)) * 256 + threadIdx.x) * 4;
+  const int64_t off = ((int64_t)bx * 256 + threadIdx.x) * 4;
   if (off >= a.C * r) return;
   const int len = a.seg_off[t + 1] - a.seg_off[t];
   if (a.opt.on && len == 0) return;
   const int nch = (len + a.tchunk - 1) / a.tchunk;
   if (a.ragged && nch <= 1) return;      // (written by its one block)
   const int64_t slot0 = a.ragged ? (int64_t)a.chunk_base[t] : (int64_t)t * a.chunks_max, slot = a.C * a.r_stride;
-  // (C is a multiple of 8: only ranks that are no multiples of 4 leave an element's neighbours in another row)
-  const bool whole = a.form == FORM_NT || (r & 3) == 0;
-  const float* from[4];
+  // (C is a multiple of 8: only ranks that are no multiples of 4 leave an element's neighbours in another row; C r is
+  // at most 2^31)
+  const bool whole = FORM == FORM_NT || (r & 3) == 0;
+  auto place = [&](uint32_t o) { return FORM == FORM_NT ? (int64_t)o : (int64_t)(o / (uint32_t)r) * a.r_stride + o % (uint32_t)r; };
+  const float* from = a.partials + slot0 * slot + place((uint32_t)off);
+  int next[4] = {0, 1, 2, 3};            // the four elements, counted from the first
+  if (!whole)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) from[i] = a.partials + slot0 * slot + (a.form == FORM_NT ? off + i : (off + i) / r * a.r_stride + (off + i) % r);
+    for (int i = 1; i < 4; ++i) next[i] = (int)(place((uint32_t)off + i) - place((uint32_t)off));
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   auto read = [&](int ch) {
     f32x4 s;
-    if (whole) s = *(const f32x4*)(from[0] + ch * slot);
+    if (whole) s = *(const f32x4*)(from + ch * slot);
     else
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s[i] = from[i][ch * slot];
+      for (int i = 0; i < 4; ++i) s[i] = from[ch * slot + next[i]];
     return s;
   };
   int ch = 0;
@@ -892,6 +892,11 @@ __global__ __launch_bounds__(256) void reduce_finalize_kernel(ReducePair p) {
     if (a.accumulate) { const f32x4 was = *out; sum[0] += was[0]; sum[1] += was[1]; sum[2] += was[2]; sum[3] += was[3]; }
     *out = sum;
   }
+}
+
+__global__ __launch_bounds__(256) void reduce_finalize_kernel(ReducePair p) {
+  if ((int)blockIdx.x < p.n0) reduce_finalize<FORM_NN>(p.a[0], blockIdx.x);
+  else reduce_finalize<FORM_NT>(p.a[1], blockIdx.x - p.n0);
 }
 
 static void reduce_plan(int64_t C, int n_adapters, int max_seg, int* tchunk, int* chunks_max) {
@@ -938,7 +943,7 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   a.order = order;
   a.ragged = 0; a.chunk_base = nullptr; a.ragged_slots = a.ragged_adapters = 0; a.n_adapters = n_adapters;
   a.X = j.X; a.ldx = j.ldx; a.C = j.C; a.perm = perm; a.seg_off = seg_off; a.table = table;
-  a.grads = grads; a.which = j.which; a.form = j.form; a.V = j.V; a.r_stride = r_stride; a.accumulate = accumulate;
+  a.grads = grads; a.which = j.which; a.V = j.V; a.r_stride = r_stride; a.accumulate = accumulate;
   a.slabs = (int)((j.C + RD_COLS - 1) / RD_COLS);
   a.partials = nullptr;
   reduce_plan(j.C, n_adapters, max_seg, &a.tchunk, &a.chunks_max);
@@ -982,9 +987,10 @@ hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, c
   const int64_t slot_rows = ((jobs[0].C + RD_COLS - 1) / RD_COLS + (jobs[1].C + RD_COLS - 1) / RD_COLS) * T_lora / 512;
   ReducePair p;
   size_t bytes[2];
+  if (jobs[0].form == jobs[1].form) return hipErrorInvalidValue;           // (one layout of the factors: each form once)
   for (int j = 0; j < 2; ++j) {
-    const hipError_t e = reduce_args(jobs[j], perm, seg_off, n_adapters, max_seg, table, grads, r_stride, accumulate, partial_bytes, order, chunk_base,
-                                     ragged_chunk, ragged_slots, ragged_adapters, slot_rows, &p.a[j], &bytes[j]);
+    const hipError_t e = reduce_args(jobs[jobs[0].form == FORM_NN ? j : 1 - j], perm, seg_off, n_adapters, max_seg, table, grads, r_stride, accumulate,
+                                     partial_bytes, order, chunk_base, ragged_chunk, ragged_slots, ragged_adapters, slot_rows, &p.a[j], &bytes[j]);
     if (e != hipSuccess) return e;
     bytes[j] = (bytes[j] + 255) / 256 * 256;
     p.a[j].partials = partials;
@@ -1001,28 +1007,23 @@ hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, c
     if (e != hipSuccess) return e;
   }
   for (int first = 0; first < 2; first += both ? 2 : 1) {
-    ReducePair q = p;
-    if (first == 1) q.a[0] = p.a[1];
-    int x[2] = {0, 0}, y = 0;
-    for (int j = 0; j < (both ? 2 : 1); ++j) {
-      const ReduceArgs& a = q.a[j];
+    int x[2] = {0, 0}, y = 0, adapters = 0;
+    int64_t blocks[2] = {0, 0};
+    for (int j = first; j < (both ? 2 : first + 1); ++j) {
+      const ReduceArgs& a = p.a[j];
       x[j] = a.slabs * (a.ragged ? 1 : a.chunks_max);
       y = std::max(y, a.ragged ? reduce_ragged_rows(n_adapters, ragged_slots, ragged_adapters) : n_adapters);
+      if (!a.to_partials) continue;
+      blocks[j] = (a.C * r_stride + 1023) / 1024;
+      adapters = std::max(adapters, a.ragged ? ragged_adapters : n_adapters);
     }
-    q.n0 = x[0];
-    hipLaunchKernelGGL(kern, dim3(x[0] + x[1], y), dim3(RD_THREADS), lds, stream, q);
+    p.n0 = x[0];
+    hipLaunchKernelGGL(kern, dim3(x[0] + x[1], y), dim3(RD_THREADS), lds, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    int64_t blocks[2] = {0, 0};
-    int adapters = 0;
-    for (int j = 0; j < (both ? 2 : 1); ++j)
-      if (q.a[j].to_partials) {
-        blocks[j] = (q.a[j].C * r_stride + 1023) / 1024;
-        adapters = std::max(adapters, q.a[j].ragged ? ragged_adapters : n_adapters);
-      }
     if (adapters == 0) continue;
-    q.n0 = (int)blocks[0];
-    hipLaunchKernelGGL(reduce_finalize_kernel, dim3((unsigned)(blocks[0] + blocks[1]), adapters), dim3(256), 0, stream, q);
+    p.n0 = (int)blocks[0];
+    hipLaunchKernelGGL(reduce_finalize_kernel, dim3((unsigned)(blocks[0] + blocks[1]), adapters), dim3(256), 0, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -164,6 +164,14 @@ def test_some_rows_keep_their_registers(listings):
     assert len(spills) == 4 and all(n == "0" for n in spills)
 
 
+# The reductions of both gradients share a launch; the arguments of each storage form stay its own.
+def test_reductions_keep_their_scalars(listings):
+    spills = dict(re.findall(r"\.name: +(_ZN7marlaas18reduce_bf16_kernelILi\d+E\w+)\n(?:.*\n)*?.*\.sgpr_spill_count: +(\d+)", listings["lora_small"]))
+    assert len(spills) == 4
+    for name, n in spills.items():
+        assert "ILi8E" in name or n == "0", name
+
+
 @pytest.mark.parametrize("f", ["gemm_mid", "gemm_decode"])
 def test_no_write_over_a_pending_lds_read(listings, f):
     for name, blocks in _functions(listings[f]):
