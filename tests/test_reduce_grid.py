@@ -2,7 +2,6 @@
 import ctypes
 import subprocess
 
-import numpy as np
 import pytest
 
 from paper_2605_08527_amd import build
@@ -27,8 +26,7 @@ def rows(tmp_path_factory):
     subprocess.run([build.HIPCC, "--cuda-host-only", "-std=c++17", "-shared", "-fPIC", "-I", build.CSRC, str(d / "rows.hip"), "-o", str(d / "rows.so")],
                    check=True, stderr=subprocess.DEVNULL)
     f = ctypes.CDLL(str(d / "rows.so")).rows
-    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
-    return lambda lens: f(int(sum(lens)), len(lens), np.ascontiguousarray(lens, dtype=np.int32).ctypes.data)
+    return lambda lens: f(ctypes.c_int64(sum(lens)), len(lens), (ctypes.c_int32 * len(lens))(*lens))
 
 
 # one adapter with half of all rows among hundreds that are just cut; as many as there can be; a few; none is cut
