@@ -155,7 +155,5 @@ hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream);
 // Up to MID_ROWS rows likewise (gemm_mid.hip); partials, thin_u: the context's areas.
 hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream_t stream);
-MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora, int max_split);
-bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext);
 
 }  // namespace marlaas

@@ -7,7 +7,7 @@
 // computed by the same kernel as 32 extended columns per column tile; the finish kernel adds the
 // splits, applies the expand in fp32 and scatters the rows.  transpose_bf16_kernel: per-call
 // transposed copy of a weight that is stored output-contiguous, for large batches.
-#include "gemm_args.h"
+#include "mid_plan.h"
 
 #include <atomic>
 #include <cstring>
