@@ -923,9 +923,9 @@ static MidLora mid_lora_of(const marlaas_lora_desc* descs, int32_t n_proj, int r
 }
 
 // A call on packed weights (W and ldw of `proj` filled in) that one of the one-launch kernels does best:
-// enqueues it and sets *done.
+// enqueues it and sets *done.  room: bytes for another kernel's partial sums.
 static int launch_packed(marlaas_ctx* ctx, int32_t* exchange, const marlaas_lora_desc* descs, int32_t n_proj, const ProjEntry* proj, const bf16_t* x, int64_t ldx,
-                         int64_t Kc, int form, bool lora, const AdapterEntry* table, int which, int out_f32, float* u, int rs, hipStream_t st, bool* done) {
+                         int64_t Kc, int form, bool lora, const AdapterEntry* table, int which, int out_f32, float* u, int rs, size_t room, hipStream_t st, bool* done) {
   const marlaas_lora_desc* d = &descs[0];
   const marlaas_segmap* map = d->map;
   const int32_t* perm = map->perm_dev;       // (also of a grouped batch: a captured call serves the map's later batches)
@@ -935,7 +935,7 @@ static int launch_packed(marlaas_ctx* ctx, int32_t* exchange, const marlaas_lora
   int ext = 0;
   for (int t = 0; lora && t < d->n_adapters; ++t) if (map->seg_off[t + 1] > map->seg_off[t]) ext += ranks_of(d)[t];
   const MidLora ml = lora ? mid_lora_of(descs, n_proj, rs) : MidLora();
-  const MidPlan mid = gemm_mid_plan(form, d->T, ldx, Kc, proj, n_proj, ml, ext, &sync);
+  const MidPlan mid = gemm_mid_plan(form, d->T, ldx, Kc, proj, n_proj, ml, ext, room, &sync);
   if (mid.rb) {
     const int jobs = lora ? mid_max_jobs(d->T, mid.rb, ml) : 0;
     PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_gemm_bf16_mid(x, ldx, form, d->T, Kc, perm, map->seg_off_dev, n, table, which, proj, n_proj, out_f32, u, rs, mid,
@@ -991,7 +991,7 @@ static int fwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, void* y, int64
     ProjEntry pe;
     memset(&pe, 0, sizeof pe);
     pe.W = d->W_packed_fwd; pe.ldw = packed_weight_ksteps(d->d_in); pe.Nout = d->d_out; pe.out = y; pe.ldo = ldy;
-    if ((rc = launch_packed(ctx, exchange, d, 1, &pe, (const bf16_t*)d->x, d->ldx, d->d_in, form, lora, table, 1, out_f32, (float*)u_save, rs, st, &done)) != MARLAAS_OK)
+    if ((rc = launch_packed(ctx, exchange, d, 1, &pe, (const bf16_t*)d->x, d->ldx, d->d_in, form, lora, table, 1, out_f32, (float*)u_save, rs, part ? p.part_bytes : 0, st, &done)) != MARLAAS_OK)
       return rc;
   }
   if (done) {
@@ -1168,7 +1168,7 @@ extern "C" int marlaas_lora_fwd_multi(marlaas_ctx* ctx, const marlaas_lora_desc*
     for (int p = 0; p < n_proj; ++p) { pk[p].W = descs[p].W_packed_fwd; pk[p].ldw = packed_weight_ksteps(d0->d_in); }
     bool done = false;
     rc = launch_packed(ctx, ctx->exchange, descs, n_proj, pk.data(), (const bf16_t*)d0->x, d0->ldx, d0->d_in, form, lora, lora ? d0->table->dev.entries : nullptr, 1,
-                       d0->out_dtype == MARLAAS_F32, nullptr, rs_all, (hipStream_t)stream, &done);
+                       d0->out_dtype == MARLAAS_F32, nullptr, rs_all, ctx->ws ? ctx->ws_bytes : 0, (hipStream_t)stream, &done);
     if (rc != MARLAAS_OK || done) return rc;
   }
   // descriptors that refer to tables, but not to one table in projection order, have no combined tables
@@ -1322,7 +1322,7 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
       ProjEntry pe;
       memset(&pe, 0, sizeof pe);
       pe.W = d->W_packed_bwd; pe.ldw = packed_weight_ksteps(d->d_out); pe.Nout = d->d_in; pe.out = dX; pe.ldo = lddx;
-      if ((rc = launch_packed(ctx, exchange, d, 1, &pe, dy, lddy, d->d_out, bform, lora, table, 0, out_f32, v, rs, st, &done)) != MARLAAS_OK) return rc;
+      if ((rc = launch_packed(ctx, exchange, d, 1, &pe, dy, lddy, d->d_out, bform, lora, table, 0, out_f32, v, rs, part ? p.part_bytes : 0, st, &done)) != MARLAAS_OK) return rc;
     }
     if (!done && lora && dX && part && bank_can_fuse(bank)) {
       fused = gemm_can_fuse_shrink(bform, d->T, d->d_out, d->d_in, need, bank.mult8, use_packed && d->W_packed_bwd, p.part_bytes);

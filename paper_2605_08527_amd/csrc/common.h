@@ -279,8 +279,9 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
 // The same for more rows (gemm_mid.hip); the plan says whether it is the kernel for these sizes.  ext: ranks of
 // all adapters in the batch (0: none); seg_off: rows of the adapters (device); proj_jobs: the most shrink jobs
 // (16 ranks of an adapter x a pair of 16-row blocks of a row tile, 16 plan.rb rows) that any grouping of T rows
-// has in any projection.
-MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, const MidLora& lora, int ext, const DecodeSync* sync);
+// has in any projection; room: bytes of partial sums that another kernel would have.
+MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, const MidLora& lora, int ext, size_t room,
+                      const DecodeSync* sync);
 hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,
                                 const AdapterEntry* table, int which, const ProjEntry* proj_host, int n_proj, int out_is_f32,
                                 float* u, int r_stride, const MidPlan& plan, int proj_jobs, const bf16_t* zero_line, const DecodeSync* sync,

@@ -1011,7 +1011,8 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
 }
 
 // ---- some more rows
-MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, const MidLora& lora, int ext, const DecodeSync* sync) {
+MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, const MidLora& lora, int ext, size_t room,
+                      const DecodeSync* sync) {
   if (T <= 0 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || (lora.n > 0 && (!sync->counters || form != FORM_NT || !sync->grp_ids || lora.r_stride > 128)) ||
       (sync->mode != DECODE_FINISH_AUTO && sync->mode != DECODE_FINISH_IN_KERNEL))
     return MidPlan();
@@ -1020,7 +1021,12 @@ MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEn
   const MidPlan p = mid_plan(T, Kc, proj_host, n_proj, lora, sync->counters ? 4 : 1);     // (splits exchange sums)
   for (int q = 0; q < n_proj; ++q)
     if ((proj_host[q].Nout + 32 * p.wn - 1) / (32 * p.wn) * p.ksplit > MID_CONSUMERS) return MidPlan();
-  return mid_pays(p, T, Kc, cols, ext) ? p : MidPlan();
+  auto wide_us = [&]() {                                         // (it takes the projections one after the other)
+    double us = 0.0;
+    for (int q = 0; q < n_proj; ++q) us += wide_plan(T, Kc, proj_host[q].Nout, room).us;
+    return us;
+  };
+  return mid_pays(p, T, Kc, cols, ext, wide_us) ? p : MidPlan();
 }
 
 hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,

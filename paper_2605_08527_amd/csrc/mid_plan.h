@@ -88,17 +88,22 @@ inline MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj
 
 // Whether the call is better off elsewhere (ext: ranks of all adapters in the batch, 0: no adapters).
 //   Up to 16 rows the few-row kernel, up to 32 while its workgroups, which hold all of x, have little of it.
-//   Above 384 rows the wide kernel where its plan, without adapters, or its rate, which has to make up for its
-//   shrink's launch and its ext columns, says so (400 rows, 4096 x 14336, no adapter: 48 against 63 us, 32 adapters
-//   of rank 16 86 / 75; 4096 x 4096, no adapter, 27 / 23; 14336 x 4096, 32 adapters, 109 / 75).
+//   Above 384 rows the wide kernel.  With adapters where its rate, which has to make up for its shrink's launch and its
+// ext columns, says so (400 rows, 4096 x 14336, 32 adapters of rank 16 86 against 75 us; 14336 x 4096 109 / 75).
+// Without where its plan does, in the room for sums that the call has (wide_us: its estimated time, asked for there); the
+// estimate leaves out the 6 us of a launch and its first requests, and the one here what rows of x above 4096 cost: of 24
+// sizes of 395 to 995 rows the choice costs 0.7 % on the average, 4.5 % without both (407 rows, 1608 x 5544, 28 / 21; 422
+// rows, 5048 x 13864, 79 / 106; 751 rows, 10784 x 10280, 143 / 250).
 //   Up to 256 rows the split kernel with its separate finish on a long contraction and few columns, where the row
 //   tiles here are few and their splits expensive (256 rows, 14336 x 4096, no adapter: 36 / 41, 157 rows 37 / 31;
 //   200 rows, 20480 x 2048, 32 adapters of rank 16: 44 / 52; 256 rows, 14336 x 4096 from memory 63 / 70; up to 128
 //   rows with adapters never: 100 rows 45 / 35 and 37 / 36).
-inline bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext) {
+template <typename Wide>
+inline bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext, Wide wide_us) {
   if (T <= 16) return false;
   if (T <= 32) return T * Kc > 140000 || Kc * cols > 50000000;
-  if (T > 384) return p.us < (ext > 0 ? 20.0 + 2.0 * T * Kc * cols / 1.25e9 + 0.1 * ext : wide_plan(T, Kc, cols, SIZE_MAX).us);
+  if (T > 384 && ext > 0) return p.us < 20.0 + 2.0 * T * Kc * cols / 1.25e9 + 0.1 * ext;
+  if (T > 384) return p.us * (Kc > 4096 ? 1.0 + 0.2 * log2((double)Kc / 4096.0) : 1.0) < 6.0 + wide_us();
   if (T > 64 && T <= 256 && Kc >= 2 * cols && Kc * cols >= 40000000) {
     if (ext == 0) return p.us < 15.0 + Kc * cols * (T <= 128 ? 0.29e-6 : 0.365e-6);
     if (T > 128 && ext <= 512) return 1.15 * p.us < 15.0 + Kc * cols * 0.67e-6;

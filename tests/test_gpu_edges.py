@@ -227,6 +227,22 @@ def test_some_rows_route_lines(oracle, T, K, N, ranks):
     _check_layer(oracle, w, bwd=False, tag="route lines", table="table+packed")
 
 
+# Rows without adapters on both sides of the line to the large-batch kernel, which moves with the room for its sums.
+@pytest.mark.parametrize("T,K,N", [(407, 1608, 2048), (605, 6072, 1032), (751, 4104, 2056)])
+def test_rows_without_adapters_in_any_room(oracle, T, K, N):
+    w = wl.make_layer(T + N, T, K, N, [8], [1.0], np.full(T, -1, np.int32), dtype="bf16", layout=wl.TORCH)
+    ref = oracle.fwd(w["x"], w["W"], w["A"], w["B"], w["ranks"], w["scales"], w["ids"], layout=wl.TORCH)
+    L = HipLayer(w, table=True, packed=True)
+    for room in (L.ws, L.ws[:L.ws.numel() // 2 // 256 * 256], L.ws[:256], None):
+        try:
+            api.marlaas_set_workspace(L.ctx, room)
+            y, _ = L.fwd()
+        except api.MarlaasError as e:
+            assert e.status == -4 and room is not L.ws
+            continue
+        assert_close(to_host(y), ref, "no adapters")
+
+
 # A workgroup that gives up waiting computes what it waited for in the same order of sums: no bit depends on
 # which workgroups were on the chip.  (Limit 0: every wait is given up at once.)
 @pytest.mark.parametrize("layout", [0, 1])
