@@ -58,7 +58,6 @@ struct MidShape {
   static constexpr int NS = RB == 4 || WN == 4 ? 4 : 3; // ring slots = k-tiles on the way (registers, LDS)
   static constexpr int SLOT = RB * 16 * K * 2;
   static constexpr int RED = RB * WN * 2 * (KG - 1) * 1024;       // exchange of the contraction groups
-  
 };
 
 // Job `job` of a projection's shrink, counted over all row tiles (16 RB rows each): 16 ranks of an adapter for its
