@@ -242,8 +242,8 @@ int marlaas_transpose_weight(marlaas_ctx* ctx, const void* W, int64_t ldw, int64
  * kernels that exchange nothing (for few rows on packed weights up to twice the
  * time), so a program keeps its workspaces and does not allocate one per call.  It holds the intermediates u, v, partial sums, a transposed
  * weight copy for some large batches and, for descriptors without an adapter
- * table, a per-call copy of their pointer tables (written by a small kernel at
- * the start of the pass).  marlaas_workspace_bytes returns the size at which
+ * table, a per-call copy of their pointer tables (written at the start of the pass,
+ * by a small kernel or by the shrink's launch).  marlaas_workspace_bytes returns the size at which
  * marlaas_lora_fwd (want_bwd = 0) or fwd and bwd (want_bwd = 1) run their
  * fastest plans for this descriptor (only sizes, ranks, dtypes, table and map
  * are read), or 0 if the descriptor is invalid.  With a smaller workspace a pass

@@ -12,10 +12,11 @@
 // workgroups share a compute unit (128 registers, 80 KB of LDS).
 //
 // Measured (microseconds, before: extended columns through the split kernel and a second launch): 256 rows
-// 4096 x 4096 with 32 adapters of rank 16 28.4 -> 22.5, q/k/v of 4096 + 1024 + 1024 columns 42.0 -> 31.0, the
-// four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 196, 512 rows of 64 adapters of ranks 8
-// to 64, 5120 x 5120, 63 (weights from memory).  Stamps in the 256 rows: indices 1.8, first tile 3.8, loop done 15.4 (17.5 where a
-// producer shares the unit; 14.6 without adapters), sums and u 17.4, expand 18.5, stored 19.1.
+// 4096 x 4096 with 32 adapters of rank 16 28.4 -> 22.4, q/k/v of 4096 + 1024 + 1024 columns 42.0 -> 31.0, the
+// four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 194, 512 rows of 64 adapters of ranks 8
+// to 64, 5120 x 5120, 63 (weights from memory).  Stamps in the 256 rows, of a version that asked for u before the
+// sums and took 23.1: indices 1.8, first tile 3.8, loop done 15.4 (17.5 where a producer shares the unit; 14.6 without
+// adapters), sums and u 17.4, expand 18.5, stored 19.1.
 //
 // Whatever crosses workgroups carries its own flag: it travels through areas of the context that are all
 // zero bits between launches, no value is stored as zero bits (+0 becomes -0), and a reader reads until
