@@ -149,10 +149,10 @@ __host__ __device__ inline int reduce_ragged_chunk(int64_t T_lora, int n) {
   if (c < 512) c = 512;
   return (int)((c + 63) / 64 * 64);
 }
-// Workgroups that such a cut takes per slab of columns: one for every slot, one for every adapter without.  A
-// chunk is at least twice the mean segment, so there are at most n / 2 whole ones and n remainders: less than
-// 3 n, and a grid's y holds 65535.
-inline int reduce_ragged_rows(int n, int ragged_slots, int ragged_adapters) { return ragged_slots + n - ragged_adapters; }
+// Workgroups that such a cut takes per slab of columns: one for every slot, one for every adapter.  A chunk is at
+// least twice the mean segment, so the slots are at most n / 2 whole chunks and n remainders: less than 3 n in all, and a
+// grid's y holds 65535.
+inline int reduce_ragged_rows(int n, int ragged_slots) { return ragged_slots + n; }
 // The same in one launch (T <= 32768, n <= 800); host: pinned, receives seg_off[n + 2], the two
 // flags and then `seq`, in this order (n + 5 values).
 bool segmap_is_small(int64_t T, int n);

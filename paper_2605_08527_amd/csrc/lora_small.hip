@@ -622,8 +622,7 @@ struct ReduceArgs {
   // ragged = 1: only segments longer than tchunk are cut; adapter t's pieces use partial-sum slots
   // chunk_base[t] .. ([slot][C][r_stride]), every other adapter's block writes its result itself
   int ragged; const int32_t* chunk_base;
-  int ragged_slots, ragged_adapters;       // slots, adapters that have some (the first ones in `order`)
-  int n_adapters;
+  int ragged_slots, n_adapters;
   float* partials;                         // [adapter][chunk] slots when to_partials
   int to_partials;                         // 1: the chunks' sums go to `partials`, reduce_finalize_kernel completes;
                                            // a slot is laid out like the gradient, [C][r_stride] or [r_stride][C]
@@ -643,9 +642,10 @@ __device__ __forceinline__ int swz_tokc(int tk, int unit) {
   return tk * 512 + ((unit ^ (f << 1)) << 4);
 }
 
-// grid: x = slabs * chunks_max of both jobs, y = adapter; ragged: x = slabs, y = the slots, then the adapters that
-// have none (a rectangle of the longest segment's chunks for every adapter that is cut was mostly workgroups
-// without rows, and above 65535 rows of them where one of many adapters has most tokens).  The kernel is bound by the one pass over X, so the
+// grid: x = slabs * chunks_max of both jobs, y = adapter; ragged: x = slabs, y = a row for every slot, whose further
+// chunks go first, then every adapter's first chunk, the longest segment first (with the first chunks among the slots
+// 16896 rows of 64 adapters took 114 us, so 110.5; a rectangle of the longest segment's chunks for every adapter that is cut
+// is above 65535 rows where one of many adapters has most tokens).  The kernel is bound by the one pass over X, so the
 // loop is software-pipelined through registers: while a 64-token step is multiplied out of LDS,
 // the X rows and V rows of the next step are already requested (and the gather indices of the
 // step after that), and only the LDS hand-over sits between two barriers.  The operand order of the matrix
@@ -659,9 +659,10 @@ __device__ __forceinline__ void reduce_block(const ReduceArgs& a, int bx, int by
   if (a.ragged && by < a.ragged_slots) {
     t = wave_last(a.n_adapters, [&](int i) { return a.chunk_base[i] <= by; });
     ch = by - a.chunk_base[t];                  // (a chunk of twice the length has no rows for the second half of the slots)
+    if (ch == 0) return;
   } else {
     if (!a.ragged) ch = bx / a.slabs;
-    const int k = a.ragged ? by - a.ragged_slots + a.ragged_adapters : by;
+    const int k = a.ragged ? by - a.ragged_slots : by;
     if (k >= a.n_adapters) return;
     t = a.order ? a.order[k] : k;
   }
@@ -941,7 +942,7 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   ReduceArgs a;
   const size_t slot = (size_t)j.C * r_stride * sizeof(float);
   a.order = order;
-  a.ragged = 0; a.chunk_base = nullptr; a.ragged_slots = a.ragged_adapters = 0; a.n_adapters = n_adapters;
+  a.ragged = 0; a.chunk_base = nullptr; a.ragged_slots = 0; a.n_adapters = n_adapters;
   a.X = j.X; a.ldx = j.ldx; a.C = j.C; a.perm = perm; a.seg_off = seg_off; a.table = table;
   a.grads = grads; a.which = j.which; a.V = j.V; a.r_stride = r_stride; a.accumulate = accumulate;
   a.slabs = (int)((j.C + RD_COLS - 1) / RD_COLS);
@@ -957,7 +958,7 @@ static hipError_t reduce_args(const ReduceJob& j, const int32_t* perm, const int
   const bool opt = j.opt && j.opt->on;
   if (!opt && a.chunks_max == 1 && chunk_base != nullptr && order != nullptr && ragged_adapters > 0 && ragged_adapters <= n_adapters &&
       reduce_ragged(j.C, n_adapters, max_seg, ragged_chunk, ragged_slots) && partial_bytes >= ragged_slots * slot) {
-    a.ragged = 1; a.chunk_base = chunk_base; a.ragged_slots = ragged_slots; a.ragged_adapters = ragged_adapters;
+    a.ragged = 1; a.chunk_base = chunk_base; a.ragged_slots = ragged_slots;
     // (every cut costs a sum written and read: pieces of twice the length where the rows that a place on the chip
     // has to take, two workgroups a unit, are more than that.  16896 rows, 64 adapters, 5120 x 5120: pieces of
     // 576 rows 117 + 18 us, 1088 rows 110 + 13, 1600 rows 115 + 10, whole segments 151.)
@@ -1012,7 +1013,7 @@ hipError_t launch_reduce_bf16(const ReduceJob (&jobs)[2], const int32_t* perm, c
     for (int j = first; j < (both ? 2 : first + 1); ++j) {
       const ReduceArgs& a = p.a[j];
       x[j] = a.slabs * (a.ragged ? 1 : a.chunks_max);
-      y = std::max(y, a.ragged ? reduce_ragged_rows(n_adapters, ragged_slots, ragged_adapters) : n_adapters);
+      y = std::max(y, a.ragged ? reduce_ragged_rows(n_adapters, ragged_slots) : n_adapters);
       if (!a.to_partials) continue;
       blocks[j] = (a.C * r_stride + 1023) / 1024;
       adapters = std::max(adapters, a.ragged ? ragged_adapters : n_adapters);

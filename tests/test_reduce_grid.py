@@ -9,12 +9,12 @@ from paper_2605_08527_amd import build
 SOURCE = """#include "common.h"
 extern "C" int rows(int64_t T, int n, const int32_t* len) {
   const int chunk = marlaas::reduce_ragged_chunk(T, n);
-  int slots = 0, cut = 0;
+  int slots = 0;
   for (int t = 0; t < n; ++t) {
     const int pieces = (len[t] + chunk - 1) / chunk;
-    if (pieces > 1) { slots += pieces; ++cut; }
+    if (pieces > 1) slots += pieces;
   }
-  return marlaas::reduce_ragged_rows(n, slots, cut);
+  return marlaas::reduce_ragged_rows(n, slots);
 }
 """
 
@@ -35,6 +35,6 @@ def rows(tmp_path_factory):
 def test_rows_of_the_grid(rows, lens):
     got, n = rows(lens), len(lens)
     chunk = (max(512, 2 * sum(lens) // n) + 63) // 64 * 64
-    pieces = sum(max(1, -(-v // chunk)) for v in lens)     # nobody needs more: one for every piece, one for every adapter without rows
-    assert got == pieces
+    pieces = sum(-(-v // chunk) for v in lens if v > chunk)
+    assert got == n + pieces
     assert got < 3 * n and got <= 65535
