@@ -644,7 +644,7 @@ __device__ __forceinline__ int swz_tokc(int tk, int unit) {
 
 // grid: x = slabs * chunks_max of both jobs, y = adapter; ragged: x = slabs, y = a row for every slot, whose further
 // chunks go first, then every adapter's first chunk, the longest segment first (with the first chunks among the slots
-// 16896 rows of 64 adapters took 114 us, so 110.5; a rectangle of the longest segment's chunks for every adapter that is cut
+// 16896 rows of 64 adapters, 5120 x 5120, took 113.4 us, so 108.0; a rectangle of the longest segment's chunks for every adapter that is cut
 // is above 65535 rows where one of many adapters has most tokens).  The kernel is bound by the one pass over X, so the
 // loop is software-pipelined through registers: while a 64-token step is multiplied out of LDS,
 // the X rows and V rows of the next step are already requested (and the gather indices of the
