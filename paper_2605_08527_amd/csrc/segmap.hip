@@ -178,30 +178,41 @@ static constexpr int SM_THREADS = 1024, SM_WAVES = SM_THREADS / 64;
 static constexpr int64_t SEG_SMALL_T = 32768;
 static constexpr int SEG_SMALL_N = 800;       // one bucket per thread in the scans, [waves][buckets] counters in LDS
 
-// Exclusive prefix sum of one value per thread over the block (s_wave: SM_WAVES ints of LDS).
-__device__ __forceinline__ int block_scan(int v, int32_t* s_wave, int* total) {
+// Exclusive prefix sums of two values per thread over the block's first `waves` waves (s_wave: 2 SM_WAVES ints of
+// LDS that nobody else touches); every thread calls it, with 0 from the waves behind.
+__device__ __forceinline__ int2 block_scan(int2 v, int waves, int32_t* s_wave, int2* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
+  int2 inc = v;
+  if (wave < waves) {
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) { const int o = __shfl_up(inc, d); if (lane >= d) inc += o; }
-  __syncthreads();                            // (the previous scan's sums have been read)
-  if (lane == 63) s_wave[wave] = inc;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int x = __shfl_up(inc.x, d), y = __shfl_up(inc.y, d);
+      if (lane >= d) { inc.x += x; inc.y += y; }
+    }
+    if (lane == 63) { s_wave[2 * wave] = inc.x; s_wave[2 * wave + 1] = inc.y; }
+  }
   __syncthreads();
-  int before = 0, all = 0;
-#pragma unroll
-  for (int w = 0; w < SM_WAVES; ++w) { if (w < wave) before += s_wave[w]; all += s_wave[w]; }
+  int2 before = make_int2(0, 0), all = make_int2(0, 0);
+  for (int w = 0; w < waves; ++w) {
+    const int x = s_wave[2 * w], y = s_wave[2 * w + 1];
+    if (w < wave) { before.x += x; before.y += y; }
+    all.x += x; all.y += y;
+  }
   *total = all;
-  return before + inc - v;
+  return make_int2(before.x + inc.x - v.x, before.y + inc.y - v.y);
 }
 
 // The whole grouping in one block: every wave owns a contiguous run of tokens, walks it 64 at a time
 // and counts its buckets (tokens of one bucket inside a wave find each other with one ballot per bit
 // of the bucket number); one scan over (bucket, wave) then gives every wave its first slot in every
-// bucket, and a second walk hands the slots out.  No atomics, order of equal ids = order of indices.
+// bucket, and a second walk hands the slots out.  No atomics on the slots, order of equal ids = order of indices.
 // The segment sizes go straight to pinned host memory, behind them `seq`, which the host waits for.
 //
 // Bound: launch and latency.  As six launches and two copies the grouping of 512 tokens kept the host
 // waiting 45 us (each of them 4 us of launch for under 2 us of work) before it could enqueue the pass.
+// So up to 256 tokens a wave the ids stay in registers for the second walk, every wave ranks a share of the adapters,
+// and one wave's fence, behind a barrier, serves for all: 512 tokens of 64 adapters 10.8 -> 6.3 us, a step that
+// regroups them and runs one 5120 x 5120 projection 85.0 -> 79.6.
 __global__ __launch_bounds__(SM_THREADS) void segmap_small(const int32_t* __restrict__ ids, int T, int n, int nbits,
                                                            int32_t* __restrict__ perm, int32_t* __restrict__ grp_ids,
                                                            int32_t* __restrict__ seg_off, RowChunk* __restrict__ chunks,
@@ -212,27 +223,34 @@ __global__ __launch_bounds__(SM_THREADS) void segmap_small(const int32_t* __rest
   int32_t* cur = lds;                         // [SM_WAVES][nb] counts, then next slots
   int32_t* off = cur + SM_WAVES * nb;         // [nb + 1] segment offsets
   int32_t* first = off + nb + 1;              // [nb] first row chunk
-  int32_t* s_wave = first + nb;               // [SM_WAVES]
-  int32_t* flag = s_wave + SM_WAVES;          // [2]
+  int32_t* rank_s = first + nb;               // [n] adapters with longer segments
+  int32_t* s_wave = rank_s + n;               // [2][2 SM_WAVES]
+  int32_t* flag = s_wave + 4 * SM_WAVES;      // [2]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int i = tid; i < SM_WAVES * nb; i += SM_THREADS) cur[i] = 0;
-  if (tid < 2) flag[tid] = 0;
-  __syncthreads();
   const int per = ((T + SM_THREADS - 1) / SM_THREADS) * 64;     // tokens per wave
   const int beg = wave * per, end = beg + per < T ? beg + per : T;
+  const bool once = per <= 256;               // (the ids of a wave's tokens stay in registers)
+  int idv[4], nxt[4];
+  auto load = [&](int s0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = s0 + 64 * j + lane;
+      idv[j] = i < end ? ids[i] : -2;
+      nxt[j] = i + 1 < T && i < end ? ids[i + 1] : idv[j];
+    }
+  };
+  if (once) load(beg);
+  for (int i = tid; i < SM_WAVES * nb; i += SM_THREADS) cur[i] = 0;
+  for (int i = tid; i < n; i += SM_THREADS) rank_s[i] = 0;
+  if (tid < 2) flag[tid] = 0;
+  __syncthreads();
   int32_t* mine = cur + wave * nb;
   bool bad = false, unsorted = false;
 #pragma unroll 1
   for (int walk = 0; walk < 2; ++walk) {
     for (int s0 = beg; s0 < end; s0 += 256) {
-      int idv[4], nxt[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int i = s0 + 64 * j + lane;
-        idv[j] = i < end ? ids[i] : -2;
-        nxt[j] = walk == 0 && i + 1 < T && i < end ? ids[i + 1] : idv[j];
-      }
+      if (!once) load(s0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = s0 + 64 * j + lane;
@@ -270,44 +288,61 @@ __global__ __launch_bounds__(SM_THREADS) void segmap_small(const int32_t* __rest
     if (bad) flag[0] = 1;
     if (unsorted) flag[1] = 1;
     __syncthreads();
-    int total = 0;
-    if (tid < nb) for (int w = 0; w < SM_WAVES; ++w) total += cur[w * nb + tid];
-    int all;
-    const int start = block_scan(total, s_wave, &all);
+    int count[SM_WAVES], total = 0;
     if (tid < nb) {
-      off[tid] = start;
-      seg_off[tid] = start;
-      host[tid] = start;
-      int run = start;
-      for (int w = 0; w < SM_WAVES; ++w) { const int c = cur[w * nb + tid]; cur[w * nb + tid] = run; run += c; }
+#pragma unroll
+      for (int w = 0; w < SM_WAVES; ++w) count[w] = cur[w * nb + tid];
+#pragma unroll
+      for (int w = 0; w < SM_WAVES; ++w) total += count[w];
+    }
+    int2 all;
+    const int2 start = block_scan(make_int2(total, (total + ROW_CHUNK - 1) / ROW_CHUNK), (nb + 63) / 64, s_wave, &all);
+    if (tid < nb) {
+      off[tid] = start.x;
+      first[tid] = start.y;
+      seg_off[tid] = start.x;
+      host[tid] = start.x;
+      int run = start.x;
+#pragma unroll
+      for (int w = 0; w < SM_WAVES; ++w) { cur[w * nb + tid] = run; run += count[w]; }
     }
     if (tid == 0) {
-      off[nb] = all; seg_off[nb] = all;
-      host[nb] = all; host[nb + 1] = flag[0]; host[nb + 2] = flag[1];
+      off[nb] = all.x; seg_off[nb] = all.x;
+      host[nb] = all.x; host[nb + 1] = flag[0]; host[nb + 2] = flag[1];
     }
-    const int fc = block_scan((total + ROW_CHUNK - 1) / ROW_CHUNK, s_wave, &all);
-    if (tid < nb) first[tid] = fc;
     __syncthreads();
   }
-  // adapters by falling segment length, and the partial-sum slots of those that are cut (see segmap_order)
-  const int len = tid < n ? off[tid + 1] - off[tid] : 0;
-  const int tc = reduce_ragged_chunk(off[n], n);
-  const int nch = (len + tc - 1) / tc;
-  int slots;
-  const int cb = block_scan(tid < n && nch > 1 ? nch : 0, s_wave, &slots);
-  if (tid < n) {
-    chunk_base[tid] = cb;
-    int before = 0;
-    for (int s = 0; s < n; ++s) {
-      const int l = off[s + 1] - off[s];
-      before += (l > len) || (l == len && s < tid);
+  // adapters by falling segment length, and the partial-sum slots of those that are cut (see segmap_order): every
+  // wave compares all adapters, a lane each, with its share of them
+  const int share = (n + SM_WAVES - 1) / SM_WAVES, s0 = wave * share, s1 = s0 + share < n ? s0 + share : n;
+  if (s0 < s1)
+    for (int t = lane; t < n; t += 64) {
+      const int len = off[t + 1] - off[t];
+      int before = 0;
+#pragma unroll 4
+      for (int s = s0; s < s1; ++s) {
+        const int l = off[s + 1] - off[s];
+        before += (l > len) || (l == len && s < t);
+      }
+      if (before) atomicAdd(&rank_s[t], before);
     }
-    order[before] = tid;
+  const int tc = reduce_ragged_chunk(off[n], n);
+  const int nch = tid < n ? (off[tid + 1] - off[tid] + tc - 1) / tc : 0;
+  int2 slots;
+  const int2 cb = block_scan(make_int2(nch > 1 ? nch : 0, 0), (nb + 63) / 64, s_wave + 2 * SM_WAVES, &slots);    // (meets: the ranks are complete)
+  if (tid < n) {
+    chunk_base[tid] = cb.x;
+    order[rank_s[tid]] = tid;
   }
-  if (tid == 0) chunk_base[n] = slots;
-  __threadfence_system();                     // this thread's part of the host's copy is out
+  if (tid == 0) chunk_base[n] = slots.x;
+  // Every wave's stores have reached the L2 or, the host's copy, its memory; then one wave writes back what the
+  // other L2s and the host must see and says so.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0) __hip_atomic_store(host + nb + 3, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (tid == 0) {
+    __threadfence_system();
+    __hip_atomic_store(host + nb + 3, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 bool segmap_is_small(int64_t T, int n) { return T > 0 && T <= SEG_SMALL_T && n <= SEG_SMALL_N; }
@@ -316,7 +351,7 @@ hipError_t launch_segmap_small(const int32_t* ids, int64_t T, int n, int32_t* pe
                                RowChunk* chunks, int32_t* order, int32_t* chunk_base, int32_t* host, int seq, hipStream_t stream) {
   int nbits = 0;
   while ((n >> nbits) > 0) ++nbits;
-  const size_t lds = sizeof(int32_t) * ((size_t)SM_WAVES * (n + 1) + (n + 2) + (n + 1) + SM_WAVES + 2);
+  const size_t lds = sizeof(int32_t) * ((size_t)SM_WAVES * (n + 1) + (n + 2) + (n + 1) + n + 4 * SM_WAVES + 2);
   hipLaunchKernelGGL(segmap_small, dim3(1), dim3(SM_THREADS), lds, stream, ids, (int)T, n, nbits, perm, grp_ids, seg_off, chunks,
                      order, chunk_base, host, seq);
   return hipGetLastError();
