@@ -29,7 +29,7 @@ struct marlaas_ctx {
   size_t ws_bytes = 0;
   void* static_ws = nullptr;     // device address of this GPU's static scratch array
   // What the workgroups of one launch exchange through (SYNC_INTS: counters of the decode kernels, then u and
-  // partial sums of the one-launch kernels; all zero between launches).  A launch has it to itself as it has
+  // partial sums of the one-launch kernels; all zero at first, and from then on as the kernels keep it).  A launch has it to itself as it has
   // its scratch, so there is one area for every workspace that the context has been given: calls that may
   // overlap (on other streams, in branches of one graph, graphs that are replayed later) use workspaces of
   // their own, and an area stays with its workspace while the context lives.  Calls with a workspace beyond

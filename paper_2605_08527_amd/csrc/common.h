@@ -197,24 +197,26 @@ enum { DECODE_FINISH_GENERIC = 0,    // splitk_finish_kernel on fp32 rows (any s
        DECODE_FINISH_AUTO = 3 };     // whichever of the two is faster for the split count
 struct DecodeSync {
   int mode = DECODE_FINISH_GENERIC;  // the way asked for; the launcher falls back to the generic one
-  int32_t* counters = nullptr;       // SYNC_INTS, all zero between launches; null: only kernels that exchange nothing
+  int32_t* counters = nullptr;       // SYNC_INTS, all zero before the first launch; null: only kernels that exchange nothing
   const int32_t* grp_ids = nullptr;
   int spin_limit = 0;
   int cu_count = 0;
 };
 static constexpr int DECODE_SYNC_INTS = 4096;
 static constexpr int THIN_ROWS = 32;                              // rows of the few-row kernel (gemm_thin.hip)
-static constexpr int THIN_SPLITS = 4;
+static constexpr int THIN_SPLITS = 4, THIN_U_FLOATS = MAX_PROJ * THIN_SPLITS * THIN_ROWS * 128;
 // One launch for up to MID_ROWS rows (gemm_mid.hip): rows of a tile, columns of a tile / 32, contraction
-// splits.  u travels where the few-row kernel's does ([projection][piece of the contraction][T][r_stride], two pieces always fit), the partial
-// sums of at most MID_SPLIT_WGS workgroups behind it.
+// splits.  u travels in two areas ([projection][piece of the contraction][T][r_stride]) behind the few-row kernel's, the partial
+// sums of at most MID_SPLIT_WGS workgroups behind those.
 static constexpr int MID_ROWS = 1024, MID_SPLITS = 4, MID_SPLIT_WGS = 512;
-static constexpr int MID_U_FLOATS = MAX_PROJ * 2 * MID_ROWS * 128;
+static constexpr int MID_U_FLOATS = MAX_PROJ * MID_ROWS * 128;    // of u in one of its two areas
 static constexpr int MID_PART_FLOATS = MID_SPLIT_WGS * 96 * 128;
-static constexpr int SYNC_INTS = DECODE_SYNC_INTS + MID_U_FLOATS + MID_PART_FLOATS;
-// (the counter of a row tile holds its consumers and MID_JOBS, more than the shrink jobs it can have, in 16 bits)
-static constexpr int MID_JOBS = 4096, MID_CONSUMERS = 65535 - MID_JOBS;
-static_assert(80 * 8 * MID_SPLITS < MID_JOBS, "every row its own adapter of rank 128");
+// Whose turn it is (agent_memory.h): lines of 32 ints; a line counts TURN_ONE a launch, and a launch has fewer workgroups to a
+// line than that.
+static constexpr int TURN_LINES = 32, TURN_INTS = TURN_LINES * 32, TURN_SHIFT = 20;
+static constexpr int MID_CONSUMERS = 61439;                      // column tiles of a projection, times splits
+static_assert((int64_t)MID_CONSUMERS * MAX_PROJ * (MID_ROWS / 64) < (int64_t)TURN_LINES << TURN_SHIFT, "");
+static constexpr int SYNC_INTS = DECODE_SYNC_INTS + THIN_U_FLOATS + TURN_INTS + 2 * MID_U_FLOATS + MID_PART_FLOATS;
 // Readings of a bounded wait, a round trip through the fabric each (1 to 1.5 us under load): what is waited for
 // takes a tenth of it where its workgroups are on the chip, and doing without costs a few hundred microseconds.
 static constexpr int MID_POLLS = 256;

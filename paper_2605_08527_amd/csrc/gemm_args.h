@@ -53,6 +53,7 @@ struct GemmArgs {
   int prod0, proj_jobs, rot;    // (the kernel for more rows: the first of those, shrink jobs of a projection; k-tiles between neighbouring column tiles' starts)
   const bf16_t* zero_line;      // 1024 readable zero bytes
   float* thin_u;                // and where it travels: [MAX_PROJ][THIN_SPLITS][THIN_ROWS][128], zero between launches
+  int32_t* turns; float* mid_u; // the kernel for more rows: whose turn it is (agent_memory.h), and the two areas of [projection][split][T][r_stride]
   ProjEntry proj[MAX_PROJ];     // by value: read with wave-uniform loads from the kernel arguments
 };
 

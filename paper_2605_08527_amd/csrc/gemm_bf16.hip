@@ -1040,7 +1040,8 @@ hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_
   a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
   a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit < MID_POLLS ? sync->spin_limit : MID_POLLS; a.zero_line = zero_line;
   if (sync->counters) {
-    a.thin_u = (float*)(sync->counters + DECODE_SYNC_INTS);
+    a.turns = sync->counters + DECODE_SYNC_INTS + THIN_U_FLOATS;
+    a.mid_u = (float*)(a.turns + TURN_INTS);
     a.partials = (float*)(sync->counters + (SYNC_INTS - MID_PART_FLOATS));
   }
   a.n_proj = n_proj;

@@ -632,13 +632,13 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
   const int per = 32 / a.ksplit;         // units of a share (the host allows ksplit 1, 2, 4, 8 here)
 
   // One unit: sums s[cb] of row block rb (row li), columns n0 + 32 wnu + 16 cb + 4 lg .. + 3.
-  auto finish_unit = [&](int rb, int wnu, f32x4 (&s)[2], const uint4 (&pre)[2]) {
+  auto finish_unit = [&](int rb, int wnu, f32x4 (&s)[2], uint4 (&pre)[1][2]) {
     const int row = rb * 16 + li;
     const int32_t tok = tok_s[row];
     const int cnt = oct_cnt_s[rb];
     const int64_t nb = n0 + wnu * 32;
     if (cnt > 0) {
-      expand_octets(s, pre, cnt, lg, radp_s[row], u_s + row * rs,
+      expand_octets(s, pre, cnt, lg, radp_s[row], [&](int q, bool mine, bf16x8& hi, bf16x8& lo) { split_u(u_s + row * rs + q, mine, hi, lo); },
                     [&](int i) { const int oi = rb * D_MAXOCT + i; return oct_t_s[oi] << 8 | oct_q_s[oi]; },
                     [&](int i, int cb) {
                       const int oi = rb * D_MAXOCT + i;
@@ -688,14 +688,14 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
     }
   };
   // the first k-step's factor fragments of a unit: they depend on nothing that travels
-  auto prefetch_unit = [&](int rb, int wnu, uint4 (&pre)[2]) {
+  auto prefetch_unit = [&](int rb, int wnu, uint4 (&pre)[1][2]) {
     const int cnt = oct_cnt_s[rb];
     const int oi = rb * D_MAXOCT + (lg < cnt ? lg : 0);
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
-      pre[cb] = make_uint4(0, 0, 0, 0);
+      pre[0][cb] = make_uint4(0, 0, 0, 0);
       const int64_t n = n0 + wnu * 32 + cb * 16 + li;
-      if (lg < cnt && n < Nout) pre[cb] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L_s[oi] + n * oct_r_s[oi]);
+      if (lg < cnt && n < Nout) pre[0][cb] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L_s[oi] + n * oct_r_s[oi]);
     }
   };
   // One share (the units of split `share`): u of its rows into LDS, then its units, wave by wave.
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
       const int uu = wave + 8 * it;
       const bool active = from_regs || uu < per;
       const int unit = from_regs ? ((4 * g + it + 2 * wn) & 7) * 4 + wn : u0 + uu;
-      uint4 pre[2];
+      uint4 pre[1][2];
       f32x4 pv[8][2];                    // the unit's partial sums, all splits: complete after wait_vm<0>()
       if (active) {
         if (!from_regs) {

@@ -16,19 +16,21 @@
 // four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 194, 512 rows of 64 adapters of ranks 8
 // to 64, 5120 x 5120, 63 (weights from memory).  Stamps in the 256 rows, of a version that asked for u before the
 // sums and took 23.1: indices 1.8, first tile 3.8, loop done 15.4 (17.5 where a producer shares the unit; 14.6 without
-// adapters), sums and u 17.4, expand 18.5, stored 19.1.
+// adapters), sums and u 17.4, expand 18.5, stored 19.1.  Since then the expand takes u in two terms from LDS (split once a row, not
+// once a wave), nobody waits for a count of the workgroups that are through, and the launch ends with its stores: 22.3 -> 21.3,
+// q/k/v 31.0 -> 30.4, a layer's four calls of 157 rows 195.9 -> 193.8.
 //
 // Whatever crosses workgroups carries its own flag: it travels through areas of the context that are all
-// zero bits between launches, no value is stored as zero bits (+0 becomes -0), and a reader reads until
+// zero bits when a launch finds them, no value is stored as zero bits (+0 becomes -0), and a reader reads until
 // nothing is zero bits any more.
 //   u: workgroups before the others ("producers") compute it, one per 16 ranks of an adapter and pair of
 //     16-row blocks of a row tile (and piece of a long contraction).  There are as many as any grouping of the
 //     rows needs and each finds its share in the segment map, so that a captured call serves the groupings
-//     that the map object gets later.  The workgroup that is last through with a row tile clears its u.
+//     that the map object gets later.  Launches take turns over two areas, and each clears the other's (agent_memory.h).
 //   partial sums: with ksplit > 1 the splits of a tile share out its 16 x 16 units; a split hands the
 //     others' units over, reads its own ones' missing sums and clears them.
 // The reading is bounded (MID_POLLS).  u that does not come in time is computed by the reader; so are missing
-// sums, and the area is then cleared by whoever is last.  No workgroup depends on another one being scheduled,
+// sums, and the next launch then clears their area and computes all of its sums where they are wanted.  No workgroup depends on another one being scheduled,
 // and either way the sums are added in the same order: the bits are the same.
 #include "gemm_args.h"
 #include "agent_memory.h"
@@ -130,7 +132,7 @@ __device__ __forceinline__ int find_job(const GemmArgs& a, const AdapterEntry* t
 // two workgroups would not fit a compute unit otherwise (80-row tiles of 64 columns: ranks above 48; 64 x 64 and 80 x
 // 128: above 96); the rows' tables.
 template <int RB, int WN>
-__host__ __device__ inline int mid_tables(int r_stride) { return 16 * RB * 20 + RB * 4 + 16 + RB * 2 * r_stride * (int)sizeof(uint16_t); }
+__host__ __device__ inline int mid_tables(int r_stride) { return 16 * RB * 20 + RB * 4 + RB * 2 * r_stride * (int)sizeof(uint16_t); }
 template <int RB, int WN>
 __host__ __device__ inline int mid_sums(int r_stride) {
   const int u = 16 * RB * (r_stride + 4) * (int)sizeof(float), red = MidShape<RB, WN>::RED;
@@ -152,9 +154,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   int32_t* t_s = tok_s + BM;                                     // adapter (-1: none),
   int32_t* rank_s = t_s + BM;                                    // rank
   int32_t* cnt_s = rank_s + BM;                                  // [RB] octets of a row block (-1: plain expand)
-  int32_t* gave_s = cnt_s + RB;                                  // [0] a wave gave up waiting for sums,
-                                                                 // [2, 3] shrink jobs of the tile's first 64 rows, of the others
-  uint16_t* oct_s = (uint16_t*)(gave_s + 4);                     // [RB][oct_max]: row of the tile << 8 | first rank
+  uint16_t* oct_s = (uint16_t*)(cnt_s + RB);                     // [RB][oct_max]: row of the tile << 8 | first rank
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
@@ -162,49 +162,29 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   const int b = (int)blockIdx.x - a.prod0, S = a.n_split;        // the producers are workgroups prod0 ..
   const int64_t u_n = a.T * a.r_stride;                          // u: [projection][split][T][r_stride], scaled
   constexpr int UNITS = 2 * WN * RB;
-  // Workgroups through with row tile tm of projection p (bits 16 ..: those that gave up waiting for sums).  Only
-  // a consumer knows how many producers the tile has: the one of the first column tile and split counts for
-  // MID_JOBS less those, so that the count is the same, consumers + MID_JOBS, for every grouping.
-  // Called by one whole wave, when the workgroup's requests are performed.  (The count's answer is a trip through
-  // the fabric; put off until the workgroup's stores are out, it has to wait for those: 60 sizes of up to 384 rows and
-  // contractions of up to 2560 1 % longer.)
-  auto leave = [&](int p, int tm, int mine) {
-    const int p_tiles = (p + 1 < a.n_proj ? a.proj[p + 1].tile0 : a.tiles_n) - a.proj[p].tile0;
-    const int64_t m0 = (int64_t)tm * BM;
-    int32_t* done = a.sync + p * a.tiles_m + tm;
-    int old = 0;
-    if (lane == 0) old = __hip_atomic_fetch_add(done, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    old = __builtin_amdgcn_readfirstlane(old) + mine;
-    if ((old & 0xffff) != p_tiles * a.ksplit + MID_JOBS) return;
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    if (lora) {
-      const int64_t rows = a.T - m0 < BM ? a.T - m0 : BM;
-      float* u = a.thin_u + p * S * u_n + m0 * a.r_stride;
-      for (int s = 0; s < S; ++s)
-        for (int64_t i = lane; i < rows * a.r_stride / 4; i += 64) store4_agent(u + s * u_n + i * 4, zero);
-    }
-    if (__builtin_expect(old >> 16, 0)) {                        // (not reached in practice)
-      float* part = a.partials + ((int64_t)tm * a.tiles_n + a.proj[p].tile0) * (UNITS * 256) * a.ksplit;
-      for (int64_t i = lane, n = (int64_t)p_tiles * UNITS * 64 * a.ksplit; i < n; i += 64) store4_agent(part + i * 4, zero);
-    }
-    if (lane == 0) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
+  auto u_area = [&](int area) { return a.mid_u + area * (int64_t)MID_U_FLOATS; };
+  const bool joins = lora || a.ksplit > 1;                       // (exchanges something)
+  const int64_t u_all = lora ? (int64_t)a.n_proj * S * u_n : 0;
+  const int64_t consumers = (int64_t)gridDim.x - a.n_prod;
 
   if (b >= 0 && b < a.n_prod) {
     // ---- producers
-    const int pp = b / (a.proj_jobs * S);
-    if (pp >= a.n_proj) return;                                  // (they are padded to whole rounds over the XCDs)
+    const int pp = b / (a.proj_jobs * S);                        // (they are padded to whole rounds over the XCDs)
     ShrinkJob job;
     job.split = b % S;
-    const int tile = find_job<RB>(a, a.table + a.proj[pp].tab0, b / S - pp * a.proj_jobs, (int32_t*)smem, wave, lane, &job);
-    if (tile < 0) return;                                        // (there are as many as any grouping of T rows needs)
+    const int tile = pp < a.n_proj ? find_job<RB>(a, a.table + a.proj[pp].tab0, b / S - pp * a.proj_jobs, (int32_t*)smem, wave, lane, &job) : -1;
+    if (tile < 0) {                                              // (there are as many as any grouping of T rows needs)
+      turn_missed(a.turns, u_all, tid == 0);
+      return;
+    }
     const int64_t r0 = (int64_t)tile * BM + (job.row0 & ~15) + li, last = a.T - 1;
     const int64_t i0 = r0 < last ? r0 : last, i1 = r0 + 16 < last ? r0 + 16 : last;
     const int32_t tok0 = a.perm ? a.perm[i0] : (int32_t)i0, tok1 = a.perm ? a.perm[i1] : (int32_t)i1;
-    shrink_job<3, 2>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, a.thin_u + (pp * S + job.split) * u_n + (int64_t)tile * BM * a.r_stride,
-                     a.r_stride, wave, lane);
-    __syncthreads();
-    if (wave == 0) leave(pp, tile, 1);
+    int4 line;
+    auto turn = [&]() { return turn_of(line.x, line.y, line.z, line.w); };
+    shrink_job<3, 2>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, [&] { line = *(const int4*)turn_line(a.turns); },
+                     [&] { return u_area(turn().area) + (pp * S + job.split) * u_n + (int64_t)tile * BM * a.r_stride; }, a.r_stride, wave, lane);
+    if (tid == 0) turn_over(a.turns, turn(), u_all);
     return;
   }
 
@@ -213,13 +193,19 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   // share the weight through its L2.
   const int c = b < 0 ? (int)blockIdx.x : (int)blockIdx.x - a.n_prod, ng = 8 / a.ksplit;
   const int ks0 = c & (a.ksplit - 1), tm = (c >> 3) % a.tiles_m, tn = (c >> 3) / a.tiles_m * ng + (c & 7) / a.ksplit;
-  if (tn >= a.tiles_n) return;
+  if (tn >= a.tiles_n) {
+    if (joins) {
+      const Turn turn = turn_missed(a.turns, u_all, tid == 0);
+      clear_share(u_area(1 - turn.area), turn.u_before, c, consumers);
+      if (!turn.sums_ok) clear_share(a.partials, MID_PART_FLOATS, c, consumers);
+    }
+    return;
+  }
   int p = 0;
   for (int q = 1; q < a.n_proj; ++q) if (tn >= a.proj[q].tile0) p = q;
   const int64_t m0 = (int64_t)tm * BM;
   const int64_t Nout = a.proj[p].Nout, ldb = a.proj[p].ldw;
   const AdapterEntry* table = a.table + a.proj[p].tab0;
-  const float* u_p = a.thin_u + p * S * u_n;
   float* parts = a.partials + (int64_t)(tm * a.tiles_n) * (UNITS * 256) * a.ksplit;    // [tile][unit][split][lane] x 4
   const int steps = (int)((a.Kc + 31) >> 5);
   const bool lead = ks0 == 0 && tn == a.proj[p].tile0;
@@ -296,6 +282,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
   uint32_t xofs[NI];                                             // (the host keeps them below 4 GB)
   f32x4 y[NR][2];
+  Turn turn;
   const int cbo = ks0 & 1;                                       // with several splits this wave's own units are its
   const bool own = a.ksplit == 1 || ((g * WN * 2 + wn * 2 + cbo) & (a.ksplit - 1)) == ks0;   // column block cbo, if any
   // eight ranks of an octet of row block rb in column lane % 16 of column block cb
@@ -305,7 +292,22 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     if (n >= Nout) return make_uint4(0, 0, 0, 0);
     return *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[row] + (o & 255) + n * rank_s[row]);
   };
-  if (tid == 0) gave_s[0] = 0;
+  // The expand factors' fragments of the first KB steps (of four octets) of this wave's row blocks depend on nothing that
+  // has to be waited for.
+  constexpr int KB = NR == 1 ? 4 : 1;
+  uint4 pre[NR][KB][2];
+  auto request_factors = [&]() {
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+      for (int k = 0; k < KB; ++k)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          const int rb = j * KG + g, i = 4 * k + lg;
+          pre[j][k][cb] = make_uint4(0, 0, 0, 0);
+          if (rb < RB && i < cnt_s[rb]) pre[j][k][cb] = factor(rb, i, cb);
+        }
+  };
   {
     const int kt_b = ks0 * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;
     int rot = (c >> 3) / a.tiles_m % 8 * a.rot;
@@ -352,12 +354,6 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
         for (int q = 0, o = (tid >> 4) * oct_max + inc - n_oct; q < 8 * n_oct; q += 8, ++o) oct_s[o] = (uint16_t)(tid << 8 | q);
         if (li == 15) cnt_s[tid >> 4] = a.lform == FORM_NT && bad == 0 ? inc : -1;
       }
-      // jobs of these rows: the 16-wide tiles of ranks of every adapter in a pair of row blocks (1 .. 8: four bits)
-      const int rt = gid >= 0 && (gid != gid1 || (lane & 31) == 0) ? (rank + 15) >> 4 : 0;
-      int jobs = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) jobs += __popcll(__ballot(rt >> k & 1)) << k;
-      if (lane == 0) gave_s[2 + wave] = jobs;
     }
     f32x4 acc[RB][2];
 #pragma unroll
@@ -436,8 +432,14 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     int tile = MD_T(2 * NS);
 #pragma unroll 1
     for (; i0 + 2 * NS <= nt; i0 += NS) MD_ROUND(MD_STEADY);
+    // whose turn it is: the answer is there when the last k-tile is
+    f32x4 line;
+    asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(line) : "v"(joins ? turn_line(a.turns) : none) : "memory");
 #pragma unroll 1
     for (; i0 < nt; i0 += NS) MD_ROUND(MD_ITER);
+    wait_vm<0>();
+    asm volatile("" : "+v"(line));
+    turn = turn_of(__float_as_uint(line[0]), __float_as_uint(line[1]), __float_as_uint(line[2]), __float_as_uint(line[3]));
     // (the last reads are not used, but until they are there their registers must not look free)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
@@ -505,7 +507,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     for (int j = 0; j < NR; ++j)
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
-        if (j * KG + g < RB && !(own && cb == cbo)) {
+        if (j * KG + g < RB && !(own && cb == cbo) && turn.sums_ok) {
           f32x4 f;
 #pragma unroll
           for (int v = 0; v < 4; ++v) f[v] = __float_as_uint(y[j][cb][v]) == 0u ? -0.f : y[j][cb][v];
@@ -515,7 +517,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     f32x4 w[NR][3];                                              // the other splits' sums, in split order
     if (own) {
       ok = false;
-      for (int it = 0; it < a.spin_limit && !ok; ++it) {
+      for (int it = 0; it < a.spin_limit && !ok && turn.sums_ok; ++it) {
 #pragma unroll
         for (int j = 0; j < NR; ++j)
 #pragma unroll
@@ -536,7 +538,6 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
         ok = __ballot(all) == ~0ull;
       }
     }
-    wait_vm<0>();                                                // (who clears after a wait given up finds all of it)
     if (own && ok) {
 #pragma unroll
       for (int j = 0; j < NR; ++j) {
@@ -556,7 +557,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
       }
     } else if (__builtin_expect(own, 0)) {
       // (not reached in practice) the other splits' share of these units again
-      gave_s[0] = 1;
+      if (turn.sums_ok) turn_gave_up(a.turns, turn.number, lane);
 #pragma unroll 1
       for (int j = 0; j < NR && j * KG + g < RB; ++j) {
         f32x4 mine = {0.f, 0.f, 0.f, 0.f}, sum = mine;
@@ -580,16 +581,8 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   }
 
   if (lora) {
-    // the first octets' factor fragments depend on nothing that has to be waited for
-    uint4 pre[NR][2];
-#pragma unroll
-    for (int j = 0; j < NR; ++j)
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
-        const int rb = j * KG + g;
-        pre[j][cb] = make_uint4(0, 0, 0, 0);
-        if (rb < RB && lg < cnt_s[rb]) pre[j][cb] = factor(rb, lg, cb);
-      }
+    const float* u_p = u_area(turn.area) + p * S * u_n;
+    request_factors();
     // (A reading of u and the factors of eight octets requested before the sums meet, with four requests a reading and the
     // count's answer put off, took 2.8 % longer over 190 sizes in every tiling, all of a thread's readings at once 1.4 %:
     // the code around them costs every wave more than the trips it saves, but for ranks of 128, 1 % shorter with the second.)
@@ -605,20 +598,20 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
         u_again(table, a.which, a.Aop, a.lda, a.Kc, S, t_s, tok_s, row, q, !ok, lane, v);
 #pragma unroll
       for (int j = 0; j < 4; ++j) if (q + j >= rank) v[j] = 0.f;
-      *(f32x4*)(u_s + row * us + q) = v;
+      if (cnt_s[row >> 4] >= 0) store_split4((bf16_t*)(u_s + row * us) + q, a.r_stride, v);     // (as the expand wants it)
+      else *(f32x4*)(u_s + row * us + q) = v;
       if (a.u_out && lead && m0 + row < a.T && q < ((rank + 15) & ~15))
         *(f32x4*)(a.u_out + (m0 + row) * a.r_stride + q) = v;
     }
     __syncthreads();
-    if (wave == MD_WAVES - 1)
-      leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS - (gave_s[2] + (RB > 4 ? gave_s[3] : 0)) * S : 0));
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const int rb = j * KG + g;
       if (rb >= RB || !own) break;
       const int row = rb * 16 + li, cnt = cnt_s[rb];
       if (cnt >= 0) {
-        expand_octets(y[j], pre[j], cnt, lg, t_s[row], u_s + row * us,
+        expand_octets(y[j], pre[j], cnt, lg, t_s[row],
+                      [&](int q, bool mine, bf16x8& hi, bf16x8& lo) { load_split((const bf16_t*)(u_s + row * us) + q, a.r_stride, mine, hi, lo); },
                       [&](int i) { const int o = oct_s[rb * oct_max + i]; return t_s[o >> 8] << 8 | (o & 255); },
                       [&](int i, int cb) { return factor(rb, i, cb); });
       } else if (t_s[row] >= 0) {
@@ -638,9 +631,6 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
         }
       }
     }
-  } else if (a.ksplit > 1) {
-    __syncthreads();
-    if (wave == MD_WAVES - 1) leave(p, tm, 1 + (gave_s[0] << 16) + (lead ? MID_JOBS : 0));
   }
 #pragma unroll
   for (int j = 0; j < NR; ++j) {
@@ -659,6 +649,11 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
         *(uint2*)((bf16_t*)a.proj[p].out + (int64_t)otok * a.proj[p].ldo + n) = o;
       }
     }
+  }
+  if (joins) {                                                   // (nobody waits for these)
+    if (tid == MD_THREADS - 1) turn_over(a.turns, turn, u_all);
+    clear_share(u_area(1 - turn.area), turn.u_before, c, consumers);
+    if (__builtin_expect(!turn.sums_ok, 0)) clear_share(a.partials, MID_PART_FLOATS, c, consumers);
   }
 }
 

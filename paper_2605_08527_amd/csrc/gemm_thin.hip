@@ -137,7 +137,8 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 1; i < R; ++i) if (i == rb0) tok0 = tokr[i];
     const ShrinkJob job = {L, scale, r, q0, row0, row1, b % S};
-    shrink_job<R == 1 ? 4 : 3, R>(job, a.Aop, a.lda, a.Kc, tok0, tokr[R - 1], S, red, u_p + b % S * u_n, a.r_stride, wave, lane);
+    shrink_job<R == 1 ? 4 : 3, R>(job, a.Aop, a.lda, a.Kc, tok0, tokr[R - 1], S, red, [] {}, [&] { return u_p + b % S * u_n; }, a.r_stride, wave, lane);
+    wait_vm<0>();                                                // (u is out)
     __syncthreads();
     if (wave == 0) leave();
     return;
@@ -232,15 +233,15 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
 
   if (lora) {
     // the first octets' factor fragments depend on nothing that has to be waited for
-    uint4 pre[MINE][1];
+    uint4 pre[MINE][1][1];
 #pragma unroll
     for (int k = 0; k < MINE; ++k) {
       const int tile = wave + k * TH_WAVES, rb = tile / NC, c = tile - rb * NC;
-      pre[k][0] = make_uint4(0, 0, 0, 0);
+      pre[k][0][0] = make_uint4(0, 0, 0, 0);
       if (tile < TILES && lg < cnt_s[rb]) {
         const int64_t n = n0 + c * 16 + li;
         const int o = rb * oct_max + lg;
-        if (n < Nout) pre[k][0] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
+        if (n < Nout) pre[k][0][0] = *(const uint4*)((const bf16_t*)(uintptr_t)oct_L[o] + n * oct_r[o]);
       }
     }
     for (int i = tid; i < 16 * R * (a.r_stride >> 2); i += TH_THREADS) {      // (whole waves)
@@ -264,7 +265,9 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
       if (tile >= TILES) break;
       const int row = rb * 16 + li, cnt = cnt_s[rb];
       if (cnt >= 0) {
-        expand_octets(y[k], pre[k], cnt, lg, t_s[row], u_s + row * us, [&](int i) { return (int)oct_tq[rb * oct_max + i]; },
+        expand_octets(y[k], pre[k], cnt, lg, t_s[row],
+                      [&](int q, bool mine, bf16x8& hi, bf16x8& lo) { split_u(u_s + row * us + q, mine, hi, lo); },
+                      [&](int i) { return (int)oct_tq[rb * oct_max + i]; },
                       [&](int i, int) {
                         const int o = rb * oct_max + i;
                         const int64_t n = n0 + c * 16 + li;

@@ -14,12 +14,13 @@ struct ShrinkJob {
 };
 
 // Eight waves share the part's 32-deep steps, their sums meet in `red` (8 x NB x 64) and are added in wave
-// order: the bits do not depend on who computes the job.  u: [row of the tile][r_stride] of this split; no
+// order: the bits do not depend on who computes the job.  u(): [row of the tile][r_stride] of this split; ask() requests what
+// u() needs, behind the first operands, which would have to wait for it.  No
 // value is stored as zero bits.  tok0, tok1: tokens of row lane % 16 of the first and of the second block.
-// UP: steps requested together (twice); NB: blocks a job can have.  All eight waves call it; the stores are complete behind the next barrier.
-template <int UP, int NB>
+// UP: steps requested together (twice); NB: blocks a job can have.  All eight waves call it.
+template <int UP, int NB, typename Ask, typename At>
 __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, int64_t lda, int64_t Kc, int32_t tok0, int32_t tok1, int S,
-                                           f32x4* red, float* u, int r_stride, int wave, int lane) {
+                                           f32x4* red, Ask ask, At u, int r_stride, int wave, int lane) {
   constexpr int WAVES = 8;
   union Frag { uint4 u; bf16x8 v; };
   const int li = lane & 15, lg = lane >> 4;
@@ -64,6 +65,7 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
       for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i][NB].v, f[i][b].v, acc[b], 0, 0, 0);
   };
   request(fa, s0);
+  ask();
 #pragma unroll 1
   for (int s = s0; s < s1; s += 2 * UP) {
     if (s + UP < s1) request(fb, s + UP);
@@ -89,9 +91,8 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
       f32x4 f;
 #pragma unroll
       for (int v = 0; v < 4; ++v) { const float z = j.scale * s[v]; f[v] = __float_as_uint(z) == 0u ? -0.f : z; }
-      store4_agent(u + (int64_t)row * r_stride + j.q0 + 4 * lg, f);
+      store4_agent(u() + (int64_t)row * r_stride + j.q0 + 4 * lg, f);
     }
-    wait_vm<0>();
   }
 }
 
