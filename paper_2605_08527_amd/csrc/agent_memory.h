@@ -29,12 +29,13 @@ __device__ __forceinline__ void load4_agent(f32x4& v, const float* p) {     // c
 // line b mod TURN_LINES.  Every workgroup adds to its line's count once, when it has read the line, the first to each line so
 // much that a launch adds 2^TURN_SHIFT to every line, however few workgroups it has: before its own share is in, a workgroup
 // finds the launch's number above.
-// Fourth word: number of a launch that must not use the area of partial sums, because somebody gave up waiting in the one
-// before it and sums may lie there; it clears the area instead.
+// Fourth word: number (+ 1) of a launch that must not use the area of partial sums, because somebody gave up waiting in the one
+// before it and sums may lie there; it clears the area instead.  All workgroups of that launch have to find the same, however
+// late they come (one that did not would take what lies there for sums), so the word stays until the launch after it.
 struct Turn {
   uint32_t number; int area;
   int64_t u_before;                  // floats of u in the other area
-  bool sums_ok;
+  bool sums_ok, was_not;             // (this launch's, the one's before it)
 };
 __device__ __forceinline__ const int32_t* turn_line(const int32_t* turns) { return turns + blockIdx.x % TURN_LINES * 32; }
 __device__ __forceinline__ Turn turn_of(uint32_t count, uint32_t u0, uint32_t u1, uint32_t sums) {
@@ -43,7 +44,9 @@ __device__ __forceinline__ Turn turn_of(uint32_t count, uint32_t u0, uint32_t u1
   t.area = t.number & 1;
   const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t.area ? u0 : u1));
   t.u_before = n < (uint32_t)MID_U_FLOATS ? n : MID_U_FLOATS;
-  t.sums_ok = (uint32_t)__builtin_amdgcn_readfirstlane((int)sums) != t.number + 1;     // (0: nobody ever gave up)
+  const uint32_t gave = (uint32_t)__builtin_amdgcn_readfirstlane((int)sums);           // (0: nobody ever gave up)
+  t.sums_ok = gave != t.number + 1;
+  t.was_not = gave == ((t.number - 1) & (~0u >> TURN_SHIFT)) + 1;
   return t;
 }
 // Once for every workgroup, by one lane; u_floats: what the launch may use of its area.
@@ -58,8 +61,11 @@ __device__ __forceinline__ void turn_over(int32_t* turns, const Turn& t, int64_t
     uint32_t* l = (uint32_t*)turns + line * 32;
     const uint32_t others = line < gridDim.x ? (gridDim.x - line - 1) / TURN_LINES : 0;
     __hip_atomic_store(l + 1 + t.area, (uint32_t)u_floats, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // (a workgroup that comes later and does not find this any more waits in vain, gives up and says so)
-    if (!t.sums_ok) __hip_atomic_store(l + 3, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // done with, or the number would come round; whoever gives up in this launch may have put the next one's there
+    if (t.was_not) {
+      uint32_t old = ((t.number - 1) & (~0u >> TURN_SHIFT)) + 1;
+      (void)__hip_atomic_compare_exchange_strong(l + 3, &old, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     (void)__hip_atomic_fetch_add(l, (1u << TURN_SHIFT) - others, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     line = line == 0 ? gridDim.x : line + 1;
   } while (blockIdx.x == 0 && line < TURN_LINES);

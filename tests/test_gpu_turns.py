@@ -11,7 +11,7 @@ from helpers import HipLayer
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("spin", [None, "0"])
+@pytest.mark.parametrize("spin", [None, "0", "1", "3"])
 def test_calls_take_turns(monkeypatch, spin):
     if spin is not None:
         monkeypatch.setenv("MARLAAS_SPIN_LIMIT", spin)
