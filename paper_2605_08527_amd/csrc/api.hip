@@ -1372,10 +1372,8 @@ static int bwd_impl(marlaas_ctx* ctx, const marlaas_lora_desc* d, const void* dY
       PROFILED(ctx, MARLAAS_KERNEL_GEMM, st, launch_layer_f32(dy, lddy, (const float*)d->W, d->ldw, bform, d->T, d->d_out, d->d_in, perm, grp,
                                    tb, 0, lora && want_grads ? v : nullptr, rs, dX, lddx, out_f32, st));
     if (want_grads && d->n_adapters > 0) {
-      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_f32(dy, lddy, d->d_out, perm, map->seg_off_dev, d->n_adapters, tb, 1,
-                                     db_form, u, rs, accumulate, st));
-      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_f32(x, d->ldx, d->d_in, perm, map->seg_off_dev, d->n_adapters, tb, 0,
-                                     da_form, v, rs, accumulate, st));
+      const ReduceF32Job jobs[2] = {{dy, lddy, d->d_out, u, 1, db_form}, {x, d->ldx, d->d_in, v, 0, da_form}};
+      PROFILED(ctx, MARLAAS_KERNEL_REDUCE, st, launch_reduce_f32(jobs, perm, map->seg_off_dev, d->n_adapters, tb, rs, accumulate, st));
     }
   }
   return MARLAAS_OK;

@@ -372,8 +372,9 @@ struct TablesF32 {
 hipError_t launch_layer_f32(const float* X, int64_t ldx, const float* W, int64_t ldw, int form, int64_t T, int64_t Kc, int64_t Nout,
                             const int32_t* perm, const int32_t* grp, const TablesF32& tb, int which, float* u_out, int r_stride,
                             void* out, int64_t ldo, int out_is_f32, hipStream_t stream);
-hipError_t launch_reduce_f32(const float* X, int64_t ldx, int64_t C, const int32_t* perm, const int32_t* seg_off, int n_adapters,
-                             const TablesF32& tb, int which, int out_form, const float* V, int r_stride, int accumulate,
-                             hipStream_t stream);
+// One gradient: [C columns][ranks] (oform FORM_NN) or the other way round, of X's columns and the rows' V; which: dB (1) or dA.
+struct ReduceF32Job { const float* X; int64_t ldx, C; const float* V; int which, oform; };
+hipError_t launch_reduce_f32(const ReduceF32Job (&jobs)[2], const int32_t* perm, const int32_t* seg_off, int n_adapters, const TablesF32& tb,
+                             int r_stride, int accumulate, hipStream_t stream);
 
 }  // namespace marlaas
