@@ -29,6 +29,16 @@ def test_fp32_layer(oracle, T, K, N, ranks, table, layout):
     _check_layer(oracle, w, bwd=True, tol=(1e-4, 1e-5), tag="fp32", table="table" if table else "lists")
 
 
+# as many shrink tiles in a row block as one pass takes, one less and one more, either kind of factor
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("ranks", [[16, 8], [24, 8], [8] * 4, [33, 16], [8, 1, 16, 7, 24], [128]])
+def test_fp32_shrink_tiles_of_a_row_block(oracle, ranks, layout):
+    T, K, N = 19, 264, 136
+    ids = (np.arange(T) * 7 % len(ranks)).astype(np.int32)
+    w = wl.make_layer(T + sum(ranks), T, K, N, ranks, [0.5 + t for t in range(len(ranks))], ids, dtype="f32", layout=layout, want_dY=True)
+    _check_layer(oracle, w, bwd=True, tol=(1e-4, 1e-5), tag="fp32", table="lists")
+
+
 @pytest.mark.parametrize("T,n", [(1, 1), (63, 800), (64, 1), (65, 2), (1024, 31), (1025, 32), (4097, 800), (4097, 801), (32768, 64), (32769, 64)])
 def test_segment_map_one_launch_and_several(T, n):
     rng = np.random.default_rng(T * 7 + n)
