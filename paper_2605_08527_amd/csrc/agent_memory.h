@@ -39,17 +39,22 @@ struct Turn {
 };
 __device__ __forceinline__ const int32_t* turn_line(const int32_t* turns) { return turns + blockIdx.x % TURN_LINES * 32; }
 __device__ __forceinline__ Turn turn_of(uint32_t count, uint32_t u0, uint32_t u1, uint32_t sums) {
+  uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)count), n0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)u0);
+  uint32_t n1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)u1), gave = (uint32_t)__builtin_amdgcn_readfirstlane((int)sums);
+  // (the line has arrived here, and not where its words are used: a barrier waits for no load from memory)
+  asm volatile("" : "+s"(c), "+s"(n0), "+s"(n1), "+s"(gave) :: "memory");
   Turn t;
-  t.number = (uint32_t)__builtin_amdgcn_readfirstlane((int)count) >> TURN_SHIFT;
+  t.number = c >> TURN_SHIFT;
   t.area = t.number & 1;
-  const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t.area ? u0 : u1));
+  const uint32_t n = t.area ? n0 : n1;
   t.u_before = n < (uint32_t)MID_U_FLOATS ? n : MID_U_FLOATS;
-  const uint32_t gave = (uint32_t)__builtin_amdgcn_readfirstlane((int)sums);           // (0: nobody ever gave up)
+  // (gave 0: nobody ever gave up)
   t.sums_ok = gave != t.number + 1;
   t.was_not = gave == ((t.number - 1) & (~0u >> TURN_SHIFT)) + 1;
   return t;
 }
-// Once for every workgroup, by one lane; u_floats: what the launch may use of its area.
+// Once for every workgroup, by one lane, behind a barrier that every wave which reads the line meets with its Turn in hand: one
+// that read after the launch's last share would find the next launch's number.  u_floats: what the launch may use of its area.
 __device__ __forceinline__ void turn_over(int32_t* turns, const Turn& t, int64_t u_floats) {
   uint32_t line = blockIdx.x % TURN_LINES;
   if (blockIdx.x >= TURN_LINES) {
@@ -70,10 +75,11 @@ __device__ __forceinline__ void turn_over(int32_t* turns, const Turn& t, int64_t
     line = line == 0 ? gridDim.x : line + 1;
   } while (blockIdx.x == 0 && line < TURN_LINES);
 }
-// The same for a workgroup without any other business.
+// The same for a workgroup without any other business; all its waves call it.
 __device__ __forceinline__ Turn turn_missed(int32_t* turns, int64_t u_floats, bool one) {
   const int4 l = *(const int4*)turn_line(turns);
   const Turn t = turn_of(l.x, l.y, l.z, l.w);
+  __syncthreads();
   if (one) turn_over(turns, t, u_floats);
   return t;
 }
