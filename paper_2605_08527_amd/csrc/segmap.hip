@@ -232,15 +232,19 @@ __global__ __launch_bounds__(SM_THREADS) void segmap_small(const int32_t* __rest
   const int beg = wave * per, end = beg + per < T ? beg + per : T;
   const bool once = per <= 256;               // (the ids of a wave's tokens stay in registers)
   int idv[4], nxt[4];
-  auto load = [&](int s0) {
+  // (every lane reads, from an index inside: a request under a condition of its own waits for the one before it, 12000
+  // tokens 44.6 -> 42.3 us; neighbours are the first walk's)
+  auto load = [&](int s0, bool first_walk) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = s0 + 64 * j + lane;
-      idv[j] = i < end ? ids[i] : -2;
-      nxt[j] = i + 1 < T && i < end ? ids[i + 1] : idv[j];
+    for (int j = 0; j < 4; ++j) { const int i = s0 + 64 * j + lane; idv[j] = ids[i < T ? i : T - 1]; }
+    if (first_walk) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { const int i = s0 + 64 * j + lane + 1; nxt[j] = ids[i < T ? i : T - 1]; }
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) if (s0 + 64 * j + lane >= end) idv[j] = -2;
   };
-  if (once) load(beg);
+  if (once) load(beg, true);
   for (int i = tid; i < SM_WAVES * nb; i += SM_THREADS) cur[i] = 0;
   for (int i = tid; i < n; i += SM_THREADS) rank_s[i] = 0;
   if (tid < 2) flag[tid] = 0;
@@ -250,7 +254,7 @@ __global__ __launch_bounds__(SM_THREADS) void segmap_small(const int32_t* __rest
 #pragma unroll 1
   for (int walk = 0; walk < 2; ++walk) {
     for (int s0 = beg; s0 < end; s0 += 256) {
-      if (!once) load(s0);
+      if (!once) load(s0, walk == 0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = s0 + 64 * j + lane;

@@ -1,95 +1,22 @@
 """Launches that exchange u find out from lines of counters which of two areas is theirs (agent_memory.h).  The functions
-themselves, compiled for the host: a workgroup's waves run one after the other between barriers, wave 0 as far ahead as it
-gets, and a value that a load brings is read when it is first used, as late as a load may arrive."""
-import os
+themselves, compiled for the host: wave 0 of a workgroup runs as far ahead as it gets, and a value that a load brings is
+read when it is first used, as late as a load may arrive."""
 import subprocess
 
 import pytest
 
-from paper_2605_08527_amd import build
-
-# what the headers take from the compiler for the GPU
-STUB = r"""
-#pragma once
-#include <condition_variable>
-#include <cstdio>
-#include <cstdlib>
-#include <cstring>
-#include <mutex>
-#include <random>
-#include <stdint.h>
-#include <thread>
-#include <vector>
-#define __host__
-#define __device__
-#define __forceinline__ inline
-#define __HIP_MEMORY_SCOPE_AGENT 0
-typedef int hipError_t;
-typedef void* hipStream_t;
-struct int4 { int x, y, z, w; };
-struct uint2 { unsigned x, y; };
-struct uint4 { unsigned x, y, z, w; };
-inline uint4 make_uint4(unsigned x, unsigned y, unsigned z, unsigned w) { return {x, y, z, w}; }
-struct Dim { unsigned x; };
-static thread_local Dim threadIdx, blockIdx, blockDim, gridDim;
-inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f; }
-inline uint32_t __float_as_uint(float f) { uint32_t u; memcpy(&u, &f, 4); return u; }
-template <typename T> T __shfl(T v, int) { return v; }
-inline uint64_t __ballot(bool b) { return b; }
-inline int __ffsll(unsigned long long v) { return __builtin_ffsll((long long)v); }
-void __syncthreads();
-#define __builtin_amdgcn_readfirstlane(x) (x)
-#define __builtin_amdgcn_readlane(x, l) (x)
-#define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
-#define __hip_atomic_fetch_add(p, v, order, scope) __atomic_fetch_add(p, v, order)
-#define __hip_atomic_store(p, v, order, scope) __atomic_store_n(p, v, order)
-#define __hip_atomic_compare_exchange_strong(p, old, v, o1, o2, scope) __atomic_compare_exchange_n(p, old, v, false, o1, o2)
-// (asm volatile(...); is an empty statement)
-#define asm
-#define volatile(...)
-"""
+from host_kernels import compile_host
 
 SOURCE = r"""
 #include "lora_shrink.h"
 using namespace marlaas;
 
-// Waves of one workgroup, one at a time: the next one runs when this one has ended or stands at a barrier.
-struct Group {
-  static constexpr int WAVES = 8;
-  std::mutex m;
-  std::condition_variable cv;
-  int now = 0, state[WAVES] = {0};                // 0: may run, 1: at a barrier, 2: ended
-  void pass(int w, int s) {
-    std::unique_lock<std::mutex> l(m);
-    state[w] = s;
-    int next = -1;
-    for (int k = 0; k < WAVES && next < 0; ++k) if (state[k] == 0) next = k;
-    if (next < 0)
-      for (int k = 0; k < WAVES; ++k) if (state[k] == 1) { state[k] = 0; if (next < 0) next = k; }
-    now = next;
-    cv.notify_all();
-    if (s != 2) cv.wait(l, [&] { return now == w; });
-  }
-};
-static Group* group;
-static thread_local int my_wave;
-void __syncthreads() { if (group) group->pass(my_wave, 1); }
-
+static constexpr int WAVES = 8;
+// Its waves as one lane each.
 template <typename F>
 static void workgroup(unsigned b, unsigned grid, F f) {
-  Group g;
-  group = &g;
-  std::vector<std::thread> t;
-  for (int w = 0; w < Group::WAVES; ++w)
-    t.emplace_back([&, w] {
-      my_wave = w;
-      threadIdx.x = 64 * w; blockIdx.x = b; gridDim.x = grid; blockDim.x = 64 * Group::WAVES;
-      { std::unique_lock<std::mutex> l(g.m); g.cv.wait(l, [&] { return g.now == w; }); }
-      f(w);
-      g.pass(w, 2);
-    });
-  for (auto& x : t) x.join();
-  group = nullptr;
+  blockIdx.x = b; gridDim.x = grid;
+  run_workgroup(WAVES, 1, [&](int w) { threadIdx.x = 64 * w; f(w); });
 }
 
 static int32_t turns[TURN_INTS];
@@ -99,7 +26,7 @@ static int32_t turns[TURN_INTS];
 int idle_workgroup() {
   for (unsigned n = 0; n < 3; ++n) {
     for (unsigned b = 0; b < 16; ++b) {
-      Turn t[Group::WAVES];
+      Turn t[WAVES];
       workgroup(b, 16, [&](int w) { t[w] = turn_missed(turns, 1000 + n, threadIdx.x == 0); });
       for (auto& x : t) CHECK(x.number == n && x.area == (int)(n & 1) && x.u_before == (n ? 999 + n : 0) && x.sums_ok);
     }
@@ -115,8 +42,8 @@ int producer() {
   std::vector<f32x4> red(8 * 2 * 64);
   std::vector<float> u(64 * 16);
   ShrinkJob job = {L.data(), 1.f, 16, 0, 0, 32, 0};
-  Turn t[Group::WAVES];
-  bool met[Group::WAVES] = {false};
+  Turn t[WAVES];
+  bool met[WAVES] = {false};
   workgroup(0, 1, [&](int w) {
     shrink_job<3, 2>(job, x.data(), Kc, Kc, 0, 0, 1, red.data(), [] {},
                      [&] {
@@ -130,7 +57,7 @@ int producer() {
     if (w == 0) turn_over(turns, t[0], 512);
   });
   CHECK(met[0] && met[1]);
-  for (int w = 0; w < Group::WAVES; ++w) CHECK(!met[w] || t[w].number == 0);
+  for (int w = 0; w < WAVES; ++w) CHECK(!met[w] || t[w].number == 0);
   return 0;
 }
 
@@ -170,7 +97,6 @@ int full_round() {
 }
 
 int main(int, char** v) {
-  blockDim.x = 512;
   return !strcmp(v[1], "idle_workgroup") ? idle_workgroup() : !strcmp(v[1], "producer") ? producer() : full_round();
 }
 """
@@ -178,15 +104,7 @@ int main(int, char** v) {
 
 @pytest.fixture(scope="module")
 def program(tmp_path_factory):
-    d = tmp_path_factory.mktemp("turns")
-    (d / "hip").mkdir()
-    (d / "hip" / "hip_runtime.h").write_text(STUB)
-    (d / "turns.cpp").write_text("#include <algorithm>\n" + SOURCE)
-    clang = os.path.join(os.path.dirname(build.HIPCC), "amdclang++")
-    p = subprocess.run([clang, "-x", "c++", "-O1", "-std=c++17", "-pthread", "-w", "-I", str(d), "-I", build.CSRC, str(d / "turns.cpp"), "-o", str(d / "turns")],
-                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert p.returncode == 0, p.stdout
-    return str(d / "turns")
+    return compile_host(tmp_path_factory.mktemp("turns"), SOURCE)
 
 
 @pytest.mark.parametrize("what", ["idle_workgroup", "producer", "full_round"])
