@@ -209,7 +209,7 @@ static constexpr int THIN_SPLITS = 4, THIN_U_FLOATS = MAX_PROJ * THIN_SPLITS * T
 // splits.  u travels in two areas ([projection][piece of the contraction][T][r_stride]) behind the few-row kernel's, the partial
 // sums of at most MID_SPLIT_WGS workgroups behind those.
 static constexpr int MID_ROWS = 1024, MID_SPLITS = 4, MID_SPLIT_WGS = 512;
-static constexpr int MID_U_FLOATS = MAX_PROJ * MID_ROWS * 128;    // of u in one of its two areas
+static constexpr int MID_U_FLOATS = MAX_PROJ * 2 * MID_ROWS * 128;   // of u in one of its two areas: two pieces always fit
 static constexpr int MID_PART_FLOATS = MID_SPLIT_WGS * 96 * 128;
 // Whose turn it is (agent_memory.h): lines of 32 ints; a line counts TURN_ONE a launch, and a launch has fewer workgroups to a
 // line than that.

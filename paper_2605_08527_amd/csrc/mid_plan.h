@@ -18,13 +18,16 @@ static constexpr int MID_WAVES = 8;
 //   rank 64, 568 workgroups in two pieces at most: 33.3, whole 36.5).
 //   Else whole as far as the steps allow (300 rows of rank 128: 50 us, in two 62; 512 rows, 5120 x 5120, 64
 //   adapters, with their regrouping 82 and 88).
-// Few steps are not cut: a value of u is read once for each piece.
-inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t consumers, int64_t jobs, int cu_count) {
+// Few steps are not cut: a value of u is read once for each piece.  More than 24 always are (eight projections of 1024
+// columns, contraction 8192, 1000 rows of 4 adapters of rank 128: 364 us, whole 402, 600 rows of 8 adapters 288 and 282; of
+// 512 columns, contraction 7168, 640 rows of 32 adapters: 340 and 1035, as whole producers come so late that waits are given up).
+//   u_room: floats of u that there is room for.
+inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t consumers, int64_t jobs, int cu_count) {
   const int64_t steps = ((Kc + 31) / 32 + MID_WAVES - 1) / MID_WAVES;      // 32-deep steps of a wave
   if (steps <= 8 || (steps <= 16 && consumers + jobs <= cu_count)) return 1;
   int s = MID_SPLITS;
-  while (s > 1 && (consumers + jobs * s > (s == 2 ? 9 : 8) * cu_count / 4 || u_floats * s > MID_U_FLOATS)) s /= 2;
-  return s == 1 && steps > 24 && 2 * u_floats <= MID_U_FLOATS ? 2 : s;
+  while (s > 1 && (consumers + jobs * s > (s == 2 ? 9 : 8) * cu_count / 4 || u_floats * s > u_room)) s /= 2;
+  return s == 1 && steps > 24 && 2 * u_floats <= u_room ? 2 : s;
 }
 
 // Estimated run time of a tiling in microseconds, for the order of the tilings.  A k-tile's time when a workgroup has
@@ -66,7 +69,9 @@ inline MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj
         const double fabric = (2.0 * cols * Kc + 16.0 * T * Kc / s) / 11.6e6;
         double us = 7.687 + cbrt(fill * fill * fill + fabric * fabric * fabric);
         if (lora.n > 0) {
-          const int pieces = mid_u_splits(Kc, T * lora.r_stride * n_proj, wgs, (int64_t)n_proj * mid_max_jobs(T, rb, lora), 256);
+          // (the most u there can be, of five projections and more, counts as whole: the estimate of such calls is low, and with
+          // two pieces would take six of 1024 columns, contraction 14336, 1000 rows of rank 128, here, 496 us, not one by one, 298)
+          const int pieces = mid_u_splits(Kc, T * lora.r_stride * n_proj, MID_U_FLOATS / 2, wgs, (int64_t)n_proj * mid_max_jobs(T, rb, lora), 256);
           const int64_t with_rows = (int64_t)(0.6 * T) + 1 < lora.n ? (int64_t)(0.6 * T) + 1 : lora.n;      // (adapters, about)
           const int64_t prods = n_proj * pieces * (with_rows * (lora.tiles / lora.n > 1 ? lora.tiles / lora.n : 1) + T / (16 * rb) * ((rb + 1) / 2));
           // (the expand of more ranks is not proportionally more: 184 rows, 1872 x 8368, rank 32, 23.1 -> 22.1 us

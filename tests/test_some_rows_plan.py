@@ -32,17 +32,28 @@ extern "C" int plan(int64_t T, int64_t Kc, const int32_t* cols, int n_proj, cons
   const MidPlan p = mid_plan(T, Kc, proj, n_proj, l, 4);
   return p.rb * 100 + p.wn * 10 + p.ksplit;
 }
+// pieces of u, -1: more of it than an area holds
+extern "C" int pieces(int64_t T, int64_t Kc, int n_proj, int r_stride, int64_t consumers, int64_t jobs) {
+  const int64_t u = T * r_stride * n_proj;
+  const int s = marlaas::mid_u_splits(Kc, u, marlaas::MID_U_FLOATS, consumers, jobs, 256);
+  return s * u > marlaas::MID_U_FLOATS ? -1 : s;
+}
 """
 
 
 @pytest.fixture(scope="module")
-def excess(tmp_path_factory):
-    """(a set's values, time of the tiling taken over the best one's)"""
+def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
     (d / "plan.hip").write_text(SOURCE)
     subprocess.run([build.HIPCC, "--cuda-host-only", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", build.CSRC, str(d / "plan.hip"), "-o", str(d / "plan.so")],
                    check=True, stderr=subprocess.DEVNULL)
-    plan = ctypes.CDLL(str(d / "plan.so")).plan
+    return ctypes.CDLL(str(d / "plan.so"))
+
+
+@pytest.fixture(scope="module")
+def excess(lib):
+    """(a set's values, time of the tiling taken over the best one's)"""
+    plan = lib.plan
     plan.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_int]
     out = []
     for T, K, cols, n, rank, times in json.load(open(GOLDEN))["sets"]:
@@ -64,3 +75,13 @@ def test_tilings_taken(excess):
     assert _mean([q for _, q in excess]) < 1.026
     assert _mean([q for (_, _, n), q in excess if n == 0]) < 1.02
     assert max(q for _, q in excess) < 1.35
+
+
+# Contractions too long for a whole producer are cut, however much u there is: up to eight projections, 1024 rows, rank 128.
+@pytest.mark.parametrize("n_proj", [1, 3, 5, 8])
+@pytest.mark.parametrize("T,K", [(600, 6400), (1000, 14336), (1024, 8192)])
+def test_long_contractions_are_cut(lib, n_proj, T, K):
+    f = lib.pieces
+    f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64]
+    for r_stride in (16, 64, 112, 128):
+        assert f(T, K, n_proj, r_stride, 1024, 4096) == 2
