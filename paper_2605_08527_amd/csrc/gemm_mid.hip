@@ -296,20 +296,26 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     return *(const uint4*)((const bf16_t*)(uintptr_t)rL_s[row] + (o & 255) + n * rank_s[row]);
   };
   // The expand factors' fragments of the first KB steps (of four octets) of this wave's row blocks depend on nothing that
-  // has to be waited for.
+  // has to be waited for.  Four steps where a wave has one row block and the registers for them (200 rows of 64 adapters of
+  // rank 64, 2048 x 2048, 24.0 -> 23.2 us; 128 rows of 16 of rank 128 24.9 -> 24.5), as far as the block has octets for them:
+  // requested under a lane's condition alone they cost the blocks with few (64 rows of 4 adapters of rank 16, 1024 x
+  // 1024, 10.64, one step or as many as there are 10.28).
   constexpr int KB = NR == 1 ? 4 : 1;
   uint4 pre[NR][KB][2];
   auto request_factors = [&]() {
 #pragma unroll
-    for (int j = 0; j < NR; ++j)
+    for (int j = 0; j < NR; ++j) {
+      const int rb = j * KG + g, cnt = rb < RB ? __builtin_amdgcn_readfirstlane(cnt_s[rb]) : 0;
 #pragma unroll
-      for (int k = 0; k < KB; ++k)
+      for (int k = 0; k < KB; ++k) {
+        if (k > 0 && 4 * k >= cnt) break;
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
-          const int rb = j * KG + g, i = 4 * k + lg;
           pre[j][k][cb] = make_uint4(0, 0, 0, 0);
-          if (rb < RB && i < cnt_s[rb]) pre[j][k][cb] = factor(rb, i, cb);
+          if (4 * k + lg < cnt) pre[j][k][cb] = factor(rb, 4 * k + lg, cb);
         }
+      }
+    }
   };
   {
     const int kt_b = ks0 * chunk, kt_e = kt_b + chunk > ktiles ? ktiles : kt_b + chunk, nt = kt_e > kt_b ? kt_e - kt_b : 0;

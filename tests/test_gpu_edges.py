@@ -39,6 +39,17 @@ def test_fp32_shrink_tiles_of_a_row_block(oracle, ranks, layout):
     _check_layer(oracle, w, bwd=True, tol=(1e-4, 1e-5), tag="fp32", table="lists")
 
 
+# octets (8 ranks of one adapter) of a row block around the steps of four that are requested together, and around the four steps of them
+@pytest.mark.parametrize("octets", [1, 3, 4, 5, 8, 9, 12, 13, 16, 17, 32, 33])
+def test_some_rows_octets_of_a_row_block(oracle, octets):
+    ranks = [8 * k for k in [16] * (octets // 16) + [octets % 16] if k > 0]
+    T, K, N = 70, 520, 200
+    # (the first row block of the grouped order has rows of all of them)
+    ids = np.random.default_rng(octets).permutation(np.minimum(np.arange(T) // 5, len(ranks) - 1)).astype(np.int32)
+    w = wl.make_layer(octets, T, K, N, ranks, [0.5 + t % 3 for t in range(len(ranks))], ids, dtype="bf16", layout=wl.TORCH)
+    _check_layer(oracle, w, bwd=False, tag="octets", table="table packed")
+
+
 @pytest.mark.parametrize("T,n", [(1, 1), (63, 800), (64, 1), (65, 2), (1024, 31), (1025, 32), (4097, 800), (4097, 801), (32768, 64), (32769, 64)])
 def test_segment_map_one_launch_and_several(T, n):
     rng = np.random.default_rng(T * 7 + n)
