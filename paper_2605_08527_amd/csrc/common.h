@@ -211,11 +211,15 @@ static constexpr int THIN_SPLITS = 4, THIN_U_FLOATS = MAX_PROJ * THIN_SPLITS * T
 static constexpr int MID_ROWS = 1024, MID_SPLITS = 4, MID_SPLIT_WGS = 512;
 static constexpr int MID_U_FLOATS = MAX_PROJ * 2 * MID_ROWS * 128;   // of u in one of its two areas: two pieces always fit
 static constexpr int MID_PART_FLOATS = MID_SPLIT_WGS * 96 * 128;
-// Whose turn it is (agent_memory.h): lines of 32 ints; a line counts TURN_ONE a launch, and a launch has fewer workgroups to a
-// line than that.
+// Whose turn it is (agent_memory.h): lines of 32 ints; a line counts 2^TURN_SHIFT a launch, and a launch has fewer
+// workgroups to a line than that.
 static constexpr int TURN_LINES = 32, TURN_INTS = TURN_LINES * 32, TURN_SHIFT = 20;
-static constexpr int MID_CONSUMERS = 61439;                      // column tiles of a projection, times splits
-static_assert((int64_t)MID_CONSUMERS * MAX_PROJ * (MID_ROWS / 64) < (int64_t)TURN_LINES << TURN_SHIFT, "");
+// Column tiles of a projection, times splits: with all row tiles and projections, and a sixteenth as many producers, whose
+// number is bounded by the rows, no more threads than the 2^32 of a launch.
+static constexpr int64_t MID_WGS = (1ll << 32) / 512, MID_PRODUCERS = MID_WGS / 16;
+static constexpr int MID_CONSUMERS = (int)((MID_WGS - MID_PRODUCERS) / (MAX_PROJ * (MID_ROWS / 64)));
+// (16-rank tiles of adapters of rank 128: one a row, and again for every pair of row blocks)
+static_assert((int64_t)MAX_PROJ * MID_SPLITS * 8 * (MID_ROWS + 3 * (MID_ROWS / 64)) <= MID_PRODUCERS && MID_WGS <= (int64_t)TURN_LINES << TURN_SHIFT, "");
 static constexpr int SYNC_INTS = DECODE_SYNC_INTS + THIN_U_FLOATS + TURN_INTS + 2 * MID_U_FLOATS + MID_PART_FLOATS;
 // Readings of a bounded wait, a round trip through the fabric each (1 to 1.5 us under load): what is waited for
 // takes a tenth of it where its workgroups are on the chip, and doing without costs a few hundred microseconds.

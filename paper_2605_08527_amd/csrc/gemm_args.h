@@ -154,7 +154,7 @@ hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t stream);
 // receives the scaled u (one projection; may be null), sync = counters, n_prod = n_proj times the most 16-rank tiles that
 // any grouping of T rows can use.  Factors of the shrink stored contraction-contiguous.
 hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream);
-// Up to MID_ROWS rows likewise (gemm_mid.hip); partials, thin_u: the context's areas.
+// Up to MID_ROWS rows likewise (gemm_mid.hip); turns, mid_u, partials: the context's areas.
 hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream_t stream);
 
 }  // namespace marlaas

@@ -1038,7 +1038,7 @@ hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_
   memset(&a, 0, sizeof a);
   a.Aop = Aop; a.lda = lda; a.T = T; a.Kc = Kc; a.perm = perm; a.seg_off = seg_off; a.n_adapters = n_adapters; a.table = table; a.which = which;
   a.u_out = u; a.r_stride = r_stride; a.out_is_f32 = out_is_f32; a.lform = form;
-  a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit < MID_POLLS ? sync->spin_limit : MID_POLLS; a.zero_line = zero_line;
+  a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit < MID_POLLS ? sync->spin_limit : MID_POLLS; a.zero_line = zero_line;
   if (sync->counters) {
     a.turns = sync->counters + DECODE_SYNC_INTS + THIN_U_FLOATS;
     a.mid_u = (float*)(a.turns + TURN_INTS);
