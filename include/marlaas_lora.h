@@ -25,7 +25,7 @@
  *    marlaas_adapter_table_update) only enqueue kernels on it and return: they
  *    allocate nothing, copy nothing from host memory, wait for nothing, and may
  *    be recorded into a HIP graph by stream capture, first call included.
- *    Device memory is only ever allocated by the *_create / *_build calls and, 42 MB for a buffer
+ *    Device memory is only ever allocated by the *_create / *_build calls and, 38 MB for a buffer
  *    that a ctx has not been given before (at most 15 times), by marlaas_set_workspace.
  *    marlaas_segmap_update enqueues, then waits for its own kernels.
  *  - Argument errors are reported synchronously as negative status codes with a
@@ -284,7 +284,7 @@ int marlaas_lora_fwd(marlaas_ctx* ctx, const marlaas_lora_desc* desc, void* y, i
  * share the array: calls that may overlap in time (different streams, different
  * contexts or threads) race on it; calls on one stream are ordered and safe.
  * Nothing in the array has to be cleared between calls.  (What the workgroups of
- * a launch exchange goes through a second static array of 42 MB, shared alike.)
+ * a launch exchange goes through a second static array of 38 MB, shared alike.)
  */
 #define MARLAAS_STATIC_SCRATCH_BYTES (32u << 20)
 int marlaas_lora_fwd_static(marlaas_ctx* ctx, const marlaas_lora_desc* desc, void* y, int64_t ldy,

@@ -210,7 +210,7 @@ static constexpr int THIN_SPLITS = 4, THIN_U_FLOATS = MAX_PROJ * THIN_SPLITS * T
 // sums of at most MID_SPLIT_WGS workgroups behind those.
 static constexpr int MID_ROWS = 1024, MID_SPLITS = 4, MID_SPLIT_WGS = 512;
 static constexpr int MID_U_FLOATS = MAX_PROJ * 2 * MID_ROWS * 128;   // of u in one of its two areas: two pieces always fit
-static constexpr int MID_PART_FLOATS = MID_SPLIT_WGS * 96 * 128;
+static constexpr int MID_TILE_FLOATS = 80 * 128, MID_PART_FLOATS = MID_SPLIT_WGS * MID_TILE_FLOATS;      // (of the largest tile)
 // Whose turn it is (agent_memory.h): lines of 32 ints; a line counts 2^TURN_SHIFT a launch, and a launch has fewer
 // workgroups to a line than that.
 static constexpr int TURN_LINES = 32, TURN_INTS = TURN_LINES * 32, TURN_SHIFT = 20;

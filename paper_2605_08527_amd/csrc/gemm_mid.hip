@@ -162,6 +162,7 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
   const int b = (int)blockIdx.x - a.prod0, S = a.n_split;        // the producers are workgroups prod0 ..
   const int64_t u_n = a.T * a.r_stride;                          // u: [projection][split][T][r_stride], scaled
   constexpr int UNITS = 2 * WN * RB;
+  static_assert(UNITS * 256 <= MID_TILE_FLOATS, "room for the splits' sums");
   auto u_area = [&](int area) { return a.mid_u + area * (int64_t)MID_U_FLOATS; };
   const bool joins = lora || a.ksplit > 1;                       // (exchanges something)
   const int64_t u_all = lora ? (int64_t)a.n_proj * S * u_n : 0;
