@@ -21,10 +21,11 @@ __device__ __forceinline__ void load4_agent(f32x4& v, const float* p) {     // c
 }
 
 // Launches that exchange u take turns over two areas, each all zero bits when its turn comes: a launch uses one and
-// clears what the launch before it used of the other, so that nobody has to find out who is last through (counting the
-// workgroups for that, with the answer's trip and the clearing behind it, was 2 us of 256 rows of 4096 x 4096; the line is asked
-// for behind a workgroup's operands, which would have to wait for it.  Few rows, whose u is wanted sooner, keep the count:
-// 6 rows 11.5 us, taking turns 12.2).
+// clears what the launch before it used of the other, so that nobody has to find out who is last through (a count of the
+// workgroups, with the answer's trip and the clearing behind it: 256 rows of 4096 x 4096 23.1 us, taking turns 22.5; 300 rows,
+// 1024 x 3080, 40 adapters of rank 8, 13.2 and 11.9).  The line is asked for behind a workgroup's operands, which would have to
+// wait for it.  (Read with the kernel's first loads instead, a layer's four calls of 157 rows took 194 us, not 190.6: its values
+// are in the way of the loop's.)  Few rows, whose u is wanted sooner, keep the count: 6 rows 11.5 us, taking turns 12.2.
 // Whose turn it is comes from TURN_LINES lines of {count, floats of u in area 0, in area 1, ...}; workgroup b has
 // line b mod TURN_LINES.  Every workgroup adds to its line's count once, when it has read the line, the first to each line so
 // much that a launch adds 2^TURN_SHIFT to every line, however few workgroups it has: before its own share is in, a workgroup

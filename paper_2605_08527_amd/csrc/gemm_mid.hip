@@ -12,13 +12,15 @@
 // workgroups share a compute unit (128 registers, 80 KB of LDS).
 //
 // Measured (microseconds, before: extended columns through the split kernel and a second launch): 256 rows
-// 4096 x 4096 with 32 adapters of rank 16 28.4 -> 22.4, q/k/v of 4096 + 1024 + 1024 columns 42.0 -> 31.0, the
-// four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 194, 512 rows of 64 adapters of ranks 8
-// to 64, 5120 x 5120, 63 (weights from memory).  Stamps in the 256 rows, of a version that asked for u before the
-// sums and took 23.1: indices 1.8, first tile 3.8, loop done 15.4 (17.5 where a producer shares the unit; 14.6 without
-// adapters), sums and u 17.4, expand 18.5, stored 19.1.  Since then the expand takes u in two terms from LDS (split once a row, not
-// once a wave), nobody waits for a count of the workgroups that are through, and the launch ends with its stores: 22.3 -> 21.3,
-// q/k/v 31.0 -> 30.4, a layer's four calls of 157 rows 195.9 -> 193.8.
+// 4096 x 4096 with 32 adapters of rank 16 28.4 -> 21.5, q/k/v of 4096 + 1024 + 1024 columns 42.0 -> 29.8, the
+// four calls of a decoder layer (4096, ffn 14336) of 157 rows 252 -> 190, 512 rows of 64 adapters of ranks 8
+// to 64, 5120 x 5120, 62 (weights from memory).  Stamps in the 256 rows (a workgroup in the middle, the last one): indices
+// 2.0, 2.4; first tile 3.8, 6.3 (a producer shares the unit; u is out after 5.6, 7.2); loop done 15.0, 17.3; sums met
+// 15.6, 17.8; u in LDS 17.4, 19.4; expanded 17.8, 19.9; stored 18.2, 20.3.  q/k/v: first tile 4.7, 13.7; loop 19.4, 25.9; u in LDS
+// 21.7, 28.4; stored 22.6, 29.3.
+// What the last changes gave, each against a build without it: turns instead of a count (agent_memory.h); u in two terms once a
+// row, on its way into LDS, not once a wave (100 rows of 32 adapters of rank 64, 4096 x 4096, 28.9 -> 28.2; q/k/v and 256 rows of
+// rank 16 no more than runs differ); octet steps requested together (KB below).
 //
 // Whatever crosses workgroups carries its own flag: it travels through areas of the context that are all
 // zero bits when a launch finds them, no value is stored as zero bits (+0 becomes -0), and a reader reads until
@@ -30,8 +32,8 @@
 //   partial sums: with ksplit > 1 the splits of a tile share out its 16 x 16 units; a split hands the
 //     others' units over, reads its own ones' missing sums and clears them.
 // The reading is bounded (MID_POLLS).  u that does not come in time is computed by the reader; so are missing
-// sums, and the next launch then clears their area and computes all of its sums where they are wanted.  No workgroup depends on another one being scheduled,
-// and either way the sums are added in the same order: the bits are the same.
+// sums, and the next launch then clears their area and computes all of its sums where they are wanted.  No workgroup depends
+// on another one being scheduled, and either way the sums are added in the same order: the bits are the same.
 #include "gemm_args.h"
 #include "agent_memory.h"
 #include "lora_expand.h"

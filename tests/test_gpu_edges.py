@@ -29,9 +29,9 @@ def test_fp32_layer(oracle, T, K, N, ranks, table, layout):
     _check_layer(oracle, w, bwd=True, tol=(1e-4, 1e-5), tag="fp32", table="table" if table else "lists")
 
 
-# as many shrink tiles in a row block as one pass takes, one less and one more, either kind of factor
+# as many shrink tiles in a row block as one pass takes (two), one less, one more and further ones, either kind of factor
 @pytest.mark.parametrize("layout", [0, 1])
-@pytest.mark.parametrize("ranks", [[16, 8], [24, 8], [8] * 4, [33, 16], [8, 1, 16, 7, 24], [128]])
+@pytest.mark.parametrize("ranks", [[16], [16, 8], [24, 8], [8] * 4, [33, 16], [8, 1, 16, 7, 24], [128]])
 def test_fp32_shrink_tiles_of_a_row_block(oracle, ranks, layout):
     T, K, N = 19, 264, 136
     ids = (np.arange(T) * 7 % len(ranks)).astype(np.int32)
