@@ -16,7 +16,8 @@ struct ShrinkJob {
 // Eight waves share the part's 32-deep steps, their sums meet in `red` (8 x NB x 64) and are added in wave
 // order: the bits do not depend on who computes the job.  u(): [row of the tile][r_stride] of this split; ask() requests what
 // u() needs, behind the first operands, which would have to wait for it.  Every wave has called u() when the waves meet, so that
-// behind the job whoever likes may change what u() reads.  No value is stored as zero bits.  tok0, tok1: tokens of row lane % 16 of the first and of the second block.
+// behind the job whoever likes may change what u() reads.  No value is stored as zero bits.  tok0, tok1: tokens of row
+// lane % 16 of the first and of the second block.
 // UP: steps requested together (twice); NB: blocks a job can have.  All eight waves call it.
 template <int UP, int NB, typename Ask, typename At>
 __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, int64_t lda, int64_t Kc, int32_t tok0, int32_t tok1, int S,

@@ -20,7 +20,7 @@ static constexpr int MID_WAVES = 8;
 //   adapters, with their regrouping 82 and 88).
 // Few steps are not cut: a value of u is read once for each piece.  More than 24 always are (eight projections of 1024
 // columns, contraction 8192, 1000 rows of 4 adapters of rank 128: 364 us, whole 402, 600 rows of 8 adapters 288 and 282; of
-// 512 columns, contraction 7168, 640 rows of 32 adapters: 340 and 1035, as whole producers come so late that waits are given up).
+// 512 columns, contraction 7168, 640 rows of 32 adapters: 340 and 1035).
 //   u_room: floats of u that there is room for.
 inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t consumers, int64_t jobs, int cu_count) {
   const int64_t steps = ((Kc + 31) / 32 + MID_WAVES - 1) / MID_WAVES;      // 32-deep steps of a wave
