@@ -107,6 +107,12 @@ __device__ __forceinline__ bf16_t float_to_bf16_bits(float f) {
   const __bf16 h = (__bf16)f;
   return __builtin_bit_cast(bf16_t, h);
 }
+// two of them, the first one in the lower half: one instruction
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
 
 // Segment t of the grouped token order is [seg_off[t], seg_off[t+1]).
 // Largest t in [0, n] with seg_off[t] <= m (seg_off has n + 2 entries, last = T).

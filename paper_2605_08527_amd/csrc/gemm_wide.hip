@@ -18,6 +18,9 @@
 // current one are stored, so neither the token gather nor the first memory latency nor the burst of
 // stores stands between two tiles.  Measured (16384 x 16384 outputs, K = 2048 / 4096 / 8192): as one
 // workgroup per tile each tile paid 12 us besides its k-tiles of 1.36 us.
+// What bounds a k-tile: 2048 cycles of matrix instructions a wave, with one wave per SIMD, so every instruction that does not
+// fit an MFMA's shadow is added to them (stamps, 40960 rows, 4096 x 14336: 2342 cycles with requests in one piece, 2200
+// with one instruction a shadow; the clock falls as the power limit has it, 3.50 -> 3.41 ms with the expand, 2.6 %).
 #include "gemm_args.h"
 
 #include <atomic>
@@ -44,9 +47,6 @@ __device__ __forceinline__ uint4 pack8(const bf16_t* o) {
   pk.z = o[4] | ((uint32_t)o[5] << 16); pk.w = o[6] | ((uint32_t)o[7] << 16);
   return pk;
 }
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  return float_to_bf16_bits(lo) | ((uint32_t)float_to_bf16_bits(hi) << 16);
-}
 // Two 16 x 16 accumulator blocks side by side (lane: row lane % 16, columns 4 (lane / 16) .. + 3 of
 // each) as eight consecutive bf16 columns per lane: odd lane groups take the right-hand block.
 // Lane group lg ends up with columns 16 (lg & 1) + 8 (lg / 2) .. + 7 of the 32.
@@ -64,9 +64,25 @@ __device__ __forceinline__ void store_out(void* p, uint4 v) {
 }
 __device__ __forceinline__ void store_out(void* p, const f32x4& v) { __builtin_nontemporal_store(v, (f32x4*)p); }
 
+// c += a b on an accumulator that stays where it is: left to choose, the compiler moves accumulators between the two register
+// files, with waits, in every k-tile but the steady ones, and spills (16384 rows, 14336 x 4096, a task's forward and backward
+// 2960 us, 2910 so).  It knows nothing of the instruction: whoever reads accumulators otherwise calls acc_settle first, and no
+// vector arithmetic writes an operand right before; where fragments are put together from transposing reads it does (MOVED).
+// tests/test_generated_code.py reads the code for both.
+template <bool MOVED>
+__device__ __forceinline__ void mma(f32x4& c, bf16x8 a, bf16x8 b) {
+  if (MOVED) asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+template <bool MOVED>
+__device__ __forceinline__ void mma_first(f32x4& c, bf16x8 a, bf16x8 b) {     // c = a b
+  if (MOVED) asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 // An accumulator's values as arithmetic sees them, read here and not earlier: left to the compiler all
 // of them are copied out ahead of the stores, into registers that are not there.
-__device__ __forceinline__ f32x4 acc_read(f32x4 c) { asm volatile("" : "+a"(c)); return c; }
+__device__ __forceinline__ f32x4 acc_read(f32x4 c) { asm volatile("" : "+v"(c)); return c; }
 // The value, recomputed from here on: what is derived from it is not kept in registers across the
 // item loop (the accumulators leave few, and a reload from scratch would wait for every request).
 __device__ __forceinline__ int fresh(int v) { asm volatile("" : "+v"(v)); return v; }
@@ -99,7 +115,7 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
   constexpr int C1 = (10 + HB) / 3, C2 = (9 + HB) / 3, C3 = (8 + HB) / 3;   // the 8 + HB first requests over three phases
   static_assert(C1 + C2 + C3 == 8 + HB, "");
   constexpr int NST = (OUT_F32 ? 8 : 4) * MT;               // stores per wave of a whole tile
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+  extern __shared__ __attribute__((aligned(128))) char smem[];
   char* lt_s = smem + 2 * SLOT;
   int32_t* tok3 = (int32_t*)(lt_s + W_LT_BYTES);            // [3][ROWS] tokens of items i - 1, i, i + 1
 
@@ -171,6 +187,8 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
   int ntile = 0, tail_k = WK;        // k-tiles of the item; contraction values of its last one
   int nfast = 0;                     // k-tiles that are whole
   const int a_dma = wave * MT * 1024, b_dma = A_BYTES + wave * 8 * 1024;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
+  const uint32_t a_to = lds0 + ((wave >> 1) * (16 * MT) + (wave & 1) * (8 * HB)) * 128, b_to = lds0 + b_dma;   // of request 0, slot 0
   // Instruction j < HB of a wave moves 8 of the rows that phases 0 and 1 multiply (the first half of
   // each wave row's row blocks), instruction j >= HB rows of the other half.
 #define W_AROW(j_) (((j_) >= HB ? 8 * MT : 0) + (wave * HB + (j_) % HB) / (2 * HB) * (16 * MT) + (wave * HB + (j_) % HB) % (2 * HB) * 8)
@@ -234,6 +252,22 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
   // Request q_ of the part of a k-tile that is needed first: its weights (8) and the first half's rows (HB)
 #define W_DMA_FIRST(slot_, q_, tail_)                                                                          \
   do { if ((q_) < 8) W_DMA_B(slot_, (q_) & 7, tail_); else W_DMA_A(slot_, ((q_) - 8) % HB, tail_); } while (0)
+  // The same of a whole k-tile in three parts, each one instruction in the shadow of an MFMA of its own (W_PHASE): m0 = LDS
+  // byte address of lane 0's 16 bytes, the request, the address's advance.  Nothing else between the first two parts writes m0.
+#define W_PART_A(part_, to_, j_)                                                                          \
+  do {                                                                                                    \
+    if ((part_) == 0) asm volatile("s_add_u32 m0, %0, %1" :: "s"((to_) + a_to), "n"(((j_) >= HB ? 8 * MT * 128 : 0) + (j_) % HB * 1024) : "memory", "m0", "scc"); \
+    if ((part_) == 1) asm volatile("global_load_lds_dwordx4 %0, off" :: "v"(a_src[j_]) : "memory");       \
+    if ((part_) == 2) a_src[j_] += WK;                                                                    \
+  } while (0)
+#define W_PART_B(part_, to_, j_)                                                                          \
+  do {                                                                                                    \
+    if ((part_) == 0) asm volatile("s_add_u32 m0, %0, %1" :: "s"((to_) + b_to), "n"((j_) * 1024) : "memory", "m0", "scc"); \
+    if ((part_) == 1) asm volatile("global_load_lds_dwordx4 %0, %1" :: "v"(b_off[j_]), "s"(b_base) : "memory"); \
+    if ((part_) == 2 && (j_) == 7) b_base += b_step;                                                      \
+  } while (0)
+#define W_PART_FIRST(part_, to_, q_)                                                                      \
+  do { if ((q_) < 8) W_PART_B(part_, to_, (q_) & 7); else W_PART_A(part_, to_, ((q_) - 8) % HB); } while (0)
   // contraction values of k-tile kt_
 #define W_KLEN(kt_) ((kt_) == ntile - 1 ? tail_k : WK)
   // an item's first requests, oldest first: the tokens of the item after it, its list of extra
@@ -270,6 +304,17 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
   }
 #define W_READ_X(slot_, ks_, mt_, dst_)                                                                   \
   dst_ = *(const bf16x8*)(smem + (slot_) * SLOT + a_off_row + (mt_) * 2048 + ((((ks_) * 4 + fg) ^ f_swz) << 4))
+  // The main loop's reads: byte addresses of the wave's rows of x and of the weight in k-step 0 and 1, each moved to
+  // the other slot (toggle) behind its last use in a k-tile.
+  typedef const bf16x8 __attribute__((address_space(3)))* lds_x8;
+  uint32_t x_at[2] = {0, 0}, w_at[2] = {0, 0};
+#define W_TOGGLE(r_) asm volatile("v_add_u32 %0, %1, %0" : "+v"(r_) : "s"(_nto - _to))
+#define W_NEXT_X(ks_, mt_, dst_) dst_ = *(lds_x8)(x_at[ks_] + (mt_) * 2048)
+#define W_NEXT_W(slot_, ks_, nt_, dst_)                                                                   \
+  do {                                                                                                    \
+    if (FORM == FORM_NT) dst_ = *(lds_x8)(w_at[ks_] + (nt_) * 2048);                                      \
+    else W_READ_W(FORM, slot_, ks_, nt_, dst_);                                                           \
+  } while (0)
 #define W_READ_W(form_, slot_, ks_, nt_, dst_)                                                            \
   do {                                                                                                    \
     const char* _bs = smem + (slot_) * SLOT + A_BYTES;                                                    \
@@ -286,24 +331,27 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
   // One phase: the MFMAs of HB row blocks (x fragments ux_) against all eight column blocks (weight
   // fragments uw_).  In their shadow, spread over its first three quarters, the LDS reads for the
   // next phase: HB x fragments of k-step xks_, row half xh_ and, rd_w_, the eight weight fragments of
-  // k-step wks_; and, spread evenly, cnt_ DMA instructions (dma_(r_) is the r_-th).  sched_barrier pins
-  // the order: with one wave per SIMD nothing else hides the issue of LDS and DMA instructions.
-#define W_PHASE(h_, ux_, uw_, rd_, xslot_, xks_, xh_, lx_, rd_w_, wks_, lw_, cnt_, dma_)                  \
+  // k-step wks_; and, spread evenly, cnt_ DMA instructions (dma_(p_, r_): part p_ of the r_-th).  sched_barrier pins
+  // the order: with one wave per SIMD nothing else hides the issue of LDS and DMA instructions, and an MFMA's shadow hides
+  // three instructions, so that a request's parts go into three of them.
+#define W_PHASE(z_, h_, ux_, uw_, rd_, xslot_, xks_, xh_, lx_, rd_w_, wks_, lw_, cnt_, dma_, end_)            \
   do {                                                                                                    \
     _Pragma("unroll") for (int _i = 0; _i < 8 * HB; ++_i) {                                               \
-      acc[HB * (h_) + (_i >> 3)][_i & 7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                       \
-          uw_[_i & 7], ux_[_i >> 3], acc[HB * (h_) + (_i >> 3)][_i & 7], 0, 0, 0);                        \
+      if (z_) mma_first<FORM == FORM_NN>(acc[HB * (h_) + (_i >> 3)][_i & 7], uw_[_i & 7], ux_[_i >> 3]);                   \
+      else mma<FORM == FORM_NN>(acc[HB * (h_) + (_i >> 3)][_i & 7], uw_[_i & 7], ux_[_i >> 3]);                            \
       __builtin_amdgcn_sched_barrier(0);                                                                  \
       constexpr int _nr = HB + ((rd_w_) ? 8 : 0), _at = 8 * HB * 3 / 4;                                   \
       if (rd_) {                                                                                          \
         _Pragma("unroll") for (int _r = 0; _r < _nr; ++_r)                                                \
           if (_r * _at / _nr == _i) {                                                                     \
-            if ((rd_w_) && _r < 8) W_READ_W(FORM, xslot_, wks_, _r & 7, lw_[_r & 7]);                     \
-            else W_READ_X(xslot_, xks_, HB * (xh_) + (_r - ((rd_w_) ? 8 : 0)) % HB, lx_[(_r - ((rd_w_) ? 8 : 0)) % HB]); \
+            if ((rd_w_) && _r < 8) W_NEXT_W(xslot_, wks_, _r & 7, lw_[_r & 7]);                           \
+            else W_NEXT_X(xks_, HB * (xh_) + (_r - ((rd_w_) ? 8 : 0)) % HB, lx_[(_r - ((rd_w_) ? 8 : 0)) % HB]); \
           }                                                                                               \
       }                                                                                                   \
       _Pragma("unroll") for (int _r = 0; _r < (cnt_); ++_r)                                               \
-        if ((2 * _r + 1) * 8 * HB / (2 * (cnt_)) == _i) dma_(_r);                                         \
+        _Pragma("unroll") for (int _p = 0; _p < 3; ++_p)                                                  \
+          if ((2 * _r + 1) * 8 * HB / (2 * ((cnt_) > 0 ? (cnt_) : 1)) - 1 + _p == _i) dma_(_p, _r);       \
+      if (_i == 8 * HB - 2) { end_; }                                                                     \
       __builtin_amdgcn_sched_barrier(0);                                                                  \
     }                                                                                                     \
   } while (0)
@@ -317,22 +365,32 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
   // phases, 0.91 without any) and each has three phases or more to arrive.  At each meeting everything
   // but the youngest requests has arrived (x1_, f2_: the part of tile kt + 1 / kt + 2 is requested in
   // this tile, 1 whole, 2 perhaps partial; st_: the stores of the item before are younger than tile 1).
-#define W_X1(r_) W_DMA_A(_nslot, HB + (r_), _l1)
-#define W_F1(r_) W_DMA_FIRST(_slot, (r_), _l2)
-#define W_F2(r_) W_DMA_FIRST(_slot, C1 + (r_), _l2)
-#define W_F3(r_) W_DMA_FIRST(_slot, C1 + C2 + (r_), _l2)
+#define W_X1(p_, r_, k_) do { if ((k_) == 1) W_PART_A(p_, _nto, HB + (r_)); else if ((p_) == 1) W_DMA_A(_slot ^ 1, HB + (r_), _l1); } while (0)
+#define W_FQ(p_, q_, k_) do { if ((k_) == 1) W_PART_FIRST(p_, _to, q_); else if ((p_) == 1) W_DMA_FIRST(_slot, q_, _l2); } while (0)
+#define W_X1_1(p_, r_) W_X1(p_, r_, 1)
+#define W_X1_2(p_, r_) W_X1(p_, r_, 2)
+#define W_F1_1(p_, r_) W_FQ(p_, r_, 1)
+#define W_F1_2(p_, r_) W_FQ(p_, r_, 2)
+#define W_F2_1(p_, r_) W_FQ(p_, C1 + (r_), 1)
+#define W_F2_2(p_, r_) W_FQ(p_, C1 + (r_), 2)
+#define W_F3_1(p_, r_) W_FQ(p_, C1 + C2 + (r_), 1)
+#define W_F3_2(p_, r_) W_FQ(p_, C1 + C2 + (r_), 2)
+#define W_X1_0 W_X1_1
+#define W_F1_0 W_F1_1
+#define W_F2_0 W_F2_1
+#define W_F3_0 W_F3_1
 #define W_TILE(kt_, x1_, f2_, st_)                                                                        \
   do {                                                                                                    \
-    const int _slot = (kt_) & 1, _nslot = _slot ^ 1;                                                      \
+    const int _slot = (kt_) & 1, _to = _slot * SLOT, _nto = SLOT - _to;                                   \
     const int _l1 = (x1_) == 2 ? W_KLEN((kt_) + 1) : 0, _l2 = (f2_) == 2 ? W_KLEN((kt_) + 2) : 0;         \
-    W_PHASE(0, xa0, wb0, 1, _slot, 1, 0, xa1, 1, 1, wb1, (x1_) ? HB : 0, W_X1);                           \
+    W_PHASE((st_) > 0, 0, xa0, wb0, 1, _slot, 1, 0, xa1, 1, 1, wb1, (x1_) ? HB : 0, W_X1_##x1_, );                   \
     if (x1_) wide_meet<8 + 2 * HB + (st_), 0>();                                                          \
     else if (lt_cnt > 0) wide_meet<8 + MT, 0>();                                                          \
     else wide_meet<0, 0>();                                                                               \
-    W_PHASE(0, xa1, wb1, 1, _slot, 0, 1, xa0, 0, 0, wb0, (f2_) ? C1 : 0, W_F1);                           \
-    W_PHASE(1, xa0, wb0, 1, _slot, 1, 1, xa1, 0, 0, wb0, (f2_) ? C2 : 0, W_F2);                           \
+    W_PHASE(0, 0, xa1, wb1, 1, _slot, 0, 1, xa0, 0, 0, wb0, (f2_) ? C1 : 0, W_F1_##f2_, W_TOGGLE(w_at[1]));  \
+    W_PHASE((st_) > 0, 1, xa0, wb0, 1, _slot, 1, 1, xa1, 0, 0, wb0, (f2_) ? C2 : 0, W_F2_##f2_, W_TOGGLE(x_at[0]); W_TOGGLE(w_at[0])); \
     if (x1_) wide_meet<HB + ((f2_) ? C1 + C2 : 0) + (st_), 0>();                                          \
-    W_PHASE(1, xa1, wb1, x1_, _nslot, 0, 0, xa0, 1, 0, wb0, (f2_) ? C3 : 0, W_F3);                        \
+    W_PHASE(0, 1, xa1, wb1, x1_, _slot ^ 1, 0, 0, xa0, 1, 0, wb0, (f2_) ? C3 : 0, W_F3_##f2_, W_TOGGLE(x_at[1])); \
   } while (0)
 
   // One extra contraction tile of the LoRA expand (entry i_ of the row tile's list) into slot slot_:
@@ -380,8 +438,7 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
     _Pragma("unroll") for (int _mt = 0; _mt < MT; ++_mt) {                                                \
       const int64_t _r0 = m0 + wm * (16 * MT) + _mt * 16;                                                 \
       if (_r0 + 16 > (lo_) && _r0 < (hi_)) {                                                              \
-        _Pragma("unroll") for (int _n = 0; _n < W_NT; ++_n)                                               \
-          acc[_mt][_n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(_wf[_n], _xf[_mt], acc[_mt][_n], 0, 0, 0); \
+        _Pragma("unroll") for (int _n = 0; _n < W_NT; ++_n) mma<LFORM == FORM_NN>(acc[_mt][_n], _wf[_n], _xf[_mt]);         \
         shared_rows |= __builtin_amdgcn_readfirstlane(_r0 < (lo_) || _r0 + 16 > (hi_)) << _mt;            \
       }                                                                                                   \
     }                                                                                                     \
@@ -395,10 +452,15 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
   bool stores = false;               // the previous item's NST stores are younger than this item's first requests
 
   for (int item = 0; item < n_items; ++item) {
+    // (a tile behind stores starts its sums with its first products)
+    if (!stores || nfast <= 2) {
+      bf16x8 z = {};
+      asm volatile("" : "+v"(z));
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int j = 0; j < W_NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < W_NT; ++j) mma_first<true>(acc[i][j], z, z);
+    }
     // the first part of k-tile 0 (and everything older) has landed
     if (ntile > 1) {
       if (stores) wide_meet<8 + 2 * HB + NST, 0>(); else wide_meet<8 + 2 * HB, 0>();
@@ -411,6 +473,12 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
     int lslot = 0;                   // slot of the first extra contraction tile
     {
       bf16x8 xa0[HB], xa1[HB], wb0[W_NT], wb1[W_NT];
+      {
+        const int _ln = fresh(lane), _row = _ln & 15, _g = (_ln >> 4) ^ ((_row >> 1) & 7);
+        x_at[0] = lds0 + (wm * (MT * 16) + _row) * 128 + (_g << 4);
+        w_at[0] = lds0 + A_BYTES + (wn * 128 + _row) * 128 + (_g << 4);
+        x_at[1] = x_at[0] ^ 64; w_at[1] = w_at[0] ^ 64;      // (k-step 1: unit ^ 4)
+      }
 #pragma unroll
       for (int i = 0; i < HB; ++i) W_READ_X(0, 0, i, xa0[i]);
 #pragma unroll
@@ -511,6 +579,7 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
     // not a number is not 0: such sums are computed again behind the stores.  (The test reads the shared
     // blocks' accumulators; 40960 rows of 32 adapters, 4096 x 14336: 3.58 ms without it, 3.56 with.)
     bool again = false;
+    acc_settle();
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
       if (shared_rows >> mt & 1) {
@@ -541,6 +610,18 @@ __global__ __launch_bounds__(W_THREADS) void gemm_wide_kernel(WideArgs a) {
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < W_NT; ++nt) part[(mt * W_NT + nt) * 64] = acc[mt][nt];
+    } else if (!OUT_F32 && stores) {
+      // a whole tile
+      const int32_t* tok = tok3 + (item % 3) * ROWS + wm * (16 * MT) + erow;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        bf16_t* o = (bf16_t*)a.out + (int64_t)tok[mt * 16] * a.ldo + en0 + wn * 128 + (eg & 1) * 16 + (eg >> 1) * 8;
+#pragma unroll
+        for (int np = 0; np < W_NT / 2; ++np) {
+          __builtin_amdgcn_sched_barrier(0);
+          store_out(o + np * 32, pair_rows(acc_read(acc[mt][2 * np]), acc_read(acc[mt][2 * np + 1])));
+        }
+      }
     } else {
       const int32_t* tok = tok3 + (item % 3) * ROWS + wm * (16 * MT) + erow;
       const int64_t mrow = em0 + wm * (16 * MT) + erow;

@@ -12,7 +12,7 @@ import pytest
 
 from paper_2605_08527_amd import build
 
-FILES = ["gemm_mid", "gemm_decode", "gemm_bf16", "lora_small"]
+FILES = ["gemm_mid", "gemm_decode", "gemm_bf16", "lora_small", "gemm_wide"]
 
 
 def _registers(operand):
@@ -138,6 +138,61 @@ def masked_waits(blocks):
             if before in ("s_cbranch_execz", "s_cbranch_execnz") and op == "s_waitcnt" and re.search(r"vmcnt\([1-9]", s)]
 
 
+def unsettled_products(blocks):
+    """Matrix products by inline assembly, for which the compiler counts no wait states: an accumulator read by anything but a
+    product less than SETTLE instructions behind one, a product whose operand vector arithmetic wrote less than two before."""
+    order = list(blocks)
+    after = dict(zip(order, order[1:]))
+    seen, work, found = set(), [("", SETTLE, ())], []
+
+    def reach(label, since, fresh):
+        if label is not None and (label, since, fresh) not in seen:
+            seen.add((label, since, fresh))
+            work.append((label, since, fresh))
+
+    while work:
+        label, since, fresh = work.pop()             # instructions since the last product; registers written by the last two
+        for s, op, operands, asm in blocks[label]:
+            if op == "s_branch":
+                reach(operands[0], since, fresh)
+                break
+            if op.startswith("s_cbranch"):
+                reach(operands[0], since, fresh)
+            if op == "s_endpgm":
+                break
+            touched = [_registers(t) for t in operands]
+            if op.startswith("v_mfma"):
+                if asm and any(r in f for t in touched[1:] for r in t for f in fresh):
+                    found.append(s)
+                since, wrote = 0, ()
+            else:
+                if since < SETTLE and any(r[0] == "a" for t in touched for r in t):
+                    found.append(s)
+                wrote = tuple(touched[0]) if op.startswith("v_") and touched else ()
+            waits = int(operands[0]) + 1 if op == "s_nop" else 1
+            since = min(SETTLE, since + (waits if not op.startswith("v_mfma") else 0))
+            fresh = ((wrote,) + fresh)[:2] if waits == 1 else ()
+        else:
+            reach(after.get(label), since, fresh)
+    return found
+
+
+def mixed_destinations(blocks):
+    """Requests into LDS by inline assembly whose m0 something else has written since: (m0 set in an earlier statement)"""
+    found = []
+    for instructions in blocks.values():
+        ours = False
+        for s, op, operands, asm in instructions:
+            if operands[0] == "m0" and op.startswith("s_"):
+                ours = asm
+            if asm and op.startswith("global_load_lds") and not ours:
+                found.append(s)
+    return found
+
+
+SETTLE = 19
+
+
 @pytest.fixture(scope="module")
 def listings(tmp_path_factory):
     out = tmp_path_factory.mktemp("listings")
@@ -162,6 +217,17 @@ def test_no_move_of_a_load_before_a_wait(listings, f):
 def test_some_rows_keep_their_registers(listings):
     spills = re.findall(r"\.vgpr_spill_count: +(\d+)", listings["gemm_mid"])
     assert len(spills) == 4 and all(n == "0" for n in spills)
+
+
+# The large-batch kernel's accumulators take half of the registers, and its products are inline assembly.
+def test_large_batches_keep_their_accumulators(listings):
+    spills = re.findall(r"\.vgpr_spill_count: +(\d+)", listings["gemm_wide"])
+    assert len(spills) == 20 and all(n == "0" for n in spills)
+    kernels = [(name, blocks) for name, blocks in _functions(listings["gemm_wide"]) if "gemm_wide_kernel" in name]
+    assert len(kernels) == 18
+    for name, blocks in kernels:
+        assert not unsettled_products(blocks), name
+        assert not mixed_destinations(blocks), name
 
 
 # The reductions of both gradients share a launch; the arguments of each storage form stay its own.
@@ -221,3 +287,21 @@ def test_early_move_is_seen():
     for wait, moves in waits.items():
         (_, blocks), = _functions(text % wait)
         assert len(early_moves(blocks)) == moves, wait
+
+
+def test_unsettled_product_is_seen():
+    text = """_Zk:
+%s
+\t;;#ASMSTART
+\tv_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]
+\t;;#ASMEND
+%s
+\tv_accvgpr_read_b32 v1, a2
+.LBB0_1:
+\ts_endpgm
+.Lfunc_end0:
+"""
+    for before, behind, n in (("", "", 1), ("", "\ts_nop 15", 1), ("", "\ts_nop 15\n\ts_nop 15", 0), ("\tv_mov_b32_e32 v5, v1", "\ts_nop 15\n\ts_nop 15", 1),
+                              ("\tv_mov_b32_e32 v5, v1\n\ts_nop 1", "\ts_nop 15\n\ts_nop 15", 0)):
+        (_, blocks), = _functions(text % (before, behind))
+        assert len(unsettled_products(blocks)) == n, (before, behind)
