@@ -114,6 +114,20 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
+// A wave's 16 rows x 32 values, requested a row at a time (lane: row lane / 4, eight values lane % 4), as an operand of the
+// matrix instructions (lane: row lane % 16, eight values lane / 16).  `stage`: 1 KB of LDS of this wave alone; a wave's LDS
+// instructions are carried out in order, so the next call may follow at once.  What it is for: four neighbouring lanes in one
+// line are one look-up of the unit's L1, and in operand order every lane is one: a kilobyte out of L2 keeps a unit busy for
+// 27 ns, in rows for 8.3, in one piece for 7.0.  The trip through LDS (0.1 us) goes into the chain of requests.
+__device__ __forceinline__ uint4 rows_to_operand(char* stage, uint4 v, int lane) {
+  const int li = lane & 15, lg = lane >> 4;
+  *(uint4*)(stage + (lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 3) & 3)) << 4)) = v;
+  asm volatile("" ::: "memory");
+  const uint4 o = *(const uint4*)(stage + li * 64 + ((lg ^ ((li >> 1) & 3)) << 4));
+  asm volatile("" ::: "memory");
+  return o;
+}
+
 // Segment t of the grouped token order is [seg_off[t], seg_off[t+1]).
 // Largest t in [0, n] with seg_off[t] <= m (seg_off has n + 2 entries, last = T).
 __device__ __forceinline__ int segment_of(const int32_t* __restrict__ seg_off, int n, int m) {

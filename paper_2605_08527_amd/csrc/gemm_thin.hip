@@ -7,8 +7,8 @@
 // launch to add the pieces up (6 rows x 4096 x 4096: 17.9 + 6.9 us).  Here a workgroup owns all rows
 // times 16 NC output columns and its eight waves split the contraction, so a weight fragment is read
 // once, by the one wave that multiplies it, a wave requests 8 to 20 KB at a time, and the sums meet in
-// LDS.  x fragments come straight from L2 (for the row counts of this kernel no more bytes than the
-// weight).  Workgroups before the consumers ("producers") compute u: one per 16 ranks of an adapter
+// LDS.  x comes straight from L2 (for the row counts of this kernel no more bytes than the weight), a row at
+// a time.  Workgroups before the consumers ("producers") compute u: one per 16 ranks of an adapter
 // that has rows, the same loop over the adapter's factor in place of the weight.  They are scheduled
 // first and take little longer than a consumer's loop.  Every round trip through the fabric costs 1 to
 // 1.5 us, so u carries its own flag: it travels through an area of the context that is all zero bits
@@ -88,11 +88,16 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
   const int steps = (int)((a.Kc + 31) >> 5), per = (steps + TH_WAVES - 1) / TH_WAVES;
   const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
 
-  // tokens of the rows this lane supplies; adapter, and its entry, of row `lane`
+  // x is requested a row at a time (rows_to_operand) where a wave has more than eight steps of it and the rows are not mostly
+  // repeats of the last one: 32 rows 4096 x 4096 16.8 -> 14.7 us, 16 rows 12.6 -> 11.7; 6 rows, everything from memory, 11.4 and
+  // 11.9, 30 rows, 2000 x 2000, 8.7 and 9.3.  (Producers do not: their chain is what u waits for.)
+  const bool in_rows = !producer && per > 8 && a.T > 8;
+  const int xr = in_rows ? lane >> 2 : li, xu = in_rows ? lane & 3 : lg;   // row, eight values that this lane requests
+  // tokens of the rows this lane requests; adapter, and its entry, of row `lane`
   int32_t tokr[R];
 #pragma unroll
   for (int i = 0; i < R; ++i) {
-    const int64_t m = 16 * i + li < a.T ? 16 * i + li : a.T - 1;
+    const int64_t m = 16 * i + xr < a.T ? 16 * i + xr : a.T - 1;
     tokr[i] = a.perm ? a.perm[m] : (int32_t)m;
   }
   int g = -1, g_before = -1;
@@ -103,7 +108,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
 
 #define TH_X(dst_, i_, ks_)                                                                               \
   do {                                                                                                    \
-    const int64_t _k = (int64_t)(ks_) * 32 + 8 * lg;                                                      \
+    const int64_t _k = (int64_t)(ks_) * 32 + 8 * xu;                                                      \
     dst_ = make_uint4(0, 0, 0, 0);                                                                        \
     if ((ks_) < s1 && _k < a.Kc) dst_ = *(const uint4*)(a.Aop + (int64_t)tokr[i_] * a.lda + _k);          \
   } while (0)
@@ -146,6 +151,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
 
   // ---- consumers.  Column block c of this workgroup is block n0 / 16 + c of the packed weight
   // (blocks past the last one repeat it: those columns are never stored)
+  char* const stage = smem + wave * (TILES * 1024);
   const bf16_t* wp[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -166,6 +172,9 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
   } while (0)
 #define TH_MMA(set_)                                                                                      \
   do {                                                                                                    \
+    if (in_rows)                                                                                          \
+      _Pragma("unroll") for (int _u = 0; _u < U; ++_u)                                                    \
+        _Pragma("unroll") for (int _i = 0; _i < R; ++_i) set_[_u][_i].u = rows_to_operand(stage, set_[_u][_i].u, lane); \
     _Pragma("unroll") for (int _u = 0; _u < U; ++_u)                                                      \
       _Pragma("unroll") for (int _i = 0; _i < R; ++_i)                                                    \
         _Pragma("unroll") for (int _c = 0; _c < NC; ++_c)                                                 \

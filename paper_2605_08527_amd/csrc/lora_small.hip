@@ -417,7 +417,7 @@ __global__ __launch_bounds__(256) void shrink_ring_kernel(ShrinkArgs a) {
 // contraction, take both operands straight from global memory (L_t stored [r_t, C], so a lane's 8
 // contraction values are one 16-byte load) and add their partial tiles through LDS in wave order,
 // so the result does not depend on timing.  Bound by latency: a wave has U steps of 32 contraction values
-// under way while U others are multiplied, and the four lanes of a row read 64 bytes in a row.
+// under way while U others are multiplied.
 static constexpr int SS_WAVES = 8;
 template <int NQT>
 __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkArgs a) {
@@ -433,11 +433,17 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
   const int r = e.rank, r_pad = (r + 15) & ~15, nqt = r_pad >> 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, li = lane & 15;
-  int m = row0 + li;
+  const int steps = (int)((a.C + 31) >> 5), per = (steps + SS_WAVES - 1) / SS_WAVES;
+  // Requests in operand order are look-ups of the unit's L1, one a lane (two kilobytes a step, 54 ns: at 4096 values 6.9 us
+  // of a block's 9), so they go a row at a time (rows_to_operand) where a wave has more than eight steps: a prefill chunk of
+  // 2011 rows, 4096 x 4096, rank 16, 69.3 -> 68.0 us.
+  const bool in_rows = per > 8;
+  const int lr = in_rows ? lane >> 2 : li, lu = in_rows ? lane & 3 : g;    // row, eight values that this lane requests
+  char* const stage = red + wave * nqt * 1024;
+  int m = row0 + lr;
   if (m >= hi) m = hi - 1;
   const int64_t tok = a.perm ? a.perm[m] : m;
-  const bf16_t* xrow = a.X + tok * a.ldx + 8 * g;
-  const int steps = (int)((a.C + 31) >> 5), per = (steps + SS_WAVES - 1) / SS_WAVES;
+  const bf16_t* xrow = a.X + tok * a.ldx + 8 * lu;
   const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
   f32x4 acc[NQT];
 #pragma unroll
@@ -447,16 +453,21 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
 #pragma unroll
     for (int i = 0; i < U; ++i) {
       const int64_t k = (int64_t)(s + i) * 32;
-      const bool in = s + i < s1 && k + 8 * g < a.C;
+      const bool in = s + i < s1 && k + 8 * lu < a.C;
 #pragma unroll
       for (int q = 0; q <= NQT; ++q) f[i][q].u = make_uint4(0, 0, 0, 0);
 #pragma unroll
       for (int q = 0; q < NQT; ++q)
-        if (in && q * 16 + li < r) f[i][q].u = *(const uint4*)(L + (int64_t)(q * 16 + li) * a.C + k + 8 * g);
+        if (in && q * 16 + lr < r) f[i][q].u = *(const uint4*)(L + (int64_t)(q * 16 + lr) * a.C + k + 8 * lu);
       if (in) f[i][NQT].u = *(const uint4*)(xrow + k);
     }
   };
   auto multiply = [&](Frag (&f)[U][NQT + 1]) {
+    if (in_rows)
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int q = 0; q <= NQT; ++q) if (q < nqt || q == NQT) f[i][q].u = rows_to_operand(stage, f[i][q].u, lane);
 #pragma unroll
     for (int i = 0; i < U; ++i)
 #pragma unroll

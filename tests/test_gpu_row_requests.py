@@ -1,0 +1,34 @@
+"""Operands that are requested a row at a time and put in order through LDS, on both sides of the lines from which that is done:
+contractions that end inside a 32-deep step, and with waves that have fewer steps than others or none."""
+import numpy as np
+import pytest
+
+from harness import workloads as wl
+from paper_2605_08527_amd import api
+from helpers import HipLayer, assert_close, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+# x of few rows: more than eight of them, more than eight 32-deep steps a wave (2048)
+@pytest.mark.parametrize("T", [8, 9, 16, 17, 32])
+@pytest.mark.parametrize("K", [2048, 2056, 2088, 4104])
+def test_few_rows(oracle, T, K):
+    _check(oracle, T, K, 72, [16, 8, 24])
+
+
+# u of batches with few rows for a compute unit, in a launch of its own
+@pytest.mark.parametrize("K,ranks", [(2048, [16]), (2056, [8, 24, 32]), (2088, [64, 40]), (2056, [128, 100]), (4104, [16, 9])])
+def test_shrink_of_few_rows_a_unit(oracle, K, ranks):
+    _check(oracle, 1030, K, 4104, ranks, packed=False)
+
+
+def _check(oracle, T, K, N, ranks, packed=True):
+    ids = np.random.default_rng(T * K).integers(-1, len(ranks), size=T).astype(np.int32)
+    w = wl.make_layer(T + K, T, K, N, ranks, [0.5 + t for t in range(len(ranks))], ids, dtype="bf16", layout=wl.TORCH)
+    L = HipLayer(w, table=True, packed=packed)
+    api.marlaas_profile_enable(L.ctx, True)
+    y, u = L.fwd(save_u=True)
+    assert api.marlaas_profile_read(L.ctx, api.MARLAAS_KERNEL_SHRINK)[1] == (0 if packed else 1)
+    ref = oracle.fwd(w["x"], w["W"], w["A"], w["B"], w["ranks"], w["scales"], ids, layout=wl.TORCH)
+    assert_close(to_host(y), ref, "y %d x %d" % (T, K))
