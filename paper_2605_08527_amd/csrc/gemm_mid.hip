@@ -185,11 +185,13 @@ __global__ __launch_bounds__(MD_THREADS, 4) void gemm_mid_kernel(GemmArgs a) {
     const int32_t tok0 = a.perm ? a.perm[i0] : (int32_t)i0, tok1 = a.perm ? a.perm[i1] : (int32_t)i1;
     int4 line;
     Turn turn;
-    shrink_job<3, 2>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, [&] { line = *(const int4*)turn_line(a.turns); },
-                     [&] {
-                       turn = turn_of(line.x, line.y, line.z, line.w);
-                       return u_area(turn.area) + (pp * S + job.split) * u_n + (int64_t)tile * BM * a.r_stride;
-                     }, a.r_stride, wave, lane);
+    auto ask = [&] { line = *(const int4*)turn_line(a.turns); };
+    auto at = [&] {
+      turn = turn_of(line.x, line.y, line.z, line.w);
+      return u_area(turn.area) + (pp * S + job.split) * u_n + (int64_t)tile * BM * a.r_stride;
+    };
+    if (shrink_rows(a.Kc, S)) shrink_job<3, 2, true>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, ask, at, a.r_stride, wave, lane);
+    else shrink_job<3, 2, false>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, ask, at, a.r_stride, wave, lane);
     if (tid == 0) turn_over(a.turns, turn, u_all);
     return;
   }

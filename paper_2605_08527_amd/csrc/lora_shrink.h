@@ -13,13 +13,17 @@ struct ShrinkJob {
   int rank, q0, row0, row1, split;
 };
 
+__host__ __device__ inline bool shrink_rows(int64_t Kc, int S) { return (((Kc + 31) >> 5) + S - 1) / S > 4 * 8; }
 // Eight waves share the part's 32-deep steps, their sums meet in `red` (8 x NB x 64) and are added in wave
 // order: the bits do not depend on who computes the job.  u(): [row of the tile][r_stride] of this split; ask() requests what
 // u() needs, behind the first operands, which would have to wait for it.  Every wave has called u() when the waves meet, so that
 // behind the job whoever likes may change what u() reads.  No value is stored as zero bits.  tok0, tok1: tokens of row
 // lane % 16 of the first and of the second block.
+// ROWS (where a wave has more than four steps of two blocks, shrink_rows): operands are requested a row at a time and put in order through LDS
+// (rows_to_operand): 157 rows, 14336 x 4096, 32 adapters of rank 16, 42.4 -> 40.2 us, q/k/v of 157 rows 26.5 -> 25.1, 512 rows, 5120 x
+// 5120, 64 adapters, in tiles of 96 rows 55.8 -> 53.4; with four steps the trip costs what it saves (256 rows, 4096 x 4096, 21.4 and 21.5).
 // UP: steps requested together (twice); NB: blocks a job can have.  All eight waves call it.
-template <int UP, int NB, typename Ask, typename At>
+template <int UP, int NB, bool ROWS, typename Ask, typename At>
 __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, int64_t lda, int64_t Kc, int32_t tok0, int32_t tok1, int S,
                                            f32x4* red, Ask ask, At u, int r_stride, int wave, int lane) {
   constexpr int WAVES = 8;
@@ -30,7 +34,6 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
   const int per = (part + WAVES - 1) / WAVES;
   const int s0 = k0 + wave * per, s1 = s0 + per < k1 ? s0 + per : k1;
   const int blk = j.row0 >> 4;
-  const bool row_in = j.q0 + li < j.rank;
   const bool two = (j.row1 - 1) >> 4 > blk;
   // (rows of others read the job's first row in the block, in a tile of many adapters most of it, and are not stored;
   // one block of few rows has its start delayed by the exchange: 11.6 -> 11.7 us for 6 rows)
@@ -40,7 +43,12 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
     if (r0 < j.row0 || r0 >= j.row1) tok0 = first0;
     if (r1 >= j.row1) tok1 = first1;
   }
-  const bf16_t* lrow = j.L + (int64_t)(row_in ? j.q0 + li : 0) * Kc;
+  // (ROWS: lane / 4 is the row that a lane requests and lane % 4 its eight values, put in order through this wave's part of red)
+  const int lr = ROWS ? lane >> 2 : li, lk = ROWS ? lane & 3 : lg;
+  if (ROWS) { tok0 = __shfl(tok0, lr); tok1 = __shfl(tok1, lr); }
+  const bool row_in = j.q0 + lr < j.rank;
+  char* const stage = (char*)(red + wave * NB * 64);
+  const bf16_t* lrow = j.L + (int64_t)(row_in ? j.q0 + lr : 0) * Kc;
   const bf16_t* xrow[2] = {X + (int64_t)tok0 * lda, X + (int64_t)tok1 * lda};
   f32x4 acc[NB];
 #pragma unroll
@@ -49,7 +57,7 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
   auto request = [&](Frag (&f)[UP][NB + 1], int s) {
 #pragma unroll
     for (int i = 0; i < UP; ++i) {
-      const int64_t k = (int64_t)(s + i) * 32 + 8 * lg;
+      const int64_t k = (int64_t)(s + i) * 32 + 8 * lk;
 #pragma unroll
       for (int b = 0; b <= NB; ++b) f[i][b].u = make_uint4(0, 0, 0, 0);
       if (s + i < s1 && k < Kc) {
@@ -61,9 +69,14 @@ __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, 
   };
   auto multiply = [&](Frag (&f)[UP][NB + 1]) {
 #pragma unroll
-    for (int i = 0; i < UP; ++i)
+    for (int i = 0; i < UP; ++i) {
+      if (ROWS) {
+#pragma unroll
+        for (int b = 0; b <= NB; ++b) if (b != 1 || NB == 1 || two) f[i][b].u = rows_to_operand(stage, f[i][b].u, lane);
+      }
 #pragma unroll
       for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i][NB].v, f[i][b].v, acc[b], 0, 0, 0);
+    }
   };
   request(fa, s0);
   ask();

@@ -23,6 +23,14 @@ def test_shrink_of_few_rows_a_unit(oracle, K, ranks):
     _check(oracle, 1030, K, 4104, ranks, packed=False)
 
 
+# u of some more rows, by producers beside the consumers: more than four steps a wave (from a contraction of 1032 on where it is not cut), two
+# blocks of rows and one, rows of others in them, ranks that leave rows of the factor out
+@pytest.mark.parametrize("T", [33, 100, 257])
+@pytest.mark.parametrize("K,ranks", [(1024, [16]), (1032, [16]), (1032, [8, 24, 9] * 8), (2072, [64, 40, 16] * 4), (4104, [16] * 6), (4136, [128, 100])])
+def test_producers_of_some_rows(oracle, T, K, ranks):
+    _check(oracle, T, K, 1096, ranks)
+
+
 def _check(oracle, T, K, N, ranks, packed=True):
     ids = np.random.default_rng(T * K).integers(-1, len(ranks), size=T).astype(np.int32)
     w = wl.make_layer(T + K, T, K, N, ranks, [0.5 + t for t in range(len(ranks))], ids, dtype="bf16", layout=wl.TORCH)
