@@ -142,7 +142,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 1; i < R; ++i) if (i == rb0) tok0 = tokr[i];
     const ShrinkJob job = {L, scale, r, q0, row0, row1, b % S};
-    shrink_job<R == 1 ? 4 : 3, R, false>(job, a.Aop, a.lda, a.Kc, tok0, tokr[R - 1], S, red, [] {}, [&] { return u_p + b % S * u_n; }, a.r_stride, wave, lane);
+    shrink_job<R == 1 ? 4 : 3, R>(job, a.Aop, a.lda, a.Kc, tok0, tokr[R - 1], S, red, [] {}, [&] { return u_p + b % S * u_n; }, a.r_stride, wave, lane);
     wait_vm<0>();                                                // (u is out)
     __syncthreads();
     if (wave == 0) leave();

@@ -23,7 +23,7 @@ __host__ __device__ inline bool shrink_rows(int64_t Kc, int S) { return (((Kc + 
 // (rows_to_operand): 157 rows, 14336 x 4096, 32 adapters of rank 16, 42.4 -> 40.2 us, q/k/v of 157 rows 26.5 -> 25.1, 512 rows, 5120 x
 // 5120, 64 adapters, in tiles of 96 rows 55.8 -> 53.4; with four steps the trip costs what it saves (256 rows, 4096 x 4096, 21.4 and 21.5).
 // UP: steps requested together (twice); NB: blocks a job can have.  All eight waves call it.
-template <int UP, int NB, bool ROWS, typename Ask, typename At>
+template <int UP, int NB, bool ROWS = false, typename Ask, typename At>
 __device__ __forceinline__ void shrink_job(const ShrinkJob& j, const bf16_t* X, int64_t lda, int64_t Kc, int32_t tok0, int32_t tok1, int S,
                                            f32x4* red, Ask ask, At u, int r_stride, int wave, int lane) {
   constexpr int WAVES = 8;
