@@ -50,7 +50,7 @@ struct GemmArgs {
   const int32_t* grp_ids;
   ExtRows ext;                  // the row tiles' shares of the extended columns
   int n_prod, n_split;          // few-row kernel: workgroups that compute u (a multiple of n_proj n_split), the splits of their contraction,
-  int prod0, proj_jobs, rot;    // (the kernel for more rows: the first of those, shrink jobs of a projection; k-tiles between neighbouring column tiles' starts)
+  int prod0, n_jobs, proj_jobs, rot;    // (the kernel for more rows: the first of those, their jobs, those of a projection; k-tiles between neighbouring column tiles' starts)
   const bf16_t* zero_line;      // 1024 readable zero bytes
   float* thin_u;                // and where it travels: [MAX_PROJ][THIN_SPLITS][THIN_ROWS][128], zero between launches
   int32_t* turns; float* mid_u; // the kernel for more rows: whose turn it is (agent_memory.h), and the two areas of [projection][split][T][r_stride]
@@ -156,5 +156,6 @@ hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream);
 // Up to MID_ROWS rows likewise (gemm_mid.hip); turns, mid_u, partials: the context's areas.
 hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream_t stream);
+hipError_t launch_gemm_tall(const GemmArgs& a, const MidPlan& p, int cu_count, hipStream_t stream);    // (its taller tiles: gemm_tall.hip)
 
 }  // namespace marlaas

@@ -1013,12 +1013,13 @@ hipError_t launch_gemm_bf16_thin(const bf16_t* Aop, int64_t lda, int form, int64
 // ---- some more rows
 MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEntry* proj_host, int n_proj, const MidLora& lora, int ext, size_t room,
                       const DecodeSync* sync) {
-  if (T <= 0 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || (lora.n > 0 && (!sync->counters || form != FORM_NT || !sync->grp_ids || lora.r_stride > 128)) ||
+  if (T <= 16 || T > MID_ROWS || lda > (1 << 20) || n_proj < 1 || n_proj > MAX_PROJ || !sync || (lora.n > 0 && (!sync->counters || form != FORM_NT || !sync->grp_ids || lora.r_stride > 128)) ||
       (sync->mode != DECODE_FINISH_AUTO && sync->mode != DECODE_FINISH_IN_KERNEL))
     return MidPlan();
   int64_t cols = 0;
   for (int q = 0; q < n_proj; ++q) cols += proj_host[q].Nout;
-  const MidPlan p = mid_plan(T, Kc, proj_host, n_proj, lora, sync->counters ? 4 : 1);     // (splits exchange sums)
+  const MidPlan small = mid_plan(T, Kc, proj_host, n_proj, lora, sync->counters ? 4 : 1);     // (splits exchange sums)
+  const MidPlan p = mid_taller(small, T, Kc, proj_host, n_proj, lora);
   for (int q = 0; q < n_proj; ++q)
     if ((proj_host[q].Nout + 32 * p.wn - 1) / (32 * p.wn) * p.ksplit > MID_CONSUMERS) return MidPlan();
   auto wide_us = [&]() {                                         // (it takes the projections one after the other)

@@ -8,6 +8,10 @@
 namespace marlaas {
 
 static constexpr int MID_WAVES = 8;
+// Tiles of 128 rows and more take all of a compute unit's registers.
+__host__ __device__ constexpr bool mid_alone(int rb) { return rb > 6; }
+// Whether producers take several jobs each: `free` units that the consumers leave.
+inline bool mid_jobs_in_turn(int64_t free, int64_t jobs) { return free >= 32 && jobs > free && jobs <= 5 * free; }
 
 // Pieces of a producer's contraction.  A compute unit that has a producer besides its consumer is behind the
 // others by what the producer reads (256 rows, 4096 x 4096: first tile after 9 us instead of 4 with two pieces,
@@ -22,11 +26,11 @@ static constexpr int MID_WAVES = 8;
 // columns, contraction 8192, 1000 rows of 4 adapters of rank 128: 364 us, whole 402, 600 rows of 8 adapters 288 and 282; of
 // 512 columns, contraction 7168, 640 rows of 32 adapters: 340 and 1035).
 //   u_room: floats of u that there is room for.
-inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t consumers, int64_t jobs, int cu_count) {
+inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t consumers, int64_t jobs, int cu_count, bool alone = false) {
   const int64_t steps = ((Kc + 31) / 32 + MID_WAVES - 1) / MID_WAVES;      // 32-deep steps of a wave
   if (steps <= 8 || (steps <= 16 && consumers + jobs <= cu_count)) return 1;
   int s = MID_SPLITS;
-  while (s > 1 && (consumers + jobs * s > (s == 2 ? 9 : 8) * cu_count / 4 || u_floats * s > u_room)) s /= 2;
+  while (s > 1 && (consumers + jobs * s > (alone ? 4 : s == 2 ? 9 : 8) * cu_count / 4 || u_floats * s > u_room)) s /= 2;
   return s == 1 && steps > 24 && 2 * u_floats <= u_room ? 2 : s;
 }
 
@@ -42,51 +46,113 @@ inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t co
 //   Few units with two workgroups count for little (64 units, over which a second workgroup comes to count in
 // full): with weights from memory 512 rows, 5120 x 5120, 32 adapters of rank 16, take 54 us in 280 workgroups of 80
 // rows and 67 in 320 of 64; from the cache 53 and 52.
-inline MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora, int max_split) {
-  static const double tile_us[2][2] = {{0.306, 0.252}, {0.334, 0.282}};   // [rb - 4][wn == 4]
-  MidPlan best;
-  int64_t cols = 0;
-  for (int q = 0; q < n_proj; ++q) cols += proj[q].Nout;
-  auto up_to_1 = [](double v) { return v < 0.0 ? 0.0 : v > 1.0 ? 1.0 : v; };
-  for (int wn = 2; wn <= 4; wn += 2) {
-    const int64_t kt = 32 * (MID_WAVES / wn), ktiles = (Kc + kt - 1) / kt;
-    int64_t tiles_n = 0;
-    for (int q = 0; q < n_proj; ++q) tiles_n += (proj[q].Nout + 32 * wn - 1) / (32 * wn);
-    for (int rb = 4; rb <= 5; ++rb) {
-      const int64_t tiles_m = (T + 16 * rb - 1) / (16 * rb);
-      for (int s = 1; s <= max_split; s *= 2) {
-        const int64_t wgs = tiles_m * tiles_n * s;
-        if (s > 1 && (wgs > MID_SPLIT_WGS || ktiles < 4 * s)) continue;
-        const double t1 = tile_us[rb - 4][wn == 4] * (double)((ktiles + s - 1) / s), t2 = 1.827 * t1;
-        double fill;
-        if (wgs <= 256) {
-          fill = t1 * (wgs > 128 ? 1.0 + 0.066 * (double)(wgs - 128) / 128.0 : 1.0);
-        } else {
-          const int64_t left = wgs % 512;
-          fill = (double)(wgs / 512) * (t2 + 2.172);
-          if (left > 0) fill += 2.172 + 1.066 * t1 + (t2 - 1.066 * t1) * up_to_1((double)(left - 256) / 64.0);
-        }
-        const double fabric = (2.0 * cols * Kc + 16.0 * T * Kc / s) / 11.6e6;
-        double us = 7.687 + cbrt(fill * fill * fill + fabric * fabric * fabric);
-        if (lora.n > 0) {
-          // (the most u there can be, of five projections and more, counts as whole: the estimate of such calls is low, and with
-          // two pieces would take six of 1024 columns, contraction 14336, 1000 rows of rank 128, here, 496 us, not one by one, 298)
-          const int pieces = mid_u_splits(Kc, T * lora.r_stride * n_proj, MID_U_FLOATS / 2, wgs, (int64_t)n_proj * mid_max_jobs(T, rb, lora), 256);
-          const int64_t with_rows = (int64_t)(0.6 * T) + 1 < lora.n ? (int64_t)(0.6 * T) + 1 : lora.n;      // (adapters, about)
-          const int64_t prods = n_proj * pieces * (with_rows * (lora.tiles / lora.n > 1 ? lora.tiles / lora.n : 1) + T / (16 * rb) * ((rb + 1) / 2));
-          // (the expand of more ranks is not proportionally more: 184 rows, 1872 x 8368, rank 32, 23.1 -> 22.1 us
-          // in tiles of 128 columns; a split makes every rank's u travel to more readers: 277 rows, 2144 x 1048, rank 64,
-          // 20.0 -> 18.4 unsplit)
-          const double rank = std::min(16.0, (double)lora.ranks / lora.n);
-          const double prod_us = 10.735 * Kc / 4096.0 / pieces + 0.498;
-          us += 0.562 + 2.009 * ((rb * wn + 7) / 8) * rank / 16.0 + (s > 1 ? 0.02 * lora.ranks / lora.n : 0.0);
-          us += prod_us * (wgs <= 256 ? 0.574 * up_to_1((double)(wgs + prods - 256) / 17.45) : 0.289 * up_to_1((double)prods / 256.0));
-          us += prod_us * 0.918 * up_to_1((double)((wgs < 512 ? wgs : 512) + prods - 512) / 17.45);
-        }
-        if (s > 1) us += (lora.n > 0 ? 0.0 : 1.5) + (s > 2 ? 2.442 : 2.257) * (0.5 + rb * wn / 32.0) + (wgs > 192 ? 0.186 * (double)(wgs - 192) / 64.0 : 0.0);
-        if (best.rb == 0 || us < best.us) { best.us = us; best.rb = rb; best.wn = wn; best.ksplit = s; best.tiles_m = (int)tiles_m; }
+static constexpr double mid_tile_us[2][2] = {{0.306, 0.252}, {0.334, 0.282}};   // [rb - 4][wn == 4]
+
+// What the comparisons differ in: the rank up to which the expand takes longer, units with two workgroups that count in full, the
+// fabric's rate and the share of a weight that a further row tile reads again, and the producers beside more consumers than units.
+struct MidRates { double rank_cap, ramp, rate, again, beside; };
+static constexpr MidRates MID_SMALL = {16.0, 64.0, 11.6e6, 0.0, 256.0}, MID_TALL = {48.0, 19.3, 11.9e6, 0.074, 91.0};
+
+struct MidModel {
+  int64_t T, Kc, cols;
+  const MidRates c;
+  const ProjEntry* proj; int n_proj;
+  const MidLora& lora;
+  MidModel(int64_t T_, int64_t Kc_, const ProjEntry* proj_, int n_proj_, const MidLora& lora_, const MidRates& rates)
+      : T(T_), Kc(Kc_), cols(0), c(rates), proj(proj_), n_proj(n_proj_), lora(lora_) {
+    for (int q = 0; q < n_proj; ++q) cols += proj[q].Nout;
+  }
+  static double up_to_1(double v) { return v < 0.0 ? 0.0 : v > 1.0 ? 1.0 : v; }
+  int64_t ktiles(int wn) const { const int64_t kt = 32 * (MID_WAVES / wn); return (Kc + kt - 1) / kt; }
+  int64_t tiles_m(int rb) const { return (T + 16 * rb - 1) / (16 * rb); }
+  int64_t tiles_n(int wn) const {
+    int64_t n = 0;
+    for (int q = 0; q < n_proj; ++q) n += (proj[q].Nout + 32 * wn - 1) / (32 * wn);
+    return n;
+  }
+  // column tiles (times splits) if all XCDs, which have whole ones, had as many as the fullest
+  int64_t over_xcds(int wn, int s) const { return (tiles_n(wn) + 8 / s - 1) / (8 / s) * 8; }
+  // the most shrink jobs, and the pieces that each is in
+  int64_t jobs(int rb) const { return lora.n > 0 ? (int64_t)n_proj * mid_max_jobs(T, rb, lora) : 0; }
+  int pieces(int rb, int64_t wgs, int64_t u_room) const { return mid_u_splits(Kc, T * lora.r_stride * n_proj, u_room, wgs, jobs(rb), 256, mid_alone(rb)); }
+  // t1: a k-tile's time; wgs: consumers
+  double us(int rb, int wn, int s, double t1, int64_t wgs) const {
+    const bool alone = mid_alone(rb);
+    t1 *= (double)((ktiles(wn) + s - 1) / s);
+    const double t2 = 1.827 * t1;
+    double fill;
+    if (wgs <= 256) {
+      fill = t1 * (wgs > 128 ? 1.0 + 0.066 * (double)(wgs - 128) / 128.0 : 1.0);
+    } else {
+      const int64_t left = wgs % 512;
+      fill = (double)(wgs / 512) * (t2 + 2.172);
+      if (left > 0) fill += 2.172 + 1.066 * t1 + (t2 - 1.066 * t1) * up_to_1((double)(left - 256) / c.ramp);
+    }
+    const double fabric = (2.0 * cols * Kc * (1.0 + c.again * (double)(tiles_m(rb) - 1)) + 16.0 * T * Kc / s) / c.rate;
+    const double loop = cbrt(fill * fill * fill + fabric * fabric * fabric);
+    double us = 7.687 + loop;
+    if (lora.n > 0) {
+      // (the most u there can be, of five projections and more, counts as whole: the estimate of such calls is low, and with
+      // two pieces would take six of 1024 columns, contraction 14336, 1000 rows of rank 128, here, 496 us, not one by one, 298)
+      const int p = pieces(rb, wgs, MID_U_FLOATS / 2);
+      const int64_t with_rows = (int64_t)(0.6 * T) + 1 < lora.n ? (int64_t)(0.6 * T) + 1 : lora.n;      // (adapters, about)
+      const int64_t prods = n_proj * p * (with_rows * (lora.tiles / lora.n > 1 ? lora.tiles / lora.n : 1) + T / (16 * rb) * ((rb + 1) / 2));
+      // (the expand of more ranks is not proportionally more: 184 rows, 1872 x 8368, rank 32, 23.1 -> 22.1 us
+      // in tiles of 128 columns; a split makes every rank's u travel to more readers: 277 rows, 2144 x 1048, rank 64,
+      // 20.0 -> 18.4 unsplit)
+      const double rank = std::min(c.rank_cap, (double)lora.ranks / lora.n);
+      const double prod_us = 10.735 * Kc / 4096.0 / p + 0.498;
+      us += 0.562 + 2.009 * ((rb * wn + 7) / 8) * rank / 16.0 + (s > 1 ? 0.02 * lora.ranks / lora.n : 0.0);
+      if (alone) {
+        if (mid_jobs_in_turn(256 - wgs, prods)) us += std::max(0.0, prod_us * (double)prods / (double)(256 - wgs) - 1.4 * loop);
+        else us += prod_us * 1.12 * up_to_1((double)(wgs + prods - 256) / 17.45);
+      } else {
+        us += prod_us * (wgs <= 256 ? 0.574 * up_to_1((double)(wgs + prods - 256) / 17.45) : 0.289 * up_to_1((double)prods / 256.0) * (256.0 / c.beside));
+        us += prod_us * 0.918 * up_to_1((double)((wgs < 512 ? wgs : 512) + prods - 512) / 17.45);
       }
     }
+    if (s > 1) us += (lora.n > 0 ? 0.0 : 1.5) + (s > 2 ? 2.442 : 2.257) * (0.5 + rb * wn / 32.0) + (wgs > 192 ? 0.186 * (double)(wgs - 192) / 64.0 : 0.0);
+    return us;
+  }
+};
+
+// Of the smaller tiles.  Without adapters the workgroups count as the fullest XCD has them (1.006 times the best on the average,
+// 1.017 as they are); with adapters that is no better.
+inline MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora, int max_split) {
+  const MidModel m(T, Kc, proj, n_proj, lora, MID_SMALL);
+  MidPlan best;
+  for (int wn = 2; wn <= 4; wn += 2)
+    for (int rb = 4; rb <= 5; ++rb)
+      for (int s = 1; s <= max_split; s *= 2) {
+        const int64_t wgs = m.tiles_m(rb) * m.tiles_n(wn) * s;
+        if (s > 1 && (wgs > MID_SPLIT_WGS || m.ktiles(wn) < 4 * s)) continue;
+        const int64_t units = lora.n > 0 ? wgs : m.tiles_m(rb) * m.over_xcds(wn, s);
+        const double us = m.us(rb, wn, s, mid_tile_us[rb - 4][wn == 4], units);
+        if (best.rb == 0 || us < best.us) { best.us = us; best.rb = rb; best.wn = wn; best.ksplit = s; best.tiles_m = (int)m.tiles_m(rb); }
+      }
+  return best;
+}
+
+// The same call in taller tiles of 128 columns, unsplit, where the estimate says that they are faster.
+//   Both sides are estimated with other constants than the smaller tiles have among themselves, fitted to 267 sets of 40 to 900
+// rows, contractions of 1024 to 14336, one to three projections, up to 64 adapters of ranks 8 to 64, timed with the weight
+// from the memory-side cache and from memory: the choice takes 0.970 and 0.959 of the time of the smaller tile, 94 sets change,
+// 70 of them get faster by more than 3 %, the worst from 21.8 to 23.6 us (397 rows, 1040 x 8984; 3 % in hand keep most such away).
+//   96 rows only with all workgroups on the chip at once (669 rows, 6168 x 2248, 32 adapters of rank 64, would be 1.34 times as
+// long), 128 and 160 rows where they fill one round and most of the units (512 rows, 5120 x 5120, 160 workgroups of 128 rows: 56.7
+// us, 240 of 96 rows 52.4).
+inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora) {
+  static const double tile_us[3] = {0.355, 0.351, 0.407};
+  const MidModel m(T, Kc, proj, n_proj, lora, MID_TALL);
+  MidPlan best = p;
+  double least = 0.0;                                            // (0: not asked for yet)
+  for (int i = 0; i < 3; ++i) {
+    const int rb = 6 + 2 * i;
+    const int64_t wgs = m.tiles_m(rb) * m.over_xcds(4, 1), jobs = m.jobs(rb);
+    if (wgs < 176 || (mid_alone(rb) ? wgs > 256 : wgs + jobs * m.pieces(rb, wgs, MID_U_FLOATS) > 512)) continue;
+    if (least == 0.0) least = 0.97 * m.us(p.rb, p.wn, p.ksplit, mid_tile_us[p.rb - 4][p.wn == 4], m.tiles_m(p.rb) * m.over_xcds(p.wn, p.ksplit));
+    const double us = m.us(rb, 4, 1, tile_us[i], wgs);
+    if (us < least) { least = us; best.us = std::min(p.us, us); best.rb = rb; best.wn = 4; best.ksplit = 1; best.tiles_m = (int)m.tiles_m(rb); }
   }
   return best;
 }
