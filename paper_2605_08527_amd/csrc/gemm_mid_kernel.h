@@ -22,11 +22,11 @@
 // row, on its way into LDS, not once a wave (100 rows of 32 adapters of rank 64, 4096 x 4096, 28.9 -> 28.2; q/k/v and 256 rows of
 // rank 16 no more than runs differ); octet steps requested together (KB below).
 //
-// Tall tiles (gemm_tall.hip): 96 x 128 in the registers that two workgroups a unit have, 128 and 160 x 128 with a unit each.  A
-// unit's time goes by what comes into it, 32 or 36 KB for 64 values of a contraction where two workgroups of 80 rows take 52, and by how
+// Tall tiles (gemm_tall.hip): 96 x 128 in the registers that two workgroups a unit have, 128 160 and 256 x 128 with a unit each.  A
+// unit's time goes by what comes into it, 32, 36 or 48 KB for 64 values of a contraction where two workgroups of 80 rows take 52, and by how
 // even the tiles fall on the 256 units.  Products by inline assembly: left to the compiler, sums moved between registers and 96
 // rows spilled 12 of them, requests under way among those.  512 rows of 64 adapters of ranks 8 to 64, 5120 x 5120, 61.1 -> 52.4 us in 240 tiles of 96
-// rows (280 of 80 before); 157 rows, 4096 x 28672, 32 adapters of rank 16, 72 -> 62, weights from memory 80 -> 68.6.  A ring of six k-tiles in
+// rows (280 of 80 before); 157 rows, 4096 x 28672, 32 adapters of rank 16, 72 -> 62, weights from memory 80 -> 68.6; 256 rows 105 -> 78, from memory 112 -> 81.  A ring of six k-tiles in
 // place of four is no faster (256 rows, 4096 x 14336, 35.0 and 36.7).
 //
 // Whatever crosses workgroups carries its own flag: it travels through areas of the context that are all
@@ -77,7 +77,7 @@ struct MidShape {
   static constexpr int KG = MD_WAVES / WN, K = 32 * KG;           // contraction groups; contraction values of a k-tile
   static constexpr bool SPLITS = RB <= 5;               // (the contraction may be split over workgroups; the others are "tall")
   static constexpr int PER_UNIT = RB <= 6 ? 2 : 1;      // workgroups that a compute unit has room for
-  static constexpr int NS = RB == 4 || (RB == 5 && WN == 4) || RB > 6 ? 4 : 3; // ring slots = k-tiles on the way (registers, LDS)
+  static constexpr int NS = RB == 4 || (RB == 5 && WN == 4) || (RB > 6 && RB < 14) ? 4 : 3; // ring slots = k-tiles on the way (registers, LDS)
   static constexpr int SLOT = RB * 16 * K * 2;
   static constexpr int RED = RB * WN * 2 * (KG - 1) * 1024;       // exchange of the contraction groups
 };
@@ -420,6 +420,7 @@ __global__ __launch_bounds__(MD_THREADS, (2 * MidShape<RB, WN>::PER_UNIT)) void 
     __builtin_amdgcn_sched_barrier(0);                                                                    \
     MD_STEP(0, s_); MD_STEP(1, s_); MD_STEP(2, s_); MD_STEP(3, s_); MD_STEP(4, s_);                             \
     MD_STEP(5, s_); MD_STEP(6, s_); MD_STEP(7, s_); MD_STEP(8, s_); MD_STEP(9, s_);                       \
+    MD_STEP(10, s_); MD_STEP(11, s_); MD_STEP(12, s_); MD_STEP(13, s_); MD_STEP(14, s_); MD_STEP(15, s_); \
   } while (0)
   /* after it everyone's part of tile i + 1 is there, and nobody reads the slot of tile i any more */
 #define MD_SYNC(s_)                                                                                       \

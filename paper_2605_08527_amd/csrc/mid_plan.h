@@ -139,15 +139,17 @@ inline MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj
 // from the memory-side cache and from memory: the choice takes 0.970 and 0.959 of the time of the smaller tile, 94 sets change,
 // 70 of them get faster by more than 3 %, the worst from 21.8 to 23.6 us (397 rows, 1040 x 8984; 3 % in hand keep most such away).
 //   96 rows only with all workgroups on the chip at once (669 rows, 6168 x 2248, 32 adapters of rank 64, would be 1.34 times as
-// long), 128 and 160 rows where they fill one round and most of the units (512 rows, 5120 x 5120, 160 workgroups of 128 rows: 56.7
-// us, 240 of 96 rows 52.4).
+// long), 128, 160 and 256 rows where they fill one round and most of the units (512 rows, 5120 x 5120, 160 workgroups of 128 rows: 56.7
+// us, 240 of 96 rows 52.4).  256 rows, of which the sets above know nothing: 180 to 512 rows, 4096 x 14336 to 28672, 32 adapters of rank
+// 16, 0.71 to 0.9 of the time of the smaller tile, from memory 0.73 to 0.84.
 inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora) {
-  static const double tile_us[3] = {0.355, 0.351, 0.407};
+  static const int rbs[4] = {6, 8, 10, 16};
+  static const double tile_us[4] = {0.355, 0.351, 0.407, 0.78};
   const MidModel m(T, Kc, proj, n_proj, lora, MID_TALL);
   MidPlan best = p;
   double least = 0.0;                                            // (0: not asked for yet)
-  for (int i = 0; i < 3; ++i) {
-    const int rb = 6 + 2 * i;
+  for (int i = 0; i < 4; ++i) {
+    const int rb = rbs[i];
     const int64_t wgs = m.tiles_m(rb) * m.over_xcds(4, 1), jobs = m.jobs(rb);
     if (wgs < 176 || (mid_alone(rb) ? wgs > 256 : wgs + jobs * m.pieces(rb, wgs, MID_U_FLOATS) > 512)) continue;
     if (least == 0.0) least = 0.97 * m.us(p.rb, p.wn, p.ksplit, mid_tile_us[p.rb - 4][p.wn == 4], m.tiles_m(p.rb) * m.over_xcds(p.wn, p.ksplit));

@@ -1,4 +1,4 @@
-"""Some rows in tall tiles (96, 128 and 160 rows): edges of tiles, contractions that end inside a k-tile or a ring, more adapters than lanes,
+"""Some rows in tall tiles (96, 128, 160 and 256 rows): edges of tiles, contractions that end inside a k-tile or a ring, more adapters than lanes,
 ranks off the octets, producers with several jobs each and with none, and waits given up at once."""
 import numpy as np
 import pytest
@@ -23,6 +23,7 @@ CASES = {
     "96, last tile of one row": (481, 3080, 5120, [8, 16, 32, 64] * 8), "96, whole tiles": (288, 2056, 10240, [16] * 4), "96, ranks off the octets": (257, 2120, 10232, [16, 12, 20]),
     "128": (128, 2056, 28664, [16] * 32), "128, last tile short": (200, 3000, 14336, [32] * 40),
     "160": (157, 2056, 28672, [16] * 70), "160, several jobs each": (320, 2056, 14336, [16, 8] * 20), "160, few with rows": (160, 2056, 28672, [16] * 32),
+    "256": (256, 2056, 28672, [16, 8] * 16), "256, last tile short": (490, 4104, 14344, [16] * 8),
 }
 
 
@@ -46,7 +47,7 @@ def test_tall_tiles(oracle, monkeypatch, name, spin):
     assert_close(to_host(y), to_host(z), name + ", all columns", tol_max=1e-4, tol_mean=1e-5)
 
 
-@pytest.mark.parametrize("T,K,N", [(512, 1160, 6144), (97, 4096, 28672), (320, 2304, 14336)])
+@pytest.mark.parametrize("T,K,N", [(512, 1160, 6144), (97, 4096, 28672), (320, 2304, 14336), (255, 2304, 28672)])
 def test_without_adapters(oracle, T, K, N):
     w = _layer(T, K, N, [8], seed=1)
     w["ids"] = np.full(T, -1, dtype=np.int32)

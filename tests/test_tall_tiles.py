@@ -37,18 +37,18 @@ def taller(tmp_path_factory):
 
 
 def test_where_they_are_taken(taller):
-    """Timed: 512 rows in 240 tiles, 128 and 157 rows of a wide output in 224, a square weight and a few rows in smaller ones.
-    Over the whole range a plan is one of the four that there are, unsplit, or the smaller one."""
+    """Timed: 512 rows in 240 tiles, 128, 157 and 256 rows of a wide output in 224, a square weight and a few rows in smaller ones.
+    Over the whole range a plan is one of those that there are, unsplit, or the smaller one."""
     small = ctypes.c_int()
     plan = lambda *a: taller(*a, ctypes.byref(small))
-    assert [plan(512, 5120, 5120, 64, 16), plan(128, 4096, 28672, 32, 16), plan(157, 4096, 28672, 32, 16)] == [641, 841, 1041]
+    assert [plan(512, 5120, 5120, 64, 16), plan(128, 4096, 28672, 32, 16), plan(157, 4096, 28672, 32, 16), plan(256, 4096, 28672, 32, 16)] == [641, 841, 1041, 1641]
     assert plan(256, 4096, 4096, 32, 16) == small.value and plan(40, 4096, 4096, 4, 16) == small.value
     for T in (1, 17, 65, 96, 97, 129, 160, 161, 300, 511, 640, 1000, 1024):
         for K in (8, 72, 1024, 4104, 14336):
             for N in (8, 136, 2056, 10240, 14336, 28672):
                 for n, rank in ((0, 0), (1, 1), (4, 128), (64, 16), (800, 8)):
                     p = plan(T, K, N, n, rank)
-                    assert p == small.value or p in (641, 841, 1041), (T, K, N, n, rank, p)
+                    assert p == small.value or p in (641, 841, 1041, 1641), (T, K, N, n, rank, p)
 
 
 def _loose_sums(blocks):
@@ -77,7 +77,7 @@ def test_code():
     out = subprocess.run([build.HIPCC] + build.FLAGS + ["-S", "--cuda-device-only", os.path.join(build.CSRC, "gemm_tall.hip"), "-o", "-"],
                          check=True, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL).stdout.decode()
     spills, counts = re.findall(r"\.vgpr_spill_count: +(\d+)", out), [int(n) for n in re.findall(r"\.vgpr_count: +(\d+)", out)]
-    assert spills == ["0"] * 3 and counts[0] <= 128 and max(counts) <= 256
+    assert spills == ["0"] * 4 and counts[0] <= 128 and max(counts) <= 256
     for name, blocks in _functions(out):
         assert not early_moves(blocks) and not overwritten_reads(blocks) and not _loose_sums(blocks), name
 
