@@ -8,7 +8,7 @@
 // times 16 NC output columns and its eight waves split the contraction, so a weight fragment is read
 // once, by the one wave that multiplies it, a wave requests 8 to 20 KB at a time, and the sums meet in
 // LDS.  x comes straight from L2 (for the row counts of this kernel no more bytes than the weight), a row at
-// a time.  Workgroups before the consumers ("producers") compute u: one per 16 ranks of an adapter
+// a time where that pays (thin_rows).  Workgroups before the consumers ("producers") compute u: one per 16 ranks of an adapter
 // that has rows, the same loop over the adapter's factor in place of the weight.  They are scheduled
 // first and take little longer than a consumer's loop.  Every round trip through the fabric costs 1 to
 // 1.5 us, so u carries its own flag: it travels through an area of the context that is all zero bits
@@ -29,8 +29,8 @@ static constexpr int TH_WAVES = 8, TH_THREADS = 64 * TH_WAVES;
 
 // Registers are held to what lets two workgroups share a compute unit: with one each, a launch of one
 // consumer per unit and a single producer took a second round of workgroups (1 row, 8 us against 15).
-// R: 16-row blocks (T <= 16 R), NC: 16-column blocks per workgroup
-template <int R, int NC>
+// R: 16-row blocks (T <= 16 R), NC: 16-column blocks per workgroup, ROWS: consumers request x a row at a time (rows_to_operand)
+template <int R, int NC, bool ROWS>
 __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
   constexpr int U = R + NC <= 2 ? 4 : R + NC <= 3 ? 3 : R + NC <= 5 ? 2 : 1;   // k-steps requested together (twice: two sets of registers)
   constexpr int TILES = R * NC;
@@ -88,10 +88,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
   const int steps = (int)((a.Kc + 31) >> 5), per = (steps + TH_WAVES - 1) / TH_WAVES;
   const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
 
-  // x is requested a row at a time (rows_to_operand) where a wave has more than eight steps of it and the rows are not mostly
-  // repeats of the last one: 32 rows 4096 x 4096 16.8 -> 14.7 us, 16 rows 12.6 -> 11.7; 6 rows, everything from memory, 11.4 and
-  // 11.9, 30 rows, 2000 x 2000, 8.7 and 9.3.  (Producers do not: their chain is what u waits for.)
-  const bool in_rows = !producer && per > 8 && a.T > 8;
+  const bool in_rows = ROWS && !producer;       // (producers do not: their chain is what u waits for)
   const int xr = in_rows ? lane >> 2 : li, xu = in_rows ? lane & 3 : lg;   // row, eight values that this lane requests
   // tokens of the rows this lane requests; adapter, and its entry, of row `lane`
   int32_t tokr[R];
@@ -172,7 +169,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
   } while (0)
 #define TH_MMA(set_)                                                                                      \
   do {                                                                                                    \
-    if (in_rows)                                                                                          \
+    if (ROWS)                                                                                             \
       _Pragma("unroll") for (int _u = 0; _u < U; ++_u)                                                    \
         _Pragma("unroll") for (int _i = 0; _i < R; ++_i) set_[_u][_i].u = rows_to_operand(stage, set_[_u][_i].u, lane); \
     _Pragma("unroll") for (int _u = 0; _u < U; ++_u)                                                      \
@@ -315,7 +312,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void gemm_thin_kernel(GemmArgs a) {
   }
 }
 
-template <int R, int NC>
+template <int R, int NC, bool ROWS>
 static hipError_t launch_thin(const GemmArgs& a, hipStream_t stream) {
   const size_t lds = (size_t)TH_WAVES * R * NC * 1024 + (size_t)16 * R * (a.r_stride + 4) * sizeof(float) +
                      (size_t)R * 2 * a.r_stride * 16 + (size_t)16 * R * 20 + R * 4 + 64;
@@ -325,11 +322,11 @@ static hipError_t launch_thin(const GemmArgs& a, hipStream_t stream) {
   if (e != hipSuccess) return e;
   const uint64_t bit = 1ull << (dev & 63);
   if (!(done_dev.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute((const void*)gemm_thin_kernel<R, NC>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    e = hipFuncSetAttribute((const void*)gemm_thin_kernel<R, NC, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     done_dev.fetch_or(bit, std::memory_order_release);
   }
-  hipLaunchKernelGGL((gemm_thin_kernel<R, NC>), dim3(a.n_prod + a.tiles_n), dim3(TH_THREADS), lds, stream, a);
+  hipLaunchKernelGGL((gemm_thin_kernel<R, NC, ROWS>), dim3(a.n_prod + a.tiles_n), dim3(TH_THREADS), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -350,9 +347,10 @@ hipError_t launch_gemm_thin(GemmArgs a, hipStream_t stream) {
     a.proj[p].tile0 = a.tiles_n;
     a.tiles_n += (int)((a.proj[p].Nout + 16 * nc - 1) / (16 * nc));
   }
-#define TH_PICK(R_) (nc == 1 ? launch_thin<R_, 1>(a, stream) : launch_thin<R_, 2>(a, stream))
-  if (nc == 4) return R == 1 ? launch_thin<1, 4>(a, stream) : launch_thin<2, 4>(a, stream);
-  return R == 1 ? TH_PICK(1) : TH_PICK(2);
+  const bool rows = thin_rows(a.T, a.Kc, a.lda);
+#define TH_PICK(R_, NC_) (rows ? launch_thin<R_, NC_, true>(a, stream) : launch_thin<R_, NC_, false>(a, stream))
+  if (R == 1) return nc == 4 ? TH_PICK(1, 4) : nc == 2 ? TH_PICK(1, 2) : TH_PICK(1, 1);
+  return nc == 4 ? TH_PICK(2, 4) : nc == 2 ? TH_PICK(2, 2) : TH_PICK(2, 1);
 #undef TH_PICK
 }
 

@@ -13,7 +13,18 @@ struct ShrinkJob {
   int rank, q0, row0, row1, split;
 };
 
+// Whether a job requests its operands a row at a time (ROWS below).
 __host__ __device__ inline bool shrink_rows(int64_t Kc, int S) { return (((Kc + 31) >> 5) + S - 1) / S > 4 * 8; }
+// Whether the consumers of the kernel for few rows request x a row at a time (rows_to_operand): from 17 rows on with more than eight
+// 32-deep steps a wave; 8 to 16 rows only where rows lie a multiple of 2 KB apart (neighbours in operand order then share the L1's
+// sets), by rows times steps.  980 sizes without and with it, 1 to 32 rows, a graph of 16 calls: 32 rows, 4096 x 4096, 16.2 and 13.7 us,
+// 3072 x 1280 11.7 and 8.7, 17 to 32 rows of other pitches, nine to eleven steps 0.97 of the time, from memory 1.00, more of them 0.93
+// to 0.98; 16 rows, 4096 x 4096, 12.4 and 11.5, 10 rows, 5120 values, 0.95, 4096 values 1.00; other pitches up to 16 rows 0.99 to
+// 1.00, from memory 1.00 to 1.02; 1 to 6 rows 1.01 to 1.03.
+inline bool thin_rows(int64_t T, int64_t Kc, int64_t lda) {
+  const int64_t steps = ((Kc + 31) / 32 + 7) / 8;
+  return T > 16 ? steps > 8 : T >= 8 && lda % 1024 == 0 && T * steps > 192;
+}
 // Eight waves share the part's 32-deep steps, their sums meet in `red` (8 x NB x 64) and are added in wave
 // order: the bits do not depend on who computes the job.  u(): [row of the tile][r_stride] of this split; ask() requests what
 // u() needs, behind the first operands, which would have to wait for it.  Every wave has called u() when the waves meet, so that

@@ -17,6 +17,13 @@ def test_few_rows(oracle, T, K):
     _check(oracle, T, K, 72, [16, 8, 24])
 
 
+# around the lines themselves: more than eight steps a wave from 17 rows on, before that rows 2 KB apart and more than 192 rows times steps
+@pytest.mark.parametrize("T,K", [(1, 14336), (7, 8192), (8, 6144), (8, 7168), (12, 4096), (13, 4096), (13, 4104), (16, 3072), (16, 5120), (17, 2048), (17, 2056), (32, 2056)])
+def test_few_rows_around_the_line(oracle, T, K):
+    _check(oracle, T, K, 72, [16, 8, 24])
+    _check(oracle, T, K, 4168, [16])
+
+
 # u of batches with few rows for a compute unit, in a launch of its own
 @pytest.mark.parametrize("K,ranks", [(2048, [16]), (2056, [8, 24, 32]), (2088, [64, 40]), (2056, [128, 100]), (4104, [16, 9])])
 def test_shrink_of_few_rows_a_unit(oracle, K, ranks):

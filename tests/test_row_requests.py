@@ -1,0 +1,29 @@
+"""Which calls request their operands a row at a time, against timed runs of both."""
+import ctypes
+import subprocess
+
+import pytest
+
+from paper_2605_08527_amd import build
+
+SOURCE = """#include "lora_shrink.h"
+extern "C" int few(int64_t T, int64_t Kc, int64_t lda) { return marlaas::thin_rows(T, Kc, lda); }
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rows")
+    (d / "p.hip").write_text(SOURCE)
+    subprocess.run([build.HIPCC, "--cuda-host-only", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", build.CSRC, str(d / "p.hip"), "-o", str(d / "p.so")],
+                   check=True, stderr=subprocess.DEVNULL)
+    so = ctypes.CDLL(str(d / "p.so"))
+    so.few.argtypes = [ctypes.c_int64] * 3
+    return so
+
+
+# (rows, contraction, distance of the rows) that took 1.5 % longer and more with such requests, and 3 % less and more
+def test_few_rows(lib):
+    assert not any(lib.few(T, K, K) for T, K in ((1, 2600), (1, 14336), (2, 2000), (2, 14336), (4, 2600), (4, 7000), (8, 2600), (8, 7464), (9, 6152), (10, 2600), (12, 1024), (16, 2000), (20, 2000)))
+    assert all(lib.few(T, K, K) for T, K in ((8, 8192), (10, 5120), (12, 8192), (14, 14336), (16, 4096), (18, 3072), (24, 5120), (32, 2600), (32, 4096)))
+    assert lib.few(16, 8192, 8192) and not lib.few(16, 8192, 8200) and lib.few(16, 8184, 9216)
