@@ -416,10 +416,14 @@ __global__ __launch_bounds__(256) void shrink_ring_kernel(ShrinkArgs a) {
 // Batches of few rows a compute unit: one block per (adapter, 16 grouped rows); its 8 waves split the
 // contraction, take both operands straight from global memory (L_t stored [r_t, C], so a lane's 8
 // contraction values are one 16-byte load) and add their partial tiles through LDS in wave order,
-// so the result does not depend on timing.  Bound by latency: a wave has U steps of 32 contraction values
-// under way while U others are multiplied.
+// so the result does not depend on timing.  Bound by latency: a wave requests U steps of 32 contraction values
+// together, and the next U before it multiplies them, but what it then waits for is all of them.
+// ROWS: requests in operand order are look-ups of the unit's L1, one a lane (two kilobytes a step, 54 ns: at 4096 values
+// 6.9 us of a block's 9), so they go a row at a time (rows_to_operand) from twelve steps a wave on: a prefill chunk of 2011
+// rows, 4096 x 4096, rank 16, 69.3 -> 68.0 us.  400 sizes of 1025 to 5600 rows and 1800 to 6000 values with and without: nine
+// to eleven steps 0.999 of the call's time (0.957 to 1.016), twelve and more 0.98, 0.95 where rows lie a multiple of 2 KB apart.
 static constexpr int SS_WAVES = 8;
-template <int NQT>
+template <int NQT, bool ROWS>
 __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkArgs a) {
   constexpr int U = NQT == 1 ? 4 : NQT == 2 ? 3 : NQT == 4 ? 2 : 1;
   union Frag { uint4 u; bf16x8 v; };
@@ -434,11 +438,7 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, li = lane & 15;
   const int steps = (int)((a.C + 31) >> 5), per = (steps + SS_WAVES - 1) / SS_WAVES;
-  // Requests in operand order are look-ups of the unit's L1, one a lane (two kilobytes a step, 54 ns: at 4096 values 6.9 us
-  // of a block's 9), so they go a row at a time (rows_to_operand) where a wave has more than eight steps: a prefill chunk of
-  // 2011 rows, 4096 x 4096, rank 16, 69.3 -> 68.0 us.
-  const bool in_rows = per > 8;
-  const int lr = in_rows ? lane >> 2 : li, lu = in_rows ? lane & 3 : g;    // row, eight values that this lane requests
+  const int lr = ROWS ? lane >> 2 : li, lu = ROWS ? lane & 3 : g;    // row, eight values that this lane requests
   char* const stage = red + wave * nqt * 1024;
   int m = row0 + lr;
   if (m >= hi) m = hi - 1;
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(64 * SS_WAVES) void shrink_small_nt_kernel(ShrinkAr
     }
   };
   auto multiply = [&](Frag (&f)[U][NQT + 1]) {
-    if (in_rows)
+    if (ROWS)
 #pragma unroll
       for (int i = 0; i < U; ++i)
 #pragma unroll
@@ -562,7 +562,10 @@ hipError_t launch_shrink_bf16(const bf16_t* X, int64_t ldx, int64_t C, const int
     if (wrote_u2) *wrote_u2 = u2 != nullptr;
     const size_t lds = (size_t)SS_WAVES * (r_stride / 16) * 64 * sizeof(f32x4);
     const int nq = r_stride / 16;
-    auto kern = nq <= 1 ? shrink_small_nt_kernel<1> : nq <= 2 ? shrink_small_nt_kernel<2> : nq <= 4 ? shrink_small_nt_kernel<4> : shrink_small_nt_kernel<8>;
+    const bool in_rows = (C + 31) / 32 > 11 * SS_WAVES;
+#define SS_PICK(N_) (in_rows ? shrink_small_nt_kernel<N_, true> : shrink_small_nt_kernel<N_, false>)
+    auto kern = nq <= 1 ? SS_PICK(1) : nq <= 2 ? SS_PICK(2) : nq <= 4 ? SS_PICK(4) : SS_PICK(8);
+#undef SS_PICK
     a.row_blocks = (int)((T_lora + 15) / 16) + n_adapters;
     hipLaunchKernelGGL(kern, dim3(a.row_blocks + side_blocks(a, SS_WAVES)), dim3(64 * SS_WAVES), lds, stream, a);
     return hipGetLastError();

@@ -30,6 +30,11 @@ def test_shrink_of_few_rows_a_unit(oracle, K, ranks):
     _check(oracle, 1030, K, 4104, ranks, packed=False)
 
 
+@pytest.mark.parametrize("K,ranks", [(2816, [16]), (2824, [8, 24, 32]), (2824, [64, 40]), (2856, [128, 100])])
+def test_shrink_around_its_line(oracle, K, ranks):
+    _check(oracle, 1030, K, 4104, ranks, packed=False)
+
+
 # u of some more rows, by producers beside the consumers: more than four steps a wave (from a contraction of 1032 on where it is not cut), two
 # blocks of rows and one, rows of others in them, ranks that leave rows of the factor out
 @pytest.mark.parametrize("T", [33, 100, 257])
