@@ -13,8 +13,11 @@ struct ShrinkJob {
   int rank, q0, row0, row1, split;
 };
 
-// Whether a job requests its operands a row at a time (ROWS below).
-__host__ __device__ inline bool shrink_rows(int64_t Kc, int S) { return (((Kc + 31) >> 5) + S - 1) / S > 4 * 8; }
+// Whether a job requests its operands a row at a time (ROWS below): with more than four steps a wave, and more than eight rows (of
+// fewer, most lanes in operand order repeat the first row, which is no look-up of its own: 281 rows of 92 adapters of rank 64, q/k/v of
+// 5992 + 976 + 976 columns, contraction 1864, 74.4 us with, 71.5 without; 408 rows of 50 adapters of rank 32, 4112 x 10648, 78.2 and 75.1;
+// 34 rows of 19 of rank 64, 6432 x 3240, 23.8 and 23.1).
+__host__ __device__ inline bool shrink_rows(int64_t Kc, int S, int rows) { return rows > 8 && (((Kc + 31) >> 5) + S - 1) / S > 4 * 8; }
 // Whether the consumers of the kernel for few rows request x a row at a time (rows_to_operand): from 17 rows on with more than eight
 // 32-deep steps a wave; 8 to 16 rows only where rows lie a multiple of 2 KB apart (neighbours in operand order then share the L1's
 // sets), by rows times steps.  980 sizes without and with it, 1 to 32 rows, a graph of 16 calls: 32 rows, 4096 x 4096, 16.2 and 13.7 us,
@@ -30,7 +33,7 @@ inline bool thin_rows(int64_t T, int64_t Kc, int64_t lda) {
 // u() needs, behind the first operands, which would have to wait for it.  Every wave has called u() when the waves meet, so that
 // behind the job whoever likes may change what u() reads.  No value is stored as zero bits.  tok0, tok1: tokens of row
 // lane % 16 of the first and of the second block.
-// ROWS (where a wave has more than four steps of two blocks, shrink_rows): operands are requested a row at a time and put in order through LDS
+// ROWS (shrink_rows): operands are requested a row at a time and put in order through LDS
 // (rows_to_operand): 157 rows, 14336 x 4096, 32 adapters of rank 16, 42.4 -> 40.2 us, q/k/v of 157 rows 26.5 -> 25.1, 512 rows, 5120 x
 // 5120, 64 adapters, in tiles of 96 rows 55.8 -> 53.4; with four steps the trip costs what it saves (256 rows, 4096 x 4096, 21.4 and 21.5).
 // UP: steps requested together (twice); NB: blocks a job can have.  All eight waves call it.
