@@ -1018,16 +1018,16 @@ MidPlan gemm_mid_plan(int form, int64_t T, int64_t lda, int64_t Kc, const ProjEn
     return MidPlan();
   int64_t cols = 0;
   for (int q = 0; q < n_proj; ++q) cols += proj_host[q].Nout;
-  const MidPlan small = mid_plan(T, Kc, proj_host, n_proj, lora, sync->counters ? 4 : 1);     // (splits exchange sums)
-  const MidPlan p = mid_taller(small, T, Kc, proj_host, n_proj, lora);
-  for (int q = 0; q < n_proj; ++q)
-    if ((proj_host[q].Nout + 32 * p.wn - 1) / (32 * p.wn) * p.ksplit > MID_CONSUMERS) return MidPlan();
   auto wide_us = [&]() {                                         // (it takes the projections one after the other)
     double us = 0.0;
     for (int q = 0; q < n_proj; ++q) us += wide_plan(T, Kc, proj_host[q].Nout, room).us;
     return us;
   };
-  return mid_pays(p, T, Kc, cols, ext, wide_us) ? p : MidPlan();
+  const MidPlan small = mid_plan(T, Kc, proj_host, n_proj, lora, sync->counters ? 4 : 1);     // (splits exchange sums)
+  const MidPlan p = mid_taller(small, T, Kc, proj_host, n_proj, lora, mid_limit(T, Kc, cols, ext, wide_us));
+  for (int q = 0; q < n_proj && p.rb; ++q)
+    if ((proj_host[q].Nout + 32 * p.wn - 1) / (32 * p.wn) * p.ksplit > MID_CONSUMERS) return MidPlan();
+  return p;
 }
 
 hipError_t launch_gemm_bf16_mid(const bf16_t* Aop, int64_t lda, int form, int64_t T, int64_t Kc, const int32_t* perm, const int32_t* seg_off, int n_adapters,

@@ -27,7 +27,7 @@
 //
 // Most calls on packed weights run in one launch of other kernels (gemm_thin.hip, gemm_mid.hip); this one
 // serves more than 1024 rows whose tiles do not fill the chip, 65 to 256 rows against a long contraction with
-// few columns (mid_pays), and calls that have no area to exchange values through.
+// few columns (mid_limit), and calls that have no area to exchange values through.
 //
 // Who finishes the call (adds the splits, adds the expand, rounds, scatters the rows), decode_finish_mode():
 //   generic: splitk_finish_kernel, a second launch; partial sums as fp32 rows.

@@ -731,7 +731,7 @@ static hipError_t launch_mid(const GemmArgs& a, int cu_count, hipStream_t stream
     // its own, as many consumers start behind them: 157 rows, 4096 x 28672, 32 adapters in two projections, 66.8 -> 61.7 us; 256 rows,
     // 4096 x 14336, 48.1 -> 42.6; 200 rows, 3000 x 14336, 40 adapters of rank 32, 43.8 -> 39.1).  Behind the consumers they would run on the same
     // units, but a launch beside this one could take those places.
-    const int64_t free = (cu_count - consumers) & ~7;
+    const int64_t free = mid_free_units(cu_count, consumers);
     g.prod0 = 0;
     if (mid_jobs_in_turn(free, a.n_prod)) g.n_prod = (int)free;
   } else {

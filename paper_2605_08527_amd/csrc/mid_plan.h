@@ -10,7 +10,8 @@ namespace marlaas {
 static constexpr int MID_WAVES = 8;
 // Tiles of 128 rows and more take all of a compute unit's registers.
 __host__ __device__ constexpr bool mid_alone(int rb) { return rb > 6; }
-// Whether producers take several jobs each: `free` units that the consumers leave.
+// Whether producers take several jobs each: `free` units that the consumers leave, in whole rounds over the XCDs.
+inline int64_t mid_free_units(int64_t cu_count, int64_t consumers) { return (cu_count - consumers) & ~7; }
 inline bool mid_jobs_in_turn(int64_t free, int64_t jobs) { return free >= 32 && jobs > free && jobs <= 5 * free; }
 
 // Pieces of a producer's contraction.  A compute unit that has a producer besides its consumer is behind the
@@ -41,7 +42,7 @@ inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t co
 // for anyway (298 rows without adapters, 1496 x 1160, 11.5 us in two splits, whole 9.5).
 //   Against 425 sets of 17 to 1024 rows, contractions of 1024 to 14336, 1024 to 28672 columns in one to three
 // projections, without adapters and with 1 to 96 of ranks 8 to 128, timed in every tiling with weights from the
-// memory-side cache and from memory (tests/golden/some_rows_tilings.json): the one chosen takes 2.5 % longer than the
+// memory-side cache and from memory (tests/golden/some_rows_tilings.json): the one chosen takes 2.3 % longer than the
 // best on the average, at most 1.31 times as long.
 //   Few units with two workgroups count for little (64 units, over which a second workgroup comes to count in
 // full): with weights from memory 512 rows, 5120 x 5120, 32 adapters of rank 16, take 54 us in 280 workgroups of 80
@@ -51,7 +52,7 @@ static constexpr double mid_tile_us[2][2] = {{0.306, 0.252}, {0.334, 0.282}};   
 // What the comparisons differ in: the rank up to which the expand takes longer, units with two workgroups that count in full, the
 // fabric's rate and the share of a weight that a further row tile reads again, and the producers beside more consumers than units.
 struct MidRates { double rank_cap, ramp, rate, again, beside; };
-static constexpr MidRates MID_SMALL = {16.0, 64.0, 11.6e6, 0.0, 256.0}, MID_TALL = {48.0, 19.3, 11.9e6, 0.074, 91.0};
+static constexpr MidRates MID_SMALL = {16.0, 64.0, 11.6e6, 0.0, 256.0}, MID_TALL = {12.3, 15.5, 32.0e6, 0.042, 102.0};
 
 struct MidModel {
   int64_t T, Kc, cols;
@@ -90,7 +91,7 @@ struct MidModel {
     }
     const double fabric = (2.0 * cols * Kc * (1.0 + c.again * (double)(tiles_m(rb) - 1)) + 16.0 * T * Kc / s) / c.rate;
     const double loop = cbrt(fill * fill * fill + fabric * fabric * fabric);
-    double us = 7.687 + loop;
+    double us = 7.687 + loop + (alone ? 1.65 + 0.229 * rb : 0.0);     // (alone: nothing else runs on the unit while a tile starts and ends)
     if (lora.n > 0) {
       // (the most u there can be, of five projections and more, counts as whole: the estimate of such calls is low, and with
       // two pieces would take six of 1024 columns, contraction 14336, 1000 rows of rank 128, here, 496 us, not one by one, 298)
@@ -104,8 +105,12 @@ struct MidModel {
       const double prod_us = 10.735 * Kc / 4096.0 / p + 0.498;
       us += 0.562 + 2.009 * ((rb * wn + 7) / 8) * rank / 16.0 + (s > 1 ? 0.02 * lora.ranks / lora.n : 0.0);
       if (alone) {
-        if (mid_jobs_in_turn(256 - wgs, prods)) us += std::max(0.0, prod_us * (double)prods / (double)(256 - wgs) - 1.4 * loop);
-        else us += prod_us * 1.12 * up_to_1((double)(wgs + prods - 256) / 17.45);
+        // As the launch has them (launch_mid): the jobs that there can be, each first on a unit of its own, a round of units after
+        // another, or in turn on the units that the consumers leave.  Those that no grouping of these rows has look for themselves.
+        const int64_t padded = (jobs(rb) * p + 7) / 8 * 8, free = mid_free_units(256, wgs);
+        const double real = (double)std::min(prods, padded), none = (double)padded - real;
+        if (mid_jobs_in_turn(free, padded)) us += std::max(0.0, prod_us * real / (double)free + 5.39 * none / (double)free - 1.776 * loop);
+        else us += prod_us * 0.743 * (up_to_1(((double)wgs + real - 256.0) / 17.45) + std::max(0.0, ceil(((double)wgs + real) / 256.0) - 2.0)) + 5.39 * none / 256.0;
       } else {
         us += prod_us * (wgs <= 256 ? 0.574 * up_to_1((double)(wgs + prods - 256) / 17.45) : 0.289 * up_to_1((double)prods / 256.0) * (256.0 / c.beside));
         us += prod_us * 0.918 * up_to_1((double)((wgs < 512 ? wgs : 512) + prods - 512) / 17.45);
@@ -133,33 +138,7 @@ inline MidPlan mid_plan(int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj
   return best;
 }
 
-// The same call in taller tiles of 128 columns, unsplit, where the estimate says that they are faster.
-//   Both sides are estimated with other constants than the smaller tiles have among themselves, fitted to 267 sets of 40 to 900
-// rows, contractions of 1024 to 14336, one to three projections, up to 64 adapters of ranks 8 to 64, timed with the weight
-// from the memory-side cache and from memory: the choice takes 0.970 and 0.959 of the time of the smaller tile, 94 sets change,
-// 70 of them get faster by more than 3 %, the worst from 21.8 to 23.6 us (397 rows, 1040 x 8984; 3 % in hand keep most such away).
-//   96 rows only with all workgroups on the chip at once (669 rows, 6168 x 2248, 32 adapters of rank 64, would be 1.34 times as
-// long), 128, 160 and 256 rows where they fill one round and most of the units (512 rows, 5120 x 5120, 160 workgroups of 128 rows: 56.7
-// us, 240 of 96 rows 52.4).  256 rows, of which the sets above know nothing: 180 to 512 rows, 4096 x 14336 to 28672, 32 adapters of rank
-// 16, 0.71 to 0.9 of the time of the smaller tile, from memory 0.73 to 0.84.
-inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora) {
-  static const int rbs[4] = {6, 8, 10, 16};
-  static const double tile_us[4] = {0.355, 0.351, 0.407, 0.78};
-  const MidModel m(T, Kc, proj, n_proj, lora, MID_TALL);
-  MidPlan best = p;
-  double least = 0.0;                                            // (0: not asked for yet)
-  for (int i = 0; i < 4; ++i) {
-    const int rb = rbs[i];
-    const int64_t wgs = m.tiles_m(rb) * m.over_xcds(4, 1), jobs = m.jobs(rb);
-    if (wgs < 176 || (mid_alone(rb) ? wgs > 256 : wgs + jobs * m.pieces(rb, wgs, MID_U_FLOATS) > 512)) continue;
-    if (least == 0.0) least = 0.97 * m.us(p.rb, p.wn, p.ksplit, mid_tile_us[p.rb - 4][p.wn == 4], m.tiles_m(p.rb) * m.over_xcds(p.wn, p.ksplit));
-    const double us = m.us(rb, 4, 1, tile_us[i], wgs);
-    if (us < least) { least = us; best.us = std::min(p.us, us); best.rb = rb; best.wn = 4; best.ksplit = 1; best.tiles_m = (int)m.tiles_m(rb); }
-  }
-  return best;
-}
-
-// Whether the call is better off elsewhere (ext: ranks of all adapters in the batch, 0: no adapters).
+// The estimate from which on the call is better off elsewhere (ext: ranks of all adapters in the batch, 0: no adapters).
 //   Up to 16 rows the few-row kernel, up to 32 while its workgroups, which hold all of x, have little of it.
 //   Above 384 rows the wide kernel.  With adapters where its rate, which has to make up for its shrink's launch and its
 // ext columns, says so (400 rows, 4096 x 14336, 32 adapters of rank 16 86 against 75 us; 14336 x 4096 109 / 75).
@@ -172,16 +151,50 @@ inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEnt
 //   200 rows, 20480 x 2048, 32 adapters of rank 16: 44 / 52; 256 rows, 14336 x 4096 from memory 63 / 70; up to 128
 //   rows with adapters never: 100 rows 45 / 35 and 37 / 36).
 template <typename Wide>
-inline bool mid_pays(const MidPlan& p, int64_t T, int64_t Kc, int64_t cols, int ext, Wide wide_us) {
-  if (T <= 16) return false;
-  if (T <= 32) return T * Kc > 140000 || Kc * cols > 50000000;
-  if (T > 384 && ext > 0) return p.us < 20.0 + 2.0 * T * Kc * cols / 1.25e9 + 0.1 * ext;
-  if (T > 384) return p.us * (Kc > 4096 ? 1.0 + 0.2 * log2((double)Kc / 4096.0) : 1.0) < 6.0 + wide_us();
+inline double mid_limit(int64_t T, int64_t Kc, int64_t cols, int ext, Wide wide_us) {
+  const double always = 1e30;
+  if (T <= 32) return T * Kc > 140000 || Kc * cols > 50000000 ? always : 0.0;
+  if (T > 384 && ext > 0) return 20.0 + 2.0 * T * Kc * cols / 1.25e9 + 0.1 * ext;
+  if (T > 384) return (6.0 + wide_us()) / (Kc > 4096 ? 1.0 + 0.2 * log2((double)Kc / 4096.0) : 1.0);
   if (T > 64 && T <= 256 && Kc >= 2 * cols && Kc * cols >= 40000000) {
-    if (ext == 0) return p.us < 15.0 + Kc * cols * (T <= 128 ? 0.29e-6 : 0.365e-6);
-    if (T > 128 && ext <= 512) return 1.15 * p.us < 15.0 + Kc * cols * 0.67e-6;
+    if (ext == 0) return 15.0 + Kc * cols * (T <= 128 ? 0.29e-6 : 0.365e-6);
+    if (T > 128 && ext <= 512) return (15.0 + Kc * cols * 0.67e-6) / 1.15;
   }
-  return true;
+  return always;
+}
+
+// The same call in taller tiles of 128 columns, unsplit, where the estimate says that they are faster: than the smaller tile, or,
+// where that one does not pay (limit), than the kernel that has the call otherwise.
+//   Both sides are estimated with other constants than the smaller tiles have among themselves, fitted to 1758 sets of 33 to 1024
+// rows, contractions of 1024 to 14336, 1024 to 28672 columns in one or three projections, without adapters and with up to 400 of
+// ranks 8 to 128, timed as they run without taller tiles and in every taller one that fits, with the weight from the memory-side
+// cache and from memory, neither of which is to get slower.  Of these and 390 timed afterwards, 2148, 555 change, 500 of them get faster by
+// more than 3 % in both, 29 slower in one of the two by more than 1 %, the worst by 20 (tests/golden/tall_tilings.json has 728 of them).
+//   96 rows only with all workgroups on the chip at once (669 rows, 6168 x 2248, 32 adapters of rank 64, would be 1.34 times as
+// long), 128, 160 and 256 rows where they fill one round and most of the units (512 rows, 5120 x 5120, 160 workgroups of 128 rows: 56.7
+// us, 240 of 96 rows 52.4).  Contractions of a few k-tiles are over before a tile
+// alone on its unit has started (310 rows, 1608 x 15520, 31.4 -> 35.5 us in tiles of 160 rows; 386 rows, 1280 x 13720, 23.6 -> 26.9
+// in tiles of 256; 514 rows, 2400 x 10240, 52.5 and 58.1), and tall tiles win most where the weight comes from memory (362 rows, 2808 x
+// 9952, in tiles of 128: from memory 47.3 -> 42.7, from the cache 36.2 -> 40.8): hence the least contractions and a tenth in hand.
+inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora, double limit = 1e30) {
+  static const int rbs[4] = {6, 8, 10, 16};
+  static const double tile_us[4] = {0.320, 0.333, 0.378, 0.650};
+  static const int least_k[4] = {1400, 2600, 3200, 3000};
+  MidPlan best = p.us < limit ? p : MidPlan();
+  if (best.rb == 0 && T <= 384) return best;
+  const MidModel m(T, Kc, proj, n_proj, lora, MID_TALL);
+  double least = 0.0;                                            // (0: not asked for yet)
+  for (int i = 0; i < 4; ++i) {
+    const int rb = rbs[i];
+    const int64_t wgs = m.tiles_m(rb) * m.over_xcds(4, 1);
+    if (Kc < least_k[i] || wgs < 176 || (mid_alone(rb) ? wgs > 256 : wgs + m.jobs(rb) * m.pieces(rb, wgs, MID_U_FLOATS) > 512)) continue;
+    if (least == 0.0)
+      least = p.us < limit ? 0.9 * m.us(p.rb, p.wn, p.ksplit, mid_tile_us[p.rb - 4][p.wn == 4], m.tiles_m(p.rb) * m.over_xcds(p.wn, p.ksplit))
+                           : (lora.n == 0 ? 0.85 : n_proj == 1 ? 1.0 : 1.2) * limit;
+    const double us = m.us(rb, 4, 1, tile_us[i], wgs);
+    if (us < least) { least = us; best.us = std::min(p.us, us); best.rb = rb; best.wn = 4; best.ksplit = 1; best.tiles_m = (int)m.tiles_m(rb); }
+  }
+  return best;
 }
 
 }  // namespace marlaas
