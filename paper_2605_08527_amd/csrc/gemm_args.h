@@ -148,6 +148,33 @@ static constexpr int SK_BM = 128, SK_BN = 128, SK_BX = 32;
 // copy, ldb (ProjEntry::ldw) its k-steps per column block; the adapters' factors must be stored
 // contraction-contiguous when the shrink is fused (n_ext > 0).
 hipError_t launch_gemm_decode(const GemmArgs& a, hipStream_t stream);
+// Its tile (row tile, column tile) and split of workgroup b.  Workgroup b runs on XCD b mod 8, and every XCD has its own L2.  Where the sizes allow it, an
+// XCD works on ONE contraction split (and on every 8 / ksplit-th column tile): it then pulls only its own K-range of x (and of the shrink factors)
+// through the fabric, instead of all of x once per XCD.  The row tiles of a column tile stay neighbours on one XCD and share the
+// weight tile through its L2.  Otherwise: a compact run of (column tile, split, row tile).
+__host__ __device__ inline void decode_tile(int b, int tiles_m, int tiles_n, int ksplit, int* tm, int* tn, int* ks) {
+  const int G = tiles_m * tiles_n * ksplit, xcd = b & 7, idx = b >> 3;
+  const int ng = 8 / ksplit;                     // XCDs that share a split
+  if (ksplit <= 8 && ng * ksplit == 8 && tiles_n % ng == 0) {
+    *ks = xcd % ksplit;
+    *tm = idx % tiles_m;
+    *tn = (idx / tiles_m) * ng + xcd / ksplit;
+  } else {
+    const int q = G >> 3, rem = G & 7;
+    const int bbs = xcd * q + (xcd < rem ? xcd : rem) + idx;
+    *tm = bbs % tiles_m;
+    const int rest = bbs / tiles_m;
+    *ks = rest % ksplit;
+    *tn = rest / ksplit;
+  }
+}
+// Whether u of an unsplit call is there without waiting for a workgroup that has no unit yet: a workgroup has a unit to itself until it
+// is through, so the column tiles that carry the `ext` extended columns have to be among the first on their XCDs.
+inline bool decode_u_comes_first(int tiles_m, int tiles_n, int ext, int cu_count) {
+  const int carry = (ext + 31) / 32 < tiles_n ? (ext + 31) / 32 : tiles_n;
+  if (tiles_m * tiles_n <= cu_count) return true;
+  return (tiles_n % 8 == 0 ? (carry + 7) / 8 * tiles_m : carry * tiles_m) <= cu_count / 8;
+}
 
 // Few rows (T <= THIN_ROWS) on packed weights, one launch (gemm_thin.hip): every ProjEntry filled in
 // (also for one projection; W packed, ldw its k-steps, tile0 set here), u_out = [T][r_stride] fp32 that

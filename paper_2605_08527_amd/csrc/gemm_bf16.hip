@@ -904,16 +904,17 @@ bool gemm_can_fuse_shrink(int form, int64_t T, int64_t Kc, int64_t Nout, int nee
 // several splits it is only taken when every workgroup of the launch fits on the chip at once, so
 // that the splits of a tile normally run at the same time (a split that does not see the others
 // in time leaves its share to the last one: correct either way).  DECODE_FINISH_AUTO: in the
-// kernel when there is one split (the sums never leave the registers; only u crosses workgroups,
-// and the column tiles that carry it are the first to be scheduled), a launch of its own otherwise
+// kernel when there is one split and u is not waited for in vain (`ext` extended columns; the sums never
+// leave the registers, only u crosses workgroups), a launch of its own otherwise
 // (measured: the counters' round trips cost more than the second launch once 16 MB of partial
-// sums have to cross anyway).
-static int decode_finish_mode(const DecodeSync* sync, int n_adapters, int r_stride, int tiles_m, int tiles_n, int ksplit) {
+// sums have to cross anyway; 412 rows of q/k/v of 9912 + 2944 + 2944 columns, contraction 8440, 20 adapters of rank 8,
+// waited 201 ms for workgroups that had no unit, 217 us with the second launch).
+static int decode_finish_mode(const DecodeSync* sync, int n_adapters, int r_stride, int tiles_m, int tiles_n, int ksplit, int ext) {
   if (!sync || sync->mode == DECODE_FINISH_GENERIC || (n_adapters > 0 && !sync->grp_ids)) return DECODE_FINISH_GENERIC;
   if (n_adapters > 0 && r_stride > 128) return DECODE_FINISH_GENERIC;
   if (ksplit != 1 && ksplit != 2 && ksplit != 4 && ksplit != 8) return DECODE_FINISH_GENERIC;
   int want = sync->mode;
-  if (want == DECODE_FINISH_AUTO) want = ksplit == 1 ? DECODE_FINISH_IN_KERNEL : DECODE_FINISH_LAUNCH;
+  if (want == DECODE_FINISH_AUTO) want = ksplit == 1 && decode_u_comes_first(tiles_m, tiles_n, ext, sync->cu_count) ? DECODE_FINISH_IN_KERNEL : DECODE_FINISH_LAUNCH;
   if (want == DECODE_FINISH_LAUNCH) return DECODE_FINISH_LAUNCH;
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
   if (sync->counters && 2 * tiles + 2 * tiles_m <= DECODE_SYNC_INTS && (ksplit == 1 || tiles * ksplit <= sync->cu_count))
@@ -981,7 +982,7 @@ hipError_t launch_gemm_bf16(const bf16_t* Aop, int64_t lda, const bf16_t* Bop, i
   // a packed copy of the weight: the decode kernel reads it instead of Bop
   if (packed) {
     a.Bop = Bpacked; a.ldb = packed_weight_ksteps(Kc);
-    a.fin_in_kernel = decode_finish_mode(sync, n_adapters, r_stride, p.tiles_m, p.tiles_n, p.ksplit);
+    a.fin_in_kernel = decode_finish_mode(sync, n_adapters, r_stride, p.tiles_m, p.tiles_n, p.ksplit, fuse ? fuse->need : 0);
     if (a.fin_in_kernel) { a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit; }
   }
   if (form == FORM_NT)
@@ -1119,7 +1120,7 @@ hipError_t launch_gemm_bf16_multi(const bf16_t* Aop, int64_t lda, int form, int6
   if (packed != 0 && !pk) return hipErrorInvalidValue;
   a.fin_in_kernel = 0; a.out_is_f32 = out_is_f32; a.lform = form; a.spin_limit = 0;
   a.sync = nullptr; a.grp_ids = nullptr;
-  if (pk) a.fin_in_kernel = decode_finish_mode(sync, n_adapters, r_stride, p.tiles_m, p.tiles_n, p.ksplit);
+  if (pk) a.fin_in_kernel = decode_finish_mode(sync, n_adapters, r_stride, p.tiles_m, p.tiles_n, p.ksplit, need);
   if (a.fin_in_kernel) {
     a.sync = sync->counters; a.grp_ids = sync->grp_ids; a.spin_limit = sync->spin_limit;
     a.r_stride = r_stride;

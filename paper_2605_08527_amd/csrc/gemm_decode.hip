@@ -33,7 +33,7 @@
 //   generic: splitk_finish_kernel, a second launch; partial sums as fp32 rows.
 //   launch (where the contraction is split): a second launch of this kernel's own finish (PHASE 1), the expand
 //     on the matrix instructions.
-//   in the kernel (where it is not split: the sums never leave the registers).  Splits of a tile share out
+//   in the kernel (where it is not split and u comes first, decode_u_comes_first: the sums never leave the registers).  Splits of a tile share out
 //     its 32 units (16 rows x 32 columns) and meet through counters in device memory; the column tiles that
 //     carry extended columns publish their partial u the same way.  Everything that crosses workgroups is
 //     written and read with the agent-scope policy on the instruction itself.  There is one bounded wait; a
@@ -133,29 +133,7 @@ __global__ __launch_bounds__(D_THREADS) void gemm_decode_kernel(GemmArgs a) {
   const int g = wave >> 2, wn = wave & 3;        // k-step of the wave, its 32-column group
   const int li = lane & 15, lg = lane >> 4;      // MFMA operand: row / column li, k values 8 lg .. + 7
   int tm, tn, ks_idx;
-  {
-    // Workgroup b runs on XCD b mod 8, and every XCD has its own L2.  Where the sizes allow it, an
-    // XCD works on ONE contraction split (and on every 8 / ksplit-th column tile): it then pulls
-    // only its own K-range of x (and of the shrink factors) through the fabric, instead of all of
-    // x once per XCD.  The row tiles of a column tile stay neighbours on one XCD and share the
-    // weight tile through its L2.  Otherwise: a compact run of (column tile, split, row tile).
-    const int G = a.tiles_m * a.tiles_n * a.ksplit;
-    const int b = blockIdx.x;
-    const int xcd = b & 7, idx = b >> 3;
-    const int ng = 8 / a.ksplit;                 // XCDs that share a split
-    if (a.ksplit <= 8 && ng * a.ksplit == 8 && a.tiles_n % ng == 0) {
-      ks_idx = xcd % a.ksplit;
-      tm = idx % a.tiles_m;
-      tn = (idx / a.tiles_m) * ng + xcd / a.ksplit;
-    } else {
-      const int q = G >> 3, rem = G & 7;
-      const int bbs = xcd * q + (xcd < rem ? xcd : rem) + idx;
-      tm = bbs % a.tiles_m;
-      const int rest = bbs / a.tiles_m;
-      ks_idx = rest % a.ksplit;
-      tn = rest / a.ksplit;
-    }
-  }
+  decode_tile(blockIdx.x, a.tiles_m, a.tiles_n, a.ksplit, &tm, &tn, &ks_idx);
   const int64_t m0 = (int64_t)tm * SK_BM;
   const int64_t pn0 = (int64_t)tn * SK_BN;       // column of this tile in the partial sums
   const bf16_t* Bop = a.Bop;                     // packed weight; ldb = its k-steps per column block

@@ -167,3 +167,31 @@ def test_hip_graph_replay_of_the_fused_call():
         got = snapshot()
         for a, b in zip(got, eager):
             assert torch.equal(a, b), "replay %d differs from the eager call" % rep
+
+
+def test_nobody_waits_for_a_workgroup_without_a_unit(oracle):
+    """More column tiles than units, with more of them carrying extended columns than an XCD's units at first: u in the kernel would be
+    waited for in vain, for as long as a bounded wait lasts (0.2 s)."""
+    T, K, Ns, ranks = 1100, 264, (2136, 2976, 2976), [64, 64]
+    ids = np.random.default_rng(5).integers(-1, 2, size=T).astype(np.int32)
+    ws = _projections(11, T, K, Ns, [ranks] * 3, [0.5, 2.0], ids, wl.TORCH)
+    ctx = api.marlaas_create(0)
+    x, n = to_dev(ws[0]["x"]), len(ranks)
+    seg = api.marlaas_segmap_build(ctx, torch.from_numpy(ids).cuda(), n)
+    descs, ys = [], []
+    for w in ws:
+        W = to_dev(w["W"])
+        descs.append(api.LoraDesc(x, W, [to_dev(a) for a in w["A"]], [to_dev(b) for b in w["B"]], w["ranks"], w["scales"], seg, layout=wl.TORCH,
+                                  out_dtype=torch.float32, W_packed_fwd=api.marlaas_pack_weight(ctx, W, wl.TORCH, 0)))
+        ys.append(torch.empty((T, W.shape[0]), dtype=torch.float32, device="cuda"))
+    room = torch.empty(api.marlaas_workspace_bytes_multi(descs), dtype=torch.uint8, device="cuda")
+    api.marlaas_set_workspace(ctx, room)
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    api.marlaas_lora_fwd_multi(ctx, descs, ys)
+    start.record()
+    api.marlaas_lora_fwd_multi(ctx, descs, ys)
+    end.record()
+    torch.cuda.synchronize()
+    assert start.elapsed_time(end) < 20.0
+    for w, y in zip(ws, ys):
+        assert_close(to_host(y), oracle.fwd(w["x"], w["W"], w["A"], w["B"], w["ranks"], w["scales"], ids, layout=wl.TORCH), "%d columns" % y.shape[1])
