@@ -207,7 +207,7 @@ __global__ __launch_bounds__(MD_THREADS, (2 * MidShape<RB, WN>::PER_UNIT)) void 
           if (!asked) turn = turn_of(line.x, line.y, line.z, line.w);
           return u_area(turn.area) + (pp * S + job.split) * u_n + (int64_t)tile * BM * a.r_stride;
         };
-        if (shrink_rows(a.Kc, S, job.row1 - job.row0)) shrink_job<3, 2, true>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, ask, at, a.r_stride, wave, lane);
+        if (shrink_rows(a.Kc, S, job.row1 - job.row0, (int)gridDim.x)) shrink_job<3, 2, true>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, ask, at, a.r_stride, wave, lane);
         else shrink_job<3, 2, false>(job, a.Aop, a.lda, a.Kc, tok0, tok1, S, red, ask, at, a.r_stride, wave, lane);
         asked = true;
       }

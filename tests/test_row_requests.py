@@ -8,7 +8,7 @@ from paper_2605_08527_amd import build
 
 SOURCE = """#include "lora_shrink.h"
 extern "C" int few(int64_t T, int64_t Kc, int64_t lda) { return marlaas::thin_rows(T, Kc, lda); }
-extern "C" int job(int64_t Kc, int S, int rows) { return marlaas::shrink_rows(Kc, S, rows); }
+extern "C" int job(int64_t Kc, int S, int rows, int workgroups) { return marlaas::shrink_rows(Kc, S, rows, workgroups); }
 """
 
 
@@ -20,7 +20,7 @@ def lib(tmp_path_factory):
                    check=True, stderr=subprocess.DEVNULL)
     so = ctypes.CDLL(str(d / "p.so"))
     so.few.argtypes = [ctypes.c_int64] * 3
-    so.job.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    so.job.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     return so
 
 
@@ -31,7 +31,7 @@ def test_few_rows(lib):
     assert lib.few(16, 8192, 8192) and not lib.few(16, 8192, 8200) and lib.few(16, 8184, 9216)
 
 
-# producers' jobs: few rows of an adapter, however long the contraction, and four steps a wave do without
+# producers' jobs: few rows of an adapter, however long the contraction, four steps a wave and launches of many workgroups do without
 def test_jobs(lib):
-    assert not any(lib.job(K, S, rows) for K, S, rows in ((1864, 1, 3), (4112, 1, 8), (14336, 2, 1), (1024, 1, 32), (4096, 4, 32)))
-    assert all(lib.job(K, S, rows) for K, S, rows in ((1056, 1, 9), (4096, 2, 16), (14336, 4, 32)))
+    assert not any(lib.job(*j) for j in ((1864, 1, 3, 300), (4112, 1, 8, 300), (14336, 2, 1, 300), (1024, 1, 32, 300), (4096, 4, 32, 300), (4096, 1, 32, 641)))
+    assert all(lib.job(*j) for j in ((1056, 1, 9, 300), (4096, 2, 16, 300), (14336, 4, 32, 640)))
