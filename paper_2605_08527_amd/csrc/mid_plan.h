@@ -169,7 +169,7 @@ inline double mid_limit(int64_t T, int64_t Kc, int64_t cols, int ext, Wide wide_
 // rows, contractions of 1024 to 14336, 1024 to 28672 columns in one or three projections, without adapters and with up to 400 of
 // ranks 8 to 128, timed as they run without taller tiles and in every taller one that fits, with the weight from the memory-side
 // cache and from memory, neither of which is to get slower.  Of these and 390 timed afterwards, 2148, 555 change, 500 of them get faster by
-// more than 3 % in both, 29 slower in one of the two by more than 1 %, the worst by 20 (tests/golden/tall_tilings.json has 728 of them).
+// more than 3 % in both, 29 slower in one of the two by more than 1 %, the worst by 20 (tests/golden/tall_tilings.json has 748 of them).
 //   96 rows only with all workgroups on the chip at once (669 rows, 6168 x 2248, 32 adapters of rank 64, would be 1.34 times as
 // long), 128, 160 and 256 rows where they fill one round and most of the units (512 rows, 5120 x 5120, 160 workgroups of 128 rows: 56.7
 // us, 240 of 96 rows 52.4).  Contractions of a few k-tiles are over before a tile
