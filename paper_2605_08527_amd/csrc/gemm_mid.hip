@@ -17,7 +17,7 @@ hipError_t launch_gemm_mid(GemmArgs a, const MidPlan& p, int cu_count, hipStream
     a.tiles_n += (int)((a.proj[q].Nout + 32 * p.wn - 1) / (32 * p.wn));
   }
   const int64_t consumers = (int64_t)p.tiles_m * a.tiles_n * p.ksplit, jobs = (int64_t)a.n_proj * a.proj_jobs;
-  a.n_split = mid_u_splits(a.Kc, a.T * a.r_stride * a.n_proj, MID_U_FLOATS, consumers, jobs, cu_count, mid_alone(p.rb));
+  a.n_split = mid_u_splits(a.Kc, a.T * a.r_stride * a.n_proj, MID_U_FLOATS, consumers, jobs, cu_count, p.rb);
   a.n_prod = (int)((jobs * a.n_split + 7) / 8 * 8);
   if (p.rb > 5) return launch_gemm_tall(a, p, cu_count, stream);
   if (p.wn == 4) return p.rb == 4 ? launch_mid<4, 4>(a, cu_count, stream) : launch_mid<5, 4>(a, cu_count, stream);

@@ -26,12 +26,13 @@ inline bool mid_jobs_in_turn(int64_t free, int64_t jobs) { return free >= 32 && 
 // Few steps are not cut: a value of u is read once for each piece.  More than 24 always are (eight projections of 1024
 // columns, contraction 8192, 1000 rows of 4 adapters of rank 128: 364 us, whole 402, 600 rows of 8 adapters 288 and 282; of
 // 512 columns, contraction 7168, 640 rows of 32 adapters: 340 and 1035).
+//   Tiles of 96 rows (rb 6) are taken with all workgroups on the chip only (mid_taller), so theirs are never more than fit.
 //   u_room: floats of u that there is room for.
-inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t consumers, int64_t jobs, int cu_count, bool alone = false) {
+inline int mid_u_splits(int64_t Kc, int64_t u_floats, int64_t u_room, int64_t consumers, int64_t jobs, int cu_count, int rb = 4) {
   const int64_t steps = ((Kc + 31) / 32 + MID_WAVES - 1) / MID_WAVES;      // 32-deep steps of a wave
   if (steps <= 8 || (steps <= 16 && consumers + jobs <= cu_count)) return 1;
   int s = MID_SPLITS;
-  while (s > 1 && (consumers + jobs * s > (alone ? 4 : s == 2 ? 9 : 8) * cu_count / 4 || u_floats * s > u_room)) s /= 2;
+  while (s > 1 && (consumers + jobs * s > (mid_alone(rb) ? 4 : s == 2 && rb < 6 ? 9 : 8) * cu_count / 4 || u_floats * s > u_room)) s /= 2;
   return s == 1 && steps > 24 && 2 * u_floats <= u_room ? 2 : s;
 }
 
@@ -75,7 +76,7 @@ struct MidModel {
   int64_t over_xcds(int wn, int s) const { return (tiles_n(wn) + 8 / s - 1) / (8 / s) * 8; }
   // the most shrink jobs, and the pieces that each is in
   int64_t jobs(int rb) const { return lora.n > 0 ? (int64_t)n_proj * mid_max_jobs(T, rb, lora) : 0; }
-  int pieces(int rb, int64_t wgs, int64_t u_room) const { return mid_u_splits(Kc, T * lora.r_stride * n_proj, u_room, wgs, jobs(rb), 256, mid_alone(rb)); }
+  int pieces(int rb, int64_t wgs, int64_t u_room) const { return mid_u_splits(Kc, T * lora.r_stride * n_proj, u_room, wgs, jobs(rb), 256, rb); }
   // t1: a k-tile's time; wgs: consumers
   double us(int rb, int wn, int s, double t1, int64_t wgs) const {
     const bool alone = mid_alone(rb);
@@ -176,6 +177,10 @@ inline double mid_limit(int64_t T, int64_t Kc, int64_t cols, int ext, Wide wide_
 // alone on its unit has started (310 rows, 1608 x 15520, 31.4 -> 35.5 us in tiles of 160 rows; 386 rows, 1280 x 13720, 23.6 -> 26.9
 // in tiles of 256; 514 rows, 2400 x 10240, 52.5 and 58.1), and tall tiles win most where the weight comes from memory (362 rows, 2808 x
 // 9952, in tiles of 128: from memory 47.3 -> 42.7, from the cache 36.2 -> 40.8): hence the least contractions and a tenth in hand.
+//   96 rows whose jobs are whole because two pieces would be a few more workgroups than fit (whole): the smaller tile has its jobs in two
+// there, and how long whole ones take is not in the estimate, so 7 % more are asked for, and no more than 20 steps a wave.  46 sizes of such
+// calls, from the cache and from memory 0.845 and 0.852 of the time without, at most 1.04 (512 rows, 5120 x 5120, 64 adapters of rank 32,
+// 55.2 -> 47.6 us); 17 sizes beyond these lines 0.67 to 1.19 (736 rows, 5176 x 2440, 20 adapters of rank 64, 65.9 -> 78.4).
 inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEntry* proj, int n_proj, const MidLora& lora, double limit = 1e30) {
   static const int rbs[4] = {6, 8, 10, 16};
   static const double tile_us[4] = {0.320, 0.333, 0.378, 0.650};
@@ -184,6 +189,7 @@ inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEnt
   if (best.rb == 0 && T <= 384) return best;
   const MidModel m(T, Kc, proj, n_proj, lora, MID_TALL);
   double least = 0.0;                                            // (0: not asked for yet)
+  const int64_t steps = ((Kc + 31) / 32 + MID_WAVES - 1) / MID_WAVES;
   for (int i = 0; i < 4; ++i) {
     const int rb = rbs[i];
     const int64_t wgs = m.tiles_m(rb) * m.over_xcds(4, 1);
@@ -191,8 +197,10 @@ inline MidPlan mid_taller(const MidPlan& p, int64_t T, int64_t Kc, const ProjEnt
     if (least == 0.0)
       least = p.us < limit ? 0.9 * m.us(p.rb, p.wn, p.ksplit, mid_tile_us[p.rb - 4][p.wn == 4], m.tiles_m(p.rb) * m.over_xcds(p.wn, p.ksplit))
                            : (lora.n == 0 ? 0.85 : n_proj == 1 ? 1.0 : 1.2) * limit;
+    const bool whole = rb == 6 && steps > 8 && m.pieces(rb, wgs, MID_U_FLOATS) == 1 && wgs + m.jobs(rb) > 256 && wgs + 2 * m.jobs(rb) <= 576;
+    if (whole && steps > 20) continue;
     const double us = m.us(rb, 4, 1, tile_us[i], wgs);
-    if (us < least) { least = us; best.us = std::min(p.us, us); best.rb = rb; best.wn = 4; best.ksplit = 1; best.tiles_m = (int)m.tiles_m(rb); }
+    if (us < (whole ? 0.93 : 1.0) * least) { least = us; best.us = std::min(p.us, us); best.rb = rb; best.wn = 4; best.ksplit = 1; best.tiles_m = (int)m.tiles_m(rb); }
   }
   return best;
 }

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 CASES = {
     "96, whole tiles": (288, 2056, 10240, [16] * 4), "96, u over the sums": (288, 2056, 10240, [128] * 4),
     "96, u over the sums, last tile short": (512, 5120, 5120, [128] * 8),
+    "96, jobs whole, two pieces are more than fit": (512, 5120, 5120, [32] * 64), "96, the same with a tile of one row": (481, 3080, 5120, [32] * 60),
     "128": (128, 4104, 28664, [16] * 32), "128, rank 128": (128, 4096, 28672, [128] * 4),
     "160": (157, 3208, 28672, [16] * 70), "160, several jobs each": (320, 3208, 14336, [16, 8] * 20), "160, few with rows": (160, 3208, 28672, [16] * 32),
     "160, u over the sums, last tile short": (310, 5128, 14336, [128] * 4), "160, u over the sums, last tile whole": (320, 5128, 14336, [112] * 4),

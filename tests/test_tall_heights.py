@@ -57,6 +57,13 @@ def test_gpu_cases_are_what_they_say(choice):
     assert [choice(T, K, [N], [], 0, 1e9) for T, K, N in test_gpu_tall_heights.WITHOUT] == [641, 841, 1041, 1641]
 
 
+# 96 rows: whether producers' jobs come in two pieces, which are more workgroups than fit, or whole, does not refuse a call of fewer jobs.
+def test_fewer_jobs_are_not_refused(choice):
+    mixed = lambda n: [RANKS[t % 4] for t in range(n)]
+    for ranks in (mixed(64), mixed(48), [32] * 64, [16] * 32, [8] * 4):          # (188, 156, 158, 47 and 19 jobs beside 240 consumers)
+        assert choice(512, 5120, [5120], ranks, sum(ranks), 1e9) == 641, len(ranks)
+
+
 # Against timed runs, with the weight from the memory-side cache and from memory: what the choice takes of the time without tall
 # tiles, and how often it is the wrong one in either.
 def test_tiles_taken(choice):
