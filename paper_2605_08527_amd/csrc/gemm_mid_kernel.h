@@ -402,7 +402,7 @@ __global__ __launch_bounds__(MD_THREADS, (2 * MidShape<RB, WN>::PER_UNIT)) void 
 #define MD_STEP(i_, s_)                                                                                   \
   if ((i_) < RB) {                                                                                        \
     constexpr int _i = (i_) < RB ? (i_) : 0;                                                              \
-    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(xf[_i]) : "n"(RB - 1));                                   \
+    asm volatile("" : "+v"(xf[_i]));                                                                      \
     md_product<S_::SPLITS>(acc[_i][0], wreg[s_][0], xf[_i]);                                              \
     md_product<S_::SPLITS>(acc[_i][1], wreg[s_][1], xf[_i]);                                              \
     __builtin_amdgcn_sched_barrier(0);                                                                    \
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(MD_THREADS, (2 * MidShape<RB, WN>::PER_UNIT)) void 
   }
     // k-tile i, in slot s_ = i mod NS.  The x fragments rotate: the ones multiplied were read a tile before,
     // each is replaced by its successor right after its products (the last tile's successors come from a
-    // stale slot and are not used), so a wave has RB - 1 reads under way at every product.
+    // stale slot and are not used).  No product waits for reads: MD_SYNC has, in front of every body.
     // Requests complete in order; younger than the x of tile i + 1 are, besides the x of NS - 2 tiles, the
     // weights requested since: min(i, NS - 1) tiles.
 #define MD_BODY(s_)                                                                                       \
