@@ -6,8 +6,8 @@
 // multiplies mostly padding, cuts the contraction over workgroups to occupy the chip and pays a second
 // launch to add the pieces up (6 rows x 4096 x 4096: 17.9 + 6.9 us).  Here a workgroup owns all rows
 // times 16 NC output columns and its eight waves split the contraction, so a weight fragment is read
-// once, by the one wave that multiplies it, a wave requests 8 to 20 KB at a time, and the sums meet in
-// LDS.  x comes straight from L2 (for the row counts of this kernel no more bytes than the weight), a row at
+// once, by the one wave that multiplies it, a wave requests 8 to 20 KB at a time (in two sets of registers, and what it waits
+// for is all of both: requests stand behind branches, so nobody counts them), and the sums meet in LDS.  x comes straight from L2 (for the row counts of this kernel no more bytes than the weight), a row at
 // a time where that pays (thin_rows).  Workgroups before the consumers ("producers") compute u: one per 16 ranks of an adapter
 // that has rows, the same loop over the adapter's factor in place of the weight.  They are scheduled
 // first and take little longer than a consumer's loop.  Every round trip through the fabric costs 1 to
