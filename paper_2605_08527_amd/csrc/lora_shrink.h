@@ -16,11 +16,14 @@ struct ShrinkJob {
 // Whether a job requests its operands a row at a time (ROWS below): with more than four steps a wave, more than eight rows (of
 // fewer, most lanes in operand order repeat the first row, which is no look-up of its own: 281 rows of 92 adapters of rank 64, q/k/v of
 // 5992 + 976 + 976 columns, contraction 1864, 74.4 us with, 71.5 without; 408 rows of 50 adapters of rank 32, 4112 x 10648, 78.2 and 75.1;
-// 34 rows of 19 of rank 64, 6432 x 3240, 23.8 and 23.1), and no more than 640 workgroups in the launch (beyond, nobody waits for a
+// 34 rows of 19 of rank 64, 6432 x 3240, 23.8 and 23.1; from 18 steps a wave on more than four: 512 rows of 64 adapters of ranks 8 to 64, 5120 x
+// 5120, with their regrouping 69.9, in operand order 71.4, 21 other sizes of such jobs 1.0025 of the time, from memory 1.0006, of
+// shorter jobs 1.007, up to 1.17), and no more than 640 workgroups in the launch (beyond, nobody waits for a
 // single job, and what counts is what all of them do: 382 rows of 9 adapters of rank 128, q/k/v of 5152 + 960 + 960 columns, contraction
 // 1400, 47.8 and 43.3 us; of 420 sizes those of 384 to 800 workgroups take 0.992 of the time with, of more 1.014).
 __host__ __device__ inline bool shrink_rows(int64_t Kc, int S, int rows, int workgroups) {
-  return rows > 8 && workgroups <= 640 && (((Kc + 31) >> 5) + S - 1) / S > 4 * 8;
+  const int64_t part = (((Kc + 31) >> 5) + S - 1) / S;
+  return rows > (part >= 18 * 8 ? 4 : 8) && workgroups <= 640 && part > 4 * 8;
 }
 // Whether the consumers of the kernel for few rows request x a row at a time (rows_to_operand): from 17 rows on with more than eight
 // 32-deep steps a wave; 8 to 16 rows only where rows lie a multiple of 2 KB apart (neighbours in operand order then share the L1's

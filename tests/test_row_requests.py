@@ -34,4 +34,6 @@ def test_few_rows(lib):
 # producers' jobs: few rows of an adapter, however long the contraction, four steps a wave and launches of many workgroups do without
 def test_jobs(lib):
     assert not any(lib.job(*j) for j in ((1864, 1, 3, 300), (4112, 1, 8, 300), (14336, 2, 1, 300), (1024, 1, 32, 300), (4096, 4, 32, 300), (4096, 1, 32, 641)))
+    assert not any(lib.job(*j) for j in ((5120, 1, 4, 300), (5120, 2, 8, 300), (4544, 1, 8, 300), (5120, 1, 8, 641)))
+    assert all(lib.job(*j) for j in ((5120, 1, 5, 428), (4608, 1, 8, 300)))
     assert all(lib.job(*j) for j in ((1056, 1, 9, 300), (4096, 2, 16, 300), (14336, 4, 32, 640)))
